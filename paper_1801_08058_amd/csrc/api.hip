@@ -1283,6 +1283,8 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         stem_bwd_plan(d, P, Q, &pl);
         return round256(pl.wu_bytes);
     }
+    if (op == NGC_OP_BWD_FILTERS && v == V_DIRECT)                      // optional: without it the reduction runs in one part
+        return gather_takes(*d, op, P, Q) ? round256(gather_wgrad_workspace(*d, P, Q)) : 0;
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_STEM) {
         WgradStemParams wp;
         wgrad_stem_plan(d, P, Q, &wp, nullptr);
@@ -1538,8 +1540,10 @@ int ngc_conv_fwd(const ngc_conv_desc *desc, const void *x, const void *w, const 
         if (rc != NGC_OK || !sp.cy) return rc;
         return launch_status(launch_layout_convert(2, desc->n, desc->k, P, Q, yout, NGC_NCHW16C, y, NGC_NCHW, st));
     }
-    if (v == V_DIRECT)
-        return launch_status(launch_direct_fwd(*desc, P, Q, x, w, (desc->epilogue & NGC_EPI_BIAS) ? bias : nullptr, y, st));
+    if (v == V_DIRECT) {
+        const float *b = (desc->epilogue & NGC_EPI_BIAS) ? bias : nullptr;
+        return launch_status(gather_takes(*desc, NGC_OP_FWD, P, Q) ? launch_gather_fwd(*desc, P, Q, x, w, b, y, st) : launch_direct_fwd(*desc, P, Q, x, w, b, y, st));
+    }
     if (v == V_STEM_FWD) {
         StemFwdParams sp;
         size_t lds;
@@ -1644,7 +1648,9 @@ int bwd_data_core(const ngc_conv_desc *desc, const void *dy, const void *w, cons
     if (v == V_UNSUPPORTED || v == V_STAGED) return NGC_UNSUPPORTED;    // blocked copies are the caller's part
     if (v == V_ROWS && fuse) v = V_STRIP;                  // the channel sums of dx come from the strip kernel
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (v == V_DIRECT) return launch_status(launch_direct_bwd_data(*desc, P, Q, dy, w, mask, dx, st));
+    if (v == V_DIRECT)
+        return launch_status(gather_takes(*desc, NGC_OP_BWD_DATA, P, Q) ? launch_gather_bwd_data(*desc, P, Q, dy, w, mask, dx, st)
+                                                       : launch_direct_bwd_data(*desc, P, Q, dy, w, mask, dx, st));
     if (v == V_STEM_BWD) {
         StemBwdPlan pl;
         if (!stem_bwd_plan(desc, P, Q, &pl)) return NGC_UNSUPPORTED;
@@ -2005,7 +2011,9 @@ int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *d
         return launch_status(launch_bias_grad_reduce(rows, dw, groups, elems, row, st));
     }
     const Variant v = pick(desc, NGC_OP_BWD_FILTERS);
-    if (v == V_DIRECT) return launch_status(launch_direct_bwd_filters(*desc, P, Q, x, dy, dw, st));
+    if (v == V_DIRECT)
+        return launch_status(gather_takes(*desc, NGC_OP_BWD_FILTERS, P, Q) ? launch_gather_bwd_filters(*desc, P, Q, x, dy, dw, ws, ws_bytes, st)
+                                                       : launch_direct_bwd_filters(*desc, P, Q, x, dy, dw, st));
     if (v == V_STAGED) {
         StagedPlan sp;
         if (!staged_plan(desc, NGC_OP_BWD_FILTERS, &sp)) return NGC_UNSUPPORTED;
