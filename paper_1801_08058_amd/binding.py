@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libngconv.so (the C ABI declared in include/ngconv.h).
+"""Thin binding of libngconv.so (the C ABI declared in include/ngconv.h): ctypes for the queries, and for the calls that
+launch work the extension _pycall.so (csrc/pycall.c), which converts the arguments in C.
 
 Argument marshalling only: every step of the path runs in the HIP kernels.  Tensors are
 passed as anything with a ``data_ptr()`` (torch tensors) or as raw integer device
@@ -13,6 +14,7 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libngconv.so")
+CALL_PATH = os.path.join(_HERE, "_pycall.so")
 
 # enums of include/ngconv.h
 NGC_OK, NGC_BAD_ARG, NGC_BAD_SHAPE, NGC_UNSUPPORTED, NGC_WORKSPACE_TOO_SMALL, NGC_LAUNCH_FAILED = 0, -1, -2, -3, -4, -5
@@ -61,10 +63,11 @@ class NgcError(RuntimeError):
 
 
 def _load() -> ctypes.CDLL:
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(
-            f"{LIB_PATH} is missing: build it with `python -m paper_1801_08058_amd.build` "
-            "(there is no fallback path)")
+    for path in (LIB_PATH, CALL_PATH):
+        if not os.path.exists(path):
+            raise ImportError(
+                f"{path} is missing: build it with `python -m paper_1801_08058_amd.build` "
+                "(there is no fallback path)")
     # PyTorch supplies device memory and streams and ships its own HIP runtime under the same
     # soname as the system one; the process must end up with ONE runtime, and it has to be the
     # one torch initialises, so torch is loaded first when it is installed.
@@ -149,18 +152,22 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 
 
+def _load_calls():
+    from . import _pycall
+    for name in _pycall.names():
+        _pycall.bind(name, ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value)
+    return _pycall
+
+
+_call = _load_calls()
+
+
 def _ptr(t):
     if t is None:
         return None
     if isinstance(t, int):
         return ctypes.c_void_p(t)
     return ctypes.c_void_p(t.data_ptr())
-
-
-def _nbytes(t) -> int:
-    if t is None or isinstance(t, int):
-        return 0
-    return t.numel() * t.element_size()
 
 
 def _stream(s):
@@ -171,6 +178,10 @@ def _check(status: int, where: str, check: bool) -> int:
     if check and status != NGC_OK:
         raise NgcError(status, where)
     return status
+
+
+def _fail(status: int, where: str):
+    raise NgcError(status, where)
 
 
 def make_desc(n, c, h, w, k, r, s, stride=(1, 1), dilation=(1, 1), pad_below=(0, 0), pad_above=(0, 0),
@@ -212,37 +223,38 @@ def ngc_conv_variant(desc: ngc_conv_desc, op: int) -> str:
 
 
 def ngc_conv_fwd(desc, x, w, bias, y, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_fwd(ctypes.byref(desc), _ptr(x), _ptr(w), _ptr(bias), _ptr(y), _ptr(ws), _nbytes(ws),
-                                    _stream(stream)), "ngc_conv_fwd", check)
+    st = _call.ngc_conv_fwd(desc, x, w, bias, y, ws, stream)
+    return _fail(st, "ngc_conv_fwd") if st and check else st
 
 
 def ngc_conv_bwd_data(desc, dy, w, dx, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_data(ctypes.byref(desc), _ptr(dy), _ptr(w), _ptr(dx), _ptr(ws), _nbytes(ws),
-                                         _stream(stream)), "ngc_conv_bwd_data", check)
+    st = _call.ngc_conv_bwd_data(desc, dy, w, dx, ws, stream)
+    return _fail(st, "ngc_conv_bwd_data") if st and check else st
 
 
 def ngc_conv_bwd_data_relu(desc, dy, w, x_in, dx, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_data_relu(ctypes.byref(desc), _ptr(dy), _ptr(w), _ptr(x_in), _ptr(dx), _ptr(ws),
-                                              _nbytes(ws), _stream(stream)), "ngc_conv_bwd_data_relu", check)
+    st = _call.ngc_conv_bwd_data_relu(desc, dy, w, x_in, dx, ws, stream)
+    return _fail(st, "ngc_conv_bwd_data_relu") if st and check else st
 
 
 def ngc_conv_bwd_data_relu_db(desc, dy, w, x_in, dx, db, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_data_relu_db(ctypes.byref(desc), _ptr(dy), _ptr(w), _ptr(x_in), _ptr(dx), _ptr(db),
-                                                 _ptr(ws), _nbytes(ws), _stream(stream)), "ngc_conv_bwd_data_relu_db", check)
+    st = _call.ngc_conv_bwd_data_relu_db(desc, dy, w, x_in, dx, db, ws, stream)
+    return _fail(st, "ngc_conv_bwd_data_relu_db") if st and check else st
 
 
 def ngc_bias_grad(desc, dy, db, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_bias_grad(ctypes.byref(desc), _ptr(dy), _ptr(db), _ptr(ws), _nbytes(ws),
-                                     _stream(stream)), "ngc_bias_grad", check)
+    st = _call.ngc_bias_grad(desc, dy, db, ws, stream)
+    return _fail(st, "ngc_bias_grad") if st and check else st
 
 
 def ngc_softmax(dtype, rows, cols, x, y, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_softmax(dtype, rows, cols, _ptr(x), _ptr(y), _stream(stream)), "ngc_softmax", check)
+    st = _call.ngc_softmax(dtype, rows, cols, x, y, stream)
+    return _fail(st, "ngc_softmax") if st and check else st
 
 
 def ngc_softmax_bwd(dtype, rows, cols, y, dy, dx, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_softmax_bwd(dtype, rows, cols, _ptr(y), _ptr(dy), _ptr(dx), _stream(stream)),
-                  "ngc_softmax_bwd", check)
+    st = _call.ngc_softmax_bwd(dtype, rows, cols, y, dy, dx, stream)
+    return _fail(st, "ngc_softmax_bwd") if st and check else st
 
 
 def ngc_softmax_variant(dtype, cols, bwd=False) -> str:
@@ -250,23 +262,23 @@ def ngc_softmax_variant(dtype, cols, bwd=False) -> str:
 
 
 def ngc_conv_bwd_filters(desc, x, dy, dw, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_filters(ctypes.byref(desc), _ptr(x), _ptr(dy), _ptr(dw), _ptr(ws), _nbytes(ws),
-                                            _stream(stream)), "ngc_conv_bwd_filters", check)
+    st = _call.ngc_conv_bwd_filters(desc, x, dy, dw, ws, stream)
+    return _fail(st, "ngc_conv_bwd_filters") if st and check else st
 
 
 def ngc_conv_bwd_data_filters(desc, x, dy, w, dx, dw, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_data_filters(ctypes.byref(desc), _ptr(x), _ptr(dy), _ptr(w), _ptr(dx), _ptr(dw), _ptr(ws),
-                                                 _nbytes(ws), _stream(stream)), "ngc_conv_bwd_data_filters", check)
+    st = _call.ngc_conv_bwd_data_filters(desc, x, dy, w, dx, dw, ws, stream)
+    return _fail(st, "ngc_conv_bwd_data_filters") if st and check else st
 
 
 def ngc_conv_bwd_data_filters_relu(desc, x, dy, w, dx, dw, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_data_filters_relu(ctypes.byref(desc), _ptr(x), _ptr(dy), _ptr(w), _ptr(dx), _ptr(dw), _ptr(ws),
-                                                      _nbytes(ws), _stream(stream)), "ngc_conv_bwd_data_filters_relu", check)
+    st = _call.ngc_conv_bwd_data_filters_relu(desc, x, dy, w, dx, dw, ws, stream)
+    return _fail(st, "ngc_conv_bwd_data_filters_relu") if st and check else st
 
 
 def ngc_conv_bwd_filters_noalloc(desc, x, dy, dw, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv_bwd_filters_noalloc(ctypes.byref(desc), _ptr(x), _ptr(dy), _ptr(dw), _stream(stream)),
-                  "ngc_conv_bwd_filters_noalloc", check)
+    st = _call.ngc_conv_bwd_filters_noalloc(desc, x, dy, dw, stream)
+    return _fail(st, "ngc_conv_bwd_filters_noalloc") if st and check else st
 
 
 def ngc_reload_switches() -> None:
@@ -278,8 +290,8 @@ def ngc_static_scratch_bytes() -> int:
 
 
 def ngc_layout_convert(dtype, n, c, h, w, src, src_layout, dst, dst_layout, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_layout_convert(dtype, n, c, h, w, _ptr(src), src_layout, _ptr(dst), dst_layout,
-                                          _stream(stream)), "ngc_layout_convert", check)
+    st = _call.ngc_layout_convert(dtype, n, c, h, w, src, src_layout, dst, dst_layout, stream)
+    return _fail(st, "ngc_layout_convert") if st and check else st
 
 
 def ngc_filter_convert(desc, w_kcrs, w_blocked, dst_layout, stream=None, check: bool = True) -> int:
@@ -323,18 +335,18 @@ def ngc_conv3d_variant(desc: ngc_conv3d_desc, op: int) -> str:
 
 
 def ngc_conv3d_fwd(desc, x, w, bias, y, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv3d_fwd(ctypes.byref(desc), _ptr(x), _ptr(w), _ptr(bias), _ptr(y), _ptr(ws), _nbytes(ws),
-                                      _stream(stream)), "ngc_conv3d_fwd", check)
+    st = _call.ngc_conv3d_fwd(desc, x, w, bias, y, ws, stream)
+    return _fail(st, "ngc_conv3d_fwd") if st and check else st
 
 
 def ngc_conv3d_bwd_data(desc, dy, w, dx, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv3d_bwd_data(ctypes.byref(desc), _ptr(dy), _ptr(w), _ptr(dx), _ptr(ws), _nbytes(ws),
-                                           _stream(stream)), "ngc_conv3d_bwd_data", check)
+    st = _call.ngc_conv3d_bwd_data(desc, dy, w, dx, ws, stream)
+    return _fail(st, "ngc_conv3d_bwd_data") if st and check else st
 
 
 def ngc_conv3d_bwd_filters(desc, x, dy, dw, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv3d_bwd_filters(ctypes.byref(desc), _ptr(x), _ptr(dy), _ptr(dw), _ptr(ws), _nbytes(ws),
-                                              _stream(stream)), "ngc_conv3d_bwd_filters", check)
+    st = _call.ngc_conv3d_bwd_filters(desc, x, dy, dw, ws, stream)
+    return _fail(st, "ngc_conv3d_bwd_filters") if st and check else st
 
 
 def ngc_conv3d_filter_convert(desc, w_kctrs, w_blocked, dst_layout, stream=None, check: bool = True) -> int:
@@ -343,15 +355,15 @@ def ngc_conv3d_filter_convert(desc, w_kctrs, w_blocked, dst_layout, stream=None,
 
 
 def ngc_conv3d_bwd_data_relu(desc, dy, w, x_in, dx, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv3d_bwd_data_relu(ctypes.byref(desc), _ptr(dy), _ptr(w), _ptr(x_in), _ptr(dx), _ptr(ws),
-                                                _nbytes(ws), _stream(stream)), "ngc_conv3d_bwd_data_relu", check)
+    st = _call.ngc_conv3d_bwd_data_relu(desc, dy, w, x_in, dx, ws, stream)
+    return _fail(st, "ngc_conv3d_bwd_data_relu") if st and check else st
 
 
 def ngc_conv3d_bwd_data_relu_db(desc, dy, w, x_in, dx, db, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv3d_bwd_data_relu_db(ctypes.byref(desc), _ptr(dy), _ptr(w), _ptr(x_in), _ptr(dx), _ptr(db),
-                                                   _ptr(ws), _nbytes(ws), _stream(stream)), "ngc_conv3d_bwd_data_relu_db", check)
+    st = _call.ngc_conv3d_bwd_data_relu_db(desc, dy, w, x_in, dx, db, ws, stream)
+    return _fail(st, "ngc_conv3d_bwd_data_relu_db") if st and check else st
 
 
 def ngc_conv3d_bias_grad(desc, dy, db, ws=None, stream=None, check: bool = True) -> int:
-    return _check(_lib.ngc_conv3d_bias_grad(ctypes.byref(desc), _ptr(dy), _ptr(db), _ptr(ws), _nbytes(ws),
-                                            _stream(stream)), "ngc_conv3d_bias_grad", check)
+    st = _call.ngc_conv3d_bias_grad(desc, dy, db, ws, stream)
+    return _fail(st, "ngc_conv3d_bias_grad") if st and check else st

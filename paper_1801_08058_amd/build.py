@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libngconv.so")
+CALL = os.path.join(HERE, "_pycall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "layout.hip", "conv_direct.hip", "conv_gather.hip", "conv_igemm.hip", "conv_strip.hip", "conv_rows.hip", "conv_strip3.hip", "conv_stem.hip", "wgrad.hip", "wgrad_strip.hip", "wgrad_stem.hip", "wgrad_gemm.hip", "conv_gemm1x1.hip", "bias_grad.hip", "softmax.hip", "conv3d_direct.hip", "api3d.hip", "static_scratch.hip", "switches.hip", "bwd1x1_fused.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -51,8 +53,19 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_calls() -> None:
+    """The CPython extension behind binding.py (host C, no library to link: binding.py hands it the addresses)."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pycall.c"), "-o", CALL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the compiler failed on pycall.c:\n" + r.stderr)
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every HIP source for gfx950 and link libngconv.so next to this file."""
+    """Compile every HIP source for gfx950, link libngconv.so and build the binding's extension, next to this file."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
@@ -60,6 +73,7 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _build_calls()
     if verbose:
         print("built", LIB)
     return LIB
