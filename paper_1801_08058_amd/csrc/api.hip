@@ -1926,8 +1926,7 @@ int softmax_impl(int32_t dtype, int64_t rows, int32_t cols, bool bwd, const void
     const uintptr_t esz = dtype == NGC_BF16 ? 2 : 4;
     const uintptr_t all = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(out) | (bwd ? reinterpret_cast<uintptr_t>(b) : 0);
     if (all & (esz - 1)) return NGC_BAD_ARG;
-    const int V = softmax_vectors(dtype, cols, bwd, (all & 15) == 0);
-    return launch_status(launch_softmax(dtype, bwd, a, b, out, (uint32_t)rows, cols, V, static_cast<hipStream_t>(hip_stream)));
+    return launch_status(launch_softmax(dtype, bwd, a, b, out, (uint32_t)rows, cols, (all & 15) == 0, static_cast<hipStream_t>(hip_stream)));
 }
 
 }  // namespace

@@ -603,7 +603,7 @@ hipError_t launch_direct3_bwd_filters(const ngc_conv3d_desc &d, int O, int P, in
                                       hipStream_t st);
 int gemm1x1_dbp_tile_m(const Gemm1x1Params &p);
 int softmax_vectors(int dtype, int cols, bool bwd, bool aligned);
-hipError_t launch_softmax(int dtype, bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, int V,
+hipError_t launch_softmax(int dtype, bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, bool aligned,
                           hipStream_t st);
 hipError_t launch_bias_grad(const ngc_conv_desc &d, int P, int Q, const void *dy, float *db, float *partial, int nparts,
                             hipStream_t st);

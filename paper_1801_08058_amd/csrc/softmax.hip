@@ -5,13 +5,16 @@
 //   y[i][j]  = exp(x[i][j] - m_i) / sum_k exp(x[i][k] - m_i),  m_i = max_k x[i][k]
 //   dx[i][j] = y[i][j] * (dy[i][j] - sum_k dy[i][k] y[i][k])
 //
-// Bound: HBM (each tensor once).  The row lives in registers: a thread keeps V 16-byte vectors of
-// it (all loads of the row are in flight at once), the row maximum and sum are butterfly
-// reductions over the 64 lanes of a wave (rows of up to 4 vectors per lane) or, for longer rows,
-// over the 256 threads of a workgroup through LDS; results leave as 16-byte stores - one read and
-// one write of the row, fp32 arithmetic, one rounding.  Rows too long for the registers (or not
-// 16-byte aligned) take a workgroup-per-row kernel that walks the row three (backprop: two) times
-// element by element.
+// Bound: HBM (each tensor once).  A row lives in registers as vectors of 16 bytes, all of its loads in flight at once.  It
+// belongs to a group of GL lanes: 8, 16, 32 or 64 lanes of a wave (butterfly reductions) or a workgroup of 256 or 1024
+// (through LDS); a group of the row's own size keeps the lanes busy (rows of 100 elements with a wave each ran at 0.43 TB/s).
+// Results leave as 16-byte stores - one read and one write of the row, fp32 arithmetic, one rounding.
+//
+// Row lengths that are no multiple of 16 bytes use the same kernel: the rows then start anywhere and the vectors are read
+// and written unaligned; the last one is the last 16 bytes of the row, and its elements that the vector before it also holds
+// are left out of the sums (both lanes store the same values).  Rows beyond the registers are walked twice: the maximum and
+// the sum of a thread's part in one pass (rescaled when the maximum grows), the results in the second.  Rows below 16 bytes
+// take one thread each.
 #include "common.h"
 
 #include <math.h>
@@ -55,16 +58,18 @@ template <> struct SmElem<float> {
     __device__ static float exp_of(float d) { return expf(d); }
 };
 
-__device__ __forceinline__ float wave_max(float v)
+template <int GL>
+__device__ __forceinline__ float group_max(float v)
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    for (int o = GL / 2; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
 }
-__device__ __forceinline__ float wave_sum(float v)
+template <int GL>
+__device__ __forceinline__ float group_sum(float v)
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);       // butterfly: every lane ends with the same sum
+    for (int o = GL / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);   // butterfly: every lane ends with the same sum
     return v;
 }
 
@@ -72,7 +77,7 @@ __device__ __forceinline__ float wave_sum(float v)
 template <int NW>
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float *sm)
 {
-    v = is_max ? wave_max(v) : wave_sum(v);
+    v = is_max ? group_max<64>(v) : group_sum<64>(v);
     const int wave = threadIdx.x >> 6;
     __syncthreads();                                                     // sm may still be read from the last call
     if ((threadIdx.x & 63) == 0) sm[wave] = v;
@@ -83,104 +88,206 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float *sm)
     return r;
 }
 
-// The row in registers: V vectors of 16 bytes per thread, NT = 64 threads (one wave per row, 4 rows per
-// workgroup) or 256 / 1024 (one workgroup per row, reductions through LDS): cols <= NT * E * V,
-// cols % E == 0, 16-byte aligned tensors.  BWD: a = y, b = dy, out = dx; else a = x, out = y (b unused).
-template <typename T, int V, bool BWD, int NT>
-__global__ __launch_bounds__(NT == 64 ? 256 : NT) void softmax_rows_reg(const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out,
+// 16 bytes at any element address
+template <typename T>
+__device__ __forceinline__ uint4 load16_any(const T *p)
+{
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ void store16_any(T *p, uint4 v)
+{
+    typedef unsigned u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+    const u32x4_any w = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any *>(p));
+}
+
+// A long bf16 row stays packed between the passes over it: unpacked (and its exponentials taken) again instead of kept as
+// floats, so that twice as many rows are in flight on a compute unit (1047 x 32029: 36.2 -> 30.3 us).  fp32 exponentials
+// replace the elements; of a short bf16 row they are kept (32768 x 1000: 20.1 us against 21.6 us).
+template <int N> __device__ __forceinline__ void keep_packed(uint4 (&v)[N])
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(v[j].x), "+v"(v[j].y), "+v"(v[j].z), "+v"(v[j].w));
+}
+
+// The row in registers: V vectors per lane of a group of GL lanes: E <= cols <= GL * E * V.  TAIL: cols is no multiple of E
+// or the tensors are off the 16-byte grid.  BWD: a = y, b = dy, out = dx; else a = x, out = y (b unused).
+template <typename T, int V, bool BWD, int GL, bool TAIL>
+__global__ __launch_bounds__(GL <= 64 ? 256 : GL) void softmax_rows_reg(const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out,
                                                         uint32_t rows, int cols)
 {
     constexpr int E = SmElem<T>::E;
-    constexpr int NW = NT == 64 ? 1 : NT / 64;
+    constexpr int NW = GL <= 64 ? 1 : GL / 64;
     __shared__ float sm[NW];
-    const int lane = threadIdx.x & (NT - 1);
-    const uint32_t row = NT == 64 ? blockIdx.x * 4 + (threadIdx.x >> 6) : blockIdx.x;
-    if (row >= rows) return;                                             // wave-uniform (NT == 64 only)
-    const size_t base = (size_t)row * cols;
-    const int nvec = cols / E;
-    float va[V][E], vb[BWD ? V : 1][E];
+    const int lane = threadIdx.x & (GL - 1);
+    const uint32_t row = GL <= 64 ? blockIdx.x * (256 / GL) + threadIdx.x / GL : blockIdx.x;
+    const bool live = row < rows;                                        // groups past the end stay for the lane exchanges
+    const size_t base = (size_t)(live ? row : 0) * cols;
+    const int nvec = TAIL ? (cols + E - 1) / E : cols / E;
+    auto first = [&](int vi) { return TAIL && vi * E + E > cols ? cols - E : vi * E; };     // first element of a vector
+    uint4 va[V], vb[BWD ? V : 1];
 #pragma unroll
     for (int j = 0; j < V; ++j) {
-        const int vi = j * NT + lane;
+        const int vi = j * GL + lane;
+        va[j] = make_uint4(0, 0, 0, 0);
+        if (BWD) vb[BWD ? j : 0] = va[j];
         if (vi < nvec) {
-            SmElem<T>::unpack(*reinterpret_cast<const uint4 *>(a + base + (size_t)vi * E), va[j]);
-            if (BWD) SmElem<T>::unpack(*reinterpret_cast<const uint4 *>(b + base + (size_t)vi * E), vb[BWD ? j : 0]);
-        } else {
+            va[j] = load16_any(a + base + first(vi));
+            if (BWD) vb[BWD ? j : 0] = load16_any(b + base + first(vi));
+        }
+    }
+    auto counts = [&](int vi, int e) { return vi < nvec && (!TAIL || e >= vi * E + E - cols); };   // not held by the vector before
+    auto group = [&](float v, bool is_max) {
+        if constexpr (GL <= 64) return is_max ? group_max<GL>(v) : group_sum<GL>(v);
+        else return block_reduce<NW>(v, is_max, sm);
+    };
+    constexpr bool PACKED = sizeof(T) == 2 && V > 2, KEEP = !BWD && !PACKED;
+    float m = -INFINITY, s = 0.f, ex[KEEP ? V : 1][E];
+    if (BWD) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float fa[E], fb[E];
+            SmElem<T>::unpack(va[j], fa);
+            SmElem<T>::unpack(vb[BWD ? j : 0], fb);
+#pragma unroll
+            for (int e = 0; e < E; ++e) s += !TAIL || counts(j * GL + lane, e) ? fa[e] * fb[e] : 0.f;   // zeros past the end
+        }
+        if (PACKED) {
+            keep_packed(va);
+            keep_packed(vb);
+        }
+        s = group(s, false);
+    } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float f[E];
+            SmElem<T>::unpack(va[j], f);
+#pragma unroll
+            for (int e = 0; e < E; ++e) m = fmaxf(m, j * GL + lane < nvec ? f[e] : -INFINITY);
+        }
+        if (PACKED) keep_packed(va);
+        m = group(m, true);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float f[E];
+            SmElem<T>::unpack(va[j], f);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                va[j][e] = BWD ? 0.f : -INFINITY;                         // exp(-inf - m) = 0; 0 * dy = 0
-                if (BWD) vb[BWD ? j : 0][e] = 0.f;
+                const float v = SmElem<T>::exp_of(f[e] - m);
+                if (KEEP) ex[KEEP ? j : 0][e] = v;
+                s += counts(j * GL + lane, e) ? v : 0.f;
+            }
+        }
+        if (PACKED) keep_packed(va);
+        s = group(s, false);
+    }
+    if (!live) return;
+    const float inv = 1.0f / s;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        const int vi = j * GL + lane;
+        if (vi >= nvec) continue;
+        float f[E], fb[E];
+        SmElem<T>::unpack(va[j], f);
+        if (BWD) SmElem<T>::unpack(vb[BWD ? j : 0], fb);
+#pragma unroll
+        for (int e = 0; e < E; ++e) f[e] = BWD ? f[e] * (fb[e] - s) : (KEEP ? ex[KEEP ? j : 0][e] : SmElem<T>::exp_of(f[e] - m)) * inv;
+        if (TAIL) store16_any(out + base + first(vi), SmElem<T>::pack(f));
+        else store16_result(out + base + (size_t)vi * E, SmElem<T>::pack(f), true);
+    }
+}
+
+// Rows of any length >= E: one workgroup of 1024 threads per row, two passes over it.
+template <typename T, bool BWD>
+__global__ __launch_bounds__(1024) void softmax_rows_long(const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out,
+                                                          uint32_t rows, int cols)
+{
+    constexpr int E = SmElem<T>::E;
+    __shared__ float sm[16];
+    const size_t base = (size_t)blockIdx.x * cols;
+    const int nvec = (cols + E - 1) / E;
+    auto first = [&](int vi) { return vi * E + E > cols ? cols - E : vi * E; };
+    float m = -INFINITY, s = 0.f;
+#pragma unroll 4
+    for (int vi = threadIdx.x; vi < nvec; vi += 1024) {
+        float f[E], fb[E];
+        SmElem<T>::unpack(load16_any(a + base + first(vi)), f);
+        if (BWD) {
+            SmElem<T>::unpack(load16_any(b + base + first(vi)), fb);
+#pragma unroll
+            for (int e = 0; e < E; ++e) s += e >= vi * E + E - cols ? f[e] * fb[e] : 0.f;
+        } else {
+            float top = f[0];
+#pragma unroll
+            for (int e = 1; e < E; ++e) top = fmaxf(top, f[e]);
+            if (top > m) {
+                s *= SmElem<T>::exp_of(m - top);                         // exp(-inf) = 0 the first time
+                m = top;
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) s += e >= vi * E + E - cols ? SmElem<T>::exp_of(f[e] - m) : 0.f;
+        }
+    }
+    if (!BWD) {
+        const float mine = m;
+        m = block_reduce<16>(m, true, sm);
+        s *= mine > -INFINITY ? SmElem<T>::exp_of(mine - m) : 0.f;
+    }
+    s = block_reduce<16>(s, false, sm);
+    const float inv = 1.0f / s;
+    // The last vector may overlap the one before it, which another thread writes: where out is one of the inputs
+    // (in place), its elements are stored one by one, only those that are its own.
+#pragma unroll 4
+    for (int vi = threadIdx.x; vi < nvec; vi += 1024) {
+        const int own = vi * E;
+        float f[E], fb[E];
+        if (own + E <= cols) {
+            SmElem<T>::unpack(load16_any(a + base + own), f);
+            if (BWD) SmElem<T>::unpack(load16_any(b + base + own), fb);
+#pragma unroll
+            for (int e = 0; e < E; ++e) f[e] = BWD ? f[e] * (fb[e] - s) : SmElem<T>::exp_of(f[e] - m) * inv;
+            store16_any(out + base + own, SmElem<T>::pack(f));
+        } else {
+            for (int j = own; j < cols; ++j) {
+                const float v = SmElem<T>::load(a + base + j);
+                SmElem<T>::store(out + base + j, BWD ? v * (SmElem<T>::load(b + base + j) - s) : SmElem<T>::exp_of(v - m) * inv);
             }
         }
     }
-    if (BWD) {
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-#pragma unroll
-            for (int e = 0; e < E; ++e) s += va[j][e] * vb[BWD ? j : 0][e];
-        s = NT == 64 ? wave_sum(s) : block_reduce<NW>(s, false, sm);
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-#pragma unroll
-            for (int e = 0; e < E; ++e) va[j][e] = va[j][e] * (vb[BWD ? j : 0][e] - s);
-    } else {
-        float m = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-#pragma unroll
-            for (int e = 0; e < E; ++e) m = fmaxf(m, va[j][e]);
-        m = NT == 64 ? wave_max(m) : block_reduce<NW>(m, true, sm);
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                va[j][e] = SmElem<T>::exp_of(va[j][e] - m);
-                s += va[j][e];
-            }
-        s = NT == 64 ? wave_sum(s) : block_reduce<NW>(s, false, sm);
-        const float inv = 1.0f / s;
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-#pragma unroll
-            for (int e = 0; e < E; ++e) va[j][e] *= inv;
-    }
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-        const int vi = j * NT + lane;
-        if (vi < nvec) store16_result(out + base + (size_t)vi * E, SmElem<T>::pack(va[j]), true);
-    }
 }
 
-// Any cols / alignment: one workgroup per row, element-wise passes (the row comes from L2 after the first).
+// Rows below one vector: a thread per row.
 template <typename T, bool BWD>
-__global__ __launch_bounds__(256) void softmax_rows_block(const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out,
-                                                          uint32_t rows, int cols)
+__global__ __launch_bounds__(256) void softmax_rows_tiny(const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out,
+                                                         uint32_t rows, int cols)
 {
-    __shared__ float sm[4];
-    const size_t base = (size_t)blockIdx.x * cols;
-    const int tid = threadIdx.x;
-    if (BWD) {
-        float s = 0.f;
-        for (int j = tid; j < cols; j += 256) s += SmElem<T>::load(a + base + j) * SmElem<T>::load(b + base + j);
-        s = block_reduce<4>(s, false, sm);
-        for (int j = tid; j < cols; j += 256)
-            SmElem<T>::store(out + base + j, SmElem<T>::load(a + base + j) * (SmElem<T>::load(b + base + j) - s));
-        return;
+    constexpr int E = SmElem<T>::E;
+    const uint32_t row = blockIdx.x * 256 + threadIdx.x;
+    if (row >= rows) return;
+    const size_t base = (size_t)row * cols;
+    float f[E], fb[E], m = -INFINITY, s = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        f[e] = e < cols ? SmElem<T>::load(a + base + e) : BWD ? 0.f : -INFINITY;
+        fb[e] = BWD && e < cols ? SmElem<T>::load(b + base + e) : 0.f;
+        m = fmaxf(m, f[e]);
     }
-    float m = -INFINITY;
-    for (int j = tid; j < cols; j += 256) m = fmaxf(m, SmElem<T>::load(a + base + j));
-    m = block_reduce<4>(m, true, sm);
-    float s = 0.f;
-    for (int j = tid; j < cols; j += 256) s += SmElem<T>::exp_of(SmElem<T>::load(a + base + j) - m);
-    s = block_reduce<4>(s, false, sm);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (!BWD) f[e] = SmElem<T>::exp_of(f[e] - m);
+        s += BWD ? f[e] * fb[e] : f[e];
+    }
     const float inv = 1.0f / s;
-    for (int j = tid; j < cols; j += 256) SmElem<T>::store(out + base + j, SmElem<T>::exp_of(SmElem<T>::load(a + base + j) - m) * inv);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e < cols) SmElem<T>::store(out + base + e, BWD ? f[e] * (fb[e] - s) : f[e] * inv);
 }
 
-// Kernel choice for a row length: V = vectors per thread of the register-resident kernels (one wave per row,
-// or 256 + V / 1024 + V: one workgroup of that many threads per row), 0 = the element-wise kernel.
+// Kernel choice for a row length: 0 = rows off the 16-byte grid or longer than the registers of 1024 threads with 4 vectors
+// each, else the vectors per thread: V (at most 64 lanes per row), 256 + V or 1024 + V (a workgroup of that many threads).
 int softmax_vectors(int dtype, int cols, bool bwd, bool aligned)
 {
     const int E = dtype == NGC_BF16 ? 8 : 4;
@@ -196,34 +303,46 @@ int softmax_vectors(int dtype, int cols, bool bwd, bool aligned)
     return 0;
 }
 
-template <typename T, bool BWD>
-static hipError_t launch_softmax_t(const T *a, const T *b, T *out, uint32_t rows, int cols, int V, hipStream_t st)
+template <typename T, bool BWD, bool TAIL>
+static hipError_t launch_softmax_t(const T *a, const T *b, T *out, uint32_t rows, int cols, hipStream_t st)
 {
-    const dim3 grid_w((rows + 3) / 4), grid_r(rows), block(256);
-    switch (V) {
-    case 1: NGC_LAUNCH((softmax_rows_reg<T, 1, BWD, 64>), grid_w, block, 0, st, a, b, out, rows, cols); break;
-    case 2: NGC_LAUNCH((softmax_rows_reg<T, 2, BWD, 64>), grid_w, block, 0, st, a, b, out, rows, cols); break;
-    case 4: NGC_LAUNCH((softmax_rows_reg<T, 4, BWD, 64>), grid_w, block, 0, st, a, b, out, rows, cols); break;
-    case 256 + 2: NGC_LAUNCH((softmax_rows_reg<T, 2, BWD, 256>), grid_r, block, 0, st, a, b, out, rows, cols); break;
-    case 256 + 4: NGC_LAUNCH((softmax_rows_reg<T, 4, BWD, 256>), grid_r, block, 0, st, a, b, out, rows, cols); break;
-    case 1024 + 2: NGC_LAUNCH((softmax_rows_reg<T, 2, BWD, 1024>), grid_r, dim3(1024), 0, st, a, b, out, rows, cols); break;
-    case 1024 + 4: NGC_LAUNCH((softmax_rows_reg<T, 4, BWD, 1024>), grid_r, dim3(1024), 0, st, a, b, out, rows, cols); break;
-    case 0: NGC_LAUNCH((softmax_rows_block<T, BWD>), grid_r, block, 0, st, a, b, out, rows, cols); break;
-    default: return hipErrorInvalidValue;
-    }
+    constexpr int E = SmElem<T>::E;
+    const int nvec = (cols + E - 1) / E;
+#define NGC_SM_WAVE(V, GL) NGC_LAUNCH((softmax_rows_reg<T, V, BWD, GL, TAIL>), dim3((rows + 256 / (GL) - 1) / (256 / (GL))), dim3(256), 0, st, a, b, out, rows, cols)
+#define NGC_SM_WG(V, GL) NGC_LAUNCH((softmax_rows_reg<T, V, BWD, GL, TAIL>), dim3(rows), dim3(GL), 0, st, a, b, out, rows, cols)
+    if (cols < E) NGC_LAUNCH((softmax_rows_tiny<T, BWD>), dim3((rows + 255) / 256), dim3(256), 0, st, a, b, out, rows, cols);
+    else if (nvec <= 8) NGC_SM_WAVE(1, 8);
+    else if (nvec <= 16) NGC_SM_WAVE(1, 16);
+    else if (nvec <= 32) NGC_SM_WAVE(1, 32);
+    else if (nvec <= 64) NGC_SM_WAVE(1, 64);
+    else if (nvec <= 128) NGC_SM_WAVE(2, 64);
+    else if (nvec <= 256) NGC_SM_WAVE(4, 64);
+    else if (nvec <= 512) NGC_SM_WG(2, 256);
+    else if (nvec <= 1024) NGC_SM_WG(4, 256);
+    else if (nvec <= 2048) NGC_SM_WG(2, 1024);
+    else if (nvec <= 4096) NGC_SM_WG(4, 1024);
+    else if (nvec <= 8192 && !(BWD && sizeof(T) == 2)) {                 // bf16 backprop: two tensors unpacked do not fit
+        if constexpr (!(BWD && sizeof(T) == 2)) NGC_SM_WG(8, 1024);
+    } else NGC_LAUNCH((softmax_rows_long<T, BWD>), dim3(rows), dim3(1024), 0, st, a, b, out, rows, cols);
+#undef NGC_SM_WAVE
+#undef NGC_SM_WG
     return ngc::launch_result();
 }
 
-hipError_t launch_softmax(int dtype, bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, int V, hipStream_t st)
+template <typename T>
+static hipError_t launch_softmax_e(bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, bool grid16, hipStream_t st)
 {
-    if (dtype == NGC_BF16) {
-        const uint16_t *pa = static_cast<const uint16_t *>(a), *pb = static_cast<const uint16_t *>(b);
-        return bwd ? launch_softmax_t<uint16_t, true>(pa, pb, static_cast<uint16_t *>(out), rows, cols, V, st)
-                   : launch_softmax_t<uint16_t, false>(pa, pb, static_cast<uint16_t *>(out), rows, cols, V, st);
-    }
-    const float *pa = static_cast<const float *>(a), *pb = static_cast<const float *>(b);
-    return bwd ? launch_softmax_t<float, true>(pa, pb, static_cast<float *>(out), rows, cols, V, st)
-               : launch_softmax_t<float, false>(pa, pb, static_cast<float *>(out), rows, cols, V, st);
+    const T *pa = static_cast<const T *>(a), *pb = static_cast<const T *>(b);
+    T *po = static_cast<T *>(out);
+    if (bwd) return grid16 ? launch_softmax_t<T, true, false>(pa, pb, po, rows, cols, st) : launch_softmax_t<T, true, true>(pa, pb, po, rows, cols, st);
+    return grid16 ? launch_softmax_t<T, false, false>(pa, pb, po, rows, cols, st) : launch_softmax_t<T, false, true>(pa, pb, po, rows, cols, st);
+}
+
+hipError_t launch_softmax(int dtype, bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, bool aligned, hipStream_t st)
+{
+    const bool grid16 = aligned && cols % (dtype == NGC_BF16 ? 8 : 4) == 0;
+    return dtype == NGC_BF16 ? launch_softmax_e<uint16_t>(bwd, a, b, out, rows, cols, grid16, st)
+                             : launch_softmax_e<float>(bwd, a, b, out, rows, cols, grid16, st);
 }
 
 }  // namespace ngc

@@ -137,3 +137,14 @@ def test_softmax_workloads_full_size_sampled_rows(idx):
     ref_dx = oracle.softmax_bwd(y[rows], t["dy"][rows])
     assert np.abs(dx[rows] - ref_dx).max() / np.abs(ref_dx).max() <= tol
     assert np.abs(y.sum(axis=-1) - 1.0).max() <= (2e-2 if c.dtype == "bf16" else 1e-4)
+
+
+# every group width of a row, one vector less and more than it holds, lengths off the 16-byte grid, rows below one vector,
+# the two-pass kernel for the longest rows, several rows per wave with a ragged last group
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,cols", [(37, 3), (33, 7), (35, 9), (70, 63), (70, 64), (33, 65), (17, 127), (9, 129), (5, 511), (3, 2047), (3, 2049),
+                                       (2, 8191), (2, 16385), (2, 32767), (2, 40001), (2, 65535), (1, 65537)])
+def test_softmax_group_widths_and_tails(dtype, rows, cols):
+    x, dy = _inputs(rows, cols, dtype, 900 + rows * 7 + cols)
+    _check(x, dy, dtype)
+    _check(x, dy, dtype, offset=1, in_place=True)
