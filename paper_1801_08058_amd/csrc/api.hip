@@ -11,35 +11,18 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include <unordered_map>
+#include "plan_cache.h"
 
 using namespace ngc;
 
 namespace {
 
-// ---- plan cache -------------------------------------------------------------------------------------------
-// Planning a launch (kernel selection, strip / tile geometry, split of a reduction) is a pure function of the
-// descriptor, a few integers and the environment switches.  Each planning function below keeps what it
-// computed per thread, keyed by its arguments, so that the second call with a descriptor costs a few table
-// look-ups instead of the geometry loops; ngc_reload_switches() invalidates everything.
+// ---- plan cache (plan_cache.h), keyed by the descriptor and a few integers
 struct PlanKey {
     ngc_conv_desc d;
     int32_t a[4];
 };
 static_assert(sizeof(PlanKey) == 24 * sizeof(int32_t), "hashed and compared as 24 words, no padding");
-
-struct PlanKeyHash {
-    size_t operator()(const PlanKey &k) const
-    {
-        const uint32_t *w = reinterpret_cast<const uint32_t *>(&k);
-        uint64_t h = 0xcbf29ce484222325ull;
-        for (int i = 0; i < 24; ++i) h = (h ^ w[i]) * 0x100000001b3ull;
-        return (size_t)(h ^ (h >> 29));
-    }
-};
-struct PlanKeyEq {
-    bool operator()(const PlanKey &x, const PlanKey &y) const { return memcmp(&x, &y, sizeof(PlanKey)) == 0; }
-};
 
 PlanKey plan_key(const ngc_conv_desc *d, int a0 = 0, int a1 = 0, int a2 = 0, int a3 = 0)
 {
@@ -50,24 +33,7 @@ PlanKey plan_key(const ngc_conv_desc *d, int a0 = 0, int a1 = 0, int a2 = 0, int
 }
 
 template <class V>
-struct PlanCache {
-    std::unordered_map<PlanKey, V, PlanKeyHash, PlanKeyEq> map;
-    uint32_t epoch = 0xFFFFFFFFu;
-    V *find(const PlanKey &k)
-    {
-        if (epoch != sw_epoch()) {
-            map.clear();
-            epoch = sw_epoch();
-        }
-        auto it = map.find(k);
-        return it == map.end() ? nullptr : &it->second;
-    }
-    V &put(const PlanKey &k, const V &v)
-    {
-        if (map.size() >= 2048) map.clear();             // a process cycling through more nodes than that replans
-        return map[k] = v;
-    }
-};
+using PlanCache = KeyedPlanCache<PlanKey, V>;
 
 constexpr size_t MAX_ELEMS = (size_t)1 << 31;
 
@@ -1047,6 +1013,54 @@ bool wgrad_gemm_plan(const ngc_conv_desc *d, int P, int Q, WgradGemmParams *wp)
     return e->ok;
 }
 
+// several taps per pass (blocked nodes of more than one tap); nullptr: the per-tap GEMM.  Valid until the next plan.
+const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q)
+{
+    static thread_local PlanCache<CachedPlan<WgradTapsPlan>> cache;
+    const PlanKey key = plan_key(d);
+    auto *e = cache.find(key);
+    if (!e) {
+        CachedPlan<WgradTapsPlan> v;
+        memset(&v, 0, sizeof(v));
+        constexpr int LIM = 32767;                        // the kernel's arguments hold dimensions in 16 bits
+        if (d->dtype == NGC_BF16 && d->x_layout == NGC_NCHW16C && d->y_layout == NGC_NCHW16C && d->r * d->s > 1 && d->c % 16 == 0 && d->k % 16 == 0 && d->h <= LIM && d->w <= LIM && P <= LIM &&
+            Q <= LIM && d->pad_below_h <= LIM && d->pad_below_w <= LIM && d->c / 16 <= LIM && d->k / 16 <= LIM && d->r * d->s <= 64) {
+            WgradTapsParams &q = v.v.p;
+            q.N = d->n; q.CB = (int16_t)(d->c / 16); q.KB = (int16_t)(d->k / 16);
+            q.D = q.O = q.sd = q.dil_d = q.T = 1;
+            q.H = (int16_t)d->h; q.W = (int16_t)d->w; q.P = (int16_t)P; q.Q = (int16_t)Q;
+            q.sh = (int16_t)d->stride_h; q.sw = (int16_t)d->stride_w;
+            q.dil_h = (int16_t)d->dil_h; q.dil_w = (int16_t)d->dil_w;
+            q.pbh = (int16_t)d->pad_below_h; q.pbw = (int16_t)d->pad_below_w;
+            q.RS = (int8_t)(d->r * d->s); q.S = (int8_t)d->s;
+            v.ok = wgrad_taps_plan(&v.v);
+        }
+        e = &cache.put(key, v);
+    }
+    return e->ok ? &e->v : nullptr;
+}
+
+// A node of the all-taps strip kernel that the general kernel is expected to take less time for: few positions (one
+// part, so no second launch), or so many (k, c) tiles that the strip kernel's fixed tile and split leave compute units
+// idle or write partials needlessly.  The strip kernel's steps address their taps with constants: 0.82 of the cycles a
+// stage.  Measured: 64 -> 64 at 56x56, N = 64 strip 26.6 / general 29.5 us; 4 x 512 -> 512 at 7x7 34.0 / 11.1 us;
+// 16 x 64 x 33 x 47 -> 192 31.1 / 22.9 us; 1 x 64 -> 64 at 14x14 10.8 / 7.0 us.
+const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q)
+{
+    if (env_switch(SW_WGRAD_NCQ) || env_switch(SW_WGRAD_RING) || env_switch(SW_WGRAD_LATE) || env_switch(SW_WGRAD_G1) || env_switch(SW_WGRAD_NT))
+        return nullptr;                                   // a switch that shapes the strip kernel asks for it
+    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q);
+    WgradStripParams q;
+    if (!tp || !wgrad_strip_plan(d, P, Q, &q, nullptr)) return nullptr;
+    double fixed;
+    const double stage = 0.82 * wgrad_stage_cost(4, q.ncq, 9, (q.dyplane - 128) / 1024, (q.xplane - 128) / 1024, q.nring, &fixed);
+    const long tiles = (long)(d->k / 64) * q.ctiles, rounds = (tiles * q.nparts + NUM_CUS - 1) / NUM_CUS;
+    const size_t dw_bytes = (size_t)9 * d->k * d->c * sizeof(float);
+    const long stages = q.G > 1 ? (q.NI + q.G - 1) / q.G : (long)q.NI * q.nstages;
+    const double cost = rounds * (fixed + stages * stage) + wgrad_parts_cost(q.nparts > 1 ? q.nparts : 2, dw_bytes) + dw_bytes / 1600.0;
+    return 1.08 * tp->cost + 6500.0 < cost ? tp : nullptr;      // expected to measured cycles, 8 to 180 thousand of them
+}
+
 bool gemm1x1_plan(const ngc_conv_desc *d, int op, int P, int Q, Gemm1x1Params *gp, bool *zero)
 {
     static thread_local PlanCache<CachedPlan<Gemm1x1Params>> cache;
@@ -1291,11 +1305,13 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         return round256((size_t)d->n * wp.strips * (d->k / 64) * 2 * 4 * 6 * 64 * 16);
     }
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_GEMM) {
+        if (const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q)) return round256(tp->ws + 1);
         WgradGemmParams wp;
         wgrad_gemm_plan(d, P, Q, &wp);
         return round256((size_t)wp.nparts * d->r * d->s * wp.ktiles * wp.ctiles * wp.wk * wp.wc * 64 * 64 * sizeof(float));
     }
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_STRIP) {
+        if (const WgradTapsPlan *tp = wgrad_taps_for_strip(d, P, Q)) return round256(tp->ws + 1);
         WgradStripParams wp;
         wgrad_strip_plan(d, P, Q, &wp, nullptr);
         return round256((size_t)wp.nparts * 9 * d->k * d->c * sizeof(float));
@@ -2034,6 +2050,15 @@ int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *d
 
     const size_t need = workspace_bytes(desc, NGC_OP_BWD_FILTERS, v, P, Q);
     if (!ws || ws_bytes < need) return NGC_WORKSPACE_TOO_SMALL;
+    if (const WgradTapsPlan *tp = v == V_WGRAD_GEMM ? wgrad_taps_plan_of(desc, P, Q)
+                                  : v == V_WGRAD_STRIP ? wgrad_taps_for_strip(desc, P, Q) : nullptr) {
+        WgradTapsPlan pl = *tp;
+        pl.p.x = static_cast<const uint16_t *>(x);
+        pl.p.dy = static_cast<const uint16_t *>(dy);
+        pl.p.partial = static_cast<float *>(ws);
+        pl.p.dw = dw;
+        return launch_status(launch_wgrad_taps(pl, st));
+    }
     if (v == V_WGRAD_GEMM) {
         WgradGemmParams wp;
         if (!wgrad_gemm_plan(desc, P, Q, &wp)) return NGC_UNSUPPORTED;

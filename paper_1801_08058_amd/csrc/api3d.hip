@@ -15,6 +15,7 @@
 #include <cstring>
 
 #include "common.h"
+#include "plan_cache.h"
 
 namespace {
 
@@ -294,6 +295,43 @@ bool wgrad_gemm3_plan(const ngc_conv3d_desc *d, int O, int P, int Q, WgradGemmPa
     return true;
 }
 
+// several taps per pass; false: the per-tap GEMM
+bool wgrad_taps3_plan_uncached(const ngc_conv3d_desc *d, int O, int P, int Q, WgradTapsPlan *out)
+{
+    constexpr int LIM = 32767;                            // the kernel's arguments hold dimensions in 16 bits
+    if (d->d > LIM || d->h > LIM || d->w > LIM || O > LIM || P > LIM || Q > LIM || d->pad_below_d > LIM || d->pad_below_h > LIM ||
+        d->pad_below_w > LIM || d->c / 16 > LIM || d->k / 16 > LIM)
+        return false;
+    memset(out, 0, sizeof(*out));
+    WgradTapsParams &q = out->p;
+    q.N = d->n; q.CB = (int16_t)(d->c / 16); q.KB = (int16_t)(d->k / 16);
+    q.D = (int16_t)d->d; q.H = (int16_t)d->h; q.W = (int16_t)d->w; q.O = (int16_t)O; q.P = (int16_t)P; q.Q = (int16_t)Q;
+    q.sd = (int16_t)d->stride_d; q.sh = (int16_t)d->stride_h; q.sw = (int16_t)d->stride_w;
+    q.dil_d = (int16_t)d->dil_d; q.dil_h = (int16_t)d->dil_h; q.dil_w = (int16_t)d->dil_w;
+    q.pbd = (int16_t)d->pad_below_d; q.pbh = (int16_t)d->pad_below_h; q.pbw = (int16_t)d->pad_below_w;
+    q.RS = (int8_t)(d->r * d->s); q.S = (int8_t)d->s; q.T = (int8_t)d->t;
+    return wgrad_taps_plan(out);
+}
+
+// nullptr: the per-tap GEMM.  Valid until the next plan.
+const WgradTapsPlan *wgrad_taps3_plan(const ngc_conv3d_desc *d, int O, int P, int Q)
+{
+    struct Entry {
+        bool ok;
+        WgradTapsPlan v;
+    };
+    static_assert(sizeof(ngc_conv3d_desc) % 4 == 0, "hashed as words");
+    static thread_local KeyedPlanCache<ngc_conv3d_desc, Entry> cache;
+    Entry *e = cache.find(*d);
+    if (!e) {
+        Entry v;
+        memset(&v, 0, sizeof(v));
+        v.ok = wgrad_taps3_plan_uncached(d, O, P, Q, &v.v);
+        e = &cache.put(*d, v);
+    }
+    return e->ok ? &e->v : nullptr;
+}
+
 Variant3 pick3(const ngc_conv3d_desc *d, int op, ngc_conv_desc *r2)
 {
     int O, P, Q;
@@ -341,6 +379,7 @@ size_t workspace3(const ngc_conv3d_desc *d, int op, Variant3 v, const ngc_conv_d
         return round256_3(filter_elems3(d, op == NGC_OP_FWD ? NGC_BLOCKED_FWD : NGC_BLOCKED_BWD) * 2);
     }
     if (v == V3_WGRAD_GEMM) {
+        if (const WgradTapsPlan *tp = wgrad_taps3_plan(d, O, P, Q)) return round256_3(tp->ws + 1);
         WgradGemmParams wp;
         if (!wgrad_gemm3_plan(d, O, P, Q, &wp)) return 0;
         return round256_3((size_t)wp.nparts * d->t * d->r * d->s * wp.ktiles * wp.ctiles * wp.wk * wp.wc * 64 * 64 * sizeof(float));
@@ -770,10 +809,18 @@ int ngc_conv3d_bwd_filters(const ngc_conv3d_desc *desc, const void *x, const voi
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (v == V3_DIRECT) return status3(launch_direct3_bwd_filters(*desc, O, P, Q, x, dy, dw, st));
     if (v != V3_WGRAD_GEMM) return NGC_UNSUPPORTED;
-    WgradGemmParams wp;
-    if (!wgrad_gemm3_plan(desc, O, P, Q, &wp)) return NGC_UNSUPPORTED;
     const size_t need = workspace3(desc, NGC_OP_BWD_FILTERS, v, nullptr, O, P, Q);
     if (!ws || ws_bytes < need) return NGC_WORKSPACE_TOO_SMALL;
+    if (const WgradTapsPlan *tp = wgrad_taps3_plan(desc, O, P, Q)) {
+        WgradTapsPlan pl = *tp;
+        pl.p.x = static_cast<const uint16_t *>(x);
+        pl.p.dy = static_cast<const uint16_t *>(dy);
+        pl.p.partial = static_cast<float *>(ws);
+        pl.p.dw = dw;
+        return status3(launch_wgrad_taps(pl, st));
+    }
+    WgradGemmParams wp;
+    if (!wgrad_gemm3_plan(desc, O, P, Q, &wp)) return NGC_UNSUPPORTED;
     wp.x = static_cast<const uint16_t *>(x);
     wp.dy = static_cast<const uint16_t *>(dy);
     wp.partial = static_cast<float *>(ws);

@@ -44,7 +44,7 @@ __device__ __forceinline__ void store16_result(void *dst, uint4 v, bool stream)
 // The NGC_* variables are read once per process, at the first use, into a table; env_switch(SW_X) returns the value of
 // NGC_X or nullptr.  ngc_reload_switches() (exported for the test suite) reads them again and bumps the epoch, which
 // also drops every cached plan.
-enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_DRY_RUN, SW_COUNT };
+enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_DRY_RUN, SW_COUNT };
 const char *env_switch(Switch s);
 uint32_t sw_epoch();
 // NGC_DRY_RUN=1: every launch is skipped after the host-side planning (host-path timing without a GPU)
@@ -479,6 +479,37 @@ struct WgradGemmParams {
     FastDiv div_opq;           // divide by O*P*Q
     int32_t xcd_order;         // rank 2, blocked operands: one-dimensional grid with the workgroups of a position chunk on one XCD
 };
+
+// ---- backprop-filters, several taps per pass (wgrad_taps.hip) ----
+struct WgradTapsParams {
+    const uint16_t *x;                             // blocked [N][C/16][D][H][W][16]
+    const uint16_t *dy;                            // blocked [N][K/16][O][P][Q][16]
+    float *partial;                                // [part][tile][tap group][cq][kb][tap][lane][4]; unused with one part
+    float *dw;                                     // [K][C][T][R][S]
+    int32_t N, nib, tq;                            // images; blocks of slices, stages per part (rank 3: per depth tap, in the kernel)
+    int16_t KB, CB;                                // K / 16, C / 16
+    int16_t D, H, W, O, P, Q;                      // rank 2: D = O = 1
+    int16_t sd, sh, sw, dil_d, dil_h, dil_w, pbd, pbh, pbw;
+    int16_t SR, G, PRS, PC;                        // dy rows / whole images per stage, patch rows and columns of an image
+    int16_t ktiles, ctiles;                        // tiles of 16 nkb k, of 16 ncq c
+    int16_t nparts, nrb, trem;                     // parts, row blocks of a slice, parts with one stage more
+    int8_t RS, S, T, gpt;                          // taps of a depth slice of the window, of a row, depth taps, tap groups per slice
+    int8_t ncq, nring;                             // 16-channel groups of c per workgroup, stage buffers
+    int8_t r3, xcd;                                // rank 3; the workgroups of a part on one XCD
+};
+static_assert(sizeof(WgradTapsParams) <= 104, "longer argument lists take the host 0.7 us more to launch");
+struct WgradTapsPlan {
+    WgradTapsParams p;
+    int nt, nkb;               // taps per group, 16-channel blocks of k per workgroup
+    size_t lds, ws;            // bytes of LDS, of the partials (0: one part, dw written directly)
+    double cost;               // expected cycles
+};
+// fills in the split of out->p, whose shape fields are set; false: not for this kernel
+bool wgrad_taps_plan(WgradTapsPlan *out);
+// the terms of that expectation: a stage and (fixed) a workgroup, the partials of several parts
+double wgrad_stage_cost(int nkb, int ncq, int nt, int dy_blocks, int x_blocks, int ring, double *fixed);
+double wgrad_parts_cost(int parts, size_t part_bytes);
+hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st);
 
 // ---- both derivative ops of a 1x1 stride-1 node in one pass over dy ----
 struct Bwd1x1FusedParams {
