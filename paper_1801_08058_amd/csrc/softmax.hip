@@ -228,7 +228,8 @@ __global__ __launch_bounds__(1024) void softmax_rows_long(const T *__restrict__ 
                 m = top;
             }
 #pragma unroll
-            for (int e = 0; e < E; ++e) s += e >= vi * E + E - cols ? SmElem<T>::exp_of(f[e] - m) : 0.f;
+            for (int e = 0; e < E; ++e)                                  // a masked element counts nothing, also while all so far were
+                s += e >= vi * E + E - cols && f[e] != -INFINITY ? SmElem<T>::exp_of(f[e] - m) : 0.f;
         }
     }
     if (!BWD) {

@@ -148,3 +148,24 @@ def test_softmax_group_widths_and_tails(dtype, rows, cols):
     x, dy = _inputs(rows, cols, dtype, 900 + rows * 7 + cols)
     _check(x, dy, dtype)
     _check(x, dy, dtype, offset=1, in_place=True)
+
+
+# Masked logits: -inf gives a probability of exactly 0, also where a thread meets nothing else at first (the two-pass
+# kernel keeps a running maximum); a row that is masked throughout has no softmax (NaN), as has a row with a NaN.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("cols", [5, 100, 1000, 5000, 30000, 65537, 80000])
+def test_softmax_masked_logits(dtype, cols):
+    x, dy = _inputs(5, cols, dtype, 1200 + cols)
+    x[0, : cols * 3 // 4] = -np.inf
+    x[1, cols // 4:] = -np.inf
+    x[2, 1::2] = -np.inf
+    keep = np.isfinite(x)
+    x[3] = -np.inf
+    x[4, cols // 2] = np.nan
+    y, _ = _run(x, dy, dtype)
+    assert np.isnan(y[3:]).all()
+    ref = np.zeros((3, cols))
+    for i in range(3):
+        ref[i, keep[i]] = oracle.softmax(np.asarray(x[i : i + 1, keep[i]]))[0]
+    assert np.isfinite(y[:3]).all() and (y[:3][~keep[:3]] == 0).all()
+    assert np.abs(y[:3] - ref).max() / ref.max() <= TOL[dtype]
