@@ -1591,6 +1591,15 @@ int ngc_conv_fwd(const ngc_conv_desc *desc, const void *x, const void *w, const 
         rp.relu = (desc->epilogue & NGC_EPI_RELU) ? 1 : 0;
         return launch_status(launch_rows(rp, lds, st));
     }
+    ConvFewParams fp;
+    if ((v == V_STRIP || v == V_GEMM1X1) && desc->x_layout == NGC_NCHW16C && desc->y_layout == NGC_NCHW16C && conv_few_plan(desc, P, Q, &fp)) {
+        fp.in = static_cast<const uint16_t *>(x);
+        fp.wt = static_cast<const uint16_t *>(wt);
+        fp.out = static_cast<uint16_t *>(y);
+        fp.bias = (desc->epilogue & NGC_EPI_BIAS) ? bias : nullptr;
+        fp.relu = (desc->epilogue & NGC_EPI_RELU) ? 1 : 0;
+        return launch_status(launch_conv_few(fp, st));
+    }
     if (v == V_STRIP) {
         StripParams sp;
         int nf;

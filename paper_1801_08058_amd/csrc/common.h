@@ -44,7 +44,7 @@ __device__ __forceinline__ void store16_result(void *dst, uint4 v, bool stream)
 // The NGC_* variables are read once per process, at the first use, into a table; env_switch(SW_X) returns the value of
 // NGC_X or nullptr.  ngc_reload_switches() (exported for the test suite) reads them again and bumps the epoch, which
 // also drops every cached plan.
-enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_DRY_RUN, SW_COUNT };
+enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_FWD_FEW, SW_DRY_RUN, SW_COUNT };
 const char *env_switch(Switch s);
 uint32_t sw_epoch();
 // NGC_DRY_RUN=1: every launch is skipped after the host-side planning (host-path timing without a GPU)
@@ -510,6 +510,22 @@ bool wgrad_taps_plan(WgradTapsPlan *out);
 double wgrad_stage_cost(int nkb, int ncq, int nt, int dy_blocks, int x_blocks, int ring, double *fixed);
 double wgrad_parts_cost(int parts, size_t part_bytes);
 hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st);
+
+// ---- forward of nodes with few output tiles (conv_few.hip) ----
+struct ConvFewParams {
+    const uint16_t *in;        // blocked [N][C/16][H][W][16]
+    const uint16_t *wt;        // [R][S][C/16][K][16]
+    uint16_t *out;             // blocked [N][K/16][P][Q][16]
+    const float *bias;         // may be null
+    uint32_t in_bytes, wt_bytes;
+    uint32_t M;                // N * P * Q positions
+    int32_t CB, K, H, W, R, S, sh, sw, dil_h, dil_w, pbh, pbw;
+    FastDiv div_pq, div_q;
+    int32_t relu;
+};
+// shapes the arguments of a node it is expected to run faster than the staged kernels; false: not for this kernel
+bool conv_few_plan(const ngc_conv_desc *d, int P, int Q, ConvFewParams *q);
+hipError_t launch_conv_few(const ConvFewParams &p, hipStream_t st);
 
 // ---- both derivative ops of a 1x1 stride-1 node in one pass over dy ----
 struct Bwd1x1FusedParams {
