@@ -1305,13 +1305,13 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         return round256((size_t)d->n * wp.strips * (d->k / 64) * 2 * 4 * 6 * 64 * 16);
     }
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_GEMM) {
-        if (const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q)) return round256(tp->ws + 1);
+        if (const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q)) return wgrad_taps_workspace(*tp);
         WgradGemmParams wp;
         wgrad_gemm_plan(d, P, Q, &wp);
         return round256((size_t)wp.nparts * d->r * d->s * wp.ktiles * wp.ctiles * wp.wk * wp.wc * 64 * 64 * sizeof(float));
     }
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_STRIP) {
-        if (const WgradTapsPlan *tp = wgrad_taps_for_strip(d, P, Q)) return round256(tp->ws + 1);
+        if (const WgradTapsPlan *tp = wgrad_taps_for_strip(d, P, Q)) return wgrad_taps_workspace(*tp);
         WgradStripParams wp;
         wgrad_strip_plan(d, P, Q, &wp, nullptr);
         return round256((size_t)wp.nparts * 9 * d->k * d->c * sizeof(float));

@@ -379,7 +379,7 @@ size_t workspace3(const ngc_conv3d_desc *d, int op, Variant3 v, const ngc_conv_d
         return round256_3(filter_elems3(d, op == NGC_OP_FWD ? NGC_BLOCKED_FWD : NGC_BLOCKED_BWD) * 2);
     }
     if (v == V3_WGRAD_GEMM) {
-        if (const WgradTapsPlan *tp = wgrad_taps3_plan(d, O, P, Q)) return round256_3(tp->ws + 1);
+        if (const WgradTapsPlan *tp = wgrad_taps3_plan(d, O, P, Q)) return wgrad_taps_workspace(*tp);
         WgradGemmParams wp;
         if (!wgrad_gemm3_plan(d, O, P, Q, &wp)) return 0;
         return round256_3((size_t)wp.nparts * d->t * d->r * d->s * wp.ktiles * wp.ctiles * wp.wk * wp.wc * 64 * 64 * sizeof(float));

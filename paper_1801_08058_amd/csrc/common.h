@@ -510,6 +510,9 @@ bool wgrad_taps_plan(WgradTapsPlan *out);
 double wgrad_stage_cost(int nkb, int ncq, int nt, int dy_blocks, int x_blocks, int ring, double *fixed);
 double wgrad_parts_cost(int parts, size_t part_bytes);
 hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st);
+// what the caller is asked for: whole 256 bytes, never none (a call without a workspace is refused) and, for partials of
+// exactly the static array's size, not more than that
+inline size_t wgrad_taps_workspace(const WgradTapsPlan &pl) { return pl.ws ? (pl.ws + 255) / 256 * 256 : 256; }
 
 // ---- forward of nodes with few output tiles (conv_few.hip) ----
 struct ConvFewParams {

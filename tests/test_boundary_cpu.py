@@ -416,6 +416,14 @@ def test_noalloc_entry_point_refuses_large_nodes_before_touching_the_gpu():
     assert ng.ngc_conv_bwd_filters_noalloc(ok, None, 16, 16, None, check=False) == ng.NGC_BAD_ARG
 
 
+@pytest.mark.parametrize("node", [(133, 992, 69, 6, 224, 2, 2, 1), (62, 224, 71, 34, 1024, 2, 2, 3)])
+def test_noalloc_takes_partials_that_fill_the_static_array(node):
+    """Nodes whose partials are exactly as large as the static array fit it: the library asks for no byte more."""
+    n, c, h, w, k, r, s, st = node
+    d = ng.make_desc(n, c, h, w, k, r, s, stride=(st, st))
+    assert ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS) == ng.ngc_static_scratch_bytes()
+
+
 def test_sliced_nodes_size_their_workspace_for_every_group():
     """A node that runs as launches over groups of images (tensors of 2 GiB or more) hands every group the same
     workspace; the split of a backprop-filters reduction is not monotone in the batch, so the remainder group can need
