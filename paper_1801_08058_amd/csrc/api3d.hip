@@ -431,6 +431,20 @@ int ngc_conv3d_out_shape(const ngc_conv3d_desc *desc, int32_t *o, int32_t *p, in
     return NGC_OK;
 }
 
+// Workspace of one group of a node that runs over groups of images: the last, smaller group can need more than a full one
+// (its reduction is split into other parts)
+static size_t sliced_group_workspace3(const ngc_conv3d_desc *d, int op, const BatchSlices3 &bs)
+{
+    const ngc_conv3d_desc g = with_batch3(d, bs.images);
+    size_t need = ngc_conv3d_workspace_bytes(&g, op);
+    if (d->n % bs.images) {
+        const ngc_conv3d_desc r = with_batch3(d, d->n % bs.images);
+        const size_t b = ngc_conv3d_workspace_bytes(&r, op);
+        if (b > need) need = b;
+    }
+    return need;
+}
+
 size_t ngc_conv3d_workspace_bytes(const ngc_conv3d_desc *desc, int op)
 {
     int O, P, Q;
@@ -450,8 +464,7 @@ size_t ngc_conv3d_workspace_bytes(const ngc_conv3d_desc *desc, int op)
     const BatchSlices3 bs = batch_slices3(desc, O, P, Q);
     if (bs.images < desc->n && (op == NGC_OP_FWD || op == NGC_OP_BWD_DATA || op == NGC_OP_BWD_FILTERS)) {
         // groups of images reuse one workspace; backprop-filters keeps one dw per group behind it
-        const ngc_conv3d_desc g = with_batch3(desc, bs.images);
-        const size_t base = ngc_conv3d_workspace_bytes(&g, op);
+        const size_t base = sliced_group_workspace3(desc, op, bs);
         if (op != NGC_OP_BWD_FILTERS) return base;
         const size_t groups = (size_t)(desc->n + bs.images - 1) / bs.images;
         const size_t row = ((size_t)desc->k * desc->c * desc->t * desc->r * desc->s + 15) / 16 * 16;
@@ -788,8 +801,7 @@ int ngc_conv3d_bwd_filters(const ngc_conv3d_desc *desc, const void *x, const voi
     const BatchSlices3 bs = batch_slices3(desc, O, P, Q);
     if (bs.images < desc->n) {
         // operands of 2 GiB or more: dw of each group of images into the workspace, then their sum in index order
-        const ngc_conv3d_desc g0 = with_batch3(desc, bs.images);
-        const size_t base = round256_3(ngc_conv3d_workspace_bytes(&g0, NGC_OP_BWD_FILTERS));
+        const size_t base = round256_3(sliced_group_workspace3(desc, NGC_OP_BWD_FILTERS, bs));
         if (!ws || ws_bytes < ngc_conv3d_workspace_bytes(desc, NGC_OP_BWD_FILTERS)) return NGC_WORKSPACE_TOO_SMALL;
         const int elems = desc->k * desc->c * desc->t * desc->r * desc->s, row = (elems + 15) / 16 * 16;
         float *rows = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + base);

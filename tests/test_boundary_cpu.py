@@ -452,6 +452,22 @@ def test_sliced_nodes_size_their_workspace_for_every_group():
     assert checked >= 30
 
 
+@pytest.mark.parametrize("node", [(310, 176, 6, 80, 77, 64, 2, 2, 2, 1), (894, 192, 4, 28, 71, 48, 2, 2, 2, 1), (63, 208, 25, 48, 84, 64, 3, 3, 3, 2),
+                                  (586, 176, 19, 75, 11, 48, 1, 3, 3, 1), (30, 64, 16, 200, 200, 64, 3, 3, 3, 1)])
+def test_sliced_rank3_nodes_size_their_workspace_for_every_group(node):
+    """As for rank 2: the last group (of fewer images) has to fit the workspace the whole node asks for."""
+    n, c, dd, h, w, k, t, r, s, st = node
+    pad = (t // 2, r // 2, s // 2)
+    mk = lambda n: ng.make_desc3(n, c, dd, h, w, k, t, r, s, (st,) * 3, (1, 1, 1), pad, pad, ng.NGC_BF16, ng.NGC_NCHW16C, ng.NGC_NCHW16C)
+    d, W = mk(n), ng.NGC_OP_BWD_FILTERS
+    assert ng.ngc_conv3d_variant(d, W).startswith("sliced")
+    o, p, q = ng.ngc_conv3d_out_shape(d)
+    full = ((1 << 31) - 1) // (2 * max(c * dd * h * w, k * o * p * q))
+    rows = (n + full - 1) // full * ((k * c * t * r * s + 15) // 16 * 16) * 4
+    for g in {min(full, n), n % full} - {0}:
+        assert ng.ngc_conv3d_workspace_bytes(mk(g), W) <= ng.ngc_conv3d_workspace_bytes(d, W) - (rows + 255) // 256 * 256
+
+
 def test_host_time_per_dispatch_with_launches_stubbed():
     """Kernel selection is meant to be negligible next to kernels of 10-20 us: with NGC_DRY_RUN=1 (every launch
     skipped after the planning) a call through the C ABI with a descriptor the library has seen before has to stay
