@@ -204,7 +204,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gather_conv(const GatherCon
                 const unsigned wo = ((unsigned)ek.c * p.w_chan + ek.r * p.rst_h * p.S + ek.s * p.rst_w) * SZ;
                 unsigned char *slot = ring + (step & 3) * (ENT + ENTW);
                 *reinterpret_cast<uint2 *>(slot + tid * 8) = make_uint2(xo, live ? (unsigned)(ek.r | ek.s << 8) : 0x1F1Fu);   // bit 31: never inside
-                *reinterpret_cast<unsigned *>(slot + ENT + tid * 4) = live ? wo : GATHER_OOB;
+                // past the last index: wt_bytes, out of range on its own and on top of a wbase that already is (twice
+                // GATHER_OOB would wrap to filter element 0)
+                *reinterpret_cast<unsigned *>(slot + ENT + tid * 4) = live ? wo : p.wt_bytes;
             }
             ek.advance(dk, nr, ns);
         };
