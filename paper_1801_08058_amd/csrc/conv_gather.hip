@@ -362,7 +362,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gather_conv(const GatherCon
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[e] = acc[a][b][4 * j + e] + bias[j][e];
-                    v[e] = p.relu ? fmaxf(v[e], 0.f) : v[e];             // padding lanes of a blocked result: zeros all along
+                    v[e] = p.relu ? fmaxf(v[e], 0.f) : v[e];
+                    if (co + e >= p.Cout) v[e] = 0.f;                    // padding lanes of a blocked result (0 * infinity before)
                 }
                 if (mask) {
 #pragma unroll
