@@ -76,6 +76,14 @@ template <int N> __device__ __forceinline__ void keep_raw(uint32_t (&v)[N])
     for (int e = 0; e < N; ++e) asm volatile("" : "+v"(v[e]));
 }
 
+template <typename T>
+__device__ __forceinline__ float load_value(__amdgpu_buffer_rsrc_t rs, unsigned off)
+{
+    const uint32_t v = GElem<T>::load(rs, off);
+    if constexpr (sizeof(T) == 4) return __uint_as_float(v);
+    else return GElem<T>::widen((uint16_t)v);
+}
+
 __device__ __forceinline__ unsigned bit_mask(unsigned bits, unsigned i) { return (unsigned)__builtin_amdgcn_sbfe((int)bits, i, 1); }   // bit i % 32: 0 or ~0
 
 // acc += A (32 rows) * B (32 columns) over the 2 U reduction indices of a plane pair; a, b: this lane's 16-byte units
@@ -90,6 +98,14 @@ __device__ __forceinline__ gf32x16 mma_pair(uint4 a, uint4 b, gf32x16 acc)
     } else {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(gbf16x8, a), __builtin_bit_cast(gbf16x8, b), acc, 0, 0, 0);
     }
+}
+
+__device__ __forceinline__ bool any_nan(const gf32x16 &v)
+{
+    bool u = false;
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) u |= __builtin_isunordered(v[i], v[i + 1]);
+    return u;
 }
 
 // A walk over kk: (channel, tap row, tap column), advanced a step of the reduction at a time
@@ -326,6 +342,57 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gather_conv(const GatherCon
         }
     }
 
+    const int cw = co0 + wm * MF * 32 + 4 * half;                        // this lane's first channel
+    const unsigned mw = m0 + wn * NF * 32 + l32;
+    // ---- Taps in the padding are no part of the sum; the GEMM multiplies zeros there, which is NaN where the filter is
+    // infinite or NaN.  Sums that came out as NaN are added up again without those taps, if the position has any.
+    bool redo = false;
+#pragma unroll
+    for (int a = 0; a < MF; ++a)
+#pragma unroll
+        for (int b = 0; b < NF; ++b) redo |= any_nan(acc[a][b]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(redo) != 0, 0)) {     // uniform: the block lies out of the way
+        const __amdgpu_buffer_rsrc_t rs_in = __builtin_amdgcn_make_buffer_rsrc((void *)p.in, 0, (int)p.in_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs_wt = __builtin_amdgcn_make_buffer_rsrc((void *)p.wt, 0, (int)p.wt_bytes, 0x00020000);
+#pragma unroll
+        for (int a = 0; a < MF; ++a)
+#pragma unroll
+            for (int b = 0; b < NF; ++b) {
+                if (mw + 32 * b >= M) continue;
+                int n, i, j;
+                position(mw + 32 * b, n, i, j);
+                const int ih0 = i * p.is_h + p.base_h[ca], iw0 = j * p.is_w + p.base_w[cb];
+                const int ih1 = ih0 + (nr - 1) * p.step_h, iw1 = iw0 + (ns - 1) * p.step_w;
+                auto in_h = [&](int ih) { return (unsigned)ih < (unsigned)p.Hin; };
+                auto in_w = [&](int iw) { return (unsigned)iw < (unsigned)p.Win; };
+                if (in_h(ih0) && in_h(ih1) && in_w(iw0) && in_w(iw1)) continue;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {                            // four channels at a time: sixteen would cost the GEMM waves
+                    const int co = cw + a * 32 + 8 * g;
+                    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int c = 0; c < p.Cin; ++c) {
+                        const int chan = p.in_blocked ? (c >> 4) * p.in_c + (c & 15) : c * p.in_c;
+#pragma unroll 1
+                        for (int t = 0; t < nr * ns; ++t) {
+                            const int r = t / ns, s = t - r * ns, ih = ih0 + r * p.step_h, iw = iw0 + s * p.step_w;
+                            if (!in_h(ih) || !in_w(iw)) continue;
+                            const float x = load_value<T>(rs_in, (unsigned)(n * p.in_n + chan + (ih * p.Win + iw) * p.in_px) * SZ);
+                            const int tap = c * p.w_chan + (p.r0[ca] + r * p.rst_h) * p.S + p.s0[cb] + s * p.rst_w;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                sum[e] = fmaf(x, load_value<T>(rs_wt, co + e < p.Cout ? (unsigned)((co + e) * p.w_row + tap) * SZ : GATHER_OOB), sum[e]);
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float v = acc[a][b][4 * g + e];
+                        acc[a][b][4 * g + e] = v != v ? sum[e] : v;
+                    }
+                }
+            }
+    }
+
     // ---- epilogue: bias, ReLU, mask, one rounding; a lane holds 4 consecutive output channels of a position per group
     const size_t HW = (size_t)p.Hout * p.Wout;
     const int cend = p.out_blocked ? (p.Cout + 15) & ~15 : p.Cout;
@@ -334,8 +401,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gather_conv(const GatherCon
     const size_t step = p.out_blocked ? 1 : HW;
     // reads past the end of the bias (or of no bias at all) give zero
     const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc((void *)p.bias, 0, p.bias ? p.Cout * 4 : 0, 0x00020000);
-    const int cw = co0 + wm * MF * 32 + 4 * half;                        // this lane's first channel
-    const unsigned mw = m0 + wn * NF * 32 + l32;
 #pragma unroll
     for (int a = 0; a < MF; ++a) {
         float bias[4][4];
@@ -552,6 +617,35 @@ __global__ __launch_bounds__(64 * (BT / 32) * (BT / 32) * KS) void gather_wgrad(
     }
     const int col = ct * BT + qx + l32;
     if (col >= CRS) return;
+    if constexpr (!XV) {
+        // Positions whose tap lies in the padding are no part of the sum: see gather_conv
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(any_nan(acc)) != 0, 0)) {
+            const int c = col / RS, t = col - c * RS, r = t / p.S, s = t - r * p.S;
+            const int dh = r * p.dil_h - p.pb_h, dw = s * p.dil_w - p.pb_w;
+            if (dh < 0 || dw < 0 || (p.P - 1) * p.sh + dh >= p.H || (p.Q - 1) * p.sw + dw >= p.W) {
+                const int chan = p.x_blocked ? (c >> 4) * p.x_c + (c & 15) : c * p.x_c;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int k = kt * BT + qk + 8 * g + 4 * half;
+                    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (unsigned m = mb; m < me; ++m) {
+                        const int n = (int)fd_div(m, p.div_pq);
+                        const int pq = (int)(m - (unsigned)n * p.div_pq.d), pp = (int)fd_div((unsigned)pq, p.div_q);
+                        const int ih = pp * p.sh + dh, iw = (pq - pp * p.Q) * p.sw + dw;
+                        if ((unsigned)ih >= (unsigned)p.H || (unsigned)iw >= (unsigned)p.W) continue;
+                        const float x = load_value<T>(rs_x, (unsigned)(n * p.x_n + chan + (ih * p.W + iw) * p.x_px) * SZ);
+                        const int o = n * p.dy_n + pq * p.dy_px + (p.dy_blocked ? (k >> 4) * p.dy_c + (k & 15) : k * p.dy_c);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            sum[e] = fmaf(load_value<T>(rs_dy, k + e < p.K ? (unsigned)(o + e * (p.dy_blocked ? 1 : p.dy_c)) * SZ : GATHER_OOB), x, sum[e]);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[4 * g + e] = acc[4 * g + e] != acc[4 * g + e] ? sum[e] : acc[4 * g + e];
+                }
+            }
+        }
+    }
     float *out = p.out + (size_t)blockIdx.x * p.pitch;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {

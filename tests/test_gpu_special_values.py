@@ -45,3 +45,41 @@ def test_infinite_input_leaves_the_padding_lanes_zero(dtype, tile, monkeypatch):
     assert np.all(host(run.last_raw, bits).reshape(1, 2, 6, 6, 16)[:, 1, :, :, 4:] == 0)
     run.bwd_data(dy, w)
     assert np.all(host(run.last_raw, bits).reshape(1, 1, 6, 6, 16)[..., 5:] == 0)
+
+
+def _same(got, ref, tol):
+    """Finite where the oracle is, within tol of its largest finite value; the same infinities and NaNs elsewhere."""
+    fin = np.isfinite(ref)
+    assert fin.any()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.abs(got[fin] - ref[fin]).max() / np.abs(ref[fin]).max() <= tol
+
+
+PADDED = [
+    # n  c   h   w   k   r  s  sh sw dh dw pbh pbw pah paw
+    (Attrs(2, 7, 9, 11, 33, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), "f32", NCHW, NCHW),
+    (Attrs(2, 20, 8, 8, 21, 3, 2, 2, 3, 1, 2, 2, 0, 1, 3), "f32", NCHW, BLK),
+    (Attrs(1, 5, 12, 10, 17, 5, 5, 2, 1, 1, 1, 2, 2, 2, 2), "bf16", BLK, NCHW),
+    (Attrs(3, 9, 8, 8, 40, 3, 3, 1, 1, 2, 2, 2, 2, 2, 2), "bf16", NCHW, NCHW),
+    (Attrs(2, 12, 6, 6, 12, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), "f32", NCHW, NCHW),       # one tap, a frame of padding only
+]
+
+
+@pytest.mark.parametrize("case", range(len(PADDED)))
+@pytest.mark.parametrize("tile,wgrad", [(1, 1001), (2, 2001), (3, 3003)])
+def test_infinities_meet_no_padding(case, tile, wgrad, monkeypatch):
+    """A tap in the padding is no part of the sum: an infinite filter element or gradient does not turn it into NaN."""
+    monkeypatch.setenv("NGC_GATHER_TILE", str(tile))
+    monkeypatch.setenv("NGC_GATHER_WGRAD", str(wgrad))
+    a, dtype, xl, yl = PADDED[case]
+    x, w, b, dy = _tensors(a, dtype, 15100 + case)
+    run = Run(a, dtype, xl, yl, False)
+    wi = w.copy()
+    wi[a.k // 2, a.c // 2, 0, 0] = np.inf
+    wi[2, 1, a.r - 1, a.s - 1] = -np.inf
+    _same(run.fwd(x, wi, bias=b), oracle.conv_fwd(a, x, wi, bias=b), bound(dtype, "act"))
+    _same(run.bwd_data(dy, wi), oracle.conv_bwd_data_gather(a, dy, wi), bound(dtype, "act"))
+    di = dy.copy()
+    di[0, a.k // 2, 0, 0] = np.inf
+    di[a.n - 1, 1, -1, -1] = np.nan
+    _same(run.bwd_filters(x, di), oracle.conv_bwd_filters(a, x, di), bound(dtype, "dw"))
