@@ -47,6 +47,20 @@ __device__ __forceinline__ bf16x8 wt_frag(const unsigned char *lo, const unsigne
     return __builtin_bit_cast(bf16x8, r);
 }
 
+// Zeros the elements of the operands whose positions are not below `rem`: a lane holds positions 0 .. 3 and 16 .. 19
+template <int N> __device__ __forceinline__ void keep_first(bf16x8 (&b)[N], int rem)
+{
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 keep;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = rem - (i >> 1) * 16 - (i & 1) * 2;
+        keep[i] = n >= 2 ? 0xFFFFFFFFu : n == 1 ? 0xFFFFu : 0u;
+    }
+#pragma unroll
+    for (int t = 0; t < N; ++t) b[t] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, b[t]) & keep);
+}
+
 // Quotients of the set-up, in a handful of vector operations each (the compiler's 32-bit division is a chain of some
 // thirty scalar ones; two dozen of those cost a small launch half its time).
 // n / d for n < 65536, inv = 1 / d to one unit in the last place: n + 0.5 is at least 0.5 / d away from a multiple, the
@@ -316,7 +330,7 @@ __global__ __launch_bounds__(512) void wgrad_taps_bf16(const WgradTapsParams p)
             int rows = p.P - ms_rb * p.SR, gv = ninner - ms_ib * G;
             if (rows > p.SR) rows = p.SR;
             if (gv > G) gv = G;
-            const int nsteps = ((multi ? gv * PQ : rows * p.Q) + 31) >> 5;
+            const int nvalid = multi ? gv * PQ : rows * p.Q, nsteps = (nvalid + 31) >> 5;
             if (++ms_rb == nrb) {
                 ms_rb = 0;
                 if (++ms_ib == nib) ms_ib = 0;
@@ -370,6 +384,8 @@ __global__ __launch_bounds__(512) void wgrad_taps_bf16(const WgradTapsParams p)
                     step_body(std::true_type{});
                     j += NH;
                 }
+                // positions past the last one: dy is zero there, x is not and has to be where it is infinite or NaN
+                if (j * 32 + 32 > nvalid) keep_first(b, nvalid - j * 32 - grp * 4);
                 step_body(std::false_type{});
             }
             // streams continue across stages, so that the remainders even out

@@ -83,3 +83,29 @@ def test_infinities_meet_no_padding(case, tile, wgrad, monkeypatch):
     di[0, a.k // 2, 0, 0] = np.inf
     di[a.n - 1, 1, -1, -1] = np.nan
     _same(run.bwd_filters(x, di), oracle.conv_bwd_filters(a, x, di), bound(dtype, "dw"))
+
+
+TAPS = [
+    # n  c   h   w   k   r  s  sh sw dh dw pbh pbw pah paw
+    (Attrs(1, 32, 9, 11, 32, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), [(8, 10)]),                # one stage, 99 positions
+    (Attrs(3, 16, 7, 7, 48, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), [(6, 6), (0, 0)]),           # whole images, 49 positions each
+    (Attrs(2, 32, 21, 60, 32, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), [(20, 0), (20, 59)]),      # a last block of fewer rows
+    (Attrs(2, 16, 24, 50, 64, 2, 2, 2, 2, 1, 1, 0, 0, 0, 0), [(23, 49), (23, 0)]),
+    (Attrs(1, 64, 13, 29, 16, 5, 5, 1, 1, 1, 1, 2, 2, 2, 2), [(12, 3), (11, 28)]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(TAPS)))
+@pytest.mark.parametrize("force", [None, 11001, 21002, 11003])
+def test_infinite_inputs_meet_no_position_past_the_end(case, force, monkeypatch):
+    """Backprop-filters of several taps per pass: positions are multiplied 32 at a time, those past the last one of a stage
+    are no part of the sum, whatever x holds where their taps would reach."""
+    if force:
+        monkeypatch.setenv("NGC_WGRAD_TAPS", str(force))
+    a, pixels = TAPS[case]
+    x, w, b, dy = _tensors(a, "bf16", 15200 + case)
+    dy[dy == 0] = 0.5                                     # zero times infinity is the oracle's to find, not here
+    for i, (h, ww) in enumerate(pixels):
+        x[a.n - 1, 1 + i, h, ww] = (-1) ** i * np.inf
+    run = Run(a, "bf16", BLK, BLK, False)
+    _same(run.bwd_filters(x, dy), oracle.conv_bwd_filters(a, x, dy), bound("bf16", "dw"))
