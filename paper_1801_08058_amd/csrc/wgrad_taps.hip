@@ -554,7 +554,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     if (env_switch(SW_WGG_SP) || env_switch(SW_WGG_TILE) || env_switch(SW_WGG_SLOTS) || env_switch(SW_WGG_XCD) || env_switch(SW_WGG3_PARTS))
         return false;
     WgradTapsParams q = out->p;
-    q.r3 = q.T > 1 || q.D > 1 || q.O > 1;
+    q.r3 = q.T > 1 || q.D > 1 || q.O > 1 || q.pbd > 0;     // pbd: the one slice of dy may lie in front of x
     const int taps = q.T * q.RS;
     if (taps < 2 || q.Q > 224 || (size_t)q.N * q.CB * q.D * q.H * q.W * 32 >= 0x80000000ull ||
         (size_t)q.N * q.KB * q.O * q.P * q.Q * 32 >= 0x80000000ull) return false;

@@ -6,8 +6,8 @@ import pytest
 import oracle
 import paper_1801_08058_amd as ng
 from oracle import Attrs, Attrs3
-from gpu_util import Run, bound
-from test_gpu_conv3d import _check3
+from gpu_util import Run, Run3, bound
+from test_gpu_conv3d import _check3, _tensors3
 from test_gpu_parity import _tensors
 
 pytestmark = pytest.mark.gpu
@@ -46,6 +46,7 @@ CASES3 = [
     Attrs3(2, 32, 5, 6, 7, 48, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1),       # several slices a stage
     Attrs3(1, 16, 9, 19, 20, 80, 3, 3, 3, 2, 2, 2, 1, 1, 1, 1, 1, 1, 1, 1, 1),     # stride 2
     Attrs3(3, 16, 1, 8, 9, 16, 3, 2, 2, 1, 1, 1, 1, 1, 1, 1, 0, 0, 1, 1, 1),       # one slice: two depth taps outside
+    Attrs3(2, 32, 1, 6, 8, 16, 1, 2, 3, 3, 1, 1, 1, 1, 1, 0, 0, 1, 2, 0, 1),       # one slice each, padding behind only
 ]
 
 
@@ -56,3 +57,14 @@ def test_wgrad_taps_rank3(case, force, monkeypatch):
         monkeypatch.setenv("NGC_WGRAD_TAPS", str(force))
     a = CASES3[case]
     _check3(a, "bf16", BLK, BLK, False, 13100 + case, ("", "", "wgrad_gemm3"))
+
+
+@pytest.mark.parametrize("force", [None, 11001, 21002])
+def test_wgrad_taps_rank3_one_slice_in_front_of_x(force, monkeypatch):
+    """One depth tap, one slice of x and of dy, and the padding in front takes the tap outside x: dw is zero."""
+    if force:
+        monkeypatch.setenv("NGC_WGRAD_TAPS", str(force))
+    a = Attrs3(2, 16, 1, 7, 9, 32, 1, 3, 3, 2, 1, 1, 1, 1, 1, 1, 1, 1, 0, 1, 1)
+    x, w, b, dy = _tensors3(a, "bf16", 13200)
+    assert (oracle.conv3d_bwd_filters(a, x, dy) == 0).all()
+    assert (Run3(a, "bf16", BLK, BLK, False).bwd_filters(x, dy) == 0).all()
