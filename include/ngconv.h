@@ -166,8 +166,9 @@ int ngc_softmax(int32_t dtype, int64_t rows, int32_t cols, const void *x, void *
 int ngc_softmax_bwd(int32_t dtype, int64_t rows, int32_t cols, const void *y, const void *dy, void *dx,
                     void *hip_stream);
 
-/* Name of the kernel ngc_softmax (bwd = 0) / ngc_softmax_bwd (bwd = 1) runs for 16-byte aligned
- * tensors of this row length ("invalid" for bad arguments). */
+/* Name of the kernel ngc_softmax (bwd = 0) / ngc_softmax_bwd (bwd = 1) runs for this row length: "softmax_rows_tiny" (a
+ * thread per row), "softmax_rows_wave" (up to 64 lanes), "softmax_rows_wg" (a workgroup; the row in registers in both),
+ * "softmax_rows_long" (two passes); "invalid" for bad arguments. */
 const char *ngc_softmax_variant(int32_t dtype, int32_t cols, int32_t bwd);
 
 /* ConvolutionBackpropFilters (Sec. 3, derivative w.r.t. the filters input).

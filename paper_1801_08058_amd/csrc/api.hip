@@ -1971,8 +1971,12 @@ int ngc_softmax_bwd(int32_t dtype, int64_t rows, int32_t cols, const void *y, co
 const char *ngc_softmax_variant(int32_t dtype, int32_t cols, int32_t bwd)
 {
     if ((dtype != NGC_F32 && dtype != NGC_BF16) || cols < 1) return "invalid";
-    const int v = softmax_vectors(dtype, cols, bwd != 0, true);
-    return v == 0 ? "softmax_rows_block" : v > 256 ? "softmax_rows_wg" : "softmax_rows_wave";
+    switch (softmax_plan(dtype, cols, bwd != 0).kernel) {
+    case SM_TINY: return "softmax_rows_tiny";
+    case SM_WAVE: return "softmax_rows_wave";
+    case SM_WG: return "softmax_rows_wg";
+    default: return "softmax_rows_long";
+    }
 }
 
 static int bwd_data_filters_core(const ngc_conv_desc *desc, const void *x, const void *dy, const void *w, void *dx, float *dw,

@@ -652,7 +652,12 @@ hipError_t launch_direct3_bwd_data(const ngc_conv3d_desc &d, int O, int P, int Q
 hipError_t launch_direct3_bwd_filters(const ngc_conv3d_desc &d, int O, int P, int Q, const void *x, const void *dy, float *dw,
                                       hipStream_t st);
 int gemm1x1_dbp_tile_m(const Gemm1x1Params &p);
-int softmax_vectors(int dtype, int cols, bool bwd, bool aligned);
+enum SoftmaxKernel { SM_TINY, SM_WAVE, SM_WG, SM_LONG };
+struct SoftmaxPlan {
+    SoftmaxKernel kernel;
+    int V, GL;                 // vectors per lane, lanes per row
+};
+SoftmaxPlan softmax_plan(int dtype, int cols, bool bwd);
 hipError_t launch_softmax(int dtype, bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, bool aligned,
                           hipStream_t st);
 hipError_t launch_bias_grad(const ngc_conv_desc &d, int P, int Q, const void *dy, float *db, float *partial, int nparts,

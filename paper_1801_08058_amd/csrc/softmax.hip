@@ -287,44 +287,43 @@ __global__ __launch_bounds__(256) void softmax_rows_tiny(const T *__restrict__ a
         if (e < cols) SmElem<T>::store(out + base + e, BWD ? f[e] * (fb[e] - s) : f[e] * inv);
 }
 
-// Kernel choice for a row length: 0 = rows off the 16-byte grid or longer than the registers of 1024 threads with 4 vectors
-// each, else the vectors per thread: V (at most 64 lanes per row), 256 + V or 1024 + V (a workgroup of that many threads).
-int softmax_vectors(int dtype, int cols, bool bwd, bool aligned)
+// Kernel of a row length: below one vector a thread per row; else the smallest group of lanes and the fewest vectors per lane
+// that hold the row; else two passes.
+SoftmaxPlan softmax_plan(int dtype, int cols, bool bwd)
 {
-    const int E = dtype == NGC_BF16 ? 8 : 4;
-    if (!aligned || cols % E != 0) return 0;
-    const int nvec = cols / E;
-    (void)bwd;
-    for (int v = 1; v <= 4; v *= 2)
-        if (nvec <= 64 * v) return v;                  // up to 4 vectors per lane: a wave per row
-    for (int v = 2; v <= 4; v *= 2)
-        if (nvec <= 256 * v) return 256 + v;           // longer rows: 256 threads per row,
-    for (int v = 2; v <= 4; v *= 2)
-        if (nvec <= 1024 * v) return 1024 + v;         // then 1024 (more loads in flight than more vectors per thread)
-    return 0;
+    const int E = dtype == NGC_BF16 ? 8 : 4, nvec = (cols + E - 1) / E;
+    if (cols < E) return {SM_TINY, 1, 1};
+    static const SoftmaxPlan groups[] = {{SM_WAVE, 1, 8}, {SM_WAVE, 1, 16}, {SM_WAVE, 1, 32}, {SM_WAVE, 1, 64}, {SM_WAVE, 2, 64}, {SM_WAVE, 4, 64},
+                                         {SM_WG, 2, 256}, {SM_WG, 4, 256}, {SM_WG, 2, 1024}, {SM_WG, 4, 1024}, {SM_WG, 8, 1024}};
+    for (const SoftmaxPlan &g : groups)
+        if (nvec <= g.V * g.GL && !(g.V == 8 && bwd && dtype == NGC_BF16)) return g;     // bf16 backprop: two tensors unpacked do not fit
+    return {SM_LONG, 1, 1024};
 }
 
 template <typename T, bool BWD, bool TAIL>
 static hipError_t launch_softmax_t(const T *a, const T *b, T *out, uint32_t rows, int cols, hipStream_t st)
 {
-    constexpr int E = SmElem<T>::E;
-    const int nvec = (cols + E - 1) / E;
+    const SoftmaxPlan pl = softmax_plan(sizeof(T) == 2 ? NGC_BF16 : NGC_F32, cols, BWD);
 #define NGC_SM_WAVE(V, GL) NGC_LAUNCH((softmax_rows_reg<T, V, BWD, GL, TAIL>), dim3((rows + 256 / (GL) - 1) / (256 / (GL))), dim3(256), 0, st, a, b, out, rows, cols)
 #define NGC_SM_WG(V, GL) NGC_LAUNCH((softmax_rows_reg<T, V, BWD, GL, TAIL>), dim3(rows), dim3(GL), 0, st, a, b, out, rows, cols)
-    if (cols < E) NGC_LAUNCH((softmax_rows_tiny<T, BWD>), dim3((rows + 255) / 256), dim3(256), 0, st, a, b, out, rows, cols);
-    else if (nvec <= 8) NGC_SM_WAVE(1, 8);
-    else if (nvec <= 16) NGC_SM_WAVE(1, 16);
-    else if (nvec <= 32) NGC_SM_WAVE(1, 32);
-    else if (nvec <= 64) NGC_SM_WAVE(1, 64);
-    else if (nvec <= 128) NGC_SM_WAVE(2, 64);
-    else if (nvec <= 256) NGC_SM_WAVE(4, 64);
-    else if (nvec <= 512) NGC_SM_WG(2, 256);
-    else if (nvec <= 1024) NGC_SM_WG(4, 256);
-    else if (nvec <= 2048) NGC_SM_WG(2, 1024);
-    else if (nvec <= 4096) NGC_SM_WG(4, 1024);
-    else if (nvec <= 8192 && !(BWD && sizeof(T) == 2)) {                 // bf16 backprop: two tensors unpacked do not fit
+    switch (pl.kernel == SM_TINY ? 0 : pl.kernel == SM_LONG ? 1 : pl.GL * 16 + pl.V) {
+    case 0: NGC_LAUNCH((softmax_rows_tiny<T, BWD>), dim3((rows + 255) / 256), dim3(256), 0, st, a, b, out, rows, cols); break;
+    case 1: NGC_LAUNCH((softmax_rows_long<T, BWD>), dim3(rows), dim3(1024), 0, st, a, b, out, rows, cols); break;
+    case 8 * 16 + 1: NGC_SM_WAVE(1, 8); break;
+    case 16 * 16 + 1: NGC_SM_WAVE(1, 16); break;
+    case 32 * 16 + 1: NGC_SM_WAVE(1, 32); break;
+    case 64 * 16 + 1: NGC_SM_WAVE(1, 64); break;
+    case 64 * 16 + 2: NGC_SM_WAVE(2, 64); break;
+    case 64 * 16 + 4: NGC_SM_WAVE(4, 64); break;
+    case 256 * 16 + 2: NGC_SM_WG(2, 256); break;
+    case 256 * 16 + 4: NGC_SM_WG(4, 256); break;
+    case 1024 * 16 + 2: NGC_SM_WG(2, 1024); break;
+    case 1024 * 16 + 4: NGC_SM_WG(4, 1024); break;
+    case 1024 * 16 + 8:
         if constexpr (!(BWD && sizeof(T) == 2)) NGC_SM_WG(8, 1024);
-    } else NGC_LAUNCH((softmax_rows_long<T, BWD>), dim3(rows), dim3(1024), 0, st, a, b, out, rows, cols);
+        break;
+    default: return hipErrorInvalidValue;
+    }
 #undef NGC_SM_WAVE
 #undef NGC_SM_WG
     return ngc::launch_result();

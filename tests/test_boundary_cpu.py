@@ -134,11 +134,17 @@ def test_softmax_validates_before_launch():
     assert ng.ngc_softmax_variant(ng.NGC_BF16, 2048) == "softmax_rows_wave"            # 4 vectors of 8 per lane
     assert ng.ngc_softmax_variant(ng.NGC_BF16, 2056) == "softmax_rows_wg"
     assert ng.ngc_softmax_variant(ng.NGC_BF16, 32768, True) == "softmax_rows_wg"       # 16 vectors per thread, 256 threads
-    assert ng.ngc_softmax_variant(ng.NGC_BF16, 32776) == "softmax_rows_block"
-    assert ng.ngc_softmax_variant(ng.NGC_BF16, 1001) == "softmax_rows_block"           # rows off the 16-byte grid
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 32776) == "softmax_rows_wg"             # 8 vectors, 1024 threads
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 32776, True) == "softmax_rows_long"     # two bf16 tensors do not fit the registers
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 65536) == "softmax_rows_wg"
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 65537) == "softmax_rows_long"
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 1001) == "softmax_rows_wave"            # rows off the 16-byte grid
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 7) == "softmax_rows_tiny"
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, 8) == "softmax_rows_wave"
     assert ng.ngc_softmax_variant(ng.NGC_F32, 1024) == "softmax_rows_wave"
     assert ng.ngc_softmax_variant(ng.NGC_F32, 16384) == "softmax_rows_wg"
-    assert ng.ngc_softmax_variant(ng.NGC_F32, 16388) == "softmax_rows_block"
+    assert ng.ngc_softmax_variant(ng.NGC_F32, 32768, True) == "softmax_rows_wg"
+    assert ng.ngc_softmax_variant(ng.NGC_F32, 32769) == "softmax_rows_long"
     assert ng.ngc_softmax_variant(9, 8) == "invalid"
 
 

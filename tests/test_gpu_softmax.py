@@ -72,8 +72,8 @@ def _inputs(rows, cols, dtype, seed):
     return x, dy
 
 
-# row lengths: every vectors-per-lane variant of the wave kernel (ragged last vector row), the
-# workgroup-per-row kernel (odd lengths, lengths past the register budget), a single column
+# row lengths: every vectors-per-lane variant of the wave and workgroup kernels (ragged last vector row, odd lengths), the
+# two-pass kernel (lengths past the register budget), a single column
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rows,cols", [(5, 8), (7, 512), (9, 1000), (6, 1032), (5, 2048), (3, 3000), (3, 4096), (2, 8192),
                                        (3, 8200), (4, 1001), (6, 37), (1, 1), (2, 20000), (1030, 64), (2, 32768),
@@ -81,9 +81,10 @@ def _inputs(rows, cols, dtype, seed):
 def test_softmax_small(dtype, rows, cols):
     x, dy = _inputs(rows, cols, dtype, 100 + rows * 7 + cols)
     e = 8 if dtype == "bf16" else 4
-    expect = "softmax_rows_block" if cols % e else "softmax_rows_wave" if cols <= 256 * e else \
-        "softmax_rows_wg" if cols <= 4096 * e else "softmax_rows_block"
-    assert ng.ngc_softmax_variant(ng.NGC_BF16 if dtype == "bf16" else ng.NGC_F32, cols) == expect
+    for bwd in (False, True):
+        most = 4096 if bwd and dtype == "bf16" else 8192
+        expect = "softmax_rows_tiny" if cols < e else "softmax_rows_wave" if cols <= 256 * e else "softmax_rows_wg" if cols <= most * e else "softmax_rows_long"
+        assert ng.ngc_softmax_variant(ng.NGC_BF16 if dtype == "bf16" else ng.NGC_F32, cols, bwd) == expect
     _check(x, dy, dtype)
 
 
