@@ -226,7 +226,9 @@ size_t ngc_data_elems(const ngc_conv_desc *desc, int which);
 size_t ngc_filter_elems(const ngc_conv_desc *desc, int32_t layout);
 
 /* Name of the kernel variant the dispatcher picks for (desc, op): a static string such as
- * "igemm_bf16_128x128" or "direct"; "unsupported" / "invalid" otherwise.  Host only. */
+ * "igemm_bf16_128x128" or "direct"; "unsupported" / "invalid" otherwise.  A kernel that takes some of a variant's nodes is
+ * named behind a colon: "strip_bf16:few", "gemm1x1_bf16:few" (few output tiles), "wgrad_strip_bf16:taps",
+ * "wgrad_gemm_bf16:taps" (several taps per pass), "direct:gather" (gather GEMM).  Host only. */
 const char *ngc_conv_variant(const ngc_conv_desc *desc, int op);
 
 /* ---- Convolution over three spatial axes (N, C, D, H, W) --------------------------------------
@@ -302,7 +304,8 @@ size_t ngc_conv3d_filter_elems(const ngc_conv3d_desc *desc, int32_t layout);
 size_t ngc_conv3d_data_elems(const ngc_conv3d_desc *desc, int which);
 
 /* Name of the kernel variant picked for (desc, op): "rank2:<rank-2 variant>" for windows that
- * reduce to the rank-2 op, "igemm3_bf16_*", "wgrad_gemm3_bf16", "direct3", "unsupported", "invalid". */
+ * reduce to the rank-2 op, "igemm3_bf16_*", "wgrad_gemm3_bf16" (":taps": several taps per pass), "direct3", "unsupported",
+ * "invalid". */
 const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op);
 
 /* Test hook.  The library reads its NGC_* environment switches (kernel-variant overrides for tests and

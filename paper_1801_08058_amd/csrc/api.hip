@@ -110,7 +110,9 @@ ngc_conv_desc with_batch(const ngc_conv_desc *d, int n)
     return t;
 }
 
-enum Variant { V_INVALID, V_UNSUPPORTED, V_DIRECT, V_IGEMM_128, V_IGEMM_64, V_WGRAD_64, V_STRIP, V_WGRAD_STRIP, V_STEM_FWD, V_WGRAD_STEM, V_STEM_BWD, V_WGRAD_GEMM, V_GEMM1X1, V_ROWS, V_STAGED };
+enum Variant { V_INVALID, V_UNSUPPORTED, V_DIRECT, V_IGEMM_128, V_IGEMM_64, V_WGRAD_64, V_STRIP, V_WGRAD_STRIP, V_STEM_FWD, V_WGRAD_STEM, V_STEM_BWD, V_WGRAD_GEMM, V_GEMM1X1, V_ROWS, V_STAGED,
+               // the kernels that take some of the nodes of the variant they are named after
+               V_DIRECT_GATHER, V_STRIP_FEW, V_GEMM1X1_FEW, V_WGRAD_STRIP_TAPS, V_WGRAD_GEMM_TAPS };
 
 constexpr int NUM_CUS = 256;                      // MI355X
 constexpr size_t LDS_LIMIT = 160 * 1024;
@@ -1183,10 +1185,18 @@ bool staged_plan(const ngc_conv_desc *d, int op, StagedPlan *out)
     return false;
 }
 
+// The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
 Variant pick_uncached(const ngc_conv_desc *d, int op)
 {
     const Variant v = pick_base(d, op);
     if ((v == V_DIRECT || v == V_UNSUPPORTED) && staged_plan(d, op, nullptr)) return V_STAGED;
+    int P, Q;
+    if (validate(d, &P, &Q) != NGC_OK) return v;
+    if (v == V_DIRECT) return gather_takes(*d, op, P, Q) ? V_DIRECT_GATHER : v;
+    if (op == NGC_OP_FWD && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) && conv_few_plan(d, P, Q, nullptr))
+        return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
+    if (v == V_WGRAD_GEMM && wgrad_taps_plan_of(d, P, Q)) return V_WGRAD_GEMM_TAPS;
+    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q)) return V_WGRAD_STRIP_TAPS;
     return v;
 }
 
@@ -1288,7 +1298,7 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         return base + round256((size_t)bias_grad_parts(t, d->h, d->w) * ((d->c + 15) / 16 * 16) * sizeof(float));
     }
     if (op == NGC_OP_BIAS_GRAD) return round256((size_t)bias_grad_parts(*d, P, Q) * ((d->k + 15) / 16 * 16) * sizeof(float));
-    if (op == NGC_OP_FWD && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1))
+    if (op == NGC_OP_FWD && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW))
         return d->w_layout == NGC_KCRS ? round256(filter_elems(d, NGC_BLOCKED_FWD) * 2) : 0;
     if (op == NGC_OP_BWD_DATA && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1))
         return d->w_layout == NGC_KCRS ? round256(filter_elems(d, NGC_BLOCKED_BWD) * 2) : 0;
@@ -1297,21 +1307,19 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         stem_bwd_plan(d, P, Q, &pl);
         return round256(pl.wu_bytes);
     }
-    if (op == NGC_OP_BWD_FILTERS && v == V_DIRECT)                      // optional: without it the reduction runs in one part
-        return gather_takes(*d, op, P, Q) ? round256(gather_wgrad_workspace(*d, P, Q)) : 0;
+    if (op == NGC_OP_BWD_FILTERS && v == V_DIRECT_GATHER) return round256(gather_wgrad_workspace(*d, P, Q));    // optional: without it the reduction runs in one part
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_STEM) {
         WgradStemParams wp;
         wgrad_stem_plan(d, P, Q, &wp, nullptr);
         return round256((size_t)d->n * wp.strips * (d->k / 64) * 2 * 4 * 6 * 64 * 16);
     }
+    if (op == NGC_OP_BWD_FILTERS && (v == V_WGRAD_GEMM_TAPS || v == V_WGRAD_STRIP_TAPS)) return wgrad_taps_workspace(*wgrad_taps_plan_of(d, P, Q));
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_GEMM) {
-        if (const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q)) return wgrad_taps_workspace(*tp);
         WgradGemmParams wp;
         wgrad_gemm_plan(d, P, Q, &wp);
         return round256((size_t)wp.nparts * d->r * d->s * wp.ktiles * wp.ctiles * wp.wk * wp.wc * 64 * 64 * sizeof(float));
     }
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_STRIP) {
-        if (const WgradTapsPlan *tp = wgrad_taps_for_strip(d, P, Q)) return wgrad_taps_workspace(*tp);
         WgradStripParams wp;
         wgrad_strip_plan(d, P, Q, &wp, nullptr);
         return round256((size_t)wp.nparts * 9 * d->k * d->c * sizeof(float));
@@ -1481,6 +1489,11 @@ const char *ngc_conv_variant(const ngc_conv_desc *desc, int op)
     switch (pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op)) {
     case V_UNSUPPORTED: return "unsupported";
     case V_DIRECT: return "direct";
+    case V_DIRECT_GATHER: return "direct:gather";
+    case V_STRIP_FEW: return "strip_bf16:few";
+    case V_GEMM1X1_FEW: return "gemm1x1_bf16:few";
+    case V_WGRAD_STRIP_TAPS: return "wgrad_strip_bf16:taps";
+    case V_WGRAD_GEMM_TAPS: return "wgrad_gemm_bf16:taps";
     case V_IGEMM_128: return "igemm_bf16_128x128";
     case V_IGEMM_64: return "igemm_bf16_256x64";
     case V_WGRAD_64: return "wgrad_bf16_64x64";
@@ -1556,9 +1569,9 @@ int ngc_conv_fwd(const ngc_conv_desc *desc, const void *x, const void *w, const 
         if (rc != NGC_OK || !sp.cy) return rc;
         return launch_status(launch_layout_convert(2, desc->n, desc->k, P, Q, yout, NGC_NCHW16C, y, NGC_NCHW, st));
     }
-    if (v == V_DIRECT) {
+    if (v == V_DIRECT || v == V_DIRECT_GATHER) {
         const float *b = (desc->epilogue & NGC_EPI_BIAS) ? bias : nullptr;
-        return launch_status(gather_takes(*desc, NGC_OP_FWD, P, Q) ? launch_gather_fwd(*desc, P, Q, x, w, b, y, st) : launch_direct_fwd(*desc, P, Q, x, w, b, y, st));
+        return launch_status(v == V_DIRECT_GATHER ? launch_gather_fwd(*desc, P, Q, x, w, b, y, st) : launch_direct_fwd(*desc, P, Q, x, w, b, y, st));
     }
     if (v == V_STEM_FWD) {
         StemFwdParams sp;
@@ -1591,8 +1604,9 @@ int ngc_conv_fwd(const ngc_conv_desc *desc, const void *x, const void *w, const 
         rp.relu = (desc->epilogue & NGC_EPI_RELU) ? 1 : 0;
         return launch_status(launch_rows(rp, lds, st));
     }
-    ConvFewParams fp;
-    if ((v == V_STRIP || v == V_GEMM1X1) && desc->x_layout == NGC_NCHW16C && desc->y_layout == NGC_NCHW16C && conv_few_plan(desc, P, Q, &fp)) {
+    if (v == V_STRIP_FEW || v == V_GEMM1X1_FEW) {
+        ConvFewParams fp;
+        if (!conv_few_plan(desc, P, Q, &fp)) return NGC_UNSUPPORTED;
         fp.in = static_cast<const uint16_t *>(x);
         fp.wt = static_cast<const uint16_t *>(wt);
         fp.out = static_cast<uint16_t *>(y);
@@ -1673,9 +1687,8 @@ int bwd_data_core(const ngc_conv_desc *desc, const void *dy, const void *w, cons
     if (v == V_UNSUPPORTED || v == V_STAGED) return NGC_UNSUPPORTED;    // blocked copies are the caller's part
     if (v == V_ROWS && fuse) v = V_STRIP;                  // the channel sums of dx come from the strip kernel
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (v == V_DIRECT)
-        return launch_status(gather_takes(*desc, NGC_OP_BWD_DATA, P, Q) ? launch_gather_bwd_data(*desc, P, Q, dy, w, mask, dx, st)
-                                                       : launch_direct_bwd_data(*desc, P, Q, dy, w, mask, dx, st));
+    if (v == V_DIRECT_GATHER) return launch_status(launch_gather_bwd_data(*desc, P, Q, dy, w, mask, dx, st));
+    if (v == V_DIRECT) return launch_status(launch_direct_bwd_data(*desc, P, Q, dy, w, mask, dx, st));
     if (v == V_STEM_BWD) {
         StemBwdPlan pl;
         if (!stem_bwd_plan(desc, P, Q, &pl)) return NGC_UNSUPPORTED;
@@ -2039,9 +2052,8 @@ int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *d
         return launch_status(launch_bias_grad_reduce(rows, dw, groups, elems, row, st));
     }
     const Variant v = pick(desc, NGC_OP_BWD_FILTERS);
-    if (v == V_DIRECT)
-        return launch_status(gather_takes(*desc, NGC_OP_BWD_FILTERS, P, Q) ? launch_gather_bwd_filters(*desc, P, Q, x, dy, dw, ws, ws_bytes, st)
-                                                       : launch_direct_bwd_filters(*desc, P, Q, x, dy, dw, st));
+    if (v == V_DIRECT_GATHER) return launch_status(launch_gather_bwd_filters(*desc, P, Q, x, dy, dw, ws, ws_bytes, st));
+    if (v == V_DIRECT) return launch_status(launch_direct_bwd_filters(*desc, P, Q, x, dy, dw, st));
     if (v == V_STAGED) {
         StagedPlan sp;
         if (!staged_plan(desc, NGC_OP_BWD_FILTERS, &sp)) return NGC_UNSUPPORTED;
@@ -2063,9 +2075,8 @@ int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *d
 
     const size_t need = workspace_bytes(desc, NGC_OP_BWD_FILTERS, v, P, Q);
     if (!ws || ws_bytes < need) return NGC_WORKSPACE_TOO_SMALL;
-    if (const WgradTapsPlan *tp = v == V_WGRAD_GEMM ? wgrad_taps_plan_of(desc, P, Q)
-                                  : v == V_WGRAD_STRIP ? wgrad_taps_for_strip(desc, P, Q) : nullptr) {
-        WgradTapsPlan pl = *tp;
+    if (v == V_WGRAD_GEMM_TAPS || v == V_WGRAD_STRIP_TAPS) {
+        WgradTapsPlan pl = *wgrad_taps_plan_of(desc, P, Q);
         pl.p.x = static_cast<const uint16_t *>(x);
         pl.p.dy = static_cast<const uint16_t *>(dy);
         pl.p.partial = static_cast<float *>(ws);

@@ -140,7 +140,7 @@ bool as_rank2(const ngc_conv3d_desc *d, ngc_conv_desc *out)
     return true;
 }
 
-enum Variant3 { V3_INVALID, V3_UNSUPPORTED, V3_RANK2, V3_STRIP, V3_IGEMM_128, V3_IGEMM_64, V3_WGRAD_GEMM, V3_DIRECT };
+enum Variant3 { V3_INVALID, V3_UNSUPPORTED, V3_RANK2, V3_STRIP, V3_IGEMM_128, V3_IGEMM_64, V3_WGRAD_GEMM, V3_WGRAD_TAPS, V3_DIRECT };
 
 bool blocked_bf16_3(const ngc_conv3d_desc *d)
 {
@@ -358,7 +358,7 @@ Variant3 pick3(const ngc_conv3d_desc *d, int op, ngc_conv_desc *r2)
             return d->c % 128 == 0 ? V3_IGEMM_128 : V3_IGEMM_64;
         return direct_ok ? V3_DIRECT : V3_UNSUPPORTED;
     }
-    if (wgrad_gemm3_plan(d, O, P, Q, nullptr)) return V3_WGRAD_GEMM;
+    if (wgrad_gemm3_plan(d, O, P, Q, nullptr)) return wgrad_taps3_plan(d, O, P, Q) ? V3_WGRAD_TAPS : V3_WGRAD_GEMM;
     return V3_DIRECT;
 }
 
@@ -378,8 +378,8 @@ size_t workspace3(const ngc_conv3d_desc *d, int op, Variant3 v, const ngc_conv_d
         if (d->w_layout != NGC_KCRS) return 0;
         return round256_3(filter_elems3(d, op == NGC_OP_FWD ? NGC_BLOCKED_FWD : NGC_BLOCKED_BWD) * 2);
     }
+    if (v == V3_WGRAD_TAPS) return wgrad_taps_workspace(*wgrad_taps3_plan(d, O, P, Q));
     if (v == V3_WGRAD_GEMM) {
-        if (const WgradTapsPlan *tp = wgrad_taps3_plan(d, O, P, Q)) return wgrad_taps_workspace(*tp);
         WgradGemmParams wp;
         if (!wgrad_gemm3_plan(d, O, P, Q, &wp)) return 0;
         return round256_3((size_t)wp.nparts * d->t * d->r * d->s * wp.ktiles * wp.ctiles * wp.wk * wp.wc * 64 * 64 * sizeof(float));
@@ -527,6 +527,7 @@ const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op)
     case V3_IGEMM_128: return "igemm3_bf16_128x128";
     case V3_IGEMM_64: return "igemm3_bf16_256x64";
     case V3_WGRAD_GEMM: return "wgrad_gemm3_bf16";
+    case V3_WGRAD_TAPS: return "wgrad_gemm3_bf16:taps";
     case V3_DIRECT: return "direct3";
     case V3_UNSUPPORTED: return "unsupported";
     default: return "invalid";
@@ -820,11 +821,11 @@ int ngc_conv3d_bwd_filters(const ngc_conv3d_desc *desc, const void *x, const voi
     if (v == V3_RANK2) return ngc_conv_bwd_filters(&r2, x, dy, dw, ws, ws_bytes, hip_stream);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (v == V3_DIRECT) return status3(launch_direct3_bwd_filters(*desc, O, P, Q, x, dy, dw, st));
-    if (v != V3_WGRAD_GEMM) return NGC_UNSUPPORTED;
+    if (v != V3_WGRAD_GEMM && v != V3_WGRAD_TAPS) return NGC_UNSUPPORTED;
     const size_t need = workspace3(desc, NGC_OP_BWD_FILTERS, v, nullptr, O, P, Q);
     if (!ws || ws_bytes < need) return NGC_WORKSPACE_TOO_SMALL;
-    if (const WgradTapsPlan *tp = wgrad_taps3_plan(desc, O, P, Q)) {
-        WgradTapsPlan pl = *tp;
+    if (v == V3_WGRAD_TAPS) {
+        WgradTapsPlan pl = *wgrad_taps3_plan(desc, O, P, Q);
         pl.p.x = static_cast<const uint16_t *>(x);
         pl.p.dy = static_cast<const uint16_t *>(dy);
         pl.p.partial = static_cast<float *>(ws);

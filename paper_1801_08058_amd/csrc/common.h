@@ -526,7 +526,8 @@ struct ConvFewParams {
     FastDiv div_pq, div_q;
     int32_t relu;
 };
-// shapes the arguments of a node it is expected to run faster than the staged kernels; false: not for this kernel
+// shapes the arguments (where q is not null) of a node it is expected to run faster than the staged kernels; false: not for
+// this kernel
 bool conv_few_plan(const ngc_conv_desc *d, int P, int Q, ConvFewParams *q);
 hipError_t launch_conv_few(const ConvFewParams &p, hipStream_t st);
 

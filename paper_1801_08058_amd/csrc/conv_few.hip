@@ -116,6 +116,7 @@ bool conv_few_plan(const ngc_conv_desc *d, int P, int Q, ConvFewParams *q)
     // 3.6 / 3.6; 392 tiles of 36 7.3 / 4.5, 448 of 32 8.0 / 4.4, 400 of 288 35.1 / 17.0, but 392 of 18 5.3 / 5.5 and 400 of 8 4.3 / 4.4;
     // 784 tiles of 144 18.4 / 19.5, of 16 6.0 / 6.7.
     if (fv != 1 && !(tiles <= 256 && units >= 8) && !(tiles <= 448 && units >= 32)) return false;
+    if (!q) return true;
     memset(q, 0, sizeof(*q));
     q->in_bytes = (uint32_t)in_bytes;
     q->wt_bytes = (uint32_t)wt_bytes;

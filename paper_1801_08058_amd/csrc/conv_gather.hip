@@ -662,6 +662,8 @@ static int gcd_(int a, int b) { return b ? gcd_(b, a % b) : a; }
 // classes of backprop-data in a table
 bool gather_takes(const ngc_conv_desc &d, int op, int P, int Q)
 {
+    const char *force = env_switch(SW_GATHER_TILE);                       // tests only: 0 = never
+    if (force && atoi(force) == 0) return false;
     const size_t sz = d.dtype == NGC_F32 ? 4 : 2, lim = (size_t)1 << 31;
     auto bytes = [&](int layout, size_t n, size_t c, size_t hw) { return n * (layout == NGC_NCHW ? c : (c + 15) / 16 * 16) * hw * sz; };
     if (d.r > 31 || d.s > 31 || bytes(d.x_layout, d.n, d.c, (size_t)d.h * d.w) >= lim || bytes(d.y_layout, d.n, d.k, (size_t)P * Q) >= lim ||

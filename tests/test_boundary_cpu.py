@@ -179,9 +179,9 @@ def test_kernel_selection_and_sizes():
         assert ng.ngc_conv_variant(_good(**kw), ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16"
         kw7 = dict(kw, h=7, w=7)                                              # 49 positions per image
         # anything else with NCHW tensors runs on blocked copies in the workspace, with the kernel of the blocked node
-        assert ng.ngc_conv_variant(_good(**kw7), ng.NGC_OP_FWD) == "staged:gemm1x1_bf16"
+        assert ng.ngc_conv_variant(_good(**kw7), ng.NGC_OP_FWD) == "staged:gemm1x1_bf16:few"
         assert ng.ngc_conv_variant(_good(**kw7), ng.NGC_OP_BWD_FILTERS) == "staged:wgrad_gemm_bf16"
-        assert ng.ngc_conv_variant(_good(w_layout=ng.NGC_BLOCKED_FWD, **kw7), ng.NGC_OP_FWD) == "staged:gemm1x1_bf16"
+        assert ng.ngc_conv_variant(_good(w_layout=ng.NGC_BLOCKED_FWD, **kw7), ng.NGC_OP_FWD) == "staged:gemm1x1_bf16:few"
         kws = dict(kw, stride=(2, 2))
         assert ng.ngc_conv_variant(_good(**kws), ng.NGC_OP_BWD_DATA) == "staged:gemm1x1_bf16"
         blocked = ng.ngc_conv_workspace_bytes(_good(**dict(kw7, x_layout=ng.NGC_NCHW16C, y_layout=ng.NGC_NCHW16C)), ng.NGC_OP_FWD)
@@ -192,16 +192,16 @@ def test_kernel_selection_and_sizes():
         t3 = dict(n=8, c=c, k=k, h=28, w=28)
         assert ng.ngc_conv_variant(_good(w_layout=ng.NGC_BLOCKED_FWD, **t3), ng.NGC_OP_FWD).startswith("strip")
         assert ng.ngc_conv_variant(_good(w_layout=ng.NGC_BLOCKED_BWD, **t3), ng.NGC_OP_BWD_DATA).startswith("strip")
-        assert ng.ngc_conv_variant(_good(**t3), ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16"
+        assert ng.ngc_conv_variant(_good(**t3), ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16:taps"
         t1 = dict(t3, r=1, s=1, pad_below=(0, 0), pad_above=(0, 0))
         assert ng.ngc_conv_variant(_good(w_layout=ng.NGC_BLOCKED_FWD, **t1), ng.NGC_OP_FWD) == "gemm1x1_bf16"
         assert ng.ngc_conv_variant(_good(w_layout=ng.NGC_BLOCKED_BWD, **t1), ng.NGC_OP_BWD_DATA) == "gemm1x1_bf16"
         ws = ng.ngc_conv_workspace_bytes(_good(**t1), ng.NGC_OP_BWD_FILTERS)
         assert ws >= ((k + 63) // 64) * ((c + 63) // 64) * 64 * 64 * 4      # partials cover whole tiles
     odd = dict(n=8, c=40, k=72, h=28, w=28)
-    assert [ng.ngc_conv_variant(_good(**odd), o) for o in range(3)] == ["direct"] * 3
+    assert [ng.ngc_conv_variant(_good(**odd), o) for o in range(3)] == ["direct:gather"] * 3
     three = _good(n=8, h=56, w=56, x_layout=ng.NGC_NCHW)                      # 3x3 with NCHW x: a blocked copy of x
-    assert [ng.ngc_conv_variant(three, o) for o in range(3)] == ["staged:strip_bf16", "staged:strip_bf16", "staged:wgrad_strip_bf16"]
+    assert [ng.ngc_conv_variant(three, o) for o in range(3)] == ["staged:strip_bf16", "staged:strip_bf16", "staged:wgrad_strip_bf16:taps"]
     xcopy = 8 * 64 * 56 * 56 * 2
     three_b = _good(n=8, h=56, w=56)
     assert ng.ngc_conv_workspace_bytes(three, ng.NGC_OP_BWD_DATA) == 2 * xcopy + ng.ngc_conv_workspace_bytes(three_b, ng.NGC_OP_BWD_DATA)
@@ -213,7 +213,7 @@ def test_kernel_selection_and_sizes():
     assert ng.ngc_data_elems(d, 0) == 64 * 64 * 56 * 56 and ng.ngc_data_elems(d, 1) == 64 * 64 * 56 * 56
     assert ng.ngc_filter_elems(d, ng.NGC_BLOCKED_FWD) == 9 * 4 * 64 * 16
     f32 = _good(dtype=ng.NGC_F32, x_layout=ng.NGC_NCHW, y_layout=ng.NGC_NCHW)
-    assert [ng.ngc_conv_variant(f32, o) for o in range(3)] == ["direct"] * 3
+    assert [ng.ngc_conv_variant(f32, o) for o in range(3)] == ["direct:gather"] * 3
     stem = ng.make_desc(64, 3, 224, 224, 64, 7, 7, (2, 2), (1, 1), (3, 3), (3, 3), x_layout=ng.NGC_NCHW)
     assert ng.ngc_conv_out_shape(stem) == (112, 112)
     assert ng.ngc_data_elems(stem, 0) == 64 * 3 * 224 * 224
@@ -320,7 +320,7 @@ def test_conv3d_null_pointers_bias_and_workspace():
 def test_conv3d_kernel_selection_and_sizes(monkeypatch):
     F, B, W = ng.NGC_OP_FWD, ng.NGC_OP_BWD_DATA, ng.NGC_OP_BWD_FILTERS
     d = _good3()
-    assert [ng.ngc_conv3d_variant(d, op) for op in (F, B, W)] == ["strip3_bf16", "strip3_bf16", "wgrad_gemm3_bf16"]
+    assert [ng.ngc_conv3d_variant(d, op) for op in (F, B, W)] == ["strip3_bf16", "strip3_bf16", "wgrad_gemm3_bf16:taps"]
     monkeypatch.setenv("NGC_CONV3D_STRIP", "0")
     assert [ng.ngc_conv3d_variant(d, op) for op in (F, B)] == ["igemm3_bf16_256x64"] * 2
     d = _good3(c=128, k=128)
@@ -428,6 +428,30 @@ def test_noalloc_takes_partials_that_fill_the_static_array(node):
     n, c, h, w, k, r, s, st = node
     d = ng.make_desc(n, c, h, w, k, r, s, stride=(st, st))
     assert ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS) == ng.ngc_static_scratch_bytes()
+
+
+def test_names_tell_the_kernels_of_a_variant_apart(monkeypatch):
+    """A kernel that takes some nodes of a variant shows in the name, with and without its switch, and in the workspace."""
+    F, B, W = ng.NGC_OP_FWD, ng.NGC_OP_BWD_DATA, ng.NGC_OP_BWD_FILTERS
+    small = _good(n=1, c=256, k=256, w_layout=ng.NGC_BLOCKED_FWD)
+    one = _good(n=1, c=1024, k=256, r=1, s=1, pad_below=(0, 0), pad_above=(0, 0), w_layout=ng.NGC_BLOCKED_FWD)
+    few_images = _good(n=4, c=512, k=512, h=7, w=7)                      # the all-taps strip kernel hands it over
+    window = _good(n=8, c=48, k=48, r=5, s=5, pad_below=(2, 2), pad_above=(2, 2))
+    video = ng.make_desc3(2, 32, 8, 28, 28, 32, 3, 3, 3, pad_below=(1, 1, 1), pad_above=(1, 1, 1))
+    f32 = _good(dtype=ng.NGC_F32, x_layout=ng.NGC_NCHW, y_layout=ng.NGC_NCHW)
+    nodes = [(small, F, "strip_bf16", "few"), (one, F, "gemm1x1_bf16", "few"), (few_images, W, "wgrad_strip_bf16", "taps"),
+             (window, W, "wgrad_gemm_bf16", "taps"), (f32, F, "direct", "gather"), (f32, B, "direct", "gather"), (f32, W, "direct", "gather")]
+    ws = [ng.ngc_conv_workspace_bytes(d, op) for d, op, _, _ in nodes]
+    assert [ng.ngc_conv_variant(d, op) for d, op, _, _ in nodes] == [f"{v}:{s}" for _, _, v, s in nodes]
+    assert ng.ngc_conv3d_variant(video, W) == "wgrad_gemm3_bf16:taps"
+    large = _good(n=1024, c=128, k=128, h=6, w=6)                        # stages of several images, the strip kernel's own
+    assert ng.ngc_conv_variant(large, W) == "wgrad_strip_bf16"
+    for switch in ("NGC_FWD_FEW", "NGC_WGRAD_TAPS", "NGC_GATHER_TILE"):
+        monkeypatch.setenv(switch, "0")
+    assert [ng.ngc_conv_variant(d, op) for d, op, _, _ in nodes] == [v for _, _, v, _ in nodes]
+    assert ng.ngc_conv3d_variant(video, W) == "wgrad_gemm3_bf16"
+    off = [ng.ngc_conv_workspace_bytes(d, op) for d, op, _, _ in nodes]
+    assert off[0] == ws[0] and off[1] == ws[1] and off[2] != ws[2] and off[3] != ws[3] and off[6] == 0 < ws[6]
 
 
 def test_sliced_nodes_size_their_workspace_for_every_group():

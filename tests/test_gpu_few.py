@@ -35,6 +35,9 @@ def test_few_tiles_forward(case, epilogue, force, monkeypatch):
     a = CASES[case]
     x, w, b, dy = _tensors(a, "bf16", 14000 + case)
     bias = b if epilogue else None
-    y = Run(a, "bf16", BLK, BLK, True).fwd(x, w, bias=bias, relu=epilogue)
+    run = Run(a, "bf16", BLK, BLK, True)
+    y = run.fwd(x, w, bias=bias, relu=epilogue)
+    if force:
+        assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_FWD).endswith("_bf16:few")
     ref = oracle.conv_fwd(a, x, w, bias=bias, relu=epilogue)
     assert oracle.max_normalised_error(y, ref) <= bound("bf16", "act")

@@ -50,15 +50,29 @@ def _check_backward_compounds(run, a, x_in, w, dy, ref_dx, tol):
     assert e <= 1e-5, f"bias_grad err {e}"
 
 
-def _check_all(a: Attrs, dtype: str, xl: int, yl: int, pre: bool, seed: int, expect_variant=None):
-    print(f"case attrs={a} dtype={dtype} xl={xl} yl={yl} pre={pre} seed={seed}", flush=True)
+@pytest.fixture(params=["base", "default"])
+def route(request, monkeypatch):
+    """base: the kernels that take some of a variant's nodes (few output tiles, several taps per pass, gather GEMM: the names
+    with a suffix) are off, so that small shapes reach the kernel a test is about; default: the dispatcher's choice."""
+    if request.param == "base":
+        for switch in ("NGC_FWD_FEW", "NGC_WGRAD_TAPS", "NGC_GATHER_TILE"):
+            monkeypatch.setenv(switch, "0")
+    return request.param
+
+
+def _runs(desc, op, expect, route="default"):
+    name = ng.ngc_conv_variant(desc, op)
+    assert name.startswith(expect) and (route != "base" or ":" not in name), name
+
+
+def _check_all(a: Attrs, dtype: str, xl: int, yl: int, pre: bool, seed: int, expect_variant=None, route="default"):
+    print(f"case attrs={a} dtype={dtype} xl={xl} yl={yl} pre={pre} seed={seed} route={route}", flush=True)
     x, w, b, dy = _tensors(a, dtype, seed)
     run = Run(a, dtype, xl, yl, pre)
     tol = bound(dtype, "act")
     y = run.fwd(x, w, bias=b, relu=True)
     if expect_variant:
-        assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_FWD).startswith(expect_variant[0]), \
-            ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_FWD)
+        _runs(run.last_desc, ng.NGC_OP_FWD, expect_variant[0], route)
     e = oracle.max_normalised_error(y, oracle.conv_fwd(a, x, w, bias=b, relu=True))
     assert e <= tol, f"fwd+bias+relu err {e}"
     y0 = run.fwd(x, w)
@@ -66,15 +80,14 @@ def _check_all(a: Attrs, dtype: str, xl: int, yl: int, pre: bool, seed: int, exp
     assert e <= tol, f"fwd err {e}"
     dx = run.bwd_data(dy, w)
     if expect_variant:
-        assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_DATA).startswith(expect_variant[1]), \
-            ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_DATA)
+        _runs(run.last_desc, ng.NGC_OP_BWD_DATA, expect_variant[1], route)
     ref_dx = oracle.conv_bwd_data(a, dy, w)
     e = oracle.max_normalised_error(dx, ref_dx)
     assert e <= tol, f"bwd_data err {e}"
     _check_backward_compounds(run, a, x, w, dy, ref_dx, tol)
     dw = run.bwd_filters(x, dy)
     if expect_variant:
-        assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_FILTERS).startswith(expect_variant[2])
+        _runs(run.last_desc, ng.NGC_OP_BWD_FILTERS, expect_variant[2], route)
     e = oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy))
     assert e <= bound(dtype, "dw"), f"bwd_filters err {e}"
 
@@ -151,8 +164,9 @@ DIRECT_CASES = [
 @pytest.mark.parametrize("case", range(len(DIRECT_CASES)))
 @pytest.mark.parametrize("dtype,xl,yl", [("f32", NCHW, NCHW), ("bf16", NCHW, NCHW), ("bf16", BLK, BLK),
                                          ("f32", BLK, NCHW), ("bf16", NCHW, BLK)])
-def test_direct_kernels(case, dtype, xl, yl):
-    _check_all(DIRECT_CASES[case], dtype, xl, yl, False, 1000 + case, ("direct", "direct", "direct"))
+def test_direct_kernels(case, dtype, xl, yl, route):
+    name = "direct" if route == "base" else "direct:gather"
+    _check_all(DIRECT_CASES[case], dtype, xl, yl, False, 1000 + case, (name, name, name), route)
 
 
 def test_blocked_output_tail_lanes_are_zero():
@@ -202,8 +216,10 @@ def strip_nf(monkeypatch):
 @pytest.mark.parametrize("case", range(len(MFMA_CASES)))
 @pytest.mark.parametrize("pre", [True, False])
 @pytest.mark.parametrize("nf", [None, 0, 7, 4])
-def test_mfma_kernels_small(case, pre, nf, strip_nf):
+def test_mfma_kernels_small(case, pre, nf, strip_nf, route):
     a = MFMA_CASES[case]
+    if nf is not None and route == "default":
+        pytest.skip("a forced strip size is off the other kernels' routes")
     if nf in (7, 4) and ((a.sh, a.sw) != (1, 1) or a.r * a.s == 1 or not pre):  # forced sizes: stride-1 shapes only
         pytest.skip("strip kernel covers stride-1 multi-tap shapes; one filter-layout mode is enough for forced sizes")
     strip_nf(nf)
@@ -217,7 +233,7 @@ def test_mfma_kernels_small(case, pre, nf, strip_nf):
     bwd_v = "strip" if (bwd_strip_ok and a.k % 16 == 0 and a.c % 16 == 0) else "gemm1x1" if one_tap else \
         "igemm" if (a.k % 32 == 0 and a.c % 64 == 0) else "direct"
     wg_v = "wgrad" if (a.c % 16 == 0 and a.k % 16 == 0) else "direct"
-    _check_all(a, "bf16", BLK, BLK, pre, 2000 + case, (fwd_v, bwd_v, wg_v))
+    _check_all(a, "bf16", BLK, BLK, pre, 2000 + case, (fwd_v, bwd_v, wg_v), route)
 
 
 @pytest.mark.parametrize("case", [0, 9, 10, 11])
@@ -265,31 +281,35 @@ SMALL_IMAGE_WGRAD_CASES = [
 
 @pytest.mark.parametrize("case", range(len(SMALL_IMAGE_WGRAD_CASES)))
 @pytest.mark.parametrize("g1", [False, True])
-def test_wgrad_all_taps_small_images(case, g1, monkeypatch):
+def test_wgrad_all_taps_small_images(case, g1, monkeypatch, route):
     """Stages of several whole images (g1: forced back to one image per stage)."""
     if g1:
+        if route == "default":
+            pytest.skip("the switch is off the other kernel's route")
         monkeypatch.setenv("NGC_WGRAD_G1", "1")
     a = SMALL_IMAGE_WGRAD_CASES[case]
     x, w, b, dy = _tensors(a, "bf16", 9000 + case)
     run = Run(a, "bf16", BLK, BLK, True)
     dw = run.bwd_filters(x, dy)
-    assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_strip_bf16"
+    _runs(run.last_desc, ng.NGC_OP_BWD_FILTERS, "wgrad_strip_bf16" if route == "base" else "wgrad_strip_bf16:taps", route)
     assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
 
 
 @pytest.mark.parametrize("case", [0, 2, 3, 4, 5, 6, 8, 13])
 @pytest.mark.parametrize("sp", [0, 64, 128])
-def test_wgrad_gemm_kernel(case, sp, monkeypatch):
+def test_wgrad_gemm_kernel(case, sp, monkeypatch, route):
     """Per-tap GEMM backprop-filters (the all-taps kernel switched off so that 3x3 shapes reach it too);
     sp = positions per LDS stage (0: the dispatcher's choice)."""
     monkeypatch.setenv("NGC_WGRAD_STRIP", "0")
     if sp:
+        if route == "default":
+            pytest.skip("the switch is off the other kernel's route")
         monkeypatch.setenv("NGC_WGG_SP", str(sp))
     a = MFMA_CASES[case]
     x, w, b, dy = _tensors(a, "bf16", 6000 + case)
     run = Run(a, "bf16", BLK, BLK, True)
     dw = run.bwd_filters(x, dy)
-    assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16"
+    _runs(run.last_desc, ng.NGC_OP_BWD_FILTERS, "wgrad_gemm_bf16" if route == "base" or a.r * a.s == 1 else "wgrad_gemm_bf16:taps", route)
     assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
 
 
@@ -331,10 +351,10 @@ CHANNEL_TAIL_CASES = [
 
 @pytest.mark.parametrize("case", range(len(CHANNEL_TAIL_CASES)))
 @pytest.mark.parametrize("pre", [True, False])
-def test_channel_counts_not_multiples_of_64(case, pre):
+def test_channel_counts_not_multiples_of_64(case, pre, route):
     a = CHANNEL_TAIL_CASES[case]
     fb = "gemm1x1" if a.r * a.s == 1 else "strip"
-    _check_all(a, "bf16", BLK, BLK, pre, 7500 + case, (fb, fb, "wgrad_gemm"))
+    _check_all(a, "bf16", BLK, BLK, pre, 7500 + case, (fb, fb, "wgrad_gemm"), route)
 
 
 STRIDED_1X1_CASES = [
@@ -351,15 +371,15 @@ STRIDED_1X1_CASES = [
 
 @pytest.mark.parametrize("case", range(len(STRIDED_1X1_CASES)))
 @pytest.mark.parametrize("pre", [True, False])
-def test_strided_1x1_backprop_data_writes_every_pixel(case, pre):
+def test_strided_1x1_backprop_data_writes_every_pixel(case, pre, route):
     """The output tensor starts as NaN bit patterns (out_tensor), so a pixel that neither the computed class nor the
     zeros next to it (or the fill pass) reach fails the comparison; the ReLU-mask and channel-sum compounds run on the
     same launches."""
-    _check_all(STRIDED_1X1_CASES[case], "bf16", BLK, BLK, pre, 7700 + case, ("gemm1x1", "gemm1x1", "wgrad"))
+    _check_all(STRIDED_1X1_CASES[case], "bf16", BLK, BLK, pre, 7700 + case, ("gemm1x1", "gemm1x1", "wgrad"), route)
 
 
 @pytest.mark.parametrize("case", range(len(CHANNEL_TAIL_CASES)))
-def test_channel_tail_loads_never_look_behind_the_filter_tensor(case):
+def test_channel_tail_loads_never_look_behind_the_filter_tensor(case, route):
     """Filter rows past Cout and channel blocks past Cin of a partial tile / stage must read as zeros, not whatever
     lies behind the filter tensor: here the blocked filters sit at the front of a larger allocation whose remainder
     holds NaN bit patterns (all accesses stay inside that allocation, so nothing can fault).  A NaN picked up there
@@ -462,15 +482,16 @@ STRIDED_STRIP_CASES = [
 
 @pytest.mark.parametrize("case", range(len(STRIDED_STRIP_CASES)))
 @pytest.mark.parametrize("pre", [True, False])
-def test_strided_strip_kernel(case, pre):
+def test_strided_strip_kernel(case, pre, route):
     a = STRIDED_STRIP_CASES[case]
-    _check_all(a, "bf16", BLK, BLK, pre, 8000 + case, ("strip", "strip", "wgrad"))
+    _check_all(a, "bf16", BLK, BLK, pre, 8000 + case, ("strip", "strip", "wgrad"), route)
 
 
 @pytest.mark.parametrize("case", range(len(STRIDED_STRIP_CASES)))
 def test_strided_strip_one_launch_per_class(case, monkeypatch):
     """NGC_STRIP_MERGE=0: the residue classes of backprop-data as separate launches instead of one grid."""
     monkeypatch.setenv("NGC_STRIP_MERGE", "0")
+    monkeypatch.setenv("NGC_FWD_FEW", "0")
     _check_all(STRIDED_STRIP_CASES[case], "bf16", BLK, BLK, True, 8050 + case, ("strip", "strip", "wgrad"))
 
 
@@ -762,14 +783,16 @@ STRIP_PATH_CASES = [
 @pytest.mark.parametrize("switch", [None, ("NGC_STRIP_TAIL", "0"), ("NGC_STRIP_SPLIT", "0"), ("NGC_STRIP_CPS", "1"),
                                     ("NGC_WGRAD_NT", "0"), ("NGC_WGRAD_NT", "1")])
 @pytest.mark.parametrize("a", STRIP_PATH_CASES)
-def test_strip_epilogue_split_and_stage_paths(a, switch, monkeypatch):
+def test_strip_epilogue_split_and_stage_paths(a, switch, monkeypatch, route):
     """The strip kernel's store path with the epilogues inside the last chunk, the shared last fragment and two
     chunks per LDS stage, and each of them switched off (the paths the other launches take); the backprop-filters
     partial stores in both forms.  Forward with and without bias + ReLU, backprop-data bare and with the ReLU-backprop
     mask, backprop-filters: all against the oracle."""
     if switch:
+        if route == "default":
+            pytest.skip("one run by the dispatcher's choice is enough")
         monkeypatch.setenv(*switch)
-    _check_all(a, "bf16", BLK, BLK, True, 9250 + a.c + a.h, ("strip", "strip", "wgrad"))
+    _check_all(a, "bf16", BLK, BLK, True, 9250 + a.c + a.h, ("strip", "strip", "wgrad"), route)
 
 
 @pytest.mark.parametrize("a,variant", [
@@ -859,7 +882,7 @@ EPILOGUE_BIT_CASES = [
 
 
 @pytest.mark.parametrize("case", range(len(EPILOGUE_BIT_CASES)))
-def test_epilogue_bias_relu_single_rne_rounding_bit_exact(case, expect=None):
+def test_epilogue_bias_relu_single_rne_rounding_bit_exact(case, route, expect=None):
     """Bias, then ReLU, then exactly one round-to-nearest-even conversion of the fp32 value.  The filter is a single
     tap of ones on c == k mod C, so the fp32 accumulator of every kernel equals one input element exactly; the input
     values and the fp32 biases are chosen so that x + b lands on exact ties of the bf16 grid (both parities of the kept
@@ -883,7 +906,8 @@ def test_epilogue_bias_relu_single_rne_rounding_bit_exact(case, expect=None):
         w[k, k % a.c, r0, s0] = 1.0
     run = Run(a, "bf16", xl, yl, True)
     run.fwd(x, w, bias=b, relu=True)
-    assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_FWD).startswith(expect or variant), ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_FWD)
+    few = route == "default" and not expect and case < 2       # case 2: 6 output tiles of one unit stay with the GEMM
+    _runs(run.last_desc, ng.NGC_OP_FWD, expect or variant + (":few" if few else ":gather" if route == "default" and variant == "direct" else ""), route)
     raw = host(run.last_raw, np.uint16)
     if yl == BLK:
         got = oracle.blocked16_to_nchw(raw.reshape(a.n, (a.k + 15) // 16, P, Q, 16), a.k)
@@ -930,4 +954,4 @@ def test_filter_resident_strip_kernel(case, monkeypatch):
 
 def test_filter_resident_strip_kernel_epilogue_bits(monkeypatch):
     monkeypatch.setenv("NGC_ROWS", "1")
-    test_epilogue_bias_relu_single_rne_rounding_bit_exact(0, expect="strip_rows_bf16")
+    test_epilogue_bias_relu_single_rne_rounding_bit_exact(0, "default", expect="strip_rows_bf16")
