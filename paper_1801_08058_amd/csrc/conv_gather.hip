@@ -659,7 +659,8 @@ __global__ __launch_bounds__(64 * (BT / 32) * (BT / 32) * KS) void gather_wgrad(
 static int gcd_(int a, int b) { return b ? gcd_(b, a % b) : a; }
 
 // what the kernels address: 32-bit byte offsets into every operand, window rows / columns in 31-bit masks, the residue
-// classes of backprop-data in a table
+// classes of backprop-data in a table; what a grid holds: 2^32 - 1 threads (8 a position in the tiles that take most) and
+// 65535 tiles of channels
 bool gather_takes(const ngc_conv_desc &d, int op, int P, int Q)
 {
     const char *force = env_switch(SW_GATHER_TILE);                       // tests only: 0 = never
@@ -669,6 +670,8 @@ bool gather_takes(const ngc_conv_desc &d, int op, int P, int Q)
     if (d.r > 31 || d.s > 31 || bytes(d.x_layout, d.n, d.c, (size_t)d.h * d.w) >= lim || bytes(d.y_layout, d.n, d.k, (size_t)P * Q) >= lim ||
         (size_t)d.k * d.c * d.r * d.s * sz >= lim)
         return false;
+    const size_t positions = op == NGC_OP_FWD ? (size_t)d.n * P * Q : (size_t)d.n * d.h * d.w;
+    if (op != NGC_OP_BWD_FILTERS && (positions + 64 > (size_t)1 << 29 || ((op == NGC_OP_FWD ? d.k : d.c) + 31) / 32 > 65535)) return false;
     if (op == NGC_OP_BWD_DATA) return d.stride_h <= GATHER_CLASSES && d.stride_w <= GATHER_CLASSES;
     return op == NGC_OP_FWD || (size_t)((d.k + 63) / 64) * (((size_t)d.c * d.r * d.s + 63) / 64) <= 65535;
 }

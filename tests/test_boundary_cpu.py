@@ -454,6 +454,21 @@ def test_names_tell_the_kernels_of_a_variant_apart(monkeypatch):
     assert off[0] == ws[0] and off[1] == ws[1] and off[2] != ws[2] and off[3] != ws[3] and off[6] == 0 < ws[6]
 
 
+def test_gather_gemm_leaves_what_its_grid_does_not_hold():
+    """More than 65535 tiles of 32 channels, or so many positions that their threads pass 2^32: the kernels with a
+    thread per output take the node, as they did before the gather GEMM."""
+    kw = dict(dtype=ng.NGC_F32, x_layout=ng.NGC_NCHW, y_layout=ng.NGC_NCHW)
+    most = 32 * 65535
+    assert ng.ngc_conv_variant(ng.make_desc(1, 1, 3, 3, most, 1, 1, **kw), ng.NGC_OP_FWD) == "direct:gather"
+    assert ng.ngc_conv_variant(ng.make_desc(1, 1, 3, 3, most + 1, 1, 1, **kw), ng.NGC_OP_FWD) == "direct"
+    assert ng.ngc_conv_variant(ng.make_desc(1, most, 3, 3, 1, 1, 1, **kw), ng.NGC_OP_BWD_DATA) == "direct:gather"
+    assert ng.ngc_conv_variant(ng.make_desc(1, most + 1, 3, 3, 1, 1, 1, **kw), ng.NGC_OP_BWD_DATA) == "direct"
+    kw["dtype"] = ng.NGC_BF16
+    for h, name in ((16383, "direct:gather"), (16384, "direct")):
+        d = ng.make_desc(1, 1, h, 32768, 1, 7, 7, pad_below=(3, 3), pad_above=(3, 3), **kw)
+        assert ng.ngc_conv_variant(d, ng.NGC_OP_FWD) == ng.ngc_conv_variant(d, ng.NGC_OP_BWD_DATA) == name
+
+
 def test_sliced_nodes_size_their_workspace_for_every_group():
     """A node that runs as launches over groups of images (tensors of 2 GiB or more) hands every group the same
     workspace; the split of a backprop-filters reduction is not monotone in the batch, so the remainder group can need
