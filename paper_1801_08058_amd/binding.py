@@ -1,5 +1,5 @@
 """Thin binding of libngconv.so (the C ABI declared in include/ngconv.h): ctypes for the queries, and for the calls that
-launch work the extension _pycall.so (csrc/pycall.c), which converts the arguments in C.
+launch work the extension _pycall (csrc/pycall.c), which converts the arguments in C.
 
 Argument marshalling only: every step of the path runs in the HIP kernels.  Tensors are
 passed as anything with a ``data_ptr()`` (torch tensors) or as raw integer device
@@ -11,10 +11,11 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libngconv.so")
-CALL_PATH = os.path.join(_HERE, "_pycall.so")
+CALL_PATH = os.path.join(_HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))     # of this interpreter
 
 # enums of include/ngconv.h
 NGC_OK, NGC_BAD_ARG, NGC_BAD_SHAPE, NGC_UNSUPPORTED, NGC_WORKSPACE_TOO_SMALL, NGC_LAUNCH_FAILED = 0, -1, -2, -3, -4, -5
@@ -66,7 +67,7 @@ def _load() -> ctypes.CDLL:
     for path in (LIB_PATH, CALL_PATH):
         if not os.path.exists(path):
             raise ImportError(
-                f"{path} is missing: build it with `python -m paper_1801_08058_amd.build` "
+                f"{path} is missing: build it with `python {os.path.join(_HERE, 'build.py')}` "
                 "(there is no fallback path)")
     # PyTorch supplies device memory and streams and ships its own HIP runtime under the same
     # soname as the system one; the process must end up with ONE runtime, and it has to be the
@@ -156,6 +157,7 @@ def _load_calls():
     from . import _pycall
     for name in _pycall.names():
         _pycall.bind(name, ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value)
+    _pycall.descs(ngc_conv_desc, ngc_conv3d_desc)
     return _pycall
 
 

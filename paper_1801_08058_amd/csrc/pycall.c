@@ -9,6 +9,7 @@
 #include "../../include/ngconv.h"
 
 static PyObject *s_data_ptr, *s_numel, *s_element_size;
+static PyObject *t_desc[2];      /* the descriptor classes: two spatial axes, three */
 
 /* None -> NULL, int -> that address, anything else -> its data_ptr().  -1 with an exception set on failure. */
 static int as_ptr(PyObject *o, void **out)
@@ -40,15 +41,35 @@ static int as_bytes(PyObject *o, size_t *out)
     return PyErr_Occurred() ? -1 : 0;
 }
 
-/* the descriptor: a ctypes structure of exactly `size` bytes, copied */
-static int as_desc(PyObject *o, void *out, Py_ssize_t size)
+/* a stream: None or an address; a false value is the default stream.  What is no address (a stream object) is refused. */
+static int as_stream(PyObject *o, void **out)
+{
+    const int set = o == Py_None ? 0 : PyObject_IsTrue(o);
+    *out = NULL;
+    if (set <= 0) return set;
+    if (!PyLong_Check(o)) {
+        PyErr_Format(PyExc_TypeError, "stream: None or its address expected, not %.100s", Py_TYPE(o)->tp_name);
+        return -1;
+    }
+    *out = PyLong_AsVoidPtr(o);
+    return PyErr_Occurred() ? -1 : 0;
+}
+
+/* the descriptor: an instance of the ctypes structure, whose first `size` bytes are copied */
+static int as_desc(PyObject *o, PyObject *type, void *out, Py_ssize_t size)
 {
     Py_buffer b;
+    const int is = type ? PyObject_IsInstance(o, type) : 0;
+    if (is < 0) return -1;
+    if (!is) {
+        PyErr_Format(PyExc_TypeError, "descriptor of another type expected, not %.100s", Py_TYPE(o)->tp_name);
+        return -1;
+    }
     if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return -1;
-    const int ok = b.len == size;
+    const int ok = b.len >= size;
     if (ok) memcpy(out, b.buf, (size_t)size);
+    else PyErr_SetString(PyExc_TypeError, "descriptor of another size expected");
     PyBuffer_Release(&b);
-    if (!ok) PyErr_SetString(PyExc_TypeError, "descriptor of another type expected");
     return ok ? 0 : -1;
 }
 
@@ -73,9 +94,9 @@ static int parse(PyObject *const *a, Py_ssize_t n, int rank3, int np, int ws, Ar
         PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
         return -1;
     }
-    if (rank3 ? as_desc(a[0], &out->d3, sizeof(out->d3)) : as_desc(a[0], &out->d, sizeof(out->d))) return -1;
+    if (rank3 ? as_desc(a[0], t_desc[1], &out->d3, sizeof(out->d3)) : as_desc(a[0], t_desc[0], &out->d, sizeof(out->d))) return -1;
     for (int i = 0; i < np; ++i)
-        if (as_ptr(a[1 + i], &out->p[i])) return -1;
+        if (i == np - 1 ? as_stream(a[1 + i], &out->p[i]) : as_ptr(a[1 + i], &out->p[i])) return -1;
     return ws ? as_bytes(a[np - 1], &out->ws_bytes) : 0;
 }
 
@@ -110,7 +131,7 @@ ENTRY(ngc_conv3d_bwd_data_relu_db, 1, 7, 1, (&x.d3, x.p[0], x.p[1], x.p[2], x.p[
 ENTRY(ngc_conv3d_bias_grad, 1, 4, 1, (&x.d3, x.p[0], x.p[1], x.p[2], x.ws_bytes, x.p[3]))
 ENTRY(ngc_conv3d_bwd_filters, 1, 5, 1, (&x.d3, x.p[0], x.p[1], x.p[2], x.p[3], x.ws_bytes, x.p[4]))
 
-/* entry points whose leading arguments are integers: KINDS holds 'i' (integer) or 'p' (pointer) per argument */
+/* entry points whose leading arguments are integers: KINDS holds 'i' (integer), 'p' (pointer) or 's' (stream) per argument */
 static int parse_kinds(PyObject *const *a, Py_ssize_t n, const char *kinds, long long *i, void **p)
 {
     if (n != (Py_ssize_t)strlen(kinds)) {
@@ -118,7 +139,7 @@ static int parse_kinds(PyObject *const *a, Py_ssize_t n, const char *kinds, long
         return -1;
     }
     for (Py_ssize_t k = 0; k < n; ++k)
-        if (kinds[k] == 'i' ? as_int(a[k], i++) : as_ptr(a[k], p++)) return -1;
+        if (kinds[k] == 'i' ? as_int(a[k], i++) : kinds[k] == 's' ? as_stream(a[k], p++) : as_ptr(a[k], p++)) return -1;
     return 0;
 }
 
@@ -137,9 +158,9 @@ static int parse_kinds(PyObject *const *a, Py_ssize_t n, const char *kinds, long
         return PyLong_FromLong(rc);                                                         \
     }
 
-ENTRY_KINDS(ngc_softmax, "iiippp", ((int32_t)i[0], i[1], (int32_t)i[2], p[0], p[1], p[2]))
-ENTRY_KINDS(ngc_softmax_bwd, "iiipppp", ((int32_t)i[0], i[1], (int32_t)i[2], p[0], p[1], p[2], p[3]))
-ENTRY_KINDS(ngc_layout_convert, "iiiiipipip",
+ENTRY_KINDS(ngc_softmax, "iiipps", ((int32_t)i[0], i[1], (int32_t)i[2], p[0], p[1], p[2]))
+ENTRY_KINDS(ngc_softmax_bwd, "iiippps", ((int32_t)i[0], i[1], (int32_t)i[2], p[0], p[1], p[2], p[3]))
+ENTRY_KINDS(ngc_layout_convert, "iiiiipipis",
             ((int32_t)i[0], (int32_t)i[1], (int32_t)i[2], (int32_t)i[3], (int32_t)i[4], p[0], (int32_t)i[5], p[1], (int32_t)i[6], p[2]))
 
 static const struct {
@@ -180,10 +201,24 @@ static PyObject *bind(PyObject *self, PyObject *args)
     return NULL;
 }
 
+/* descs(class, class3): the descriptor classes the entry points take */
+static PyObject *descs(PyObject *self, PyObject *args)
+{
+    PyObject *d, *d3;
+    (void)self;
+    if (!PyArg_ParseTuple(args, "O!O!", &PyType_Type, &d, &PyType_Type, &d3)) return NULL;
+    Py_INCREF(d);
+    Py_INCREF(d3);
+    Py_XSETREF(t_desc[0], d);
+    Py_XSETREF(t_desc[1], d3);
+    Py_RETURN_NONE;
+}
+
 #define METHOD(NAME) {#NAME, (PyCFunction)(void (*)(void))w_##NAME, METH_FASTCALL, NULL}
 static PyMethodDef methods[] = {
     {"names", names, METH_NOARGS, NULL},
     {"bind", bind, METH_VARARGS, NULL},
+    {"descs", descs, METH_VARARGS, NULL},
     METHOD(ngc_conv_fwd), METHOD(ngc_conv_bwd_data), METHOD(ngc_conv_bwd_data_relu), METHOD(ngc_conv_bwd_data_relu_db), METHOD(ngc_bias_grad),
     METHOD(ngc_conv_bwd_filters), METHOD(ngc_conv_bwd_filters_noalloc), METHOD(ngc_conv_bwd_data_filters), METHOD(ngc_conv_bwd_data_filters_relu),
     METHOD(ngc_conv3d_fwd), METHOD(ngc_conv3d_bwd_data), METHOD(ngc_conv3d_bwd_data_relu), METHOD(ngc_conv3d_bwd_data_relu_db),

@@ -33,6 +33,42 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, name), name
 
 
+def test_binding_refuses_what_is_no_descriptor_or_stream():
+    """The calls that launch work convert their arguments in C: a descriptor is an instance of its class (not any buffer of
+    its size), a stream None or an address."""
+    d, bad = _good(n=0), 0x1000                          # n = 0: whatever passes the binding stops at the validation
+    call = lambda desc, stream: ng.ngc_conv_fwd(desc, bad, bad, bad, bad, None, stream, check=False)
+    assert call(d, None) == call(d, 0) == call(d, 0x40) == ng.NGC_BAD_SHAPE
+
+    class Sub(ng.ngc_conv_desc):
+        _fields_ = [("mine", ctypes.c_int32)]
+    sub = Sub()
+    ctypes.memmove(ctypes.byref(sub), ctypes.byref(d), ctypes.sizeof(d))
+    assert call(sub, None) == ng.NGC_BAD_SHAPE
+    for other in (bytes(d), bytearray(bytes(d)), _good3(), None, 7):
+        with pytest.raises(TypeError):
+            call(other, None)
+    with pytest.raises(TypeError):
+        ng.ngc_conv3d_fwd(d, bad, bad, bad, bad, None, None, check=False)
+
+    class Stream:
+        def data_ptr(self):
+            return 0x40
+    for stream in (Stream(), object(), "s", 1.5):
+        with pytest.raises(TypeError):
+            call(d, stream)
+        with pytest.raises(TypeError):
+            ng.ngc_softmax(ng.NGC_F32, 0, 0, bad, bad, stream, check=False)
+        with pytest.raises(TypeError):
+            ng.ngc_layout_convert(ng.NGC_F32, 0, 0, 0, 0, bad, ng.NGC_NCHW, bad, ng.NGC_NCHW16C, stream, check=False)
+
+
+def test_binding_extension_is_named_for_the_interpreter():
+    from importlib.machinery import EXTENSION_SUFFIXES
+    from paper_1801_08058_amd import binding
+    assert os.path.basename(binding._call.__file__) == "_pycall" + EXTENSION_SUFFIXES[0]
+
+
 def test_struct_size_matches_header():
     fields = re.findall(r"int32_t\s+([a-z_, ]+);", re.search(r"typedef struct \{(.*?)\} ngc_conv_desc;", open(HEADER).read(), re.S).group(1))
     names = [n.strip() for f in fields for n in f.split(",")]
