@@ -341,8 +341,19 @@ static hipError_t launch_softmax_e(bool bwd, const void *a, const void *b, void 
 hipError_t launch_softmax(int dtype, bool bwd, const void *a, const void *b, void *out, uint32_t rows, int cols, bool aligned, hipStream_t st)
 {
     const bool grid16 = aligned && cols % (dtype == NGC_BF16 ? 8 : 4) == 0;
-    return dtype == NGC_BF16 ? launch_softmax_e<uint16_t>(bwd, a, b, out, rows, cols, grid16, st)
-                             : launch_softmax_e<float>(bwd, a, b, out, rows, cols, grid16, st);
+    // a grid holds fewer than 2^32 threads: more rows than that take several launches
+    const uint32_t most = 0xFFFFFFFFu / (uint32_t)softmax_plan(dtype, cols, bwd).GL / 256 * 256;
+    for (uint32_t r0 = 0; r0 < rows;) {
+        const uint32_t n = rows - r0 < most ? rows - r0 : most;
+        const size_t at = (size_t)r0 * cols * (dtype == NGC_BF16 ? 2 : 4);
+        const char *pa = static_cast<const char *>(a) + at, *pb = b ? static_cast<const char *>(b) + at : nullptr;
+        char *po = static_cast<char *>(out) + at;
+        const hipError_t e = dtype == NGC_BF16 ? launch_softmax_e<uint16_t>(bwd, pa, pb, po, n, cols, grid16, st)
+                                               : launch_softmax_e<float>(bwd, pa, pb, po, n, cols, grid16, st);
+        if (e != hipSuccess) return e;
+        r0 += n;
+    }
+    return hipSuccess;
 }
 
 }  // namespace ngc

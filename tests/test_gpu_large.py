@@ -130,3 +130,17 @@ def test_rank3_ops_on_tensors_past_two_gib():
     idx = g.integers(0, k * c * 27, size=32)
     ref = REPS * oracle.conv3d_bwd_filters_at(a1, x1, dy1, idx)
     assert np.abs(dw.cpu().numpy().astype(np.float64)[idx] - ref).max() / np.abs(ref).max() <= bound("bf16", "dw")
+
+
+@pytest.mark.timeout(600)
+def test_softmax_rows_past_a_grid():
+    """4194304 rows of a workgroup of 1024 threads: a thread more than a grid holds; rows off the 16-byte grid, in place."""
+    rows, cols = 1 << 22, 8193
+    print(f"case softmax {rows} x {cols} bf16, 69 GB", flush=True)
+    t = torch.zeros(rows * cols, dtype=torch.int16, device="cuda")
+    assert ng.ngc_softmax_variant(ng.NGC_BF16, cols) == "softmax_rows_wg"
+    ng.ngc_softmax(ng.NGC_BF16, rows, cols, t, t, stream())
+    torch.cuda.synchronize()
+    want = np.full(cols, oracle.f32_to_bf16_bits_rne(np.array([1.0 / cols], dtype=np.float32))[0], dtype=np.uint16)
+    for row in (0, 1, rows // 2, rows - 257, rows - 256, rows - 255, rows - 1):
+        assert np.array_equal(host(t[row * cols : (row + 1) * cols].clone(), np.uint16), want), row
