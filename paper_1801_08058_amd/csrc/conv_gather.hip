@@ -467,6 +467,11 @@ struct GatherWgradParams {
 // One workgroup: BT output channels x BT (c, r, s) columns of dw over a chunk of positions; (BT / 32)^2 waves side by side
 // times KS slices of every step's positions, UPS units each.  DYV / XV: the U positions of a unit are contiguous and
 // aligned in dy / x.
+//
+// dw is a sum over very many positions.  A single chain of additions per element lost bits that the kernel with 256 chains
+// per element and a tree keeps (relative 2-norm error of 8 x 64 x 45 x 37 -> 96, 3x3, fp32: 2.3e-7 against 1.5e-7; in one
+// part 1.4e-6), so chains are short here: 8 positions (bf16: 32) of a step, then into a sum over the steps, and (LONG, for few
+// parts) 8 of those into a total: 1.1e-7, in one part 1.4e-7, for 43.5 -> 46.7 us.
 template <typename T, int BT, int KS, int UPS>
 struct GatherWgradTile {
     static constexpr int WT = BT / 32, NW = WT * WT * KS, NT = 64 * NW, NU = UPS * KS;
@@ -478,7 +483,7 @@ struct GatherWgradTile {
     static_assert(RPT * NT == BT * NU && NT % NU == 0 && UPS % 2 == 0, "tile shape");
 };
 
-template <typename T, int BT, int KS, int UPS, bool DYV, bool XV>
+template <typename T, int BT, int KS, int UPS, bool DYV, bool XV, bool LONG>
 __global__ __launch_bounds__(64 * (BT / 32) * (BT / 32) * KS) void gather_wgrad(const GatherWgradParams p)
 {
     preload_kernargs(p);
@@ -513,9 +518,9 @@ __global__ __launch_bounds__(64 * (BT / 32) * (BT / 32) * KS) void gather_wgrad(
         xdw[i] = (t - r * p.S) * p.dil_w;
         xoff[i] = (p.x_blocked ? (c >> 4) * p.x_c + (c & 15) : c * p.x_c) + (xdh[i] * p.W + xdw[i]) * p.x_px;
     }
-    gf32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    constexpr gf32x16 ZERO = {};
+    constexpr int NCH = sizeof(T) == 4 ? 2 : 1;                          // chains of a step: 8 positions each (fp32), 32 (bf16)
+    gf32x16 acc = ZERO, total = ZERO;
     uint32_t xr[RPT][U], kr[RPT][U];
     uint4 xv[RPT], kv[RPT];
 #pragma unroll
@@ -589,13 +594,20 @@ __global__ __launch_bounds__(64 * (BT / 32) * (BT / 32) * KS) void gather_wgrad(
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         wg_barrier_nofence();
         const unsigned char *ks = smem + (s & 1) * BUF, *xs = ks + NU * PL;
+        gf32x16 chain[2] = {ZERO, ZERO};
 #pragma unroll
         for (int q = 0; q < UPS / 2; ++q) {
             const int pl = slice * UPS + 2 * q + half;
-            acc = mma_pair<T>(*reinterpret_cast<const uint4 *>(ks + pl * PL + (qk + l32) * 16),
-                              *reinterpret_cast<const uint4 *>(xs + pl * PL + (qx + l32) * 16), acc);
+            chain[q % NCH] = mma_pair<T>(*reinterpret_cast<const uint4 *>(ks + pl * PL + (qk + l32) * 16),
+                                       *reinterpret_cast<const uint4 *>(xs + pl * PL + (qx + l32) * 16), chain[q % NCH]);
+        }
+        acc += NCH > 1 ? chain[0] + chain[1] : chain[0];                 // carried into the next step: 16 registers and a workgroup less
+        if (LONG && (s & 7) == 7) {
+            total += acc;
+            acc = ZERO;
         }
     }
+    if (LONG) acc += total;
     if constexpr (KS > 1) {                                              // slice z adds up the groups (4 rows) z, z + KS, ... over all slices
         wg_barrier_nofence();
         float *red = reinterpret_cast<float *>(smem);
@@ -828,35 +840,39 @@ size_t gather_wgrad_workspace(const ngc_conv_desc &d, int P, int Q)
     return parts > 1 ? (size_t)parts * wgrad_pitch(d) * sizeof(float) : 0;
 }
 
-template <typename T, int BT, int KS, int UPS, bool DYV, bool XV>
+template <typename T, int BT, int KS, int UPS, bool DYV, bool XV, bool LONG>
 static hipError_t launch_gather_wgrad_l(const GatherWgradParams &p, dim3 grid, hipStream_t st)
 {
     static LdsLimitOnce lds_limit;
-    const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&gather_wgrad<T, BT, KS, UPS, DYV, XV>));
+    const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&gather_wgrad<T, BT, KS, UPS, DYV, XV, LONG>));
     if (e != hipSuccess) return e;
     typedef GatherWgradTile<T, BT, KS, UPS> G;
-    NGC_LAUNCH((gather_wgrad<T, BT, KS, UPS, DYV, XV>), grid, dim3(G::NT), G::LDS, st, p);
+    NGC_LAUNCH((gather_wgrad<T, BT, KS, UPS, DYV, XV, LONG>), grid, dim3(G::NT), G::LDS, st, p);
     return launch_result();
 }
 
-template <typename T, int BT, int KS, int UPS>
+template <typename T, int BT, int KS, int UPS, bool LONG>
 static hipError_t launch_gather_wgrad_t(GatherWgradParams &p, int parts, bool dyvec, bool xvec, hipStream_t st)
 {
     constexpr uint32_t step = GatherWgradTile<T, BT, KS, UPS>::STEP;
     p.chunk = ((p.M + parts - 1) / parts + step - 1) / step * step;
     p.ctiles = (p.C * p.R * p.S + BT - 1) / BT;
     const dim3 grid((p.M + p.chunk - 1) / p.chunk, (unsigned)((p.K + BT - 1) / BT) * p.ctiles);
-    if (dyvec) return xvec ? launch_gather_wgrad_l<T, BT, KS, UPS, true, true>(p, grid, st) : launch_gather_wgrad_l<T, BT, KS, UPS, true, false>(p, grid, st);
-    return launch_gather_wgrad_l<T, BT, KS, UPS, false, false>(p, grid, st);  // x is only contiguous where dy is
+    if (dyvec) return xvec ? launch_gather_wgrad_l<T, BT, KS, UPS, true, true, LONG>(p, grid, st) : launch_gather_wgrad_l<T, BT, KS, UPS, true, false, LONG>(p, grid, st);
+    return launch_gather_wgrad_l<T, BT, KS, UPS, false, false, LONG>(p, grid, st);  // x is only contiguous where dy is
 }
 
 template <typename T>
 static hipError_t launch_gather_wgrad(GatherWgradParams &p, int v, int parts, bool dyvec, bool xvec, hipStream_t st)
 {
+    // The sum over the steps is as long as a chain of 256 per element from 8 parts on (32 positions a step in two slices),
+    // from 4 on in the small tile (64 in four).
     switch (v) {
-    case 1: return launch_gather_wgrad_t<T, 64, 2, 4>(p, parts, dyvec, xvec, st);
-    case 2: return launch_gather_wgrad_t<T, 32, 8, 4>(p, parts, dyvec, xvec, st);
-    default: return launch_gather_wgrad_t<T, 32, 4, 4>(p, parts, dyvec, xvec, st);
+    case 1:
+        return parts < 8 ? launch_gather_wgrad_t<T, 64, 2, 4, true>(p, parts, dyvec, xvec, st) : launch_gather_wgrad_t<T, 64, 2, 4, false>(p, parts, dyvec, xvec, st);
+    case 2: return launch_gather_wgrad_t<T, 32, 8, 4, false>(p, parts, dyvec, xvec, st);      // at most 512 positions
+    default:
+        return parts < 4 ? launch_gather_wgrad_t<T, 32, 4, 4, true>(p, parts, dyvec, xvec, st) : launch_gather_wgrad_t<T, 32, 4, 4, false>(p, parts, dyvec, xvec, st);
     }
 }
 
@@ -867,6 +883,12 @@ hipError_t launch_gather_bwd_filters(const ngc_conv_desc &d, int P, int Q, const
     const size_t sz = d.dtype == NGC_F32 ? 4 : 2;
     const int U = (int)(16 / sz);
     GatherWgradParams p = {};
+    p.M = (uint32_t)d.n * P * Q;
+    p.pitch = wgrad_pitch(d);
+    GatherWgradPlan plan = wgrad_plan(d, P, Q);
+    if (plan.parts > 1 && (!ws || ws_bytes < (size_t)plan.parts * p.pitch * sizeof(float))) {
+        plan = {1, 1};
+    }
     p.x = x; p.dy = dy;
     p.C = d.c; p.H = d.h; p.W = d.w; p.K = d.k; p.P = P; p.Q = Q; p.R = d.r; p.S = d.s;
     p.sh = d.stride_h; p.sw = d.stride_w; p.dil_h = d.dil_h; p.dil_w = d.dil_w; p.pb_h = d.pad_below_h; p.pb_w = d.pad_below_w;
@@ -880,15 +902,10 @@ hipError_t launch_gather_bwd_filters(const ngc_conv_desc &d, int P, int Q, const
     const bool dyvec = !p.dy_blocked && (P * Q) % U == 0;
     const bool xvec = dyvec && !p.x_blocked && d.r == 1 && d.s == 1 && d.stride_h == 1 && d.stride_w == 1 && P == d.h && Q == d.w &&
                       d.pad_below_h == 0 && d.pad_below_w == 0;
-    p.M = (uint32_t)d.n * P * Q;
-    p.pitch = wgrad_pitch(d);
-    const GatherWgradPlan plan = wgrad_plan(d, P, Q);
-    int parts = plan.parts;
-    if (parts > 1 && (!ws || ws_bytes < (size_t)parts * p.pitch * sizeof(float))) parts = 1;
-    p.out = parts > 1 ? static_cast<float *>(ws) : dw;
-    const hipError_t e = d.dtype == NGC_F32 ? launch_gather_wgrad<float>(p, plan.tile, parts, dyvec, xvec, st)
-                                            : launch_gather_wgrad<uint16_t>(p, plan.tile, parts, dyvec, xvec, st);
-    if (e != hipSuccess || parts == 1) return e;
+    p.out = plan.parts > 1 ? static_cast<float *>(ws) : dw;
+    const hipError_t e = d.dtype == NGC_F32 ? launch_gather_wgrad<float>(p, plan.tile, plan.parts, dyvec, xvec, st)
+                                            : launch_gather_wgrad<uint16_t>(p, plan.tile, plan.parts, dyvec, xvec, st);
+    if (e != hipSuccess || plan.parts == 1) return e;
     return launch_bias_grad_reduce(p.out, dw, (int)((p.M + p.chunk - 1) / p.chunk), d.k * d.c * d.r * d.s, (int)p.pitch, st);
 }
 

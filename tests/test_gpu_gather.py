@@ -44,6 +44,48 @@ def test_gather_tiles(case, tile, wgrad, monkeypatch):
     assert ng.ngc_conv_variant(desc_of(a, dtype, xl, yl), ng.NGC_OP_FWD) == names[0]
 
 
+@pytest.mark.parametrize("dtype,node", [
+    ("f32", (2, 21, 33, 10, 128, 3, 1)),      # 660 positions in 20 parts
+    ("f32", (8, 64, 45, 37, 96, 3, 1)),       # 13320 positions, partials near their limit
+    ("f32", (8, 128, 14, 14, 160, 3, 1)),
+    ("f32", (2, 300, 40, 40, 300, 3, 1)),     # few parts of a large dw
+    ("f32", (1, 520, 36, 36, 1000, 3, 1)),    # one part: dw past the limit of the partials
+    ("f32", (4, 900, 24, 24, 32, 5, 1)),      # small tiles, few parts
+    ("f32", (1, 34, 14, 9, 56, 5, 1)),        # one part, eight slices
+    ("f32", (16, 20, 30, 30, 12, 3, 1)),      # small tiles
+    ("bf16", (15, 170, 22, 14, 147, 3, 1)),
+    ("bf16", (8, 40, 28, 28, 72, 3, 1)),
+])
+@pytest.mark.parametrize("with_ws", [True, False])
+def test_backprop_filters_sums_are_as_exact_as_the_thread_per_position_kernels(dtype, node, with_ws, monkeypatch):
+    """2-norm errors against 64 bits: at most 1.35 times that of 256 chains per element and a tree (the order of the sums
+    differs; one chain per element is at 1.5 to 15 times).  Each level of additions adds the square of about 2.6e-8, and
+    neither order has more than a fifth more levels than the other here."""
+    n, c, h, w, k, r, st = node
+    d = ng.make_desc(n, c, h, w, k, r, r, (st, st), (1, 1), (r // 2, r // 2), (r // 2, r // 2), ng.NGC_F32 if dtype == "f32" else ng.NGC_BF16, NCHW, NCHW)
+    monkeypatch.setenv("NGC_STAGED", "0")
+    tt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(12200 + n)
+    x, dy = torch.randn(n, c, h, w, generator=g, device="cuda").to(tt), (0.1 * torch.randn(n, k, h, w, generator=g, device="cuda")).to(tt)
+    xp = torch.nn.functional.pad(x.double(), (r // 2,) * 4)
+    dyt = dy.double().permute(1, 0, 2, 3).reshape(k, -1)
+    ref = torch.stack([dyt @ xp[:, :, i : i + h, j : j + w].permute(1, 0, 2, 3).reshape(c, -1).t() for i in range(r) for j in range(r)], 2).flatten()
+
+    def error(name):
+        assert ng.ngc_conv_variant(d, ng.NGC_OP_BWD_FILTERS) == name
+        dw = torch.full((k * c * r * r,), float("nan"), dtype=torch.float32, device="cuda")
+        need = ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS)
+        ng.ngc_conv_bwd_filters(d, x, dy, dw, torch.empty(need, dtype=torch.uint8, device="cuda") if with_ws and need else None, stream())
+        torch.cuda.synchronize()
+        return float((dw.double() - ref).norm() / ref.norm())
+
+    got = error("direct:gather")
+    monkeypatch.setenv("NGC_GATHER_TILE", "0")
+    base = error("direct")
+    print(f"case {dtype} {node} ws={with_ws}: {got:.2e} against {base:.2e}", flush=True)
+    assert got <= 1.35 * base
+
+
 def test_backprop_filters_without_a_workspace():
     """The partial sums' workspace is optional for these nodes: without it one part runs, same result to fp32 rounding."""
     a = Attrs(6, 20, 24, 24, 24, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1)
