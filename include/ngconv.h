@@ -173,7 +173,8 @@ const char *ngc_softmax_variant(int32_t dtype, int32_t cols, int32_t bwd);
 
 /* ConvolutionBackpropFilters (Sec. 3, derivative w.r.t. the filters input).
  * x in x_layout, dy in y_layout; dw: fp32 [K][C][R][S], overwritten.  The cross-workgroup
- * reduction goes through `ws` (partials) and a fixed-order second stage. */
+ * reduction goes through `ws` (partials) and a fixed-order second stage.  Nodes of the "direct" variants run without a
+ * workspace too, more slowly where ngc_conv_workspace_bytes asks for one (the sums then run in another order). */
 int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy,
                          float *dw, void *ws, size_t ws_bytes, void *hip_stream);
 

@@ -876,7 +876,17 @@ static hipError_t launch_gather_wgrad(GatherWgradParams &p, int v, int parts, bo
     }
 }
 
-// ws may be null or too small: the reduction then runs in one part
+// A node whose reduction is split, called without the workspace for it: one part of the gather GEMM takes some 1.05 us per
+// step and round of tiles, the kernel with a workgroup per element of dw about 1 us per 550 thousand products.  Measured,
+// gather / direct, us: 8 x 64 x 45 x 37 -> 96 3x3 439 / 1091, 4 x 300 x 20 x 20 -> 300 3x3 60 / 2188; 32 x 3 x 64 x 64 -> 11 3x3
+// 3039 / 247, 64 x 3 x 224 x 224 -> 32 3x3 94063 / 7660, 22 x 25 x 10 x 29 -> 68 3x3 215 / 153.
+static bool one_part_is_slow(const ngc_conv_desc &d, size_t M)
+{
+    const size_t crs = (size_t)d.c * d.r * d.s, rounds = ((size_t)((d.k + 63) / 64) * ((crs + 63) / 64) + 255) / 256;
+    const double gather = 1.05 * (double)((M + (d.dtype == NGC_F32 ? 31 : 63)) / (d.dtype == NGC_F32 ? 32 : 64)) * (double)rounds;
+    return (double)d.k * (double)crs * (double)M / 550000.0 < gather;
+}
+
 hipError_t launch_gather_bwd_filters(const ngc_conv_desc &d, int P, int Q, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes,
                                      hipStream_t st)
 {
@@ -887,6 +897,7 @@ hipError_t launch_gather_bwd_filters(const ngc_conv_desc &d, int P, int Q, const
     p.pitch = wgrad_pitch(d);
     GatherWgradPlan plan = wgrad_plan(d, P, Q);
     if (plan.parts > 1 && (!ws || ws_bytes < (size_t)plan.parts * p.pitch * sizeof(float))) {
+        if (one_part_is_slow(d, p.M)) return launch_direct_bwd_filters(d, P, Q, x, dy, dw, st);
         plan = {1, 1};
     }
     p.x = x; p.dy = dy;

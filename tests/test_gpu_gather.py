@@ -86,6 +86,27 @@ def test_backprop_filters_sums_are_as_exact_as_the_thread_per_position_kernels(d
     assert got <= 1.35 * base
 
 
+@pytest.mark.parametrize("node,name", [((32, 3, 20, 20, 11, 3), "direct"), ((4, 100, 20, 20, 90, 3), "gather")])
+def test_split_nodes_without_a_workspace_take_the_faster_kernel(node, name, monkeypatch):
+    """Bit for bit the thread-per-position kernel where one part of the GEMM would leave the chip empty."""
+    n, c, h, w, k, r = node
+    a = Attrs(n, c, h, w, k, r, r, 1, 1, 1, 1, 1, 1, 1, 1)
+    x, _, _, dy = _tensors(a, "f32", 12300 + c)
+    d = desc_of(a, "f32", NCHW, NCHW)
+    assert ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS) > 0
+    xd, dyd, got = data_to_device(x, "f32", NCHW), data_to_device(dy, "f32", NCHW), []
+    for tile in (None, "0"):
+        if tile:
+            monkeypatch.setenv("NGC_GATHER_TILE", tile)
+        dw = torch.full((k * c * r * r,), float("nan"), dtype=torch.float32, device="cuda")
+        ng.ngc_conv_bwd_filters(d, xd, dyd, dw, None, stream())
+        torch.cuda.synchronize()
+        got.append(dw)
+    assert torch.equal(*got) == (name == "direct")
+    ref = oracle.conv_bwd_filters(a, x, dy)
+    assert oracle.max_normalised_error(got[0].cpu().numpy().astype("float64").reshape(k, c, r, r), ref) <= bound("f32", "dw")
+
+
 def test_backprop_filters_without_a_workspace():
     """The partial sums' workspace is optional for these nodes: without it one part runs, same result to fp32 rounding."""
     a = Attrs(6, 20, 24, 24, 24, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1)
