@@ -1042,12 +1042,30 @@ const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q)
     return e->ok ? &e->v : nullptr;
 }
 
+// Several taps per pass where that is expected to take less time than the per-tap GEMM.  The expected times (wgrad_taps.hip)
+// are close where many (tap, tile) pairs meet few positions: 51 x 112 x 11 x 22 -> 496, 5x5 per tap 64.6, several taps 88.0 us;
+// 2 x 32 x 71 x 33 -> 288, 3x3 stride 2 12.8 / 14.4; 100 x 48 x 16 x 46 -> 240, 3x3 78.6 / 47.4; 3 x 16 x 91 x 102 -> 288, 3x3
+// 78.6 / 29.6.  Over 298 drawn nodes the choice is 0.77 of the per-tap time (geometric mean; always several taps 0.785, with nodes
+// at up to 1.38).  Nodes whose per-tap partials the static array does not hold stay with several taps, which is what lets
+// ngc_conv_bwd_filters_noalloc take them; so do the groups of images of a larger node, whose dw go there too.
+const WgradTapsPlan *wgrad_taps_for_gemm(const ngc_conv_desc *d, int P, int Q, bool group)
+{
+    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q);
+    WgradGemmParams q;
+    if (!tp || env_switch(SW_WGRAD_TAPS) || !wgrad_gemm_plan(d, P, Q, &q)) return tp;     // the switch forces a split
+    const size_t partials = (size_t)q.nparts * d->r * d->s * q.ktiles * q.ctiles * q.wk * q.wc * 64 * 64 * sizeof(float);
+    return group || partials > NGC_STATIC_SCRATCH_BYTES || tp->us < wgrad_gemm_us(q, d->r * d->s) ? tp : nullptr;
+}
+
 // A node of the all-taps strip kernel that the general kernel is expected to take less time for: few positions (one
 // part, so no second launch), or so many (k, c) tiles that the strip kernel's fixed tile and split leave compute units
 // idle or write partials needlessly.  The strip kernel's steps address their taps with constants: 0.82 of the cycles a
-// stage.  Measured: 64 -> 64 at 56x56, N = 64 strip 26.6 / general 29.5 us; 4 x 512 -> 512 at 7x7 34.0 / 11.1 us;
-// 16 x 64 x 33 x 47 -> 192 31.1 / 22.9 us; 1 x 64 -> 64 at 14x14 10.8 / 7.0 us.
-const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q)
+// stage.  Measured, strip / general, us: 64 -> 64 at 56x56, N = 64 26.6 / 29.5; 4 x 512 -> 512 at 7x7 34.0 / 11.1;
+// 16 x 64 x 33 x 47 -> 192 31.1 / 22.9; 1 x 64 -> 64 at 14x14 10.8 / 7.0; 32 x 64 -> 64 at 56x56 21.5 / 27.7.  The weights fit
+// 187 nodes, nine tenths within 11 %; where both were measured the choice is within 0.2 % of the better one on average (1.13 at
+// worst).  Strip partials that the static array does not hold, and groups of images: here the choice is also what ngc_conv_bwd_filters_noalloc takes and
+// refuses, so it stays with the plain cycle counts (within 1.5 % on average, 1.29 at worst over the 50 largest).
+const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q, bool group)
 {
     if (env_switch(SW_WGRAD_NCQ) || env_switch(SW_WGRAD_RING) || env_switch(SW_WGRAD_LATE) || env_switch(SW_WGRAD_G1) || env_switch(SW_WGRAD_NT))
         return nullptr;                                   // a switch that shapes the strip kernel asks for it
@@ -1055,12 +1073,17 @@ const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q)
     WgradStripParams q;
     if (!tp || !wgrad_strip_plan(d, P, Q, &q, nullptr)) return nullptr;
     double fixed;
-    const double stage = 0.82 * wgrad_stage_cost(4, q.ncq, 9, (q.dyplane - 128) / 1024, (q.xplane - 128) / 1024, q.nring, &fixed);
+    const double cycles = 0.82 * wgrad_stage_cost(4, q.ncq, 9, (q.dyplane - 128) / 1024, (q.xplane - 128) / 1024, q.nring, &fixed), stage = cycles / 2400.0;
     const long tiles = (long)(d->k / 64) * q.ctiles, rounds = (tiles * q.nparts + NUM_CUS - 1) / NUM_CUS;
-    const size_t dw_bytes = (size_t)9 * d->k * d->c * sizeof(float);
+    const double dw_bytes = 9.0 * d->k * d->c * sizeof(float), operands = 2.0 * d->n * ((double)d->c * d->h * d->w + (double)d->k * P * Q);
     const long stages = q.G > 1 ? (q.NI + q.G - 1) / q.G : (long)q.NI * q.nstages;
-    const double cost = rounds * (fixed + stages * stage) + wgrad_parts_cost(q.nparts > 1 ? q.nparts : 2, dw_bytes) + dw_bytes / 1600.0;
-    return 1.08 * tp->cost + 6500.0 < cost ? tp : nullptr;      // expected to measured cycles, 8 to 180 thousand of them
+    if (group || q.nparts * dw_bytes > (double)NGC_STATIC_SCRATCH_BYTES) {
+        const double strip = rounds * (fixed + stages * cycles) + wgrad_parts_cost(q.nparts > 1 ? q.nparts : 2, (size_t)dw_bytes) + dw_bytes / 1600.0;
+        return 1.08 * tp->cycles + 6500.0 < strip ? tp : nullptr;
+    }
+    const double us = 8.7 + rounds * (1.15 + stages * (0.98 + 0.715 * stage)) + 0.365e-6 * q.nparts * dw_bytes + 0.85e-6 * dw_bytes +
+                      2.7e-9 * tiles * operands;
+    return 0.93 * tp->us < us ? tp : nullptr;             // 0.9 to 0.97 choose about as well
 }
 
 bool gemm1x1_plan(const ngc_conv_desc *d, int op, int P, int Q, Gemm1x1Params *gp, bool *zero)
@@ -1186,7 +1209,8 @@ bool staged_plan(const ngc_conv_desc *d, int op, StagedPlan *out)
 }
 
 // The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
-Variant pick_uncached(const ngc_conv_desc *d, int op)
+// group: the node is a group of images of a larger one
+Variant pick_uncached(const ngc_conv_desc *d, int op, bool group)
 {
     const Variant v = pick_base(d, op);
     if ((v == V_DIRECT || v == V_UNSUPPORTED) && staged_plan(d, op, nullptr)) return V_STAGED;
@@ -1195,17 +1219,17 @@ Variant pick_uncached(const ngc_conv_desc *d, int op)
     if (v == V_DIRECT) return gather_takes(*d, op, P, Q) ? V_DIRECT_GATHER : v;
     if (op == NGC_OP_FWD && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) && conv_few_plan(d, P, Q, nullptr))
         return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
-    if (v == V_WGRAD_GEMM && wgrad_taps_plan_of(d, P, Q)) return V_WGRAD_GEMM_TAPS;
-    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q)) return V_WGRAD_STRIP_TAPS;
+    if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, group)) return V_WGRAD_GEMM_TAPS;
+    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, group)) return V_WGRAD_STRIP_TAPS;
     return v;
 }
 
-Variant pick(const ngc_conv_desc *d, int op)
+Variant pick(const ngc_conv_desc *d, int op, bool group = false)
 {
     static thread_local PlanCache<Variant> cache;
-    const PlanKey key = plan_key(d, op);
+    const PlanKey key = plan_key(d, op, group);
     Variant *e = cache.find(key);
-    if (!e) e = &cache.put(key, pick_uncached(d, op));
+    if (!e) e = &cache.put(key, pick_uncached(d, op, group));
     return *e;
 }
 
@@ -1348,11 +1372,11 @@ size_t workspace_bytes(const ngc_conv_desc *d, int op, Variant v, int P, int Q)
 size_t sliced_group_workspace(const ngc_conv_desc *d, int op, const BatchSlices &bs, int P, int Q)
 {
     const ngc_conv_desc g = with_batch(d, bs.images);
-    size_t need = workspace_bytes(&g, op, pick(&g, op), P, Q);
+    size_t need = workspace_bytes(&g, op, pick(&g, op, true), P, Q);
     const int rem = d->n % bs.images;
     if (rem) {
         const ngc_conv_desc r = with_batch(d, rem);
-        const size_t b = workspace_bytes(&r, op, pick(&r, op), P, Q);
+        const size_t b = workspace_bytes(&r, op, pick(&r, op, true), P, Q);
         if (b > need) need = b;
     }
     return need;
@@ -1461,7 +1485,7 @@ size_t ngc_conv_workspace_bytes(const ngc_conv_desc *desc, int op)
     return workspace_bytes(desc, op, pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op), P, Q);
 }
 
-const char *ngc_conv_variant(const ngc_conv_desc *desc, int op)
+static const char *variant_name(const ngc_conv_desc *desc, int op, bool group)
 {
     if (op == NGC_OP_BWD_DATA_FILTERS) {
         int P, Q;
@@ -1481,12 +1505,12 @@ const char *ngc_conv_variant(const ngc_conv_desc *desc, int op)
             if (bs.images < desc->n) {                       // groups of images: the kernel of a group
                 static thread_local char name[64];
                 const ngc_conv_desc g = with_batch(desc, bs.images);
-                snprintf(name, sizeof(name), "sliced:%s", ngc_conv_variant(&g, op));
+                snprintf(name, sizeof(name), "sliced:%s", variant_name(&g, op, true));
                 return name;
             }
         }
     }
-    switch (pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op)) {
+    switch (pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, group)) {
     case V_UNSUPPORTED: return "unsupported";
     case V_DIRECT: return "direct";
     case V_DIRECT_GATHER: return "direct:gather";
@@ -1515,6 +1539,8 @@ const char *ngc_conv_variant(const ngc_conv_desc *desc, int op)
     default: return "invalid";
     }
 }
+
+const char *ngc_conv_variant(const ngc_conv_desc *desc, int op) { return variant_name(desc, op, false); }
 
 const char *ngc_status_string(int status)
 {
@@ -2025,8 +2051,7 @@ int ngc_conv_bwd_data_filters_relu(const ngc_conv_desc *desc, const void *x, con
     return bwd_data_filters_core(desc, x, dy, w, dx, dw, ws, ws_bytes, hip_stream, 1);
 }
 
-int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy, float *dw, void *ws,
-                         size_t ws_bytes, void *hip_stream)
+static int bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes, void *hip_stream, bool group)
 {
     int P, Q;
     const int vs = validate(desc, &P, &Q);
@@ -2044,14 +2069,14 @@ int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *d
         int groups = 0;
         for (int n0 = 0; n0 < desc->n; n0 += bs.images, ++groups) {
             const ngc_conv_desc g = with_batch(desc, desc->n - n0 < bs.images ? desc->n - n0 : bs.images);
-            const int rc = ngc_conv_bwd_filters(&g, static_cast<const unsigned char *>(x) + (size_t)n0 * bs.x_bytes,
-                                                static_cast<const unsigned char *>(dy) + (size_t)n0 * bs.y_bytes,
-                                                rows + (size_t)groups * row, ws, base, hip_stream);
+            const int rc = bwd_filters(&g, static_cast<const unsigned char *>(x) + (size_t)n0 * bs.x_bytes,
+                                       static_cast<const unsigned char *>(dy) + (size_t)n0 * bs.y_bytes,
+                                       rows + (size_t)groups * row, ws, base, hip_stream, true);
             if (rc != NGC_OK) return rc;
         }
         return launch_status(launch_bias_grad_reduce(rows, dw, groups, elems, row, st));
     }
-    const Variant v = pick(desc, NGC_OP_BWD_FILTERS);
+    const Variant v = pick(desc, NGC_OP_BWD_FILTERS, group);
     if (v == V_DIRECT_GATHER) return launch_status(launch_gather_bwd_filters(*desc, P, Q, x, dy, dw, ws, ws_bytes, st));
     if (v == V_DIRECT) return launch_status(launch_direct_bwd_filters(*desc, P, Q, x, dy, dw, st));
     if (v == V_STAGED) {
@@ -2128,6 +2153,11 @@ int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *d
     hipError_t e = launch_wgrad(p, st);
     if (e != hipSuccess) return NGC_LAUNCH_FAILED;
     return launch_status(launch_wgrad_reduce(p.partial, dw, p.splits, desc->k, desc->c, desc->r, desc->s, st));
+}
+
+int ngc_conv_bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes, void *hip_stream)
+{
+    return bwd_filters(desc, x, dy, dw, ws, ws_bytes, hip_stream, false);
 }
 
 int ngc_layout_convert(int32_t dtype, int32_t n, int32_t c, int32_t h, int32_t w, const void *src, int32_t src_layout,

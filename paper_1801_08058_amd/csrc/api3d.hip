@@ -358,7 +358,13 @@ Variant3 pick3(const ngc_conv3d_desc *d, int op, ngc_conv_desc *r2)
             return d->c % 128 == 0 ? V3_IGEMM_128 : V3_IGEMM_64;
         return direct_ok ? V3_DIRECT : V3_UNSUPPORTED;
     }
-    if (wgrad_gemm3_plan(d, O, P, Q, nullptr)) return wgrad_taps3_plan(d, O, P, Q) ? V3_WGRAD_TAPS : V3_WGRAD_GEMM;
+    WgradGemmParams wp;
+    if (wgrad_gemm3_plan(d, O, P, Q, &wp)) {
+        // the faster of the two, as for rank 2: 1 x 80 x 8 x 22 x 52 -> 48, 3x3x3 stride 2 per tap 12.8, several taps 16.8 us;
+        // 6 x 160 x 13 x 28 x 24 -> 128, 3x3x3 179.8 / 79.7
+        const WgradTapsPlan *tp = wgrad_taps3_plan(d, O, P, Q);
+        return tp && (env_switch(SW_WGRAD_TAPS) || tp->us < wgrad_gemm_us(wp, taps)) ? V3_WGRAD_TAPS : V3_WGRAD_GEMM;
+    }
     return V3_DIRECT;
 }
 

@@ -502,13 +502,15 @@ struct WgradTapsPlan {
     WgradTapsParams p;
     int nt, nkb;               // taps per group, 16-channel blocks of k per workgroup
     size_t lds, ws;            // bytes of LDS, of the partials (0: one part, dw written directly)
-    double cost;               // expected cycles
+    double us, cycles;         // expected time; the cycle count the split was chosen by
 };
 // fills in the split of out->p, whose shape fields are set; false: not for this kernel
 bool wgrad_taps_plan(WgradTapsPlan *out);
-// the terms of that expectation: a stage and (fixed) a workgroup, the partials of several parts
+// the terms of that expectation in cycles: a stage and (fixed) a workgroup
 double wgrad_stage_cost(int nkb, int ncq, int nt, int dy_blocks, int x_blocks, int ring, double *fixed);
 double wgrad_parts_cost(int parts, size_t part_bytes);
+// expected time of the per-tap GEMM for a node of `taps` taps, us
+double wgrad_gemm_us(const WgradGemmParams &q, int taps);
 hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st);
 // what the caller is asked for: whole 256 bytes, never none (a call without a workspace is refused) and, for partials of
 // exactly the static array's size, not more than that

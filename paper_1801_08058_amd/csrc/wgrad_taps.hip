@@ -684,9 +684,27 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     if (tree && red < (size_t)4 * units * 1024) red = (size_t)4 * units * 1024;
     out->lds = stages > red ? stages : red;
     if (out->lds > 160 * 1024) return false;
-    out->cost = best;
     out->ws = b_parts > 1 ? (size_t)b_parts * tiles * b_ncq * b_nkb * nt * 1024 : 0;
+    out->cycles = best;
+    // Expected time, to choose between this kernel and the others: the terms above (2400 cycles a us) with the weights that
+    // fit 435 measured nodes of the window and video ranges, nine tenths of them within 8 %
+    double fixed;
+    const double stage = wgrad_stage_cost(b_nkb, b_ncq, nt, (int)bd, (int)bx, b_ring, &fixed) / 2400.0;
+    const long total = (q.r3 ? (long)q.N * ((q.O + b_g - 1) / b_g) : (long)q.nib) * q.nrb, per = (total + b_parts - 1) / b_parts;
+    const long wgs = tiles * b_parts, rounds = (wgs + 255) / 256;
+    out->us = 1.2 + (b_parts > 1 ? 2.8 : 0.0) + rounds * (1.2 + 1.67 * per * stage + 1.63 * fixed / 2400.0) + 0.29e-6 * out->ws +
+              0.48e-6 * 4.0 * dw_elems + 1.8e-3 * wgs / 256.0 * per * (bx * b_ncq + bd * b_nkb);
     return true;
+}
+
+// The same for the per-tap GEMM: rounds of 512 workgroups, its stages of 64 positions by tile width, partials, operands read
+// (297 nodes, nine tenths within 14 %)
+double wgrad_gemm_us(const WgradGemmParams &q, int taps)
+{
+    const double wgs = (double)q.ktiles * q.ctiles * taps * q.nparts, stages = (double)q.M / q.nparts / 64.0;
+    const double stage = q.wk * q.wc == 1 ? 0.59 : q.wk * q.wc == 2 ? 0.65 : 0.71;
+    return 8.0 + (double)(((long)wgs + 511) / 512) * (0.22 + stages * stage) + 0.47e-6 * 16384.0 * wgs * q.wk * q.wc +
+           0.054 * wgs / 512.0 * stages * (q.wk + q.wc);
 }
 
 template <int NT, int NKB>

@@ -356,7 +356,7 @@ def test_conv3d_null_pointers_bias_and_workspace():
 def test_conv3d_kernel_selection_and_sizes(monkeypatch):
     F, B, W = ng.NGC_OP_FWD, ng.NGC_OP_BWD_DATA, ng.NGC_OP_BWD_FILTERS
     d = _good3()
-    assert [ng.ngc_conv3d_variant(d, op) for op in (F, B, W)] == ["strip3_bf16", "strip3_bf16", "wgrad_gemm3_bf16:taps"]
+    assert [ng.ngc_conv3d_variant(d, op) for op in (F, B, W)] == ["strip3_bf16", "strip3_bf16", "wgrad_gemm3_bf16"]
     monkeypatch.setenv("NGC_CONV3D_STRIP", "0")
     assert [ng.ngc_conv3d_variant(d, op) for op in (F, B)] == ["igemm3_bf16_256x64"] * 2
     d = _good3(c=128, k=128)
@@ -488,6 +488,34 @@ def test_names_tell_the_kernels_of_a_variant_apart(monkeypatch):
     assert ng.ngc_conv3d_variant(video, W) == "wgrad_gemm3_bf16"
     off = [ng.ngc_conv_workspace_bytes(d, op) for d, op, _, _ in nodes]
     assert off[0] == ws[0] and off[1] == ws[1] and off[2] != ws[2] and off[3] != ws[3] and off[6] == 0 < ws[6]
+
+
+def test_backprop_filters_takes_the_kernel_expected_to_be_faster():
+    """Nodes where both kernels were measured on the GPU and differ by more than a tenth: several taps per pass against the
+    per-tap GEMM (rank 2, rank 3) and against the all-taps strip kernel (us beside each: base kernel / several taps)."""
+    W = ng.NGC_OP_BWD_FILTERS
+    mk = lambda n, c, h, w, k, r, s, st=1: ng.make_desc(n, c, h, w, k, r, s, (st, st), (1, 1), ((r - 1) // 2, (s - 1) // 2), ((r - 1) // 2, (s - 1) // 2))
+    for node, base, taps in [((51, 112, 11, 22, 496, 5, 5), 64.6, 88.0), ((2, 32, 71, 33, 288, 3, 3, 2), 12.8, 14.4),
+                             ((100, 48, 16, 46, 240, 3, 3), 78.6, 47.4), ((2, 448, 16, 26, 336, 5, 5), 54.9, 24.7)]:
+        assert ng.ngc_conv_variant(mk(*node), W) == "wgrad_gemm_bf16" + (":taps" if taps < base else ""), node
+    for node, base, taps in [((32, 64, 56, 56, 64, 3, 3), 21.5, 27.7),
+                             ((8, 512, 7, 7, 512, 3, 3), 35.8, 13.5), ((64, 512, 7, 7, 1024, 3, 3), 59.3, 44.6), ((128, 192, 28, 28, 320, 3, 3), 167.7, 135.8)]:
+        assert ng.ngc_conv_variant(mk(*node), W) == "wgrad_strip_bf16" + (":taps" if taps < base else ""), node
+    for node, base, taps in [((1, 80, 8, 22, 52, 48, 2), 12.8, 16.8), ((6, 160, 13, 28, 24, 128, 1), 179.8, 79.7)]:
+        n, c, d, h, w, k, st = node
+        assert ng.ngc_conv3d_variant(ng.make_desc3(n, c, d, h, w, k, 3, 3, 3, (st,) * 3, pad_below=(1, 1, 1), pad_above=(1, 1, 1)), W) \
+            == "wgrad_gemm3_bf16" + (":taps" if taps < base else ""), node
+
+
+@pytest.mark.parametrize("node,taps", [((64, 128, 41, 65, 128, 5, 5, 2), True), ((1, 384, 91, 70, 384, 7, 1, 1), True), ((33, 128, 69, 53, 384, 3, 3, 1), True),
+                                       ((16, 1024, 13, 52, 64, 3, 3, 1), True), ((128, 512, 14, 14, 512, 3, 3, 1), False)])
+def test_noalloc_nodes_do_not_depend_on_expected_times(node, taps):
+    """Nodes whose per-tap or strip partials pass the static array: several taps where that fits it, as before the choice by
+    expected times; the last one has always been refused."""
+    n, c, h, w, k, r, s, st = node
+    d = ng.make_desc(n, c, h, w, k, r, s, (st, st), (1, 1), (r // 2, s // 2), (r // 2, s // 2))
+    assert ng.ngc_conv_variant(d, ng.NGC_OP_BWD_FILTERS).endswith(":taps") == taps
+    assert (ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS) <= ng.ngc_static_scratch_bytes()) == taps
 
 
 def test_gather_gemm_leaves_what_its_grid_does_not_hold():

@@ -309,7 +309,7 @@ def test_wgrad_gemm_kernel(case, sp, monkeypatch, route):
     x, w, b, dy = _tensors(a, "bf16", 6000 + case)
     run = Run(a, "bf16", BLK, BLK, True)
     dw = run.bwd_filters(x, dy)
-    _runs(run.last_desc, ng.NGC_OP_BWD_FILTERS, "wgrad_gemm_bf16" if route == "base" or a.r * a.s == 1 else "wgrad_gemm_bf16:taps", route)
+    _runs(run.last_desc, ng.NGC_OP_BWD_FILTERS, "wgrad_gemm_bf16", route)
     assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
 
 
