@@ -14,9 +14,10 @@
 // ds_read_b128.  fp32 runs on v_mfma_f32_32x32x2_f32 (fp32 products and sums, 157 TFLOP/s), bf16 on
 // v_mfma_f32_32x32x16_bf16.
 //
-// What bounds it: fp32 the matrix pipes (a 64 x 128 tile needs 1024 matrix cycles per wave and step against some 500 cycles
-// of gather instructions), bf16 the gather (four vector instructions and a load per element).  Small nodes are bound by
-// latency: there a workgroup takes a 32 x 32 tile and its 4 or 16 waves split the reduction.
+// What bounds it: the gather, four vector instructions and a load per element.  A 64 x 64 step of two slices takes 0.95 us on
+// a chip with work for every unit, of which the fp32 matrix pipes have 0.43 us (1024 cycles); 3x3 64 -> 96 in fp32 runs at 43
+// of the pipes' 157 TFLOP/s.  Small nodes are bound by latency: there a workgroup takes a 32 x 32 tile and its waves (4;
+// backprop-filters 4 or 8) split the reduction.
 #include "common.h"
 
 #include <stdlib.h>
