@@ -1331,7 +1331,7 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         stem_bwd_plan(d, P, Q, &pl);
         return round256(pl.wu_bytes);
     }
-    if (op == NGC_OP_BWD_FILTERS && v == V_DIRECT_GATHER) return round256(gather_wgrad_workspace(*d, P, Q));    // optional: without it the reduction runs in one part
+    if (op == NGC_OP_BWD_FILTERS && v == V_DIRECT_GATHER) return round256(gather_wgrad_workspace(*d, P, Q));    // optional (launch_gather_bwd_filters)
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_STEM) {
         WgradStemParams wp;
         wgrad_stem_plan(d, P, Q, &wp, nullptr);
