@@ -15,6 +15,10 @@
 
 using namespace ngc;
 
+extern "C" {
+static size_t workspace_of(const ngc_conv_desc *desc, int op, bool part);
+}
+
 namespace {
 
 // ---- plan cache (plan_cache.h), keyed by the descriptor and a few integers
@@ -1047,14 +1051,15 @@ const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q)
 // 2 x 32 x 71 x 33 -> 288, 3x3 stride 2 12.8 / 14.4; 100 x 48 x 16 x 46 -> 240, 3x3 78.6 / 47.4; 3 x 16 x 91 x 102 -> 288, 3x3
 // 78.6 / 29.6.  Over 298 drawn nodes the choice is 0.77 of the per-tap time (geometric mean; always several taps 0.785, with nodes
 // at up to 1.38).  Nodes whose per-tap partials the static array does not hold stay with several taps, which is what lets
-// ngc_conv_bwd_filters_noalloc take them; so do the groups of images of a larger node, whose dw go there too.
-const WgradTapsPlan *wgrad_taps_for_gemm(const ngc_conv_desc *d, int P, int Q, bool group)
+// ngc_conv_bwd_filters_noalloc take them; so do the parts of another node (the groups of images of a larger one, whose dw go
+// there too, and nodes on blocked copies, which do).
+const WgradTapsPlan *wgrad_taps_for_gemm(const ngc_conv_desc *d, int P, int Q, bool part)
 {
     const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q);
     WgradGemmParams q;
     if (!tp || env_switch(SW_WGRAD_TAPS) || !wgrad_gemm_plan(d, P, Q, &q)) return tp;     // the switch forces a split
     const size_t partials = (size_t)q.nparts * d->r * d->s * q.ktiles * q.ctiles * q.wk * q.wc * 64 * 64 * sizeof(float);
-    return group || partials > NGC_STATIC_SCRATCH_BYTES || tp->us < wgrad_gemm_us(q, d->r * d->s) ? tp : nullptr;
+    return part || partials > NGC_STATIC_SCRATCH_BYTES || tp->us < wgrad_gemm_us(q, d->r * d->s) ? tp : nullptr;
 }
 
 // A node of the all-taps strip kernel that the general kernel is expected to take less time for: few positions (one
@@ -1063,9 +1068,9 @@ const WgradTapsPlan *wgrad_taps_for_gemm(const ngc_conv_desc *d, int P, int Q, b
 // stage.  Measured, strip / general, us: 64 -> 64 at 56x56, N = 64 26.6 / 29.5; 4 x 512 -> 512 at 7x7 34.0 / 11.1;
 // 16 x 64 x 33 x 47 -> 192 31.1 / 22.9; 1 x 64 -> 64 at 14x14 10.8 / 7.0; 32 x 64 -> 64 at 56x56 21.5 / 27.7.  The weights fit
 // 187 nodes, nine tenths within 11 %; where both were measured the choice is within 0.2 % of the better one on average (1.13 at
-// worst).  Strip partials that the static array does not hold, and groups of images: here the choice is also what ngc_conv_bwd_filters_noalloc takes and
+// worst).  Strip partials that the static array does not hold, and parts of another node: here the choice is also what ngc_conv_bwd_filters_noalloc takes and
 // refuses, so it stays with the plain cycle counts (within 1.5 % on average, 1.29 at worst over the 50 largest).
-const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q, bool group)
+const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q, bool part)
 {
     if (env_switch(SW_WGRAD_NCQ) || env_switch(SW_WGRAD_RING) || env_switch(SW_WGRAD_LATE) || env_switch(SW_WGRAD_G1) || env_switch(SW_WGRAD_NT))
         return nullptr;                                   // a switch that shapes the strip kernel asks for it
@@ -1077,7 +1082,7 @@ const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q, 
     const long tiles = (long)(d->k / 64) * q.ctiles, rounds = (tiles * q.nparts + NUM_CUS - 1) / NUM_CUS;
     const double dw_bytes = 9.0 * d->k * d->c * sizeof(float), operands = 2.0 * d->n * ((double)d->c * d->h * d->w + (double)d->k * P * Q);
     const long stages = q.G > 1 ? (q.NI + q.G - 1) / q.G : (long)q.NI * q.nstages;
-    if (group || q.nparts * dw_bytes > (double)NGC_STATIC_SCRATCH_BYTES) {
+    if (part || q.nparts * dw_bytes > (double)NGC_STATIC_SCRATCH_BYTES) {
         const double strip = rounds * (fixed + stages * cycles) + wgrad_parts_cost(q.nparts > 1 ? q.nparts : 2, (size_t)dw_bytes) + dw_bytes / 1600.0;
         return 1.08 * tp->cycles + 6500.0 < strip ? tp : nullptr;
     }
@@ -1209,8 +1214,8 @@ bool staged_plan(const ngc_conv_desc *d, int op, StagedPlan *out)
 }
 
 // The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
-// group: the node is a group of images of a larger one
-Variant pick_uncached(const ngc_conv_desc *d, int op, bool group)
+// part: the node is a group of images of a larger one or runs on the blocked copies of another
+Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
 {
     const Variant v = pick_base(d, op);
     if ((v == V_DIRECT || v == V_UNSUPPORTED) && staged_plan(d, op, nullptr)) return V_STAGED;
@@ -1219,17 +1224,17 @@ Variant pick_uncached(const ngc_conv_desc *d, int op, bool group)
     if (v == V_DIRECT) return gather_takes(*d, op, P, Q) ? V_DIRECT_GATHER : v;
     if (op == NGC_OP_FWD && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) && conv_few_plan(d, P, Q, nullptr))
         return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
-    if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, group)) return V_WGRAD_GEMM_TAPS;
-    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, group)) return V_WGRAD_STRIP_TAPS;
+    if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, part)) return V_WGRAD_GEMM_TAPS;
+    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, part)) return V_WGRAD_STRIP_TAPS;
     return v;
 }
 
-Variant pick(const ngc_conv_desc *d, int op, bool group = false)
+Variant pick(const ngc_conv_desc *d, int op, bool part = false)
 {
     static thread_local PlanCache<Variant> cache;
-    const PlanKey key = plan_key(d, op, group);
+    const PlanKey key = plan_key(d, op, part);
     Variant *e = cache.find(key);
-    if (!e) e = &cache.put(key, pick_uncached(d, op, group));
+    if (!e) e = &cache.put(key, pick_uncached(d, op, part));
     return *e;
 }
 
@@ -1310,7 +1315,7 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         // the blocked copies, then whatever the node needs when it runs on them
         StagedPlan sp;
         if (!staged_plan(d, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, &sp)) return 0;
-        return sp.inner_off + ngc_conv_workspace_bytes(&sp.inner, op);
+        return sp.inner_off + workspace_of(&sp.inner, op, true);
     }
     if (op == NGC_OP_BWD_DATA_DB) {
         // backprop-data part, then the partial channel sums of dx: rows of the fused launches, or the
@@ -1459,7 +1464,7 @@ static bool bwd1x1_fused_plan(const ngc_conv_desc *d, int P, int Q, Bwd1x1FusedP
     return true;
 }
 
-size_t ngc_conv_workspace_bytes(const ngc_conv_desc *desc, int op)
+static size_t workspace_of(const ngc_conv_desc *desc, int op, bool part)
 {
     int P, Q;
     if (validate(desc, &P, &Q) != NGC_OK) return 0;
@@ -1482,10 +1487,12 @@ size_t ngc_conv_workspace_bytes(const ngc_conv_desc *desc, int op)
         const ngc_conv_desc t = dx_as_dy(desc);
         return base + round256((size_t)bias_grad_parts(t, desc->h, desc->w) * ((desc->c + 15) / 16 * 16) * sizeof(float));
     }
-    return workspace_bytes(desc, op, pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op), P, Q);
+    return workspace_bytes(desc, op, pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, part), P, Q);
 }
 
-static const char *variant_name(const ngc_conv_desc *desc, int op, bool group)
+size_t ngc_conv_workspace_bytes(const ngc_conv_desc *desc, int op) { return workspace_of(desc, op, false); }
+
+static const char *variant_name(const ngc_conv_desc *desc, int op, bool part)
 {
     if (op == NGC_OP_BWD_DATA_FILTERS) {
         int P, Q;
@@ -1510,7 +1517,7 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool group)
             }
         }
     }
-    switch (pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, group)) {
+    switch (pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, part)) {
     case V_UNSUPPORTED: return "unsupported";
     case V_DIRECT: return "direct";
     case V_DIRECT_GATHER: return "direct:gather";
@@ -1533,7 +1540,7 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool group)
         static thread_local char name[64];
         StagedPlan sp;
         if (!staged_plan(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, &sp)) return "invalid";
-        snprintf(name, sizeof(name), "staged:%s", ngc_conv_variant(&sp.inner, op));
+        snprintf(name, sizeof(name), "staged:%s", variant_name(&sp.inner, op, true));
         return name;
     }
     default: return "invalid";
@@ -2051,7 +2058,7 @@ int ngc_conv_bwd_data_filters_relu(const ngc_conv_desc *desc, const void *x, con
     return bwd_data_filters_core(desc, x, dy, w, dx, dw, ws, ws_bytes, hip_stream, 1);
 }
 
-static int bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes, void *hip_stream, bool group)
+static int bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes, void *hip_stream, bool part)
 {
     int P, Q;
     const int vs = validate(desc, &P, &Q);
@@ -2076,7 +2083,7 @@ static int bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy,
         }
         return launch_status(launch_bias_grad_reduce(rows, dw, groups, elems, row, st));
     }
-    const Variant v = pick(desc, NGC_OP_BWD_FILTERS, group);
+    const Variant v = pick(desc, NGC_OP_BWD_FILTERS, part);
     if (v == V_DIRECT_GATHER) return launch_status(launch_gather_bwd_filters(*desc, P, Q, x, dy, dw, ws, ws_bytes, st));
     if (v == V_DIRECT) return launch_status(launch_direct_bwd_filters(*desc, P, Q, x, dy, dw, st));
     if (v == V_STAGED) {
@@ -2095,7 +2102,7 @@ static int bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy,
             if (e != hipSuccess) return launch_status(e);
             dyin = base + sp.y_off;
         }
-        return ngc_conv_bwd_filters(&sp.inner, xin, dyin, dw, base + sp.inner_off, ws_bytes - sp.inner_off, hip_stream);
+        return bwd_filters(&sp.inner, xin, dyin, dw, base + sp.inner_off, ws_bytes - sp.inner_off, hip_stream, true);
     }
 
     const size_t need = workspace_bytes(desc, NGC_OP_BWD_FILTERS, v, P, Q);

@@ -518,6 +518,16 @@ def test_noalloc_nodes_do_not_depend_on_expected_times(node, taps):
     assert (ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS) <= ng.ngc_static_scratch_bytes()) == taps
 
 
+@pytest.mark.parametrize("node", [(4, 1024, 37, 30, 768, 3, 1, 1), (2, 768, 22, 30, 768, 1, 7, 1), (8, 384, 39, 24, 256, 7, 1, 1), (4, 128, 23, 35, 512, 5, 5, 1)])
+def test_noalloc_nodes_on_blocked_copies_do_not_depend_on_expected_times(node):
+    """The copies go to the static array too: several taps, with the smaller partials, also where per tap is expected faster."""
+    n, c, h, w, k, r, s, st = node
+    for xl, yl in ((ng.NGC_NCHW, ng.NGC_NCHW), (ng.NGC_NCHW, ng.NGC_NCHW16C), (ng.NGC_NCHW16C, ng.NGC_NCHW)):
+        d = ng.make_desc(n, c, h, w, k, r, s, (st, st), (1, 1), (r // 2, s // 2), (r // 2, s // 2), x_layout=xl, y_layout=yl)
+        assert ng.ngc_conv_variant(d, ng.NGC_OP_BWD_FILTERS) == "staged:wgrad_gemm_bf16:taps"
+        assert ng.ngc_conv_workspace_bytes(d, ng.NGC_OP_BWD_FILTERS) <= ng.ngc_static_scratch_bytes()
+
+
 def test_gather_gemm_leaves_what_its_grid_does_not_hold():
     """More than 65535 tiles of 32 channels, or so many positions that their threads pass 2^32: the kernels with a
     thread per output take the node, as they did before the gather GEMM."""
