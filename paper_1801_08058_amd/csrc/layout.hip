@@ -155,7 +155,43 @@ __global__ __launch_bounds__(256) void layout_generic(const E *__restrict__ src,
     dst[i] = v;
 }
 
-// ---- filter re-layout KCRS -> blocked (forward or backprop-data form); one thread per
+// ---- filter re-layout KCRS -> blocked, 2-byte elements, C a multiple of 16: tiles of 16 x G filters through LDS.
+// A destination run of 16 channels gathers elements that are R S apart in KCRS (and whole filters apart for the
+// backprop-data form), so one thread per destination element reads 2 bytes of a different line per lane, and the tile
+// below is what keeps the traffic at one read and one write.  A workgroup reads the filters of 16 lanes (the blocked axis)
+// x G rows (the other channel axis) as runs of whole 16-byte pieces, then writes, tap by tap, G runs of 32 bytes.
+// Bound: launch and load latency below a few MB, then HBM.  512 x 512 x 3 x 3 (4.7 MB): a thread per element 8.1 us, tiles 4.2 us.
+// FWD: lanes = c, rows = k, source run of a row = 16 R S elements; else lanes = k, rows = c, run of a lane = G R S.
+template <bool FWD>
+__global__ __launch_bounds__(256) void filter_tiles_b16(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int K, int C,
+                                                        int RS, int lg, FastDiv div_run)
+{
+    extern __shared__ __align__(16) uint16_t ft[];
+    const int G = 1 << lg, b = blockIdx.y, g0 = blockIdx.x << lg;
+    const int rows = FWD ? K : C, live = rows - g0 < G ? rows - g0 : G;
+    const int pitch = (FWD ? 16 : G) * RS + 8;                          // elements; whole 16-byte pieces
+    const int nrun = FWD ? live : 16, run = (FWD ? 16 : live) * RS / 8; // source runs, 16-byte pieces of a run
+    for (int i = threadIdx.x; i < nrun * run; i += 256) {
+        const int r = (int)(live == G || FWD ? fd_div((uint32_t)i, div_run) : (uint32_t)i / (uint32_t)run), o = i - r * run;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        const int k = FWD ? g0 + r : b * 16 + r, c = FWD ? b * 16 : g0;
+        if (k < K) v = *reinterpret_cast<const uint4 *>(src + ((size_t)k * C + c) * RS + o * 8);
+        *reinterpret_cast<uint4 *>(ft + r * pitch + o * 8) = v;
+    }
+    __syncthreads();
+    const int nb = gridDim.y, n = RS * G * 2;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const int h = i & 1, g = (i >> 1) & (G - 1), t = i >> (lg + 1);
+        if (g >= live) continue;
+        uint32_t e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e[j] = FWD ? ft[g * pitch + (h * 8 + j) * RS + t] : ft[(h * 8 + j) * pitch + g * RS + t];
+        *reinterpret_cast<uint4 *>(dst + (((size_t)t * nb + b) * rows + g0 + g) * 16 + h * 8) =
+            make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+    }
+}
+
+// ---- the same for what the tiles refuse (4-byte elements, C no multiple of 16, long windows); one thread per
 // destination element, padded lanes written as +0.
 template <typename E>
 __global__ __launch_bounds__(256) void filter_to_blocked(const E *__restrict__ src, E *__restrict__ dst, int K, int C,
@@ -263,6 +299,25 @@ hipError_t launch_filter_convert(int elem_bytes, int K, int C, int R, int S, con
 {
     const size_t total = (dst_layout == NGC_BLOCKED_FWD) ? (size_t)R * S * ((C + 15) / 16) * K * 16
                                                          : (size_t)R * S * ((K + 15) / 16) * C * 16;
+    // Tiles: whole 16-byte pieces in every source run (C % 16, both pointers aligned), grid and LDS within limits (64 KB: 16
+    // filters of up to 120 taps).  32 rows a tile where that leaves a workgroup for every compute unit.  Below 2^17 filter
+    // elements a thread per element is as fast or faster, one round trip to memory instead of one and one through LDS: 192 -> 32
+    // channels, 3x3 2.5 / 3.2 us (tiles); 80 -> 416, 1x7 (233 k) 4.7 / 3.7 and 2.9 / 3.3 us; 32 -> 416, 3x3 (120 k) 4.8 / 3.6 and 4.6 / 4.6.
+    const int RS = R * S, nb = dst_layout == NGC_BLOCKED_FWD ? C / 16 : (K + 15) / 16;
+    if (elem_bytes == 2 && C % 16 == 0 && RS <= 120 && nb <= 65535 && total > ((size_t)1 << 17) && aligned_to(w_kcrs, 16) && aligned_to(dst, 16)) {
+        const bool fwd = dst_layout == NGC_BLOCKED_FWD;
+        const int rows = fwd ? K : C;
+        const int lg = RS <= 16 && (size_t)((rows + 31) / 32) * nb >= 256 ? 5 : 4;
+        const int G = 1 << lg;
+        const size_t lds = (size_t)(fwd ? G : 16) * ((fwd ? 16 : G) * RS + 8) * 2;
+        const dim3 grid((unsigned)((rows + G - 1) >> lg), (unsigned)nb);
+        const FastDiv div_run = make_fastdiv((uint32_t)((fwd ? 16 : G) * RS / 8));
+        const uint16_t *s = static_cast<const uint16_t *>(w_kcrs);
+        uint16_t *d = static_cast<uint16_t *>(dst);
+        if (fwd) NGC_LAUNCH(filter_tiles_b16<true>, grid, dim3(256), lds, st, s, d, K, C, RS, lg, div_run);
+        else NGC_LAUNCH(filter_tiles_b16<false>, grid, dim3(256), lds, st, s, d, K, C, RS, lg, div_run);
+        return ngc::launch_result();
+    }
     const unsigned blocks = (unsigned)((total + 255) / 256);
     if (elem_bytes == 2)
         NGC_LAUNCH(filter_to_blocked<uint16_t>, dim3(blocks), dim3(256), 0, st,
