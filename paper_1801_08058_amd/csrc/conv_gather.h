@@ -187,7 +187,29 @@ __device__ __forceinline__ void gather_store(const GatherConvParams &p, int ca, 
     }
 }
 
+// 8 bf16 at a 2-byte aligned offset: whole dwords around them, shifted
+__device__ __forceinline__ uint4 load_bf16x8(__amdgpu_buffer_rsrc_t rs, unsigned off)
+{
+    const unsigned a = off & ~3u, sh = (off & 2u) * 8;
+    const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)a, 0, 0));
+    const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(a + 16), 0, 0);
+    return make_uint4(__builtin_amdgcn_alignbit(v.y, v.x, sh), __builtin_amdgcn_alignbit(v.z, v.y, sh), __builtin_amdgcn_alignbit(v.w, v.z, sh),
+                      __builtin_amdgcn_alignbit(w, v.w, sh));
+}
+
+// element strides of images, channels (blocked: 16-channel blocks) and pixels
+inline void gather_strides(int layout, int C, int HW, int32_t *n, int32_t *c, int32_t *px)
+{
+    const bool b = layout == NGC_NCHW16C;
+    *n = (b ? (C + 15) / 16 * 16 : C) * HW;
+    *c = b ? 16 * HW : HW;
+    *px = b ? 16 : 1;
+}
+
 // conv_stream.hip: true if it took the launch (its status in *e); max_m: positions of the largest class
 bool launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, int classes, hipStream_t st, hipError_t *e);
+// wgrad_stream.hip: the same for backprop-filters (false also where the workspace is too small); bytes of partial sums
+bool launch_wgrad_stream(const ngc_conv_desc &d, int P, int Q, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes, hipStream_t st, hipError_t *e);
+size_t wgrad_stream_workspace(const ngc_conv_desc &d, int P, int Q, bool *takes);
 
 }  // namespace ngc

@@ -527,14 +527,6 @@ bool gather_takes(const ngc_conv_desc &d, int op, int P, int Q)
     return op == NGC_OP_FWD || (size_t)((d.k + 63) / 64) * (((size_t)d.c * d.r * d.s + 63) / 64) <= 65535;
 }
 
-static void strides_of(int layout, int C, int HW, int32_t *n, int32_t *c, int32_t *px)
-{
-    const bool b = layout == NGC_NCHW16C;
-    *n = (b ? (C + 15) / 16 * 16 : C) * HW;
-    *c = b ? 16 * HW : HW;
-    *px = b ? 16 : 1;
-}
-
 template <typename T, int BM, int BN, int WM, int WN, int KS, int UPS, bool WV>
 static hipError_t launch_gather_conv_l(const GatherConvParams &p, dim3 grid, hipStream_t st)
 {
@@ -619,7 +611,7 @@ hipError_t launch_gather_fwd(const ngc_conv_desc &d, int P, int Q, const void *x
     GatherConvParams p = {};
     p.in = x; p.wt = w; p.out = y; p.bias = bias;
     p.N = d.n; p.Cin = d.c; p.Cout = d.k; p.Hin = d.h; p.Win = d.w; p.Hout = P; p.Wout = Q;
-    strides_of(d.x_layout, d.c, d.h * d.w, &p.in_n, &p.in_c, &p.in_px);
+    gather_strides(d.x_layout, d.c, d.h * d.w, &p.in_n, &p.in_c, &p.in_px);
     p.in_bytes = (uint32_t)((size_t)d.n * p.in_n * sz);
     p.wt_bytes = (uint32_t)((size_t)d.k * d.c * d.r * d.s * sz);
     p.in_blocked = d.x_layout == NGC_NCHW16C; p.out_blocked = d.y_layout == NGC_NCHW16C;
@@ -637,7 +629,7 @@ hipError_t launch_gather_bwd_data(const ngc_conv_desc &d, int P, int Q, const vo
     GatherConvParams p = {};
     p.in = dy; p.wt = w; p.out = dx; p.mask = mask;
     p.N = d.n; p.Cin = d.k; p.Cout = d.c; p.Hin = P; p.Win = Q; p.Hout = d.h; p.Wout = d.w;
-    strides_of(d.y_layout, d.k, P * Q, &p.in_n, &p.in_c, &p.in_px);
+    gather_strides(d.y_layout, d.k, P * Q, &p.in_n, &p.in_c, &p.in_px);
     p.in_bytes = (uint32_t)((size_t)d.n * p.in_n * sz);
     p.wt_bytes = (uint32_t)((size_t)d.k * d.c * d.r * d.s * sz);
     p.in_blocked = d.y_layout == NGC_NCHW16C; p.out_blocked = d.x_layout == NGC_NCHW16C;
@@ -677,6 +669,9 @@ static uint32_t wgrad_pitch(const ngc_conv_desc &d) { return (uint32_t)(((size_t
 
 size_t gather_wgrad_workspace(const ngc_conv_desc &d, int P, int Q)
 {
+    bool takes;
+    const size_t b = wgrad_stream_workspace(d, P, Q, &takes);
+    if (takes) return b;
     const int parts = wgrad_plan(d, P, Q).parts;
     return parts > 1 ? (size_t)parts * wgrad_pitch(d) * sizeof(float) : 0;
 }
@@ -731,6 +726,8 @@ static bool one_part_is_slow(const ngc_conv_desc &d, size_t M)
 hipError_t launch_gather_bwd_filters(const ngc_conv_desc &d, int P, int Q, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes,
                                      hipStream_t st)
 {
+    hipError_t se;
+    if (launch_wgrad_stream(d, P, Q, x, dy, dw, ws, ws_bytes, st, &se)) return se;
     const size_t sz = d.dtype == NGC_F32 ? 4 : 2;
     const int U = (int)(16 / sz);
     GatherWgradParams p = {};
@@ -744,8 +741,8 @@ hipError_t launch_gather_bwd_filters(const ngc_conv_desc &d, int P, int Q, const
     p.x = x; p.dy = dy;
     p.C = d.c; p.H = d.h; p.W = d.w; p.K = d.k; p.P = P; p.Q = Q; p.R = d.r; p.S = d.s;
     p.sh = d.stride_h; p.sw = d.stride_w; p.dil_h = d.dil_h; p.dil_w = d.dil_w; p.pb_h = d.pad_below_h; p.pb_w = d.pad_below_w;
-    strides_of(d.x_layout, d.c, d.h * d.w, &p.x_n, &p.x_c, &p.x_px);
-    strides_of(d.y_layout, d.k, P * Q, &p.dy_n, &p.dy_c, &p.dy_px);
+    gather_strides(d.x_layout, d.c, d.h * d.w, &p.x_n, &p.x_c, &p.x_px);
+    gather_strides(d.y_layout, d.k, P * Q, &p.dy_n, &p.dy_c, &p.dy_px);
     p.x_bytes = (uint32_t)((size_t)d.n * p.x_n * sz);
     p.dy_bytes = (uint32_t)((size_t)d.n * p.dy_n * sz);
     p.x_blocked = d.x_layout == NGC_NCHW16C; p.dy_blocked = d.y_layout == NGC_NCHW16C;

@@ -28,16 +28,6 @@ constexpr int STREAM_DEAD = 31;                        // tap bit that is set in
 
 template <typename T> constexpr int STREAM_B = sizeof(T) == 4 ? 2 : 1;      // steps per group
 
-// 8 bf16 at a 2-byte aligned offset: whole dwords around them, shifted
-__device__ __forceinline__ uint4 load_bf16x8(__amdgpu_buffer_rsrc_t rs, unsigned off)
-{
-    const unsigned a = off & ~3u, sh = (off & 2u) * 8;
-    const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)a, 0, 0));
-    const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(a + 16), 0, 0);
-    return make_uint4(__builtin_amdgcn_alignbit(v.y, v.x, sh), __builtin_amdgcn_alignbit(v.z, v.y, sh), __builtin_amdgcn_alignbit(v.w, v.z, sh),
-                      __builtin_amdgcn_alignbit(w, v.w, sh));
-}
-
 template <typename T, int NF, int KS, int WN, bool WROW>
 __global__ __launch_bounds__(64 * KS * WN) void stream_conv(const GatherConvParams p)
 {
