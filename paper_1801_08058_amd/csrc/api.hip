@@ -876,13 +876,26 @@ bool wgrad_gemm_plan_uncached(const ngc_conv_desc *d, int P, int Q, WgradGemmPar
     chunk = (chunk + 127) / 128 * 128;
     q.chunk = chunk;
     q.nparts = (int)((q.M + chunk - 1) / chunk);
-    // One-tap layers with several tiles: the tiles of a chunk share x or dy; with many chunks whose count is no
-    // multiple of 8 the two-dimensional grid spreads them over the XCDs, the XCD-ordered grid does not.  Measured
-    // on the 56x56 layers of the ResNet-50 stack (126 chunks, two tiles): 64 -> 256 53.2 -> 49.7 us, 256 -> 64
-    // 52.4 -> 46.9 us, but 256 -> 128 (128 x 128 tiles) 72.0 -> 75.5 us, so not for that tile shape.
-    if (d->r * d->s == 1 && tiles > 1 && q.wk * q.wc < 4 && q.nparts >= 64 && q.nparts % 8 != 0) {
+    // One-tap layers with several tiles: the tiles of a chunk share x or dy; the two-dimensional grid spreads them over the
+    // XCDs, each of which then fetches the chunk for itself, the XCD-ordered grid keeps them on one.  Measured, us: 256 -> 512 at
+    // 56x56 /2, N = 64 (8 tiles, 31 chunks) 53.2 / 35.3; 512 -> 256 at 56x56 /2 52.5 / 36.6; 512 -> 512 at 28x28 54.7 / 43.9; 256 -> 512
+    // at 28x28 40.1 / 31.8; 256 -> 256 at 56x56, N = 32 39.0 / 32.0; 256 -> 1024 at 14x14 24.8 / 23.8.  It
+    // needs chunks enough to keep the XCDs even (2048 -> 512 at 7x7, 7 chunks 29.7 / 32.4), and the workgroups of an XCD must be
+    // resident together (384 -> 384 at 28x28, 36 for 32 places 35.0 / 52.9, 320 -> 32 at 40x80, 65 for 64 37.1 / 60.4: fewer, longer
+    // chunks for 128 x 128 tiles if they leave four fifths of the workgroups, else the other grid).  Two or three 128 x 128 tiles lose (256 -> 128 at 56x56, N = 128 69.4 / 73.0),
+    // small tensors 3 %.
+    if (d->r * d->s == 1 && tiles > 1 && (tiles >= 4 || q.wk * q.wc < 4) && x_bytes + dy_bytes >= ((size_t)24 << 20)) {
         const char *fx = env_switch(SW_WGG_XCD);
-        if (!(fx && atoi(fx) == 0)) q.xcd_order = 1;
+        const size_t lds = (size_t)2 * 4 * (q.wk + q.wc) * (q.sp * 32 + 128);
+        const uint32_t places = lds * 2 <= LDS_LIMIT ? 64 : 32, most = 8 * (places / tiles);         // of an XCD; chunks that fit
+        uint32_t ch = chunk;
+        if (q.wk * q.wc == 4 && (uint32_t)q.nparts > most && most * 5 >= (uint32_t)q.nparts * 4) ch = ((q.M + most - 1) / most + 127) / 128 * 128;
+        const uint32_t n = (q.M + ch - 1) / ch;
+        if (n <= most && (n >= 24 || (n >= 16 && n % 8 == 0)) && !(fx && atoi(fx) == 0)) {
+            q.xcd_order = 1;
+            q.chunk = ch;
+            q.nparts = (int)n;
+        }
     }
     q.x_bytes = (uint32_t)x_bytes;
     q.dy_bytes = (uint32_t)dy_bytes;
