@@ -628,7 +628,10 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
                 const double stage = wgrad_stage_cost(nkb, ncq, nt, (int)bd, (int)bx, ring, &fixed);
                 const int units = nkb * nt;
                 const size_t part_bytes = (size_t)tiles * ncq * units * 1024;
-                const double streamed = 0.5 * (bd * nkb + bx * ncq) * 1024.0 * total * tiles > 4e7 ? 1.25 : 1.0;
+                // Large operands, parts whose workgroups lie on several XCDs: each fetches them for itself.  Rank 3 with a few tiles
+                // does not feel it, the depth taps of a part read the same slices at other times (64 -> 128, 8 x 16 x 56 x 56, 6
+                // tiles, 30 / 32 / 34 / 36 parts 220.8 / 206.5 / 198.5 / 190.3 us).
+                const double streamed = 0.5 * (bd * nkb + bx * ncq) * 1024.0 * total * tiles > 4e7 && !(q.r3 && tiles <= 8) ? 1.25 : 1.0;
                 auto consider = [&](long parts) {
                     if (parts < 1 || parts > total || parts > 1024) return;
                     if (parts > 1 && parts * part_bytes > ((size_t)NGC_STATIC_SCRATCH_BYTES)) return;
