@@ -268,6 +268,18 @@ bool launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, in
     for (int a = 0; a < p.os_h; ++a) all_h += p.nr[a];
     for (int b = 0; b < p.os_w; ++b) all_w += p.ns[b];
     const double work = tiles * all_h * all_w * p.Cin / nk / 256;
+    // Tile-steps per compute unit past which the gather GEMM's tiles in LDS, which read an operand once for several fragments, are
+    // faster (gather / this kernel, us, some 440 launches of up to 8 GFLOP).  fp32: forward never in the range, except strided (64 -> 160 at
+    // 56x56 / 2, 1033 steps 72.9 / 83.5); backprop-data, whose filter operand costs an access per lane, 121 -> 148, 3x3, 1826 steps
+    // 95.6 / 134.1, 529 48.3 / 42.8, strided 5x5, 155 18.9 / 23.8.  bf16 NCHW: forward 405 50.0 / 34.6, 1008 65.4 / 122.5, 5x5, 250
+    // 18.7 / 23.2; backprop-data 200 21.8 / 27.6, 102 40.7 / 28.1.  bf16 blocked, where the gather kernel reads 16 bytes at a time: 154 31.1 / 57.7,
+    // 29 11.3 / 13.5.
+    const bool strided = p.is_h > 1 || p.is_w > 1 || classes > 1;
+    const double most = dtype == NGC_F32 ? (wrow ? (strided ? 600.0 : 1e30) : strided ? 130.0 : 600.0)
+                        : p.in_blocked   ? 20.0
+                        : wrow           ? (ntaps > 9 ? 230.0 : 450.0)
+                                         : 100.0;
+    if (fv <= 0 && work > most) return false;
     const double *c0 = cost[dtype != NGC_F32][wrow][0], *c1 = cost[dtype != NGC_F32][wrow][1];
     const double by_pos = c0[0] + c0[1] * steps + c0[2] * work + c0[3] * (double)((max_m + 127) / 128) * cot * classes / 256;
     const double by_slice = c1[0] + c1[1] * (double)((int)(steps + 3) / 4) + c1[2] * work + c1[3] * tiles * classes / 256;
