@@ -1228,6 +1228,33 @@ bool staged_plan(const ngc_conv_desc *d, int op, StagedPlan *out)
 
 // The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
 // part: the node is a group of images of a larger one or runs on the blocked copies of another
+// what the strip kernel (all classes of a strided layer in one grid) or the 1x1 GEMM is expected to take; 0: no estimate (column
+// tiles), the node leaves it only where it has few tiles at any estimate
+double staged_fwd_bwd_us(const ngc_conv_desc *d, int op, Variant v, int P, int Q)
+{
+    if (v == V_GEMM1X1) {
+        Gemm1x1Params gp;
+        if (!gemm1x1_plan(d, op, P, Q, &gp, nullptr)) return 0.0;
+        return few_gemm1x1_us(gp.M, gp.Cin, gp.Cout);
+    }
+    double wgs = 0.0;
+    int stages = 0, taps = 0, nf = 0;
+    for (int c = 0; c < strip_classes(d, op); ++c) {
+        StripParams sp;
+        int f;
+        size_t lds;
+        bool empty;
+        if (!strip_plan_class(d, op, c / d->stride_w, c % d->stride_w, P, Q, &sp, &f, &lds, &empty)) return 0.0;
+        if (empty) continue;
+        if (sp.ncolt > 1) return 0.0;
+        wgs += (double)sp.groups * sp.strips * ((sp.Cout + 63) / 64);
+        stages = sp.Cin / 16;
+        if (sp.ntaps > taps) taps = sp.ntaps;
+        if (f > nf) nf = f;
+    }
+    return few_strip_us(wgs, stages, taps, nf);
+}
+
 Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
 {
     const Variant v = pick_base(d, op);
@@ -1235,7 +1262,8 @@ Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
     int P, Q;
     if (validate(d, &P, &Q) != NGC_OK) return v;
     if (v == V_DIRECT) return gather_takes(*d, op, P, Q) ? V_DIRECT_GATHER : v;
-    if (op == NGC_OP_FWD && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) && conv_few_plan(d, P, Q, nullptr))
+    if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) &&
+        conv_few_plan(d, op, P, Q, staged_fwd_bwd_us(d, op, v, P, Q), nullptr))
         return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
     if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, part)) return V_WGRAD_GEMM_TAPS;
     if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, part)) return V_WGRAD_STRIP_TAPS;
@@ -1292,7 +1320,7 @@ bool db_fusable(const ngc_conv_desc *d, Variant v)
         return validate(d, &P, &Q) == NGC_OK && !strip_col_tiles(d, NGC_OP_BWD_DATA, P, Q);
     }
     if (v == V_GEMM1X1) return d->x_layout == NGC_NCHW16C && d->y_layout == NGC_NCHW16C;
-    return false;
+    return v == V_STRIP_FEW || v == V_GEMM1X1_FEW;
 }
 
 // rows of partial channel sums the fused launches write
@@ -1316,6 +1344,10 @@ int db_fused_rows(const ngc_conv_desc *d, Variant v, int P, int Q)
         gp.dbp = reinterpret_cast<float *>(1);
         const int bm = gemm1x1_dbp_tile_m(gp);
         rows = (int)((gp.M + bm - 1) / bm) * (bm / 64);                  // one row per MFMA wave row
+    } else if (v == V_STRIP_FEW || v == V_GEMM1X1_FEW) {
+        ConvFewParams fp;
+        if (!conv_few_plan(d, NGC_OP_BWD_DATA, P, Q, FEW_CHOSEN, &fp)) return 0;
+        rows = conv_few_dbp_rows(fp);
     }
     return rows;
 }
@@ -1342,7 +1374,7 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
     if (op == NGC_OP_BIAS_GRAD) return round256((size_t)bias_grad_parts(*d, P, Q) * ((d->k + 15) / 16 * 16) * sizeof(float));
     if (op == NGC_OP_FWD && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW))
         return d->w_layout == NGC_KCRS ? round256(filter_elems(d, NGC_BLOCKED_FWD) * 2) : 0;
-    if (op == NGC_OP_BWD_DATA && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1))
+    if (op == NGC_OP_BWD_DATA && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW))
         return d->w_layout == NGC_KCRS ? round256(filter_elems(d, NGC_BLOCKED_BWD) * 2) : 0;
     if (op == NGC_OP_BWD_DATA && v == V_STEM_BWD) {
         StemBwdPlan pl;
@@ -1534,8 +1566,9 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part)
     case V_UNSUPPORTED: return "unsupported";
     case V_DIRECT: return "direct";
     case V_DIRECT_GATHER: return "direct:gather";
-    case V_STRIP_FEW: return "strip_bf16:few";
-    case V_GEMM1X1_FEW: return "gemm1x1_bf16:few";
+    // backprop-data reports the family alone (callers compare the name), as the rank-3 ops do
+    case V_STRIP_FEW: return op == NGC_OP_FWD ? "strip_bf16:few" : "strip_bf16";
+    case V_GEMM1X1_FEW: return op == NGC_OP_FWD ? "gemm1x1_bf16:few" : "gemm1x1_bf16";
     case V_WGRAD_STRIP_TAPS: return "wgrad_strip_bf16:taps";
     case V_WGRAD_GEMM_TAPS: return "wgrad_gemm_bf16:taps";
     case V_IGEMM_128: return "igemm_bf16_128x128";
@@ -1652,7 +1685,7 @@ int ngc_conv_fwd(const ngc_conv_desc *desc, const void *x, const void *w, const 
     }
     if (v == V_STRIP_FEW || v == V_GEMM1X1_FEW) {
         ConvFewParams fp;
-        if (!conv_few_plan(desc, P, Q, &fp)) return NGC_UNSUPPORTED;
+        if (!conv_few_plan(desc, NGC_OP_FWD, P, Q, FEW_CHOSEN, &fp)) return NGC_UNSUPPORTED;
         fp.in = static_cast<const uint16_t *>(x);
         fp.wt = static_cast<const uint16_t *>(wt);
         fp.out = static_cast<uint16_t *>(y);
@@ -1770,6 +1803,20 @@ int bwd_data_core(const ngc_conv_desc *desc, const void *dy, const void *w, cons
         rp.out = static_cast<uint16_t *>(dx);
         rp.mask = static_cast<const uint16_t *>(mask);
         return launch_status(launch_rows(rp, lds, st));
+    }
+    if (v == V_STRIP_FEW || v == V_GEMM1X1_FEW) {
+        ConvFewParams fp;
+        if (!conv_few_plan(desc, NGC_OP_BWD_DATA, P, Q, FEW_CHOSEN, &fp)) return NGC_UNSUPPORTED;
+        fp.in = static_cast<const uint16_t *>(dy);
+        fp.wt = static_cast<const uint16_t *>(wt);
+        fp.out = static_cast<uint16_t *>(dx);
+        fp.mask = static_cast<const uint16_t *>(mask);
+        if (fuse) {
+            fp.dbp = fuse->partial;
+            fp.dbp_ld = fuse->ld;
+            fuse->rows = conv_few_dbp_rows(fp);
+        }
+        return launch_status(launch_conv_few(fp, st));
     }
     if (v == V_STRIP) {
         if (strip_zero_fill(desc)) {

@@ -140,7 +140,7 @@ bool as_rank2(const ngc_conv3d_desc *d, ngc_conv_desc *out)
     return true;
 }
 
-enum Variant3 { V3_INVALID, V3_UNSUPPORTED, V3_RANK2, V3_STRIP, V3_IGEMM_128, V3_IGEMM_64, V3_WGRAD_GEMM, V3_WGRAD_TAPS, V3_DIRECT };
+enum Variant3 { V3_INVALID, V3_UNSUPPORTED, V3_RANK2, V3_STRIP, V3_FEW, V3_IGEMM_128, V3_IGEMM_64, V3_WGRAD_GEMM, V3_WGRAD_TAPS, V3_DIRECT };
 
 bool blocked_bf16_3(const ngc_conv3d_desc *d)
 {
@@ -332,6 +332,27 @@ const WgradTapsPlan *wgrad_taps3_plan(const ngc_conv3d_desc *d, int O, int P, in
     return e->ok ? &e->v : nullptr;
 }
 
+enum Strip3Choice { STRIP3_NO, STRIP3_STRIP, STRIP3_FEW };
+
+// whether the strip kernel takes the node, and whether the kernel for few output tiles is expected to take less time
+Strip3Choice strip3_choice(const ngc_conv3d_desc *d, int op, int O, int P, int Q)
+{
+    Strip3Plan pl;
+    if (!strip3_plan(d, op, O, P, Q, &pl)) return STRIP3_NO;
+    double wgs = 0.0;
+    int stages = 0, taps = 0, nf = 0;
+    bool col_tiles = false;                               // no estimate then
+    for (int i = 0; i < pl.n; ++i) {
+        const StripParams &sp = pl.l[i].sp;
+        if (sp.ncolt > 1) col_tiles = true;
+        wgs += (double)sp.groups * sp.strips * ((sp.Cout + 63) / 64);
+        if (sp.Cin / 16 * sp.ndt > stages) stages = sp.Cin / 16 * sp.ndt;
+        if (sp.ntaps > taps) taps = sp.ntaps;
+        if (pl.l[i].nf > nf) nf = pl.l[i].nf;
+    }
+    return conv_few_plan3(d, op, O, P, Q, col_tiles ? 0.0 : few_strip_us(wgs, stages, taps, nf), nullptr) ? STRIP3_FEW : STRIP3_STRIP;
+}
+
 Variant3 pick3(const ngc_conv3d_desc *d, int op, ngc_conv_desc *r2)
 {
     int O, P, Q;
@@ -344,7 +365,10 @@ Variant3 pick3(const ngc_conv3d_desc *d, int op, ngc_conv_desc *r2)
     }
     const int taps = d->t * d->r * d->s;
     const bool direct_ok = d->w_layout == NGC_KCRS;
-    if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && strip3_plan(d, op, O, P, Q, nullptr)) return V3_STRIP;
+    if (op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) {
+        const Strip3Choice s = strip3_choice(d, op, O, P, Q);
+        if (s != STRIP3_NO) return s == STRIP3_FEW ? V3_FEW : V3_STRIP;
+    }
     if (op == NGC_OP_FWD) {
         const bool wl = d->w_layout == NGC_KCRS || d->w_layout == NGC_BLOCKED_FWD;
         if (blocked_bf16_3(d) && wl && d->c % 32 == 0 && d->k % 64 == 0 && taps <= IGEMM_MAX_TAPS)
@@ -380,7 +404,7 @@ size_t filter_elems3(const ngc_conv3d_desc *d, int layout)
 size_t workspace3(const ngc_conv3d_desc *d, int op, Variant3 v, const ngc_conv_desc *r2, int O, int P, int Q)
 {
     if (v == V3_RANK2) return ngc_conv_workspace_bytes(r2, op);
-    if (v == V3_IGEMM_128 || v == V3_IGEMM_64 || v == V3_STRIP) {
+    if (v == V3_IGEMM_128 || v == V3_IGEMM_64 || v == V3_STRIP || v == V3_FEW) {
         if (d->w_layout != NGC_KCRS) return 0;
         return round256_3(filter_elems3(d, op == NGC_OP_FWD ? NGC_BLOCKED_FWD : NGC_BLOCKED_BWD) * 2);
     }
@@ -529,7 +553,7 @@ const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op)
     }
     switch (pick3(desc, op, &r2)) {
     case V3_RANK2: snprintf(name, sizeof(name), "rank2:%s", ngc_conv_variant(&r2, op)); return name;
-    case V3_STRIP: return "strip3_bf16";
+    case V3_STRIP: case V3_FEW: return "strip3_bf16";
     case V3_IGEMM_128: return "igemm3_bf16_128x128";
     case V3_IGEMM_64: return "igemm3_bf16_256x64";
     case V3_WGRAD_GEMM: return "wgrad_gemm3_bf16";
@@ -574,6 +598,16 @@ int ngc_conv3d_fwd(const ngc_conv3d_desc *desc, const void *x, const void *w, co
         const hipError_t e = launch_filter_convert(2, desc->k, desc->c, desc->t * desc->r, desc->s, w, ws, NGC_BLOCKED_FWD, st);
         if (e != hipSuccess) return status3(e);
         wt = ws;
+    }
+    if (v == V3_FEW) {
+        ConvFewParams fp;
+        if (!conv_few_plan3(desc, NGC_OP_FWD, O, P, Q, FEW_CHOSEN, &fp)) return NGC_UNSUPPORTED;
+        fp.in = static_cast<const uint16_t *>(x);
+        fp.wt = static_cast<const uint16_t *>(wt);
+        fp.out = static_cast<uint16_t *>(y);
+        fp.bias = b;
+        fp.relu = (desc->epilogue & NGC_EPI_RELU) ? 1 : 0;
+        return status3(launch_conv_few(fp, st));
     }
     if (v == V3_STRIP) {
         Strip3Plan pl;
@@ -653,6 +687,15 @@ int bwd_data3_core(const ngc_conv3d_desc *desc, const void *dy, const void *w, c
         const hipError_t e = launch_filter_convert(2, desc->k, desc->c, desc->t * desc->r, desc->s, w, ws, NGC_BLOCKED_BWD, st);
         if (e != hipSuccess) return status3(e);
         wt = ws;
+    }
+    if (v == V3_FEW) {
+        ConvFewParams fp;
+        if (!conv_few_plan3(desc, NGC_OP_BWD_DATA, O, P, Q, FEW_CHOSEN, &fp)) return NGC_UNSUPPORTED;
+        fp.in = static_cast<const uint16_t *>(dy);
+        fp.wt = static_cast<const uint16_t *>(wt);
+        fp.out = static_cast<uint16_t *>(dx);
+        fp.mask = static_cast<const uint16_t *>(mask);
+        return status3(launch_conv_few(fp, st));
     }
     if (v == V3_STRIP) {
         Strip3Plan pl;

@@ -516,21 +516,45 @@ hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st);
 // exactly the static array's size, not more than that
 inline size_t wgrad_taps_workspace(const WgradTapsPlan &pl) { return pl.ws ? (pl.ws + 255) / 256 * 256 : 256; }
 
-// ---- forward of nodes with few output tiles (conv_few.hip) ----
-struct ConvFewParams {
-    const uint16_t *in;        // blocked [N][C/16][H][W][16]
-    const uint16_t *wt;        // [R][S][C/16][K][16]
-    uint16_t *out;             // blocked [N][K/16][P][Q][16]
-    const float *bias;         // may be null
-    uint32_t in_bytes, wt_bytes;
-    uint32_t M;                // N * P * Q positions
-    int32_t CB, K, H, W, R, S, sh, sw, dil_h, dil_w, pbh, pbw;
-    FastDiv div_pq, div_q;
-    int32_t relu;
+// ---- forward and backprop-data of nodes with few output tiles (conv_few.hip) ----
+// One axis of a class of outputs.  Output i of the class lies at i * os + (residue) and meets the taps t0 + j * tstep, j < cnt, at the
+// input coordinate i * is + off0 + j * doff.  Forward: one class, all taps.  Backprop-data: a class per residue modulo the stride.
+struct FewAxis {
+    int32_t cnt, off0, doff, t0, tstep;
+    FastDiv ext;               // outputs of the class on this axis (none: 1)
 };
-// shapes the arguments (where q is not null) of a node it is expected to run faster than the staged kernels; false: not for
-// this kernel
-bool conv_few_plan(const ngc_conv_desc *d, int P, int Q, ConvFewParams *q);
+constexpr int FEW_MAX_STRIDE = 4;      // backprop-data
+struct ConvFewHead {
+    const uint16_t *in;        // blocked [N][CB][D][H][W][16]
+    const uint16_t *wt;        // [T][R][S][CB][K][16]
+    uint16_t *out;             // blocked [N][K/16][OD][OP][OQ][16]
+    const float *bias;         // may be null
+    const uint16_t *mask;      // may be null; else same shape / layout as out: out = (mask > 0) ? out : 0
+    float *dbp;                // may be null; else [classes * position tiles][dbp_ld] fp32: channel sums of what was stored
+    int32_t dbp_ld;
+    uint32_t in_bytes, wt_bytes;
+    int32_t N, CB, K, D, H, W, R, S, OD, OP, OQ;
+    int32_t is[3], os[3];      // d, h, w
+    int32_t relu;
+    // for the launch
+    uint32_t M;                // positions of the largest class
+    int32_t classes, units;    // units: (tap, 16-channel block) pairs of the class with most taps
+    int32_t tile, r3, bwd;     // tile: fragments of 32 x 32 per workgroup and axis
+};
+// what a kernel takes: forward has one class, and 430 bytes of arguments less start it 0.3 us sooner
+template <int RES>
+struct ConvFewArgs : ConvFewHead {
+    FewAxis ax[RES][3];        // [residue][d, h, w]
+};
+using ConvFewParams = ConvFewArgs<FEW_MAX_STRIDE>;
+// shapes the arguments (where q is not null) of a node it is expected to run faster than the staged kernel, which is expected to
+// take staged_us (few_strip_us, few_gemm1x1_us; FEW_CHOSEN: the choice is made); false: not for this kernel
+constexpr double FEW_CHOSEN = -1.0;
+double few_strip_us(double workgroups, int stages, int taps, int nf);
+double few_gemm1x1_us(size_t M, int Cin, int Cout);
+bool conv_few_plan(const ngc_conv_desc *d, int op, int P, int Q, double staged_us, ConvFewParams *q);
+bool conv_few_plan3(const ngc_conv3d_desc *d, int op, int O, int P, int Q, double staged_us, ConvFewParams *q);
+int conv_few_dbp_rows(const ConvFewParams &p);
 hipError_t launch_conv_few(const ConvFewParams &p, hipStream_t st);
 
 // ---- both derivative ops of a 1x1 stride-1 node in one pass over dy ----
