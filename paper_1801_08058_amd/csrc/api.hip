@@ -1226,9 +1226,7 @@ bool staged_plan(const ngc_conv_desc *d, int op, StagedPlan *out)
     return false;
 }
 
-// The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
-// part: the node is a group of images of a larger one or runs on the blocked copies of another
-// what the strip kernel (all classes of a strided layer in one grid) or the 1x1 GEMM is expected to take; 0: no estimate (column
+// What the strip kernel (all classes of a strided layer in one grid) or the 1x1 GEMM is expected to take; 0: no estimate (column
 // tiles), the node leaves it only where it has few tiles at any estimate
 double staged_fwd_bwd_us(const ngc_conv_desc *d, int op, Variant v, int P, int Q)
 {
@@ -1255,6 +1253,8 @@ double staged_fwd_bwd_us(const ngc_conv_desc *d, int op, Variant v, int P, int Q
     return few_strip_us(wgs, stages, taps, nf);
 }
 
+// The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
+// part: the node is a group of images of a larger one or runs on the blocked copies of another
 Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
 {
     const Variant v = pick_base(d, op);
