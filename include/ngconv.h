@@ -228,9 +228,14 @@ size_t ngc_filter_elems(const ngc_conv_desc *desc, int32_t layout);
 
 /* Name of the kernel variant the dispatcher picks for (desc, op): a static string such as
  * "igemm_bf16_128x128" or "direct"; "unsupported" / "invalid" otherwise.  A kernel that takes some of a variant's nodes is
- * named behind a colon: "strip_bf16:few", "gemm1x1_bf16:few" (few output tiles), "wgrad_strip_bf16:taps",
- * "wgrad_gemm_bf16:taps" (several taps per pass), "direct:gather" (gather GEMM).  Host only. */
+ * named behind a colon: "strip_bf16:few", "gemm1x1_bf16:few" (few output tiles, forward), "wgrad_strip_bf16:taps",
+ * "wgrad_gemm_bf16:taps" (several taps per pass), "direct:gather" (gather GEMM and its relatives).  Host only. */
 const char *ngc_conv_variant(const ngc_conv_desc *desc, int op);
+
+/* The same name with the kernel that runs behind the colon for every op: also "strip_bf16:few" and "gemm1x1_bf16:few" for
+ * backprop-data, and "direct:stream" for the nodes of "direct:gather" whose operands go straight to registers
+ * (backprop-filters: with the workspace that ngc_conv_workspace_bytes asks for).  Host only. */
+const char *ngc_conv_kernel(const ngc_conv_desc *desc, int op);
 
 /* ---- Convolution over three spatial axes (N, C, D, H, W) --------------------------------------
  * The IR is rank-general (Sec. 2: tensors of any rank, an op is its inputs plus constant
@@ -308,6 +313,10 @@ size_t ngc_conv3d_data_elems(const ngc_conv3d_desc *desc, int which);
  * reduce to the rank-2 op, "igemm3_bf16_*", "wgrad_gemm3_bf16" (":taps": several taps per pass), "direct3", "unsupported",
  * "invalid". */
 const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op);
+
+/* The same with the kernel that runs behind the colon: "strip3_bf16:few" for nodes with few output tiles, and what
+ * ngc_conv_kernel says after "rank2:". */
+const char *ngc_conv3d_kernel(const ngc_conv3d_desc *desc, int op);
 
 /* Test hook.  The library reads its NGC_* environment switches (kernel-variant overrides for tests and
  * experiments; NGC_DRY_RUN=1 skips every launch after the host-side planning) once per process, at first use,

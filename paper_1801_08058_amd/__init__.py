@@ -9,8 +9,8 @@ from .binding import (  # noqa: F401
     ngc_conv_out_shape, ngc_conv_workspace_bytes, ngc_conv_fwd, ngc_conv_bwd_data,
     ngc_conv_bwd_data_relu, ngc_conv_bwd_data_relu_db, ngc_bias_grad, ngc_softmax, ngc_softmax_bwd, ngc_softmax_variant,
     ngc_conv_bwd_filters, ngc_layout_convert, ngc_filter_convert, ngc_data_elems,
-    ngc_filter_elems, ngc_conv_variant, ngc_status_string,
+    ngc_filter_elems, ngc_conv_variant, ngc_conv_kernel, ngc_status_string,
     ngc_conv3d_desc, make_desc3, ngc_conv3d_out_shape, ngc_conv3d_workspace_bytes, ngc_conv3d_fwd, ngc_conv3d_bwd_data,
-    ngc_conv3d_bwd_filters, ngc_conv3d_filter_convert, ngc_conv3d_filter_elems, ngc_conv3d_data_elems, ngc_conv3d_variant,
+    ngc_conv3d_bwd_filters, ngc_conv3d_filter_convert, ngc_conv3d_filter_elems, ngc_conv3d_data_elems, ngc_conv3d_variant, ngc_conv3d_kernel,
     ngc_conv3d_bwd_data_relu, ngc_conv3d_bwd_data_relu_db, ngc_conv3d_bias_grad,
 )

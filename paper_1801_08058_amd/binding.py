@@ -28,10 +28,10 @@ NGC_OP_FWD, NGC_OP_BWD_DATA, NGC_OP_BWD_FILTERS, NGC_OP_BIAS_GRAD, NGC_OP_BWD_DA
 
 EXPORTS = ("ngc_conv_out_shape", "ngc_conv_workspace_bytes", "ngc_conv_fwd", "ngc_conv_bwd_data",
            "ngc_conv_bwd_data_relu", "ngc_conv_bwd_data_relu_db", "ngc_bias_grad", "ngc_softmax", "ngc_softmax_bwd", "ngc_softmax_variant", "ngc_conv_bwd_filters", "ngc_conv_bwd_data_filters", "ngc_conv_bwd_data_filters_relu", "ngc_layout_convert", "ngc_filter_convert", "ngc_data_elems",
-           "ngc_filter_elems", "ngc_conv_variant", "ngc_status_string",
+           "ngc_filter_elems", "ngc_conv_variant", "ngc_conv_kernel", "ngc_status_string",
            "ngc_conv3d_out_shape", "ngc_conv3d_workspace_bytes", "ngc_conv3d_fwd", "ngc_conv3d_bwd_data",
            "ngc_conv3d_bwd_filters", "ngc_conv3d_filter_convert", "ngc_conv3d_filter_elems", "ngc_conv3d_data_elems",
-           "ngc_conv3d_variant", "ngc_conv3d_bwd_data_relu", "ngc_conv3d_bwd_data_relu_db", "ngc_conv3d_bias_grad",
+           "ngc_conv3d_variant", "ngc_conv3d_kernel", "ngc_conv3d_bwd_data_relu", "ngc_conv3d_bwd_data_relu_db", "ngc_conv3d_bias_grad",
            "ngc_conv_bwd_filters_noalloc", "ngc_static_scratch_bytes", "ngc_reload_switches")
 
 
@@ -120,6 +120,8 @@ def _load() -> ctypes.CDLL:
     lib.ngc_filter_elems.restype = sz
     lib.ngc_conv_variant.argtypes = [D, ctypes.c_int]
     lib.ngc_conv_variant.restype = ctypes.c_char_p
+    lib.ngc_conv_kernel.argtypes = [D, ctypes.c_int]
+    lib.ngc_conv_kernel.restype = ctypes.c_char_p
     lib.ngc_status_string.argtypes = [ctypes.c_int]
     lib.ngc_status_string.restype = ctypes.c_char_p
     D3 = ctypes.POINTER(ngc_conv3d_desc)
@@ -147,6 +149,8 @@ def _load() -> ctypes.CDLL:
     lib.ngc_conv3d_bias_grad.restype = ctypes.c_int
     lib.ngc_conv3d_variant.argtypes = [D3, ctypes.c_int]
     lib.ngc_conv3d_variant.restype = ctypes.c_char_p
+    lib.ngc_conv3d_kernel.argtypes = [D3, ctypes.c_int]
+    lib.ngc_conv3d_kernel.restype = ctypes.c_char_p
     return lib
 
 
@@ -222,6 +226,10 @@ def ngc_filter_elems(desc: ngc_conv_desc, layout: int) -> int:
 
 def ngc_conv_variant(desc: ngc_conv_desc, op: int) -> str:
     return _lib.ngc_conv_variant(ctypes.byref(desc), op).decode()
+
+
+def ngc_conv_kernel(desc: ngc_conv_desc, op: int) -> str:
+    return _lib.ngc_conv_kernel(ctypes.byref(desc), op).decode()
 
 
 def ngc_conv_fwd(desc, x, w, bias, y, ws=None, stream=None, check: bool = True) -> int:
@@ -334,6 +342,10 @@ def ngc_conv3d_filter_elems(desc: ngc_conv3d_desc, layout: int) -> int:
 
 def ngc_conv3d_variant(desc: ngc_conv3d_desc, op: int) -> str:
     return _lib.ngc_conv3d_variant(ctypes.byref(desc), op).decode()
+
+
+def ngc_conv3d_kernel(desc: ngc_conv3d_desc, op: int) -> str:
+    return _lib.ngc_conv3d_kernel(ctypes.byref(desc), op).decode()
 
 
 def ngc_conv3d_fwd(desc, x, w, bias, y, ws=None, stream=None, check: bool = True) -> int:

@@ -1537,7 +1537,8 @@ static size_t workspace_of(const ngc_conv_desc *desc, int op, bool part)
 
 size_t ngc_conv_workspace_bytes(const ngc_conv_desc *desc, int op) { return workspace_of(desc, op, false); }
 
-static const char *variant_name(const ngc_conv_desc *desc, int op, bool part)
+// kernel: the kernel behind the colon wherever one takes some of a variant's nodes (ngc_conv_kernel)
+static const char *variant_name(const ngc_conv_desc *desc, int op, bool part, bool kernel)
 {
     if (op == NGC_OP_BWD_DATA_FILTERS) {
         int P, Q;
@@ -1557,7 +1558,7 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part)
             if (bs.images < desc->n) {                       // groups of images: the kernel of a group
                 static thread_local char name[64];
                 const ngc_conv_desc g = with_batch(desc, bs.images);
-                snprintf(name, sizeof(name), "sliced:%s", variant_name(&g, op, true));
+                snprintf(name, sizeof(name), "sliced:%s", variant_name(&g, op, true, kernel));
                 return name;
             }
         }
@@ -1565,10 +1566,13 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part)
     switch (pick(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, part)) {
     case V_UNSUPPORTED: return "unsupported";
     case V_DIRECT: return "direct";
-    case V_DIRECT_GATHER: return "direct:gather";
-    // backprop-data reports the family alone (callers compare the name), as the rank-3 ops do
-    case V_STRIP_FEW: return op == NGC_OP_FWD ? "strip_bf16:few" : "strip_bf16";
-    case V_GEMM1X1_FEW: return op == NGC_OP_FWD ? "gemm1x1_bf16:few" : "gemm1x1_bf16";
+    case V_DIRECT_GATHER: {
+        int P, Q;
+        return kernel && validate(desc, &P, &Q) == NGC_OK && gather_streams(*desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, P, Q) ? "direct:stream" : "direct:gather";
+    }
+    // as a variant backprop-data has the family alone (callers compare the name), as the rank-3 ops do
+    case V_STRIP_FEW: return kernel || op == NGC_OP_FWD ? "strip_bf16:few" : "strip_bf16";
+    case V_GEMM1X1_FEW: return kernel || op == NGC_OP_FWD ? "gemm1x1_bf16:few" : "gemm1x1_bf16";
     case V_WGRAD_STRIP_TAPS: return "wgrad_strip_bf16:taps";
     case V_WGRAD_GEMM_TAPS: return "wgrad_gemm_bf16:taps";
     case V_IGEMM_128: return "igemm_bf16_128x128";
@@ -1586,14 +1590,16 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part)
         static thread_local char name[64];
         StagedPlan sp;
         if (!staged_plan(desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, &sp)) return "invalid";
-        snprintf(name, sizeof(name), "staged:%s", variant_name(&sp.inner, op, true));
+        snprintf(name, sizeof(name), "staged:%s", variant_name(&sp.inner, op, true, kernel));
         return name;
     }
     default: return "invalid";
     }
 }
 
-const char *ngc_conv_variant(const ngc_conv_desc *desc, int op) { return variant_name(desc, op, false); }
+const char *ngc_conv_variant(const ngc_conv_desc *desc, int op) { return variant_name(desc, op, false, false); }
+
+const char *ngc_conv_kernel(const ngc_conv_desc *desc, int op) { return variant_name(desc, op, false, true); }
 
 const char *ngc_status_string(int status)
 {

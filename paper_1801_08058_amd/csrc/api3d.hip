@@ -535,7 +535,7 @@ int ngc_conv3d_filter_convert(const ngc_conv3d_desc *desc, const void *w_kctrs, 
                                          w_blocked, dst_layout, static_cast<hipStream_t>(hip_stream)));
 }
 
-const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op)
+static const char *variant_name3(const ngc_conv3d_desc *desc, int op, bool kernel)
 {
     static thread_local char name[96];
     ngc_conv_desc r2;
@@ -546,14 +546,15 @@ const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op)
             if (bs.images < desc->n) {                       // groups of images: the kernel of a group
                 static thread_local char sliced[112];
                 const ngc_conv3d_desc g = with_batch3(desc, bs.images);
-                snprintf(sliced, sizeof(sliced), "sliced:%s", ngc_conv3d_variant(&g, op));
+                snprintf(sliced, sizeof(sliced), "sliced:%s", variant_name3(&g, op, kernel));
                 return sliced;
             }
         }
     }
     switch (pick3(desc, op, &r2)) {
-    case V3_RANK2: snprintf(name, sizeof(name), "rank2:%s", ngc_conv_variant(&r2, op)); return name;
-    case V3_STRIP: case V3_FEW: return "strip3_bf16";
+    case V3_RANK2: snprintf(name, sizeof(name), "rank2:%s", kernel ? ngc_conv_kernel(&r2, op) : ngc_conv_variant(&r2, op)); return name;
+    case V3_STRIP: return "strip3_bf16";
+    case V3_FEW: return kernel ? "strip3_bf16:few" : "strip3_bf16";
     case V3_IGEMM_128: return "igemm3_bf16_128x128";
     case V3_IGEMM_64: return "igemm3_bf16_256x64";
     case V3_WGRAD_GEMM: return "wgrad_gemm3_bf16";
@@ -563,6 +564,10 @@ const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op)
     default: return "invalid";
     }
 }
+
+const char *ngc_conv3d_variant(const ngc_conv3d_desc *desc, int op) { return variant_name3(desc, op, false); }
+
+const char *ngc_conv3d_kernel(const ngc_conv3d_desc *desc, int op) { return variant_name3(desc, op, true); }
 
 int ngc_conv3d_fwd(const ngc_conv3d_desc *desc, const void *x, const void *w, const float *bias, void *y, void *ws,
                    size_t ws_bytes, void *hip_stream)

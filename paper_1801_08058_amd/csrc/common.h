@@ -663,6 +663,7 @@ hipError_t launch_wgrad_reduce(const float *partial, float *dw, int splits, int 
                                hipStream_t st);
 // gather GEMM kernels (conv_gather.hip): the nodes no blocked bf16 kernel takes, within 32-bit operand offsets
 bool gather_takes(const ngc_conv_desc &d, int op, int P, int Q);
+bool gather_streams(const ngc_conv_desc &d, int op, int P, int Q);     // of a node it takes: conv_stream.hip / wgrad_stream.hip run it
 hipError_t launch_gather_fwd(const ngc_conv_desc &d, int P, int Q, const void *x, const void *w, const float *bias, void *y, hipStream_t st);
 hipError_t launch_gather_bwd_data(const ngc_conv_desc &d, int P, int Q, const void *dy, const void *w, const void *mask, void *dx, hipStream_t st);
 size_t gather_wgrad_workspace(const ngc_conv_desc &d, int P, int Q);

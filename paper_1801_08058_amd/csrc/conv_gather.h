@@ -35,6 +35,7 @@ struct GatherConvParams {
     int32_t s0[GATHER_CLASSES], ns[GATHER_CLASSES], base_w[GATHER_CLASSES], opw[GATHER_CLASSES];
     FastDiv div_pq[4], div_q[2];   // by the lattice extents: index 2 * (oph != oph[0]) + (opw != opw[0]), and the latter
     int32_t relu;
+    int32_t wvec;                  // gather GEMM: a filter row is whole 16-byte pieces in the order of the reduction
 };
 
 template <typename T> struct GElem;
@@ -206,8 +207,13 @@ inline void gather_strides(int layout, int C, int HW, int32_t *n, int32_t *c, in
     *px = b ? 16 : 1;
 }
 
-// conv_stream.hip: true if it took the launch (its status in *e); max_m: positions of the largest class
-bool launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, int classes, hipStream_t st, hipError_t *e);
+// conv_stream.hip; max_m: positions of the largest class
+struct StreamChoice {
+    bool take, sliced, wrow;       // the node is its own; slices of the reduction (else positions); filter rows in the order of the indices
+    size_t lds;                    // of the index table
+};
+StreamChoice stream_conv_choice(const GatherConvParams &p, int dtype, unsigned max_m, int classes);
+hipError_t launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, int classes, const StreamChoice &c, hipStream_t st);
 // wgrad_stream.hip: the same for backprop-filters (false also where the workspace is too small); bytes of partial sums
 bool launch_wgrad_stream(const ngc_conv_desc &d, int P, int Q, const void *x, const void *dy, float *dw, void *ws, size_t ws_bytes, hipStream_t st, hipError_t *e);
 size_t wgrad_stream_workspace(const ngc_conv_desc &d, int P, int Q, bool *takes);

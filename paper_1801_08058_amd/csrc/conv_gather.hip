@@ -576,16 +576,21 @@ static hipError_t launch_gather_conv_t(const GatherConvParams &p, unsigned max_m
     }
 }
 
-static hipError_t launch_gather_conv(GatherConvParams &p, int dtype, int classes, bool wvec, hipStream_t st)
+static void lattice_divisions(GatherConvParams *p)
 {
-    const int last_h = p.os_h - 1, last_w = p.os_w - 1;                  // the extents of the classes: that of class 0 or one less
-    const int oph[2] = {p.oph[0], p.oph[last_h]}, opw[2] = {p.opw[0], p.opw[last_w]};
-    for (int i = 0; i < 4; ++i) p.div_pq[i] = make_fastdiv((uint32_t)(oph[i >> 1] * opw[i & 1] > 0 ? oph[i >> 1] * opw[i & 1] : 1));
-    for (int i = 0; i < 2; ++i) p.div_q[i] = make_fastdiv((uint32_t)(opw[i] > 0 ? opw[i] : 1));
+    const int last_h = p->os_h - 1, last_w = p->os_w - 1;                // the extents of the classes: that of class 0 or one less
+    const int oph[2] = {p->oph[0], p->oph[last_h]}, opw[2] = {p->opw[0], p->opw[last_w]};
+    for (int i = 0; i < 4; ++i) p->div_pq[i] = make_fastdiv((uint32_t)(oph[i >> 1] * opw[i & 1] > 0 ? oph[i >> 1] * opw[i & 1] : 1));
+    for (int i = 0; i < 2; ++i) p->div_q[i] = make_fastdiv((uint32_t)(opw[i] > 0 ? opw[i] : 1));
+}
+
+static hipError_t launch_gather_conv(const GatherConvParams &p, int dtype, hipStream_t st)
+{
     const unsigned max_m = (unsigned)p.N * p.oph[0] * p.opw[0];
-    hipError_t e;
-    if (launch_stream_conv(p, dtype, max_m, classes, st, &e)) return e;
-    return dtype == NGC_F32 ? launch_gather_conv_t<float>(p, max_m, classes, wvec, st) : launch_gather_conv_t<uint16_t>(p, max_m, classes, wvec, st);
+    const int classes = p.os_h * p.os_w;
+    const StreamChoice c = stream_conv_choice(p, dtype, max_m, classes);
+    if (c.take) return launch_stream_conv(p, dtype, max_m, classes, c, st);
+    return dtype == NGC_F32 ? launch_gather_conv_t<float>(p, max_m, classes, p.wvec, st) : launch_gather_conv_t<uint16_t>(p, max_m, classes, p.wvec, st);
 }
 
 // the classes of one axis of backprop-data: output pixels congruent to a modulo the stride meet the taps r with
@@ -605,11 +610,11 @@ static void gather_axis(int extent, int stride, int dil, int pad, int taps, int3
     }
 }
 
-hipError_t launch_gather_fwd(const ngc_conv_desc &d, int P, int Q, const void *x, const void *w, const float *bias, void *y, hipStream_t st)
+// the arguments of a node but its tensors
+static GatherConvParams fwd_params(const ngc_conv_desc &d, int P, int Q)
 {
     const size_t sz = d.dtype == NGC_F32 ? 4 : 2;
     GatherConvParams p = {};
-    p.in = x; p.wt = w; p.out = y; p.bias = bias;
     p.N = d.n; p.Cin = d.c; p.Cout = d.k; p.Hin = d.h; p.Win = d.w; p.Hout = P; p.Wout = Q;
     gather_strides(d.x_layout, d.c, d.h * d.w, &p.in_n, &p.in_c, &p.in_px);
     p.in_bytes = (uint32_t)((size_t)d.n * p.in_n * sz);
@@ -620,14 +625,15 @@ hipError_t launch_gather_fwd(const ngc_conv_desc &d, int P, int Q, const void *x
     p.rst_h = p.rst_w = 1; p.step_h = d.dil_h; p.step_w = d.dil_w;
     p.nr[0] = d.r; p.ns[0] = d.s; p.base_h[0] = -d.pad_below_h; p.base_w[0] = -d.pad_below_w; p.oph[0] = P; p.opw[0] = Q;
     p.relu = (d.epilogue & NGC_EPI_RELU) ? 1 : 0;
-    return launch_gather_conv(p, d.dtype, 1, p.w_row % (int)(16 / sz) == 0, st);
+    p.wvec = p.w_row % (int)(16 / sz) == 0;
+    lattice_divisions(&p);
+    return p;
 }
 
-hipError_t launch_gather_bwd_data(const ngc_conv_desc &d, int P, int Q, const void *dy, const void *w, const void *mask, void *dx, hipStream_t st)
+static GatherConvParams bwd_data_params(const ngc_conv_desc &d, int P, int Q)
 {
     const size_t sz = d.dtype == NGC_F32 ? 4 : 2;
     GatherConvParams p = {};
-    p.in = dy; p.wt = w; p.out = dx; p.mask = mask;
     p.N = d.n; p.Cin = d.k; p.Cout = d.c; p.Hin = P; p.Win = Q; p.Hout = d.h; p.Wout = d.w;
     gather_strides(d.y_layout, d.k, P * Q, &p.in_n, &p.in_c, &p.in_px);
     p.in_bytes = (uint32_t)((size_t)d.n * p.in_n * sz);
@@ -637,7 +643,33 @@ hipError_t launch_gather_bwd_data(const ngc_conv_desc &d, int P, int Q, const vo
     p.is_h = p.is_w = 1; p.os_h = d.stride_h; p.os_w = d.stride_w;
     gather_axis(d.h, d.stride_h, d.dil_h, d.pad_below_h, d.r, &p.rst_h, &p.step_h, p.r0, p.nr, p.base_h, p.oph);
     gather_axis(d.w, d.stride_w, d.dil_w, d.pad_below_w, d.s, &p.rst_w, &p.step_w, p.s0, p.ns, p.base_w, p.opw);
-    return launch_gather_conv(p, d.dtype, d.stride_h * d.stride_w, false, st);
+    lattice_divisions(&p);
+    return p;
+}
+
+hipError_t launch_gather_fwd(const ngc_conv_desc &d, int P, int Q, const void *x, const void *w, const float *bias, void *y, hipStream_t st)
+{
+    GatherConvParams p = fwd_params(d, P, Q);
+    p.in = x; p.wt = w; p.out = y; p.bias = bias;
+    return launch_gather_conv(p, d.dtype, st);
+}
+
+hipError_t launch_gather_bwd_data(const ngc_conv_desc &d, int P, int Q, const void *dy, const void *w, const void *mask, void *dx, hipStream_t st)
+{
+    GatherConvParams p = bwd_data_params(d, P, Q);
+    p.in = dy; p.wt = w; p.out = dx; p.mask = mask;
+    return launch_gather_conv(p, d.dtype, st);
+}
+
+bool gather_streams(const ngc_conv_desc &d, int op, int P, int Q)
+{
+    if (op == NGC_OP_BWD_FILTERS) {
+        bool takes;
+        wgrad_stream_workspace(d, P, Q, &takes);
+        return takes;
+    }
+    const GatherConvParams p = op == NGC_OP_FWD ? fwd_params(d, P, Q) : bwd_data_params(d, P, Q);
+    return stream_conv_choice(p, d.dtype, (unsigned)p.N * p.oph[0] * p.opw[0], p.os_h * p.os_w).take;
 }
 
 // How backprop-filters runs: the tile (1 = 64 x 64, two slices; 2 = 32 x 32, eight slices; 3 = 32 x 32, four slices) and the

@@ -242,20 +242,21 @@ static hipError_t launch_stream_t(const GatherConvParams &p, unsigned max_m, int
     return sliced ? launch_stream_l<T, 1, 4, 1, WROW>(p, max_m, classes, lds, st) : launch_stream_l<T, 1, 1, 4, WROW>(p, max_m, classes, lds, st);
 }
 
-bool launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, int classes, hipStream_t st, hipError_t *e)
+StreamChoice stream_conv_choice(const GatherConvParams &p, int dtype, unsigned max_m, int classes)
 {
+    constexpr StreamChoice NO = {};
     const char *force = env_switch(SW_STREAM);                            // tests only: 0 = never, 1 / 2 = positions / slices
     const int fv = force ? atoi(force) : -1;
-    if (fv == 0 || env_switch(SW_GATHER_TILE)) return false;             // a switch that shapes the gather kernel asks for it
+    if (fv == 0 || env_switch(SW_GATHER_TILE)) return NO;                // a switch that shapes the gather kernel asks for it
     int nr = 0, ns = 0;
     for (int a = 0; a < p.os_h; ++a) nr = p.nr[a] > nr ? p.nr[a] : nr;
     for (int b = 0; b < p.os_w; ++b) ns = p.ns[b] > ns ? p.ns[b] : ns;
     const int ntaps = nr * ns;
-    if (ntaps < 1 || ntaps > STREAM_DEAD) return false;
+    if (ntaps < 1 || ntaps > STREAM_DEAD) return NO;
     // a filter row lies in the order of the indices: forward (and backprop-data of a single input channel)
     const bool wrow = p.w_chan == ntaps && p.rst_h == 1 && p.rst_w == 1 && p.os_h == 1 && p.os_w == 1;
     const size_t kred = (size_t)ntaps * p.Cin, kpad = (kred + 15) / 16 * 16 + 16, lds = kpad * (wrow ? 8 : 12);
-    if (lds > 64 * 1024) return false;
+    if (lds > 64 * 1024) return NO;
     // Slices of the reduction or positions: a workgroup's four waves take a tile's reduction in turns, or four tiles.  Times in
     // us of some thirty nodes each of 0.01 to 4 GFLOP: fixed part, steps of a wave, tile-steps and workgroups per compute unit;
     // the estimates are within 10 % (fp32) and 25 % (bf16), the choice between them loses 0.3 % on average, 11 % at most.
@@ -279,14 +280,18 @@ bool launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, in
                         : p.in_blocked   ? 20.0
                         : wrow           ? (ntaps > 9 ? 230.0 : 450.0)
                                          : 100.0;
-    if (fv <= 0 && work > most) return false;
+    if (fv <= 0 && work > most) return NO;
     const double *c0 = cost[dtype != NGC_F32][wrow][0], *c1 = cost[dtype != NGC_F32][wrow][1];
     const double by_pos = c0[0] + c0[1] * steps + c0[2] * work + c0[3] * (double)((max_m + 127) / 128) * cot * classes / 256;
     const double by_slice = c1[0] + c1[1] * (double)((int)(steps + 3) / 4) + c1[2] * work + c1[3] * tiles * classes / 256;
     const bool sliced = fv > 0 ? fv == 2 : by_slice <= by_pos;
-    if (dtype == NGC_F32) *e = wrow ? launch_stream_t<float, true>(p, max_m, classes, sliced, lds, st) : launch_stream_t<float, false>(p, max_m, classes, sliced, lds, st);
-    else *e = wrow ? launch_stream_t<uint16_t, true>(p, max_m, classes, sliced, lds, st) : launch_stream_t<uint16_t, false>(p, max_m, classes, sliced, lds, st);
-    return true;
+    return {true, sliced, wrow, lds};
+}
+
+hipError_t launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, int classes, const StreamChoice &c, hipStream_t st)
+{
+    if (dtype == NGC_F32) return c.wrow ? launch_stream_t<float, true>(p, max_m, classes, c.sliced, c.lds, st) : launch_stream_t<float, false>(p, max_m, classes, c.sliced, c.lds, st);
+    return c.wrow ? launch_stream_t<uint16_t, true>(p, max_m, classes, c.sliced, c.lds, st) : launch_stream_t<uint16_t, false>(p, max_m, classes, c.sliced, c.lds, st);
 }
 
 }  // namespace ngc

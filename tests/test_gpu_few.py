@@ -7,7 +7,7 @@ import pytest
 import oracle
 import paper_1801_08058_amd as ng
 from oracle import Attrs, Attrs3
-from gpu_util import Run, bound
+from gpu_util import Run, bound, desc3_of
 from test_gpu_conv3d import _check3
 from test_gpu_parity import _check_backward_compounds, _tensors
 
@@ -63,6 +63,8 @@ def test_few_tiles_backward(case, pre, force, monkeypatch):
     x, w, b, dy = _tensors(a, "bf16", 14100 + case)
     run = Run(a, "bf16", BLK, BLK, pre)
     dx = run.bwd_data(dy, w)
+    if force:
+        assert ng.ngc_conv_kernel(run.last_desc, ng.NGC_OP_BWD_DATA).endswith(":few") == (force != "0")
     ref = oracle.conv_bwd_data(a, dy, w)
     assert oracle.max_normalised_error(dx, ref) <= bound("bf16", "act")
     _check_backward_compounds(run, a, x, w, dy, ref, bound("bf16", "act"))
@@ -86,4 +88,8 @@ CASES3 = [
 def test_few_tiles_three_axes(case, force, monkeypatch):
     if force:
         monkeypatch.setenv("NGC_FWD_FEW", force)
+    if force:
+        d = desc3_of(CASES3[case], "bf16", BLK, BLK)
+        for op in (ng.NGC_OP_FWD, ng.NGC_OP_BWD_DATA):
+            assert ng.ngc_conv3d_kernel(d, op) == ("strip3_bf16" if force == "0" else "strip3_bf16:few")
     _check3(CASES3[case], "bf16", BLK, BLK, case % 2 == 0, 14300 + case, ("strip3_bf16", "strip3_bf16", "wgrad_gemm3"))

@@ -37,6 +37,9 @@ def test_stream(case, share, monkeypatch):
     run = Run(a, dtype, xl, yl, False)
     y = run.fwd(x, w, bias=b, relu=True)
     assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_FWD) == "direct:gather"
+    takes = "stream" if share and a.r * a.s <= 31 else "gather"
+    if share or a.r * a.s > 31:
+        assert [ng.ngc_conv_kernel(run.last_desc, op) for op in (ng.NGC_OP_FWD, ng.NGC_OP_BWD_DATA)] == ["direct:" + takes] * 2
     assert oracle.max_normalised_error(y, oracle.conv_fwd(a, x, w, bias=b, relu=True)) <= bound(dtype, "act")
     assert oracle.max_normalised_error(run.bwd_data(dy, w), oracle.conv_bwd_data_gather(a, dy, w)) <= bound(dtype, "act")
     assert oracle.max_normalised_error(run.bwd_data_relu(dy, w, x), oracle.conv_bwd_data_relu(a, dy, w, x)) <= bound(dtype, "act")

@@ -37,7 +37,10 @@ def test_wgrad_stream(case, parts, monkeypatch):
     if parts:
         monkeypatch.setenv("NGC_WGRAD_STREAM", str(parts))
     x, w, b, dy = _tensors(a, dtype, 17000 + case)
-    dw = Run(a, dtype, NCHW, NCHW, False).bwd_filters(x, dy)
+    run = Run(a, dtype, NCHW, NCHW, False)
+    dw = run.bwd_filters(x, dy)
+    if parts:
+        assert ng.ngc_conv_kernel(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "direct:stream"
     assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound(dtype, "dw")
 
 

@@ -1,0 +1,54 @@
+"""Which kernel a call runs, asked on the host: the names tell the kernels apart, the switches that force one are named for it."""
+import pytest
+
+import paper_1801_08058_amd as ng
+
+FWD, BWD, WGRAD, DB = ng.NGC_OP_FWD, ng.NGC_OP_BWD_DATA, ng.NGC_OP_BWD_FILTERS, ng.NGC_OP_BWD_DATA_DB
+NCHW, BLK = ng.NGC_NCHW, ng.NGC_NCHW16C
+
+
+def node(n, c, h, w, k, r, s=None, stride=1, dtype="f32", xl=NCHW, yl=None):
+    s = r if s is None else s
+    pad = ((r - 1) // 2 if stride == 1 or r > 2 else 0, (s - 1) // 2 if stride == 1 or s > 2 else 0)
+    return ng.make_desc(n, c, h, w, k, r, s, (stride,) * 2, (1, 1), pad, pad, ng.NGC_F32 if dtype == "f32" else ng.NGC_BF16,
+                        xl, xl if yl is None else yl)
+
+
+def node3(n, c, d, h, w, k, t, r, s, stride=1):
+    pad = (t // 2, r // 2, s // 2)
+    return ng.make_desc3(n, c, d, h, w, k, t, r, s, (stride,) * 3, (1, 1, 1), pad, pad, ng.NGC_BF16, BLK, BLK)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_names_of_the_nodes_off_the_blocked_kernels(dtype, monkeypatch):
+    d, wide = node(2, 7, 13, 11, 33, 3, dtype=dtype), node(1, 3, 12, 9, 5, 4, 8, dtype=dtype)        # 9 taps, 32 taps
+    for stream, name in ((0, "direct:gather"), (1, "direct:stream"), (2, "direct:stream")):
+        monkeypatch.setenv("NGC_STREAM", str(stream))
+        monkeypatch.setenv("NGC_WGRAD_STREAM", str(stream))
+        assert [ng.ngc_conv_kernel(d, op) for op in (FWD, BWD, WGRAD)] == [name] * 3
+        assert ng.ngc_conv_kernel(wide, FWD) == ng.ngc_conv_kernel(wide, BWD) == "direct:gather"
+        assert ng.ngc_conv_variant(d, FWD) == "direct:gather"                                        # the variant stays
+    monkeypatch.setenv("NGC_GATHER_TILE", "0")
+    assert [ng.ngc_conv_kernel(d, op) for op in (FWD, BWD, WGRAD)] == ["direct"] * 3
+
+
+def test_names_of_nodes_with_few_output_tiles(monkeypatch):
+    d, one = node(1, 256, 14, 14, 256, 3, dtype="bf16", xl=BLK), node(1, 256, 14, 14, 256, 1, dtype="bf16", xl=BLK)
+    d3, flat = node3(1, 64, 4, 7, 7, 64, 3, 3, 3), node3(1, 64, 4, 7, 7, 64, 1, 1, 1)
+    for few, tail in (("0", ""), ("1", ":few"), ("2", ":few")):
+        monkeypatch.setenv("NGC_FWD_FEW", few)
+        for op in (FWD, BWD, DB):
+            assert ng.ngc_conv_kernel(d, op) == "strip_bf16" + tail
+            assert ng.ngc_conv_kernel(one, op) == "gemm1x1_bf16" + tail
+        for op in (FWD, BWD):
+            assert ng.ngc_conv3d_kernel(d3, op) == "strip3_bf16" + tail
+            assert ng.ngc_conv3d_kernel(flat, op) == "rank2:gemm1x1_bf16" + tail
+            assert ng.ngc_conv3d_variant(d3, op) == "strip3_bf16"
+
+
+def test_other_kernels_keep_their_variant_names():
+    for d in (node(64, 64, 56, 56, 64, 3, dtype="bf16", xl=BLK), node(8, 64, 56, 56, 64, 3, dtype="bf16"), node(64, 256, 56, 56, 64, 1, dtype="bf16", xl=BLK)):
+        for op in (FWD, WGRAD):
+            assert ng.ngc_conv_kernel(d, op) == ng.ngc_conv_variant(d, op)
+    bad = ng.make_desc(0, 1, 1, 1, 1, 1, 1)
+    assert ng.ngc_conv_kernel(bad, FWD) == "invalid"
