@@ -212,6 +212,7 @@ struct StreamChoice {
     bool take, sliced, wrow;       // the node is its own; slices of the reduction (else positions); filter rows in the order of the indices
     size_t lds;                    // of the index table
 };
+double gather_f32_bwd_us(const GatherConvParams &p, unsigned max_m);    // conv_gather.hip: what the gather GEMM would take
 StreamChoice stream_conv_choice(const GatherConvParams &p, int dtype, unsigned max_m, int classes);
 hipError_t launch_stream_conv(const GatherConvParams &p, int dtype, unsigned max_m, int classes, const StreamChoice &c, hipStream_t st);
 // wgrad_stream.hip: the same for backprop-filters (false also where the workspace is too small); bytes of partial sums

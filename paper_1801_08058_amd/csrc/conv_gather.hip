@@ -15,10 +15,12 @@
 // v_mfma_f32_32x32x16_bf16.
 //
 // What bounds it: the gather, four vector instructions and a load per element.  A 64 x 64 step of two slices takes 0.95 us on
-// a chip with work for every unit, of which the fp32 matrix pipes have 0.43 us (1024 cycles).  Forward and backprop-data run here
-// only where conv_stream.hip does not take them (windows of more than 31 taps, reductions past its index table).
+// a chip with work for every unit, of which the fp32 matrix pipes have 0.43 us (1024 cycles).  conv_stream.hip and wgrad_stream.hip
+// take the nodes they are expected to run faster; here run the others: large ones, windows of more than 31 taps, reductions past
+// the index table, backprop-filters of blocked tensors.
 #include "conv_gather.h"
 
+#include <math.h>
 #include <stdlib.h>
 
 namespace ngc {
@@ -550,26 +552,47 @@ static hipError_t launch_gather_conv_w(const GatherConvParams &p, unsigned max_m
 // 0.5 us (two slices: 0.95 us for twice the indices), a 32 x 32 step 0.35 us for half as many indices and a quarter of the
 // tile.  The larger of the two times the steps is within 15 % of the measured times of some forty nodes of 0.2 to 40 us; the
 // smallest estimate is taken.
-template <typename T>
-static int gather_tile(const GatherConvParams &p, unsigned max_m, int classes)
+struct GatherLoad {
+    int s4, s8;                    // steps of 4 and of 8 units
+    double t64, t32;               // tiles per compute unit
+};
+
+static GatherLoad gather_load(const GatherConvParams &p, int U, unsigned max_m, int classes)
 {
-    const char *force = env_switch(SW_GATHER_TILE);                       // tests / experiments only
-    if (force && atoi(force) >= 1 && atoi(force) <= 3) return atoi(force);
     int taps = 0;
     for (int a = 0; a < p.os_h; ++a)
         for (int b = 0; b < p.os_w; ++b) taps = p.nr[a] * p.ns[b] > taps ? p.nr[a] * p.ns[b] : taps;
-    const int kred = taps * p.Cin, U = GElem<T>::U;
-    const double t64 = (double)((max_m + 63) / 64) * ((p.Cout + 63) / 64) * classes / 256, t32 = (double)((max_m + 31) / 32) * ((p.Cout + 31) / 32) * classes / 256;
-    const int s4 = (kred + 4 * U - 1) / (4 * U), s8 = (kred + 8 * U - 1) / (8 * U);
+    const int kred = taps * p.Cin;
+    return {(kred + 4 * U - 1) / (4 * U), (kred + 8 * U - 1) / (8 * U), (double)((max_m + 63) / 64) * ((p.Cout + 63) / 64) * classes / 256,
+            (double)((max_m + 31) / 32) * ((p.Cout + 31) / 32) * classes / 256};
+}
+
+static int gather_tile(const GatherLoad &l)
+{
+    const char *force = env_switch(SW_GATHER_TILE);                       // tests / experiments only
+    if (force && atoi(force) >= 1 && atoi(force) <= 3) return atoi(force);
     auto larger = [](double x, double y) { return x > y ? x : y; };
-    const double e1 = s4 * larger(0.45, 0.5 * t64), e2 = s8 * larger(0.5, 0.95 * t64) + 0.8, e3 = s8 * larger(0.45, 0.35 * t32) + 0.8;
+    const double e1 = l.s4 * larger(0.45, 0.5 * l.t64), e2 = l.s8 * larger(0.5, 0.95 * l.t64) + 0.8, e3 = l.s8 * larger(0.45, 0.35 * l.t32) + 0.8;
     return e1 <= e2 && e1 <= e3 ? 1 : e2 < e3 ? 2 : 3;
+}
+
+// Expected time, us, of fp32 backprop-data with stride 1, to choose between this kernel and conv_stream.hip: a start and, per
+// step, latency and rounds of workgroups.  Fitted to 1057 launches of the tile chosen above, four fifths of them within 12 %.
+double gather_f32_bwd_us(const GatherConvParams &p, unsigned max_m)
+{
+    const GatherLoad l = gather_load(p, 4, max_m, 1);
+    const double r64 = ceil(l.t64), r32 = ceil(l.t32);
+    switch (gather_tile(l)) {
+    case 1: return 4.75 + l.s4 * (0.179 + 0.412 * r64);
+    case 2: return 5.61 + l.s8 * (0.165 + 0.687 * r64);
+    default: return 4.33 + l.s8 * (0.242 + 0.224 * r32);
+    }
 }
 
 template <typename T>
 static hipError_t launch_gather_conv_t(const GatherConvParams &p, unsigned max_m, int classes, bool wvec, hipStream_t st)
 {
-    switch (gather_tile<T>(p, max_m, classes)) {
+    switch (gather_tile(gather_load(p, GElem<T>::U, max_m, classes))) {
     case 1: return launch_gather_conv_w<T, 64, 64, 2, 2, 1, 4>(p, max_m, classes, wvec, st);
     case 2: return launch_gather_conv_w<T, 64, 64, 2, 2, 2, 4>(p, max_m, classes, wvec, st);
     default: return launch_gather_conv_w<T, 32, 32, 1, 1, 4, 2>(p, max_m, classes, wvec, st);

@@ -20,6 +20,7 @@
 // backprop-data the filter offset; a lane adds its pixel and masks taps in the padding with one bit per tap.
 #include "conv_gather.h"
 
+#include <math.h>
 #include <stdlib.h>
 
 namespace ngc {
@@ -269,14 +270,25 @@ StreamChoice stream_conv_choice(const GatherConvParams &p, int dtype, unsigned m
     for (int a = 0; a < p.os_h; ++a) all_h += p.nr[a];
     for (int b = 0; b < p.os_w; ++b) all_w += p.ns[b];
     const double work = tiles * all_h * all_w * p.Cin / nk / 256;
-    // Tile-steps per compute unit past which the gather GEMM's tiles in LDS, which read an operand once for several fragments, are
-    // faster (gather / this kernel, us, some 440 launches of up to 8 GFLOP).  fp32: forward never in the range, except strided (64 -> 160 at
-    // 56x56 / 2, 1033 steps 72.9 / 83.5); backprop-data, whose filter operand costs an access per lane, 121 -> 148, 3x3, 1826 steps
-    // 95.6 / 134.1, 529 48.3 / 42.8, strided 5x5, 155 18.9 / 23.8.  bf16 NCHW: forward 405 50.0 / 34.6, 1008 65.4 / 122.5, 5x5, 250
+    const bool strided = p.is_h > 1 || p.is_w > 1 || classes > 1;
+    // fp32 backprop-data with stride 1, whose filter operand costs an access per lane: the smaller of two expected times, by rounds
+    // of workgroups and the 64-byte lines of a filter load (32 rows, a window each), fitted to the same 1057 launches as the gather
+    // GEMM's time (four fifths of them within 20 %).  Over all of them that takes 1.2 % more than the better kernel of each; a
+    // limit of 600 tile-steps took 4.6 %.  Gather / this kernel, us: 8 x 96 -> 64 at 45x37, 3x3 30.8 / 33.0; 15 x 128 -> 49 at 54x39, 3x3 58.3
+    // / 72.5; 22 x 157 -> 12 at 16x42, 5x5 81.8 / 52.5.
+    if (fv < 0 && dtype == NGC_F32 && !wrow && !strided) {
+        const double lines = 2 * ntaps + 1 < 32 ? 2 * ntaps + 1 : 32, n = kred / 8.0;
+        const double rp = ceil((double)((max_m + 127) / 128) * cot / 256), rs = ceil(tiles / 256);
+        const double by_pos = 3.28 + rp * (0.70 + n * (0.1985 + 0.0024 * lines)), by_slice = 3.24 + rs * (0.655 + n / 4 * (0.173 + 0.0033 * lines));
+        const bool sliced = by_slice <= by_pos;
+        return {(sliced ? by_slice : by_pos) <= gather_f32_bwd_us(p, max_m), sliced, wrow, lds};
+    }
+    // Elsewhere: tile-steps per compute unit past which the gather GEMM's tiles in LDS, which read an operand once for several
+    // fragments, are faster (gather / this kernel, us, some 440 launches of up to 8 GFLOP).  fp32: forward never in the range, except strided (64 -> 160 at
+    // 56x56 / 2, 1033 steps 72.9 / 83.5); backprop-data, strided 5x5, 155 18.9 / 23.8.  bf16 NCHW: forward 405 50.0 / 34.6, 1008 65.4 / 122.5, 5x5, 250
     // 18.7 / 23.2; backprop-data 200 21.8 / 27.6, 102 40.7 / 28.1.  bf16 blocked, where the gather kernel reads 16 bytes at a time: 154 31.1 / 57.7,
     // 29 11.3 / 13.5.
-    const bool strided = p.is_h > 1 || p.is_w > 1 || classes > 1;
-    const double most = dtype == NGC_F32 ? (wrow ? (strided ? 600.0 : 1e30) : strided ? 130.0 : 600.0)
+    const double most = dtype == NGC_F32 ? (wrow ? (strided ? 600.0 : 1e30) : 130.0)
                         : p.in_blocked   ? 20.0
                         : wrow           ? (ntaps > 9 ? 230.0 : 450.0)
                                          : 100.0;

@@ -52,3 +52,13 @@ def test_other_kernels_keep_their_variant_names():
             assert ng.ngc_conv_kernel(d, op) == ng.ngc_conv_variant(d, op)
     bad = ng.make_desc(0, 1, 1, 1, 1, 1, 1)
     assert ng.ngc_conv_kernel(bad, FWD) == "invalid"
+
+
+def test_fp32_backprop_data_takes_the_kernel_that_is_expected_to_be_faster():
+    """Stride 1: nodes whose two kernels differ by a tenth or more where both were timed, on either side of the choice."""
+    gather = [(8, 64, 45, 37, 96, 3), (18, 62, 19, 45, 29, 5), (2, 105, 62, 52, 46, 5), (28, 41, 19, 26, 49, 5), (15, 49, 54, 39, 128, 3)]
+    stream = [(2, 16, 16, 16, 32, 3), (22, 12, 16, 42, 157, 5), (12, 33, 27, 20, 160, 5), (9, 88, 24, 25, 127, 5), (8, 3, 40, 40, 32, 3)]
+    for a in gather:
+        assert ng.ngc_conv_kernel(node(*a), BWD) == "direct:gather", a
+    for a in stream:
+        assert ng.ngc_conv_kernel(node(*a), BWD) == "direct:stream", a
