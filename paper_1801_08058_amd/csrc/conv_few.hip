@@ -21,6 +21,7 @@
 // read as zeros through out-of-range offsets.
 #include "common.h"
 
+#include <math.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -210,43 +211,51 @@ struct FewNode {
     bool r3;
 };
 
-// Expected times, us, fitted to 270 measured launches of nodes up to 3000 tiles (median error 13 .. 19 %): a start, batches of
-// loads in turn, workgroups beyond the first round (256 compute units; two workgroups of 8 waves and one fragment each on one),
-// and the operands' bytes through the L2s, at the share of them that the workgroups reach.
-double few_us(int tl, size_t M, int Cout, int classes, int units, double mean_units)
+// Expected times, us: a start and, per round of workgroups (256 compute units; two workgroups of 8 waves and one fragment start on
+// each), a start of its own, the units of a wave and the taps it walks past (every wave counts through all of them, at more cost with
+// a depth axis and for the classes of backprop-data), at least one round of the class with most taps; up to 64 units also the
+// operands' bytes through the L2s, at the share of them that the workgroups reach.  Fitted to 3245 launches of up to 3000 tiles, back
+// to back in a graph: four fifths of them within 20 % (32 x 32 tiles) and 12 % (64 x 64).
+double few_us(int tl, size_t M, int Cout, int CB, int classes, int units, double mean_units, bool r3, bool bwd)
 {
-    const double tiles = (double)((M + 32 * tl - 1) / (32 * tl)) * ((Cout + 32 * tl - 1) / (32 * tl)) * classes;
-    const int nw = tl == 1 && units > 64 ? 16 : 8, b = tl == 1 ? 8 : 4;
-    const double slots = tl == 1 && nw == 8 ? 512 : 256, over = tiles > slots ? tiles / slots : 1.0;
-    const double share = tiles < 256 ? (tiles < 5 ? 0.02 : tiles / 256) : 1.0;
-    const double batches = (units + nw * b - 1) / (nw * b), mb = tiles * mean_units * (tl == 1 ? 2048e-6 : 4096e-6);
-    return tl == 1 ? 2.9 + (0.31 * batches + 1.09) * over + mb / (22.2 * share) : 1.93 + (0.073 * batches + 2.87) * over + mb / (25.9 * share);
+    const double tiles = (double)((M + 32 * tl - 1) / (32 * tl)) * ((Cout + 32 * tl - 1) / (32 * tl)) * classes, rounds = ceil(tiles / 256);
+    const double walk = mean_units / CB, longest = (double)units / CB;
+    if (tl == 1 && units <= 64) {
+        const double tap = 0.021 + 0.035 * r3 + 0.038 * bwd, share = tiles < 256 ? (tiles < 5 ? 0.02 : tiles / 256) : 1.0;
+        return 1.77 + ceil(tiles / 512) * 0.68 + tap * (rounds * walk > longest ? rounds * walk : longest) + 65e-6 * tiles * mean_units / share;
+    }
+    const double wg = tl == 2 ? 2.43 : 1.67, unit = tl == 2 ? 0.242 / 8 : 0.212 / 16;
+    const double tap = tl == 2 ? 0.014 + 0.052 * r3 + 0.017 * bwd : 0.026 + 0.079 * r3 + 0.063 * bwd;
+    const double all = rounds * (wg + unit * mean_units + tap * walk), one = wg + unit * units + tap * longest;
+    return (tl == 2 ? 0.89 : 1.45) + (all > one ? all : one);
 }
 
-// The tile (fragments per axis) of a node, 0: the staged kernels, which take staged_us (below 0: already decided against them).
-int few_rule(size_t M, int Cout, int classes, int units, double mean_units, double staged_us, bool strided)
+// The tile (fragments per axis) of a node, 0: the staged kernels, which take staged_us (0: no estimate; below: already decided
+// against them).  units: of the class with most taps; mean_units: of a class on average
+int few_rule(size_t M, int Cout, int CB, int classes, int units, double mean_units, double staged_us, bool r3, bool bwd, bool strided)
 {
     const char *force = env_switch(SW_FWD_FEW);        // tests / benchmarks only: 0 = never, 1 / 2 = wherever it can, that tile
     const int fv = force ? atoi(force) : -1;
     if (fv >= 0) return fv > 2 ? 0 : fv;
-    const double one = few_us(1, M, Cout, classes, units, mean_units), two = few_us(2, M, Cout, classes, units, mean_units);
-    // the larger tile only where it reaches half of the compute units: 2 x 480 -> 64 at 8x7, 3x3 (8 tiles of 32, 2 of 64) 7.7 / 11.3 us
-    const int tile = two < one && (M + 63) / 64 * ((Cout + 63) / 64) * classes >= 128 ? 2 : 1;
+    const double one = few_us(1, M, Cout, CB, classes, units, mean_units, r3, bwd), two = few_us(2, M, Cout, CB, classes, units, mean_units, r3, bwd);
+    // the larger tile only where it reaches a good third of the compute units: fewer have too few loads in flight for operands from
+    // memory (1x1 backprop-data 1728 -> 64, 49 x 9x11, 304 tiles of 32, 76 of 64 10.4 / 13.5 us; in cache 8.1 / 6.7)
+    const int tile = two < one && (M + 63) / 64 * ((Cout + 63) / 64) * classes >= 96 ? 2 : 1;
     if (staged_us < 0) return tile;
     // a switch that shapes the staged kernels asks for them
     for (Switch sw : {SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_BW, SW_STRIP_XCD, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_STRIP_CPS, SW_STRIP_STRIDED, SW_G1_VARIANT, SW_ROWS})
         if (env_switch(sw)) return 0;
-    // One round of workgroups (256 compute units) and a reduction worth dealing out, or most of two rounds and a long one.  Staged
-    // kernel / this one, us: 224 tiles of 16 units (256 -> 1024 at 14x14) 5.4 / 3.5, 98 of 8 4.4 / 3.3, 4 of 18 4.4 / 3.9, 104 of 4
-    // 3.6 / 3.6; 392 tiles of 36 7.3 / 4.5, 448 of 32 8.0 / 4.4, 400 of 288 35.1 / 17.0, but 392 of 18 5.3 / 5.5 and 400 of 8 4.3 / 4.4.
+    // About one round of workgroups and a reduction worth dealing out: here, unless expected to take longer (one round: by a tenth, the
+    // estimates' error).  Beyond that only where it is expected to take a fifth less (two fifths with a reduction of under 8 units),
+    // and not for more than 3000 tiles (5220 of 124 units 36.5 / 96.7 / 65.0) nor forward with strided reads, which fetch whole lines
+    // for half of them (13 x 1024 -> 384, 1x1 stride 2 12.8 / 21.7 with tiles of 64).  Staged / 32 / 64, us: backprop-data of 4 x 64 -> 48
+    // at 40x40, 5x5 (400 tiles of 75 units) 10.0 / 12.1 / 6.8, of 224 -> 48 at 42x31 (287, 84 of 64: staged) the same; 3x3x3 48 -> 80 (390
+    // of 81) 11.6 / 15.1 / 7.8; 3x3, 176 -> 384 (468 of 99) 13.6 / 7.0 / 6.5.  2734 launches that the estimates were not fitted to take
+    // 16.2 ms so, 31.9 staged, 15.1 the best of the three; 1259 with operands from memory 8.2, 15.2 and 7.7.
+    const double us = tile == 2 ? two : one;
     const size_t tiles = (M + 31) / 32 * ((Cout + 31) / 32) * classes;
-    if ((tiles <= 256 && units >= 8) || (tiles <= 448 && units >= 32)) return tile;
-    // Beyond that where the two estimates say so by two fifths: of those 270 launches none is slower then than staged, and their sum
-    // is 5569 us staged, 4988 with the sizes above alone, 4754 so (4676 and four up to 23 % slower by one fifth).  Backprop-data
-    // 2 x 48 -> 256 at 40x39, 3x3 stride 2 35.4 -> 8.9; 784 tiles of 144 (18.4 / 19.5) stay staged, and so does all past the range of
-    // the fit (5220 of 124 36.5 / 96.7 / 65.0) and forward with strided reads, which fetch whole lines for half of them (13 x 1024 ->
-    // 384, 1x1 stride 2 12.8 / 21.7 with tiles of 64).
-    return tiles <= 3000 && !strided && (tile == 2 ? two : one) < 0.6 * staged_us ? tile : 0;
+    if ((tiles <= 256 && units >= 8) || (tiles <= 448 && units >= 32)) return staged_us == 0.0 || us < (tiles <= 256 ? 1.1 : 1.0) * staged_us ? tile : 0;
+    return tiles <= 3000 && !strided && us < (units >= 8 ? 0.8 : 0.6) * staged_us ? tile : 0;
 }
 
 bool few_plan(const FewNode &d, bool bwd, double staged_us, ConvFewParams *out)
@@ -297,7 +306,7 @@ bool few_plan(const FewNode &d, bool bwd, double staged_us, ConvFewParams *out)
     const size_t units = ntaps * (Cin / 16);
     if (units > (size_t)1 << 24) return false;
     const double mean = bwd ? (double)(wt_bytes / 2 / 16 / Cout) / q.classes : (double)units;
-    q.tile = few_rule(M, Cout, q.classes, (int)units, mean, staged_us, !bwd && d.stride[2] > 1);
+    q.tile = few_rule(M, Cout, Cin / 16, q.classes, (int)units, mean, staged_us, d.r3, bwd, !bwd && d.stride[2] > 1);
     if (q.tile == 0) return false;
     if (!out) return true;
     q.in_bytes = (uint32_t)in_bytes;
@@ -316,18 +325,19 @@ bool few_plan(const FewNode &d, bool bwd, double staged_us, ConvFewParams *out)
 
 }  // namespace
 
-// Expected times of the staged kernels on nodes of this range, fitted to the same launches: rounds of workgroups, each a chain of
-// stages of 16 input channels (times depth taps)
+// Expected times of the staged kernels on nodes of this range, back to back in a graph as few_us (2618 launches, nine tenths within
+// 15 %): rounds of workgroups, each a chain of stages of 16 input channels (times depth taps).  Strided backprop-data takes up to
+// twice as long, one class of pixels after the other; that is not in them.
 double few_strip_us(double workgroups, int stages, int taps, int nf)
 {
     const double rounds = workgroups <= 256 ? 1.0 : (double)(((long)workgroups + 255) / 256);
-    return 3.2 + rounds * (1.73 + stages * (0.067 + taps * (0.0337 * nf + 0.037)));
+    return 1.9 + rounds * (1.24 + stages * (0.243 + taps * (0.0263 * nf + 0.0289)));
 }
 
 double few_gemm1x1_us(size_t M, int Cin, int Cout)
 {
     const double tiles = (double)((M + 63) / 64) * ((Cout + 63) / 64);
-    return 4.0 + 0.16 * (tiles > 512 ? tiles / 512 : 1.0) * (Cin / 16);
+    return 3.0 + 0.171 * (tiles > 512 ? tiles / 512 : 1.0) * (Cin / 16);
 }
 
 bool conv_few_plan(const ngc_conv_desc *d, int op, int P, int Q, double staged_us, ConvFewParams *q)

@@ -62,3 +62,25 @@ def test_fp32_backprop_data_takes_the_kernel_that_is_expected_to_be_faster():
         assert ng.ngc_conv_kernel(node(*a), BWD) == "direct:gather", a
     for a in stream:
         assert ng.ngc_conv_kernel(node(*a), BWD) == "direct:stream", a
+
+
+def tile_of(d, monkeypatch):
+    """Tile of the kernel for few output tiles that backprop-data gets: the rows of channel sums of its bias gradient tell."""
+    ws = {}
+    for few in ("1", "2", None):
+        monkeypatch.setenv("NGC_FWD_FEW", few) if few else monkeypatch.delenv("NGC_FWD_FEW")
+        assert ng.ngc_conv_kernel(d, BWD).endswith(":few")
+        ws[few] = ng.ngc_conv_workspace_bytes(d, DB)
+    assert ws["1"] != ws["2"]
+    return 32 if ws[None] == ws["1"] else 64
+
+
+def test_nodes_with_few_output_tiles_take_what_is_expected_to_be_faster(monkeypatch):
+    """Many taps and more than one round of 32 x 32 tiles: those take up to 1.2 times as long as the strip kernel, 64 x 64 ones, where
+    there are enough of them, two thirds of its time.  One round or few taps: the small ones."""
+    for a in ((4, 64, 40, 40, 48, 5), (3, 192, 27, 25, 48, 5)):
+        assert tile_of(node(*a, dtype="bf16", xl=BLK), monkeypatch) == 64, a
+    for a in ((1, 256, 14, 14, 256, 3), (8, 208, 7, 7, 208, 1, 7), (1, 1024, 14, 14, 256, 1), (2, 288, 21, 30, 1968, 1, 1, 2)):
+        assert tile_of(node(*a, dtype="bf16", xl=BLK), monkeypatch) == 32, a
+    for a in ((1, 224, 42, 31, 48, 5), (1, 272, 32, 32, 48, 5)):
+        assert ng.ngc_conv_kernel(node(*a, dtype="bf16", xl=BLK), BWD) == "strip_bf16", a
