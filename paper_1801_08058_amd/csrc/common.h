@@ -502,7 +502,7 @@ struct WgradTapsPlan {
     WgradTapsParams p;
     int nt, nkb;               // taps per group, 16-channel blocks of k per workgroup
     size_t lds, ws;            // bytes of LDS, of the partials (0: one part, dw written directly)
-    double us, cycles;         // expected time; the cycle count the split was chosen by
+    double us, cycles;         // expected time; rank 2: the cycle count the split was chosen by
 };
 // fills in the split of out->p, whose shape fields are set; false: not for this kernel
 bool wgrad_taps_plan(WgradTapsPlan *out);

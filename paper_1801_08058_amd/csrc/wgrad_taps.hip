@@ -545,6 +545,24 @@ double wgrad_stage_cost(int nkb, int ncq, int nt, int dy_blocks, int x_blocks, i
 // a second launch; partials out and in
 double wgrad_parts_cost(int parts, size_t part_bytes) { return parts > 1 ? 6500.0 + 2.0 * parts * part_bytes / 1600.0 : 0.0; }
 
+// Expected time, to choose between this kernel and the others and between the splits of rank 3: the terms above (2400 cycles a us)
+// with the weights that fit 435 measured nodes of the window and video ranges, nine tenths of them within 8 %
+static double wgrad_taps_us(long rounds, long per, double stage, double fixed, size_t partial_bytes, size_t dw_elems, long wgs, long blocks)
+{
+    return 1.2 + (partial_bytes ? 2.8 : 0.0) + rounds * (1.2 + (1.67 * per * stage + 1.63 * fixed) / 2400.0) + 0.29e-6 * partial_bytes +
+           0.48e-6 * 4.0 * dw_elems + 1.8e-3 * wgs / 256.0 * per * blocks;
+}
+
+// whether the tiles of a part are kept on one XCD
+static bool wgrad_taps_xcd(long tiles, long parts) { return tiles > 1 && (parts % 8 == 0 || parts >= 64); }
+
+// Rounds of workgroups, one to a compute unit.  Rank 3 counts the fullest XCD where they are ordered by XCD: 84 parts of 3 tiles are 33
+// for its 32 compute units (3 x 32 -> 32, 21 x 17 x 43 25.1 us, 42 parts of 6 tiles 19.0).
+static long wgrad_taps_rounds(long tiles, long parts, bool r3)
+{
+    return r3 && wgrad_taps_xcd(tiles, parts) ? ((parts + 7) / 8 * tiles + 31) / 32 : (tiles * parts + 255) / 256;
+}
+
 bool wgrad_taps_plan(WgradTapsPlan *out)
 {
     const char *force = env_switch(SW_WGRAD_TAPS);        // tests / benchmarks only: 0 = never, nkb * 10000 + ncq * 1000 + parts
@@ -575,7 +593,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     const long pc = (long)(q.Q - 1) * q.sw + (long)(q.S - 1) * q.dil_w + 1;
     const int KB = q.KB, CB = q.CB, groups = q.T * q.gpt;
     const size_t dw_elems = (size_t)256 * KB * CB * taps;
-    double best = 0.0;
+    double best = 0.0, by_cycles = 0.0, by_cycles_us = 0.0;
     int b_nkb = 0, b_ncq = 0, b_sr = 0, b_g = 0, b_parts = 0, b_ring = 0;
     for (int ncq = 4; ncq >= 1; ncq >>= 1) {
         if (ncq > 1 && ncq / 2 >= CB) continue;
@@ -628,18 +646,27 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
                 const double stage = wgrad_stage_cost(nkb, ncq, nt, (int)bd, (int)bx, ring, &fixed);
                 const int units = nkb * nt;
                 const size_t part_bytes = (size_t)tiles * ncq * units * 1024;
-                // Large operands, parts whose workgroups lie on several XCDs: each fetches them for itself.  Rank 3 with a few tiles
-                // does not feel it, the depth taps of a part read the same slices at other times (64 -> 128, 8 x 16 x 56 x 56, 6
-                // tiles, 30 / 32 / 34 / 36 parts 220.8 / 206.5 / 198.5 / 190.3 us).
-                const double streamed = 0.5 * (bd * nkb + bx * ncq) * 1024.0 * total * tiles > 4e7 && !(q.r3 && tiles <= 8) ? 1.25 : 1.0;
+                // Rank 2, large operands, parts whose workgroups lie on several XCDs: each fetches them for itself.
+                const double streamed = 0.5 * (bd * nkb + bx * ncq) * 1024.0 * total * tiles > 4e7 ? 1.25 : 1.0;
                 auto consider = [&](long parts) {
                     if (parts < 1 || parts > total || parts > 1024) return;
                     if (parts > 1 && parts * part_bytes > ((size_t)NGC_STATIC_SCRATCH_BYTES)) return;
-                    const long wgs = tiles * parts, rounds = (wgs + 255) / 256;
+                    const long wgs = tiles * parts, rounds = wgrad_taps_rounds(tiles, parts, q.r3);
                     const long stages = (total + parts - 1) / parts;
+                    // Rank 3 by the expected time: the depth taps of a part read the same slices at other times, and parts in multiples
+                    // of 8 leave compute units idle.  64 -> 128, 8 x 16 x 56 x 56 206.6 us in cycles as rank 2 (32 parts), 200.8 without the
+                    // quarter, 190.2 by time (36); 152 drawn nodes take 0.92 of the time they take in cycles without the quarter up to 8
+                    // tiles: 90 are faster by 5 % and more, 7 slower, by 10 % at most.
                     const bool xcd = parts % 8 == 0 || parts >= 64 || tiles == 1;
-                    const double cost = rounds * (fixed + stages * stage * (xcd ? 1.0 : streamed)) +
-                                        wgrad_parts_cost((int)parts, part_bytes) + dw_elems * 4.0 / 1600.0;
+                    double cost = ((wgs + 255) / 256) * (fixed + stages * stage * (xcd ? 1.0 : streamed)) + wgrad_parts_cost((int)parts, part_bytes) + dw_elems * 4.0 / 1600.0;
+                    if (q.r3) {
+                        const double us = wgrad_taps_us(rounds, stages, stage, fixed, parts > 1 ? parts * part_bytes : 0, dw_elems, wgs, bx * ncq + bd * nkb);
+                        if (by_cycles == 0.0 || cost < by_cycles) {
+                            by_cycles = cost;
+                            by_cycles_us = us;
+                        }
+                        cost = us;
+                    }
                     if (best == 0.0 || cost < best) {
                         best = cost;
                         b_nkb = nkb; b_ncq = ncq; b_sr = sr; b_g = g; b_parts = (int)parts; b_ring = ring;
@@ -667,7 +694,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     q.nparts = (int16_t)b_parts;
     const long tiles = (long)q.ktiles * q.ctiles * groups;
     if (tiles * (b_parts + 7) >= (1 << 23)) return false;
-    q.xcd = tiles > 1 && (b_parts % 8 == 0 || b_parts >= 64);
+    q.xcd = wgrad_taps_xcd(tiles, b_parts);
     q.nrb = (int16_t)((q.P + b_sr - 1) / b_sr);
     q.nib = (q.N + b_g - 1) / b_g;                        // rank 3: these three per depth tap, in the kernel
     q.tq = q.nib * q.nrb / b_parts;
@@ -688,15 +715,16 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     out->lds = stages > red ? stages : red;
     if (out->lds > 160 * 1024) return false;
     out->ws = b_parts > 1 ? (size_t)b_parts * tiles * b_ncq * b_nkb * nt * 1024 : 0;
-    out->cycles = best;
-    // Expected time, to choose between this kernel and the others: the terms above (2400 cycles a us) with the weights that
-    // fit 435 measured nodes of the window and video ranges, nine tenths of them within 8 %
+    out->cycles = q.r3 ? 0.0 : best;
     double fixed;
-    const double stage = wgrad_stage_cost(b_nkb, b_ncq, nt, (int)bd, (int)bx, b_ring, &fixed) / 2400.0;
+    const double stage = wgrad_stage_cost(b_nkb, b_ncq, nt, (int)bd, (int)bx, b_ring, &fixed);
     const long total = (q.r3 ? (long)q.N * ((q.O + b_g - 1) / b_g) : (long)q.nib) * q.nrb, per = (total + b_parts - 1) / b_parts;
-    const long wgs = tiles * b_parts, rounds = (wgs + 255) / 256;
-    out->us = 1.2 + (b_parts > 1 ? 2.8 : 0.0) + rounds * (1.2 + 1.67 * per * stage + 1.63 * fixed / 2400.0) + 0.29e-6 * out->ws +
-              0.48e-6 * 4.0 * dw_elems + 1.8e-3 * wgs / 256.0 * per * (bx * b_ncq + bd * b_nkb);
+    const long wgs = tiles * b_parts, rounds = wgrad_taps_rounds(tiles, b_parts, q.r3);
+    out->us = wgrad_taps_us(rounds, per, stage, fixed, out->ws, dw_elems, wgs, bx * b_ncq + bd * b_nkb);
+    // Rank 3, against the per-tap GEMM: the smallest of many estimates is a low one, so a node that the split by cycles would leave to
+    // the GEMM has to be expected 8 % faster (1 x 80 -> 48, 8 x 22 x 52 /2, expected 12.3 / 13.4, takes 12.3 / 12.5; 40 nodes that change
+    // kernels without this margin take 0.76 to 1.07 of the GEMM's time).
+    if (q.r3) out->us = by_cycles_us < 1.09 * out->us ? by_cycles_us : 1.09 * out->us;
     return true;
 }
 

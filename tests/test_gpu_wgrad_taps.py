@@ -81,6 +81,8 @@ CASES3 = [
     (Attrs3(3, 16, 1, 8, 9, 16, 3, 2, 2, 1, 1, 1, 1, 1, 1, 1, 0, 0, 1, 1, 1), 4, (11001,)),            # one slice: two depth taps outside
     (Attrs3(2, 32, 1, 6, 8, 16, 1, 2, 3, 3, 1, 1, 1, 1, 1, 0, 0, 1, 2, 0, 1), 7, (11001,)),            # one slice each, padding behind only
     (Attrs3(2, 48, 7, 9, 12, 64, 3, 1, 1, 1, 2, 2, 1, 1, 1, 1, 0, 0, 1, 0, 0), 1, (11001, 42002, 44001)),   # one tap a pass
+    # many parts: no multiple of 8 and a multiple (then the tiles of a part on one XCD), 64 and more of any count
+    (Attrs3(6, 32, 12, 16, 20, 48, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), 9, (11009, 21013, 22016, 12065)),
 ]
 
 

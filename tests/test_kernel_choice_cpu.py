@@ -84,3 +84,20 @@ def test_nodes_with_few_output_tiles_take_what_is_expected_to_be_faster(monkeypa
         assert tile_of(node(*a, dtype="bf16", xl=BLK), monkeypatch) == 32, a
     for a in ((1, 224, 42, 31, 48, 5), (1, 272, 32, 32, 48, 5)):
         assert ng.ngc_conv_kernel(node(*a, dtype="bf16", xl=BLK), BWD) == "strip_bf16", a
+
+
+SPLITS = [
+    # n  c   d   h   w   k  t  r  s   bytes of partial sums, which tell the split; us so, and by a rule in the tiles' number
+    ((8, 64, 16, 56, 56, 128, 3, 3, 3), 31850496),       # 190.2, 206.6
+    ((6, 80, 28, 28, 22, 32, 3, 3, 3), 9289728),         # 38.8, 50.4
+    ((15, 112, 6, 16, 28, 96, 3, 3, 3), 26542080),       # 42.7, 54.2
+    ((2, 96, 8, 44, 33, 80, 2, 3, 3), 13934592),         # 26.3, 32.4
+    ((8, 192, 20, 30, 20, 96, 2, 3, 3), 27869184),       # 85.7, 103.5
+]
+
+
+def test_rank3_backprop_filters_split_positions_by_expected_time():
+    for a, parts_bytes in SPLITS:
+        d = node3(*a)
+        assert ng.ngc_conv3d_kernel(d, WGRAD) == "wgrad_gemm3_bf16:taps", a
+        assert ng.ngc_conv3d_workspace_bytes(d, WGRAD) == parts_bytes, a
