@@ -857,7 +857,7 @@ bool wgrad_gemm_plan_uncached(const ngc_conv_desc *d, int P, int Q, WgradGemmPar
     // the chunk count in multiples of 8, so only where that changes the workgroup count by at most a tenth.  Measured:
     // (3,1) window over 16 x 3136 rows, 128 -> 64: 73 -> 59 us; 3x3/2 128 -> 128 at 56x56: 33 -> 25 us (N = 32),
     // 47 -> 48 us (N = 128); small tensors and layers with 25-36 (tile, tap) pairs lose 3-40 %.
-    // NGC_WGG_XCD (tests / benchmarks only): 0 = never, 1 = every multi-tap layer.
+    // NGC_WGG_XCD (tests / benchmarks only): 0 = never, 1 = every node of several (tile, tap) pairs.
     if (d->r * d->s > 1 && !q.x_nchw && !q.dy_nchw) {
         const uint32_t xcd_slots = slots / 8;
         const uint32_t parts8 = 8 * (xcd_slots / tiles > 0 ? xcd_slots / tiles : 1);
@@ -884,14 +884,16 @@ bool wgrad_gemm_plan_uncached(const ngc_conv_desc *d, int P, int Q, WgradGemmPar
     // resident together (384 -> 384 at 28x28, 36 for 32 places 35.0 / 52.9, 320 -> 32 at 40x80, 65 for 64 37.1 / 60.4: fewer, longer
     // chunks for 128 x 128 tiles if they leave four fifths of the workgroups, else the other grid).  Two or three 128 x 128 tiles lose (256 -> 128 at 56x56, N = 128 69.4 / 73.0),
     // small tensors 3 %.
-    if (d->r * d->s == 1 && tiles > 1 && (tiles >= 4 || q.wk * q.wc < 4) && x_bytes + dy_bytes >= ((size_t)24 << 20)) {
+    if (d->r * d->s == 1 && tiles > 1) {
         const char *fx = env_switch(SW_WGG_XCD);
         const size_t lds = (size_t)2 * 4 * (q.wk + q.wc) * (q.sp * 32 + 128);
         const uint32_t places = lds * 2 <= LDS_LIMIT ? 64 : 32, most = 8 * (places / tiles);         // of an XCD; chunks that fit
         uint32_t ch = chunk;
         if (q.wk * q.wc == 4 && (uint32_t)q.nparts > most && most * 5 >= (uint32_t)q.nparts * 4) ch = ((q.M + most - 1) / most + 127) / 128 * 128;
         const uint32_t n = (q.M + ch - 1) / ch;
-        if (n <= most && (n >= 24 || (n >= 16 && n % 8 == 0)) && !(fx && atoi(fx) == 0)) {
+        bool on = (tiles >= 4 || q.wk * q.wc < 4) && x_bytes + dy_bytes >= ((size_t)24 << 20) && n <= most && (n >= 24 || (n >= 16 && n % 8 == 0));
+        if (fx) on = atoi(fx) == 1;
+        if (on) {
             q.xcd_order = 1;
             q.chunk = ch;
             q.nparts = (int)n;

@@ -761,6 +761,34 @@ def test_per_tap_backprop_filters_xcd_ordered_grid(a, monkeypatch):
     assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
 
 
+@pytest.mark.parametrize("tile", ["11", "12", "21", "22"])
+@pytest.mark.parametrize("xl,yl", [(BLK, BLK), (NCHW, BLK), (BLK, NCHW), (NCHW, NCHW)])
+def test_one_tap_backprop_filters_xcd_ordered_grid(tile, xl, yl, monkeypatch):
+    """What large one-tap layers get by default, forced on small ones: the tiles of a position chunk on one XCD.  11 chunks, the last
+    of 16 positions, ragged last tiles in both directions."""
+    monkeypatch.setenv("NGC_WGG_XCD", "1")
+    monkeypatch.setenv("NGC_WGG_TILE", tile)
+    a = Attrs(9, 160, 9, 16, 208, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0)
+    x, w, b, dy = _tensors(a, "bf16", 9150)
+    run = Run(a, "bf16", xl, yl, False)
+    dw = run.bwd_filters(x, dy)
+    assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16"
+    assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
+
+
+@pytest.mark.parametrize("a", [Attrs(4, 384, 30, 30, 384, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0),       # 29 chunks, more than fit: 15 longer ones
+                               Attrs(5, 256, 19, 17, 272, 1, 1, 2, 2, 1, 1, 0, 0, 0, 0)])      # stride 2
+def test_one_tap_backprop_filters_xcd_ordered_grid_chunks(a, monkeypatch):
+    ws = []
+    for order in ("0", "1"):
+        monkeypatch.setenv("NGC_WGG_XCD", order)
+        x, w, b, dy = _tensors(a, "bf16", 9160 + a.c)
+        run = Run(a, "bf16", BLK, BLK, False)
+        assert oracle.max_normalised_error(run.bwd_filters(x, dy), oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
+        ws.append(ng.ngc_conv_workspace_bytes(run.last_desc, ng.NGC_OP_BWD_FILTERS))
+    assert (ws[1] < ws[0]) == (a.c == 384)
+
+
 def test_strip_two_dimensional_grid_switch(monkeypatch):
     """NGC_STRIP_XCD=0: the strip kernel's launches with several output-channel tiles on the two-dimensional grid
     (default: one-dimensional, the tiles of a strip on one XCD)."""

@@ -101,3 +101,14 @@ def test_rank3_backprop_filters_split_positions_by_expected_time():
         d = node3(*a)
         assert ng.ngc_conv3d_kernel(d, WGRAD) == "wgrad_gemm3_bf16:taps", a
         assert ng.ngc_conv3d_workspace_bytes(d, WGRAD) == parts_bytes, a
+
+
+def test_one_tap_backprop_filters_lengthen_chunks_that_do_not_fit_an_xcd(monkeypatch):
+    """384 -> 384 at 28x28: 9 tiles of 128 x 128, of which an XCD holds three chunks' worth: 24 chunks instead of 28.  512 -> 512: 31 chunks of 32."""
+    for c, ordered, other in ((384, 24 * 9 << 16, 28 * 9 << 16), (512, 31 * 16 << 16, 31 * 16 << 16)):
+        d = node(64, c, 28, 28, c, 1, dtype="bf16", xl=BLK)
+        assert ng.ngc_conv_kernel(d, WGRAD) == "wgrad_gemm_bf16"
+        assert ng.ngc_conv_workspace_bytes(d, WGRAD) == ordered
+        monkeypatch.setenv("NGC_WGG_XCD", "0")
+        assert ng.ngc_conv_workspace_bytes(d, WGRAD) == other
+        monkeypatch.delenv("NGC_WGG_XCD")
