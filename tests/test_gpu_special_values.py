@@ -11,30 +11,51 @@ from test_gpu_parity import _tensors
 pytestmark = pytest.mark.gpu
 NCHW, BLK = ng.NGC_NCHW, ng.NGC_NCHW16C
 
+# the kernels of these nodes: tiles of the gather GEMM, operands straight to registers with either share of the work, the default
+TILES = [1, 2, 3, "positions", "slices", None]
+
+
+def _force(monkeypatch, tile, wgrad=None):
+    if tile in ("positions", "slices"):
+        monkeypatch.setenv("NGC_STREAM", "1" if tile == "positions" else "2")
+    elif tile:
+        monkeypatch.setenv("NGC_GATHER_TILE", str(tile))
+    if wgrad and wgrad < 1000:
+        monkeypatch.setenv("NGC_WGRAD_STREAM", str(wgrad))
+    elif wgrad:
+        monkeypatch.setenv("NGC_GATHER_WGRAD", str(wgrad))
+
+
+def _runs(run, op, tile):
+    name = ng.ngc_conv_kernel(run.last_desc, op)
+    assert name in ("direct:stream", "direct:gather") if tile is None else name == ("direct:stream" if isinstance(tile, str) else "direct:gather")
+
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("tile", [1, 2, 3])
+@pytest.mark.parametrize("tile", TILES)
 def test_infinite_filter_leaves_the_padding_lanes_zero(dtype, tile, monkeypatch):
     """Reduction indices past the end meet output channels past the end: both read zero, not filter element 0."""
-    monkeypatch.setenv("NGC_GATHER_TILE", str(tile))
+    _force(monkeypatch, tile)
     a = Attrs(1, 5, 6, 6, 20, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1)
     x, w, b, dy = _tensors(a, dtype, 15000)
     w[0, 0, 0, 0] = np.inf
     run = Run(a, dtype, BLK, BLK, False)
     bits = np.uint16 if dtype == "bf16" else np.uint32
     y = run.fwd(x, w, bias=b, relu=False)
+    _runs(run, ng.NGC_OP_FWD, tile)
     assert np.all(host(run.last_raw, bits).reshape(1, 2, 6, 6, 16)[:, 1, :, :, 4:] == 0)
     w0 = w.copy()
     w0[0] = 0
     assert oracle.max_normalised_error(y[:, 1:], oracle.conv_fwd(a, x, w0, bias=b)[:, 1:]) <= bound(dtype, "act")
     run.bwd_data(dy, w)
+    _runs(run, ng.NGC_OP_BWD_DATA, tile)
     assert np.all(host(run.last_raw, bits).reshape(1, 1, 6, 6, 16)[..., 5:] == 0)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("tile", [1, 2, 3])
+@pytest.mark.parametrize("tile", TILES)
 def test_infinite_input_leaves_the_padding_lanes_zero(dtype, tile, monkeypatch):
-    monkeypatch.setenv("NGC_GATHER_TILE", str(tile))
+    _force(monkeypatch, tile)
     a = Attrs(1, 5, 6, 6, 20, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1)
     x, w, b, dy = _tensors(a, dtype, 15001)
     x[0, 2, 3, 3] = np.inf
@@ -44,6 +65,7 @@ def test_infinite_input_leaves_the_padding_lanes_zero(dtype, tile, monkeypatch):
     run.fwd(x, w, bias=b, relu=False)
     assert np.all(host(run.last_raw, bits).reshape(1, 2, 6, 6, 16)[:, 1, :, :, 4:] == 0)
     run.bwd_data(dy, w)
+    _runs(run, ng.NGC_OP_BWD_DATA, tile)
     assert np.all(host(run.last_raw, bits).reshape(1, 1, 6, 6, 16)[..., 5:] == 0)
 
 
@@ -62,15 +84,18 @@ PADDED = [
     (Attrs(1, 5, 12, 10, 17, 5, 5, 2, 1, 1, 1, 2, 2, 2, 2), "bf16", BLK, NCHW),
     (Attrs(3, 9, 8, 8, 40, 3, 3, 1, 1, 2, 2, 2, 2, 2, 2), "bf16", NCHW, NCHW),
     (Attrs(2, 12, 6, 6, 12, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1), "f32", NCHW, NCHW),       # one tap, a frame of padding only
+    (Attrs(2, 9, 11, 13, 37, 3, 3, 2, 2, 1, 1, 1, 1, 1, 1), "bf16", NCHW, NCHW),     # strided columns
+    (Attrs(2, 7, 9, 10, 34, 5, 5, 1, 1, 1, 1, 2, 2, 2, 2), "bf16", NCHW, NCHW),      # units two elements in front of the tensor
+    (Attrs(1, 5, 9, 5, 8, 3, 9, 1, 1, 1, 1, 1, 8, 1, 8), "f32", NCHW, NCHW),         # more padding than a unit
+    (Attrs(1, 11, 7, 9, 40, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), "bf16", BLK, BLK),
 ]
 
 
 @pytest.mark.parametrize("case", range(len(PADDED)))
-@pytest.mark.parametrize("tile,wgrad", [(1, 1001), (2, 2001), (3, 3003)])
+@pytest.mark.parametrize("tile,wgrad", [(1, 1001), (2, 2001), (3, 3003), ("positions", 1), ("slices", 3), (None, None)])
 def test_infinities_meet_no_padding(case, tile, wgrad, monkeypatch):
     """A tap in the padding is no part of the sum: an infinite filter element or gradient does not turn it into NaN."""
-    monkeypatch.setenv("NGC_GATHER_TILE", str(tile))
-    monkeypatch.setenv("NGC_GATHER_WGRAD", str(wgrad))
+    _force(monkeypatch, tile, wgrad)
     a, dtype, xl, yl = PADDED[case]
     x, w, b, dy = _tensors(a, dtype, 15100 + case)
     run = Run(a, dtype, xl, yl, False)
@@ -78,11 +103,31 @@ def test_infinities_meet_no_padding(case, tile, wgrad, monkeypatch):
     wi[a.k // 2, a.c // 2, 0, 0] = np.inf
     wi[2, 1, a.r - 1, a.s - 1] = -np.inf
     _same(run.fwd(x, wi, bias=b), oracle.conv_fwd(a, x, wi, bias=b), bound(dtype, "act"))
+    _runs(run, ng.NGC_OP_FWD, tile)
     _same(run.bwd_data(dy, wi), oracle.conv_bwd_data_gather(a, dy, wi), bound(dtype, "act"))
+    _runs(run, ng.NGC_OP_BWD_DATA, tile)
     di = dy.copy()
     di[0, a.k // 2, 0, 0] = np.inf
     di[a.n - 1, 1, -1, -1] = np.nan
     _same(run.bwd_filters(x, di), oracle.conv_bwd_filters(a, x, di), bound(dtype, "dw"))
+    _runs(run, ng.NGC_OP_BWD_FILTERS, tile if xl == yl == NCHW else 1 if tile else None)   # blocked tensors: the gather GEMM
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tile", TILES)
+def test_infinities_of_the_next_filter_row(dtype, tile, monkeypatch):
+    """Filter rows of 63 elements, no multiple of a step: an infinity or NaN at the start of a row is no part of the row before."""
+    _force(monkeypatch, tile)
+    a = Attrs(2, 7, 6, 9, 35, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1)
+    x, w, b, dy = _tensors(a, dtype, 15150)
+    w[1::4, 0, 0, 0] = np.inf
+    w[3::4, 0, 0, 1] = np.nan
+    for xl, yl in ((NCHW, NCHW), (BLK, NCHW)):
+        run = Run(a, dtype, xl, yl, False)
+        got, ref = run.fwd(x, w, bias=b), oracle.conv_fwd(a, x, w, bias=b)
+        _runs(run, ng.NGC_OP_FWD, tile)
+        _same(got, ref, bound(dtype, "act"))
+        assert np.isfinite(got[:, 0::2]).all()
 
 
 TAPS = [
