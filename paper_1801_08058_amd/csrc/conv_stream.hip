@@ -10,11 +10,11 @@
 // behind the index table and in front of the sum over the slices.
 //
 // What bounds it: small nodes launch, table and one or two batches of loads; large ones the L1, which serves a load whose lanes
-// lie in different lines (the filter operand: 32 rows) a line at a time: fp32 3x3 64 -> 96, 8 x 45 x 37, 19 accesses a load, one a
-// cycle, with the matrix pipes busy half of the time.  Two fragments of positions a wave (half the filter loads) measured level,
-// eight slices slower.  Gather GEMM / now, forward and backprop-data, us: that layer 34.5 / 23.8 and 30.7 / 31.4; fp32 16 -> 32,
-// 2 x 16 x 16 6.8 / 5.2 and 8.9 / 6.4; bf16 40 -> 72, 8 x 28 x 28 9.0 / 8.9 and 16.6 / 11.6; bf16 190 -> 12, 4 x 23 x 15 /2 25.3 / 12.9 and
-// 7.3 / 5.0; 1x1 fp32 128 -> 83, 7 x 47 x 53 16.8 / 10.2 and 15.3 / 11.8.
+// lie in different lines (the filter operand: 32 rows) a line at a time: fp32 3x3 64 -> 96, 8 x 45 x 37, 19.7 accesses a load, 0.87 a
+// cycle that a compute unit is busy, the matrix pipes busy in half of those cycles (0.4 of the launch).  Two fragments of positions a
+// wave (half the filter loads) measured level, eight slices slower.  Gather GEMM / here, forward and backprop-data, us: that layer
+// 34.5 / 23.8 and 30.8 / 33.0 (which stays there); fp32 16 -> 32, 2 x 16 x 16 6.8 / 5.2 and 8.9 / 6.4; bf16 40 -> 72, 8 x 28 x 28 9.0 / 8.9 and
+// 16.6 / 11.6; bf16 190 -> 12, 4 x 23 x 15 /2 25.3 / 12.9 and 7.3 / 5.0; 1x1 fp32 128 -> 83, 7 x 47 x 53 16.8 / 10.2 and 15.3 / 11.8.
 //
 // Where the elements of an index lie is worked out once per workgroup into a table in LDS, {input offset, tap} and for
 // backprop-data the filter offset; a lane adds its pixel and masks taps in the padding with one bit per tap.

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void layout_generic(const E *__restrict__ src,
 // backprop-data form), so one thread per destination element reads 2 bytes of a different line per lane, and the tile
 // below is what keeps the traffic at one read and one write.  A workgroup reads the filters of 16 lanes (the blocked axis)
 // x G rows (the other channel axis) as runs of whole 16-byte pieces, then writes, tap by tap, G runs of 32 bytes.
-// Bound: launch and load latency below a few MB, then HBM.  512 x 512 x 3 x 3 (4.7 MB): a thread per element 8.1 us, tiles 4.2 us.
+// Bound: launch and load latency below a few MB, then HBM.  512 x 512 x 3 x 3 (4.7 MB): a thread per element 8.1 us, tiles 5.2 us.
 // FWD: lanes = c, rows = k, source run of a row = 16 R S elements; else lanes = k, rows = c, run of a lane = G R S.
 template <bool FWD>
 __global__ __launch_bounds__(256) void filter_tiles_b16(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int K, int C,

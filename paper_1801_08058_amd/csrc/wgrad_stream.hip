@@ -227,9 +227,10 @@ static bool stream_wgrad_plan(const ngc_conv_desc &d, int P, int Q, StreamWgradP
     const size_t CRS = (size_t)d.c * d.r * d.s, tiles = (size_t)((d.k + 31) / 32) * ((CRS + 31) / 32);
     pl->units = (uint32_t)((size_t)d.n * pl->P * ((pl->Q + U - 1) / U));
     if (tiles > 65535) return false;
-    // Parts of the positions by expected time, fitted to 23 drawn nodes in 1 to 64 parts each (within 7 % fp32, 17 % bf16): fixed
-    // part, steps of a wave, tile-steps per compute unit; a second launch to add up the parts and its bytes.  The choice costs
-    // 4 % over the best count on average, 24 % at most.
+    // Parts of the positions by expected time, fitted to 23 drawn nodes in 1 to 64 parts each (within 7 % fp32, 17 % bf16): steps of a
+    // wave, a second launch to add up the parts and its bytes.  Over 297 others the choice costs 4 % over the best count of 1 to 128 on
+    // average, a sixth of them 10 % and more, 43 % at most.  A term in the workgroups per compute unit fitted to those halves that, but
+    // 400 further nodes take 0.997 of the time with it, three of them 1.12 to 1.2.
     const bool f32 = d.dtype == NGC_F32;
     const size_t most = pl->units / 16 ? pl->units / 16 : 1, cap = ((size_t)16 << 20) / ((d.k * CRS + 15) / 16 * 64);
     double best = 0;

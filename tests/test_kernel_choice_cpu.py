@@ -112,3 +112,27 @@ def test_one_tap_backprop_filters_lengthen_chunks_that_do_not_fit_an_xcd(monkeyp
         monkeypatch.setenv("NGC_WGG_XCD", "0")
         assert ng.ngc_conv_workspace_bytes(d, WGRAD) == other
         monkeypatch.delenv("NGC_WGG_XCD")
+
+
+LIMITS = [
+    # n  c  h   w   k  r  stride, dtype, layout, op; us on the gather GEMM and straight to registers
+    ((26, 126, 41, 22, 67, 5), 2, "f32", NCHW, BWD, 49.4, 64.7),
+    ((10, 8, 29, 9, 152, 5), 2, "f32", NCHW, BWD, 25.1, 13.0),
+    ((4, 90, 42, 19, 143, 5), 1, "f32", NCHW, FWD, 78.6, 31.6),
+    ((31, 59, 26, 19, 65, 5), 2, "f32", NCHW, FWD, 56.8, 23.0),
+    ((32, 216, 49, 8, 148, 3), 1, "bf16", NCHW, FWD, 60.1, 83.7),
+    ((2, 233, 12, 52, 212, 3), 1, "bf16", NCHW, FWD, 50.2, 21.6),
+    ((23, 43, 36, 33, 91, 3), 1, "bf16", NCHW, BWD, 26.9, 37.3),
+    ((4, 6, 19, 35, 166, 3), 1, "bf16", NCHW, BWD, 19.2, 12.1),
+    ((14, 80, 59, 17, 50, 3), 1, "bf16", BLK, FWD, 24.5, 48.1),
+    ((4, 108, 10, 18, 74, 3), 2, "bf16", BLK, FWD, 22.1, 12.6),
+    ((16, 166, 14, 45, 158, 3), 1, "bf16", BLK, BWD, 107.0, 197.9),
+    ((3, 14, 21, 7, 232, 3), 2, "bf16", BLK, BWD, 18.1, 13.0),
+    ((4, 130, 56, 35, 219, 1), 1, "bf16", NCHW, WGRAD, 11.1, 13.4),      # 128 channels or more on both sides
+    ((22, 155, 24, 22, 90, 1), 1, "bf16", NCHW, WGRAD, 10.0, 9.5),
+]
+
+
+def test_large_nodes_off_the_blocked_kernels_keep_the_gather_gemm():
+    for a, stride, dtype, layout, op, gather, stream in LIMITS:
+        assert ng.ngc_conv_kernel(node(*a, stride=stride, dtype=dtype, xl=layout), op) == ("direct:gather" if gather < stream else "direct:stream"), a
