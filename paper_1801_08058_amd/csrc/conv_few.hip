@@ -215,19 +215,21 @@ struct FewNode {
 // each), a start of its own, the units of a wave and the taps it walks past (every wave counts through all of them, at more cost with
 // a depth axis and for the classes of backprop-data), at least one round of the class with most taps; up to 64 units also the
 // operands' bytes through the L2s, at the share of them that the workgroups reach.  Fitted to 3245 launches of up to 3000 tiles, back
-// to back in a graph: four fifths of them within 20 % (32 x 32 tiles) and 12 % (64 x 64).
+// to back in a graph: four fifths of them within 20 % (32 x 32 tiles) and 12 % (64 x 64).  Small tiles over the classes of rank 3 take
+// 0.025 a unit more (303 launches: the choice of the tile costs 0.9 % with it, 4 % without, 1.7 times the better tile at worst).
 double few_us(int tl, size_t M, int Cout, int CB, int classes, int units, double mean_units, bool r3, bool bwd)
 {
     const double tiles = (double)((M + 32 * tl - 1) / (32 * tl)) * ((Cout + 32 * tl - 1) / (32 * tl)) * classes, rounds = ceil(tiles / 256);
     const double walk = mean_units / CB, longest = (double)units / CB;
+    const double classes3 = tl == 1 && r3 && classes > 1 ? 0.025 * (rounds * mean_units > units ? rounds * mean_units : units) : 0.0;
     if (tl == 1 && units <= 64) {
         const double tap = 0.021 + 0.035 * r3 + 0.038 * bwd, share = tiles < 256 ? (tiles < 5 ? 0.02 : tiles / 256) : 1.0;
-        return 1.77 + ceil(tiles / 512) * 0.68 + tap * (rounds * walk > longest ? rounds * walk : longest) + 65e-6 * tiles * mean_units / share;
+        return 1.77 + ceil(tiles / 512) * 0.68 + tap * (rounds * walk > longest ? rounds * walk : longest) + 65e-6 * tiles * mean_units / share + classes3;
     }
     const double wg = tl == 2 ? 2.43 : 1.67, unit = tl == 2 ? 0.242 / 8 : 0.212 / 16;
     const double tap = tl == 2 ? 0.014 + 0.052 * r3 + 0.017 * bwd : 0.026 + 0.079 * r3 + 0.063 * bwd;
     const double all = rounds * (wg + unit * mean_units + tap * walk), one = wg + unit * units + tap * longest;
-    return (tl == 2 ? 0.89 : 1.45) + (all > one ? all : one);
+    return (tl == 2 ? 0.89 : 1.45) + (all > one ? all : one) + classes3;
 }
 
 // The tile (fragments per axis) of a node, 0: the staged kernels, which take staged_us (0: no estimate; below: already decided
