@@ -252,8 +252,8 @@ int few_rule(size_t M, int Cout, int CB, int classes, int units, double mean_uni
     // and not for more than 3000 tiles (5220 of 124 units 36.5 / 96.7 / 65.0) nor forward with strided reads, which fetch whole lines
     // for half of them (13 x 1024 -> 384, 1x1 stride 2 12.8 / 21.7 with tiles of 64).  Staged / 32 / 64, us: backprop-data of 4 x 64 -> 48
     // at 40x40, 5x5 (400 tiles of 75 units) 10.0 / 12.1 / 6.8, of 224 -> 48 at 42x31 (287, 84 of 64: staged) the same; 3x3x3 48 -> 80 (390
-    // of 81) 11.6 / 15.1 / 7.8; 3x3, 176 -> 384 (468 of 99) 13.6 / 7.0 / 6.5.  2734 launches that the estimates were not fitted to take
-    // 16.2 ms so, 31.9 staged, 15.1 the best of the three; 1259 with operands from memory 8.2, 15.2 and 7.7.
+    // of 81) 11.6 / 15.1 / 7.8; 3x3, 176 -> 384 (468 of 99) 13.6 / 7.0 / 6.5.  2733 launches that the estimates were not fitted to take
+    // 16.0 ms so, 31.5 staged, 15.0 the best of the three; 1269 with operands from memory 8.1, 15.5 and 7.5.
     const double us = tile == 2 ? two : one;
     const size_t tiles = (M + 31) / 32 * ((Cout + 31) / 32) * classes;
     if ((tiles <= 256 && units >= 8) || (tiles <= 448 && units >= 32)) return staged_us == 0.0 || us < (tiles <= 256 ? 1.1 : 1.0) * staged_us ? tile : 0;
