@@ -12,9 +12,11 @@ constexpr int LT_PITCH = LT_PIX + 2; // LDS row pitch in elements (odd dword cou
 
 // ---- NCHW -> blocked, 2-byte elements.  grid = (ceil(HW/256), CB, N), block = 256.
 // V = pixels per global read (1, 2, 4 or 8), chosen by the host from the alignment of HW.
+// stream: the copy is written past the memory-side cache.  The next kernel reads it, so only copies that would not stay
+// there are (launch_layout_convert).
 template <int V>
 __global__ __launch_bounds__(256) void nchw_to_blocked16_b16(const uint16_t *__restrict__ src,
-                                                             uint16_t *__restrict__ dst, int C, int HW)
+                                                             uint16_t *__restrict__ dst, int C, int HW, int stream)
 {
     __shared__ __align__(16) uint16_t tile[16 * LT_PITCH];
     const int tid = threadIdx.x;
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(256) void nchw_to_blocked16_b16(const uint16_t *__r
                 w[e] = lo | (hi << 16);
             }
             uint16_t *g = dst + (((size_t)n * CB + cb) * HW + px0 + px) * 16 + half * 8;
-            store16_result(g, make_uint4(w[0], w[1], w[2], w[3]), true);
+            store16_result(g, make_uint4(w[0], w[1], w[2], w[3]), stream != 0);
         }
     }
 }
@@ -271,10 +273,16 @@ hipError_t launch_layout_convert(int elem_bytes, int n, int c, int h, int w, con
         uint16_t *d = static_cast<uint16_t *>(dst);
         const int v = (HW % 8 == 0) ? 8 : (HW % 4 == 0) ? 4 : (HW % 2 == 0) ? 2 : 1;
         if (src_layout == NGC_NCHW) {
-            if (v == 8) NGC_LAUNCH(nchw_to_blocked16_b16<8>, grid, block, 0, st, s, d, c, HW);
-            else if (v == 4) NGC_LAUNCH(nchw_to_blocked16_b16<4>, grid, block, 0, st, s, d, c, HW);
-            else if (v == 2) NGC_LAUNCH(nchw_to_blocked16_b16<2>, grid, block, 0, st, s, d, c, HW);
-            else NGC_LAUNCH(nchw_to_blocked16_b16<1>, grid, block, 0, st, s, d, c, HW);
+            // Ordinary stores leave the copy in the memory-side cache (256 MB) for the kernel that reads it, streaming ones save
+            // the conversion a tenth.  Streaming / ordinary, us, conversion alone and with a read of the copy behind it: 26 MB
+            // 10.1 / 11.8 and 28.5 / 27.9, 103 MB 34.7 / 36.9 and 68.1 / 64.4, 257 MB 83.7 / 86.0 and 149.5 / 149.0, 411 MB
+            // 134.6 / 140.0 and 234.1 / 239.2.  256 channels at 56x56, 64 images, with the three calls of a 1x1 layer of 64
+            // channels behind it 118.9 / 110.9.
+            const int stream = (size_t)n * CB * HW * 32 > ((size_t)240 << 20);
+            if (v == 8) NGC_LAUNCH(nchw_to_blocked16_b16<8>, grid, block, 0, st, s, d, c, HW, stream);
+            else if (v == 4) NGC_LAUNCH(nchw_to_blocked16_b16<4>, grid, block, 0, st, s, d, c, HW, stream);
+            else if (v == 2) NGC_LAUNCH(nchw_to_blocked16_b16<2>, grid, block, 0, st, s, d, c, HW, stream);
+            else NGC_LAUNCH(nchw_to_blocked16_b16<1>, grid, block, 0, st, s, d, c, HW, stream);
         } else {
             if (v == 8) NGC_LAUNCH(blocked16_to_nchw_b16<8>, grid, block, 0, st, s, d, c, HW);
             else if (v == 4) NGC_LAUNCH(blocked16_to_nchw_b16<4>, grid, block, 0, st, s, d, c, HW);

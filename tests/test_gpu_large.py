@@ -14,7 +14,7 @@ from oracle import Attrs
 from gpu_util import bound, dev, host, stream
 
 pytestmark = pytest.mark.gpu
-BLK = ng.NGC_NCHW16C
+NCHW, BLK = ng.NGC_NCHW, ng.NGC_NCHW16C
 PERIOD, REPS = 4, 17
 
 
@@ -144,3 +144,12 @@ def test_softmax_rows_past_a_grid():
     want = np.full(cols, oracle.f32_to_bf16_bits_rne(np.array([1.0 / cols], dtype=np.float32))[0], dtype=np.uint16)
     for row in (0, 1, rows // 2, rows - 257, rows - 256, rows - 255, rows - 1):
         assert np.array_equal(host(t[row * cols : (row + 1) * cols].clone(), np.uint16), want), row
+
+
+@pytest.mark.parametrize("images", [240, 241])                    # 16 x 256 x 128: 1 MiB an image; past 240 MiB the copy is streamed
+def test_layout_convert_either_side_of_the_streaming_limit(images):
+    gen = torch.Generator(device="cuda").manual_seed(images)
+    x = torch.randint(-32768, 32768, (images, 16, 256, 128), generator=gen, device="cuda", dtype=torch.int16)
+    got = torch.empty(images, 1, 256, 128, 16, device="cuda", dtype=torch.int16)
+    ng.ngc_layout_convert(ng.NGC_BF16, images, 16, 256, 128, x, NCHW, got, BLK, stream())
+    assert torch.equal(got[:, 0], x.permute(0, 2, 3, 1))
