@@ -53,7 +53,8 @@ constexpr unsigned G1_OOB = 0x80000000u;
 // DB (blocked result only): every MFMA wave also writes the per-channel sums over its positions of the values
 // it stored (fp32, fixed order) to row (p.dbp_row0 + m-tile) * WM + wm of p.dbp: partials of a bias gradient
 // of the result.
-template <int WM, int WN, int NS, int KB, int NL, int FA, bool XN, bool YN, bool DB = false>
+// SIB (strided backprop-data, 2 x 2 pixels per position): see SibLanes.
+template <int WM, int WN, int NS, int KB, int NL, int FA, bool XN, bool YN, bool DB, bool SIB>
 __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const Gemm1x1Params p)
 {
     preload_kernargs(p);
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const G
             wg_barrier_nofence();                      // stage s visible to all; buffer of stage s-1 is free
             if (s + NS - 1 < nsteps) issue_loads(s + NS - 1, (s + NS - 1) % NS);
         }
-        if constexpr (YN) wg_barrier_nofence();        // the ring becomes the staging area of the stores
+        if constexpr (YN || SIB) wg_barrier_nofence(); // the ring becomes the staging area of the stores
         return;
     }
 
@@ -276,9 +277,11 @@ __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const G
     // ---- epilogue: ReLU (bias is in the accumulators), one RNE rounding, lane-pair exchange, 16-byte stores
     const int CBout = p.Cout >> 4;
     const bool dense_out = p.os_h == 1 && p.os_w == 1;     // every pixel written: whole cache lines
-    const bool fast = !DB && p.out_bytes != 0 && p.mask == nullptr && !p.zero_sib;
+    const bool fast = !DB && !SIB && p.out_bytes != 0 && p.mask == nullptr && !p.zero_sib;
     const bool relu_b = p.relu != 0;
     const __amdgpu_buffer_rsrc_t rs_out = __builtin_amdgcn_make_buffer_rsrc((void *)p.out, 0, (int)p.out_bytes, 0x00020000);
+    unsigned char *const mine = smem + wave * 1024;       // SIB: a 32-position block of results
+    if constexpr (SIB) wg_barrier_nofence();              // every wave is done with the ring
     float csum[DB ? FA : 1][2][8];                        // DB: channel sums of this lane's stored values
 #pragma unroll
     for (int a = 0; a < (DB ? FA : 1); ++a)
@@ -319,6 +322,16 @@ __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const G
                 }
             continue;
         }
+        SibLanes sib;
+        if constexpr (SIB) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t ms = m0 + (uint32_t)(wm * 64 + b * 32 + 16 * u + (lane >> 2));
+                const uint32_t mu = ms < p.M ? ms : 0;
+                const uint32_t ns = fd_div(mu, p.div_pq), rs = mu - ns * p.div_pq.d, is = fd_div(rs, p.div_q), js = rs - is * p.div_q.d;
+                sib.place(u, lane, ms < p.M, (unsigned)((int)ns * CBout * HWout + 2 * (int)is * p.Wout + 2 * (int)js) * 32u, 2 * (int)is, 2 * (int)js, p.Hout, p.Wout);
+            }
+        }
 #pragma unroll
         for (int a = 0; a < FA; ++a) {
             const int co_base = n0 + wn * 32 * FA + a * 32;
@@ -334,8 +347,8 @@ __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const G
                 if (ok && (co_base >> 4) + h < CBout) {
                     const size_t blk = pix + (size_t)((co_base >> 4) + h) * HWout;
                     if (p.mask) o = relu_keep8(o, *reinterpret_cast<const uint4 *>(p.mask + blk * 16 + lg * 8));
-                    store16_result(p.out + blk * 16 + lg * 8, o, dense_out);
-                    if (p.zero_sib) {
+                    if (!SIB) store16_result(p.out + blk * 16 + lg * 8, o, dense_out);
+                    if (!SIB && p.zero_sib) {
                         // strided backprop-data whose one class of pixels starts at (0, 0): the pixels of the block
                         // that no tap reaches are zero, written here instead of by a fill pass over the whole dx
                         for (int zh = 0; zh < p.os_h; ++zh)
@@ -352,6 +365,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const G
                         }
                     }
                 }
+                if constexpr (SIB) sib.store(mine, lane, o, rs_out, (co_base >> 4) + h < CBout, (unsigned)(((co_base >> 4) + h) * HWout) * 32u);
             }
         }
     }
@@ -387,12 +401,12 @@ hipError_t launch_zero_fill(void *dst, size_t bytes, hipStream_t st)
     return ngc::launch_result();
 }
 
-template <int WM, int WN, int NS, int KB, int NL, int FA, bool XN, bool YN, bool DB = false>
+template <int WM, int WN, int NS, int KB, int NL, int FA, bool XN, bool YN, bool DB = false, bool SIB = false>
 static hipError_t launch_gemm1x1_l(const Gemm1x1Params &p, hipStream_t st)
 {
     static LdsLimitOnce lds_limit;                  // per template instantiation
     {
-        const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&conv_gemm1x1_bf16<WM, WN, NS, KB, NL, FA, XN, YN, DB>));
+        const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&conv_gemm1x1_bf16<WM, WN, NS, KB, NL, FA, XN, YN, DB, SIB>));
         if (e != hipSuccess) return e;
     }
     constexpr int BM = 64 * WM, BN = 32 * FA * WN;
@@ -401,12 +415,15 @@ static hipError_t launch_gemm1x1_l(const Gemm1x1Params &p, hipStream_t st)
     const int nsteps = (p.Cin + 16 * KB - 1) / (16 * KB);
     size_t lds = (size_t)(nsteps < NS ? nsteps : NS) * stage;
     constexpr size_t staging = (size_t)WM * WN * 32 * FA * 144;        // YN: one [channel][64 positions] tile per MFMA wave
-    if (YN && lds < staging) lds = staging;
+    if (YN && lds < staging) lds = staging;                             // SIB: 1 KB per MFMA wave, less than a stage
     const unsigned mtiles = (p.M + BM - 1) / BM;
     const unsigned grid = ((mtiles + 7) / 8) * 8 * ((p.Cout + BN - 1) / BN);
-    NGC_LAUNCH((conv_gemm1x1_bf16<WM, WN, NS, KB, NL, FA, XN, YN, DB>), dim3(grid), dim3(64 * (WM * WN + NL)), lds, st, p);
+    NGC_LAUNCH((conv_gemm1x1_bf16<WM, WN, NS, KB, NL, FA, XN, YN, DB, SIB>), dim3(grid), dim3(64 * (WM * WN + NL)), lds, st, p);
     return ngc::launch_result();
 }
+
+// Strided backprop-data with 2 x 2 pixels per position, of results that take 32-bit offsets
+static bool siblings2x2(const Gemm1x1Params &p) { return p.zero_sib && p.os_h == 2 && p.os_w == 2 && p.out_bytes != 0; }
 
 // the NCHW modes exist for the dispatcher's own tile choices (FA = 2)
 template <int WM, int WN, int NS, int KB, int NL, int FA = 2>
@@ -418,6 +435,7 @@ static hipError_t launch_gemm1x1_t(const Gemm1x1Params &p, hipStream_t st)
     if constexpr (dispatcher_tile) {
         if (p.dbp) {
             if (p.in_nchw || p.out_nchw) return hipErrorInvalidValue;
+            if (siblings2x2(p)) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, true, true>(p, st);
             return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, true>(p, st);
         }
         if (p.in_nchw && p.out_nchw) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, true, true>(p, st);
@@ -425,6 +443,9 @@ static hipError_t launch_gemm1x1_t(const Gemm1x1Params &p, hipStream_t st)
         if (p.out_nchw) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, true>(p, st);
     }
     if (p.in_nchw || p.out_nchw || p.dbp) return hipErrorInvalidValue;
+    if constexpr (dispatcher_tile || FA == 4) {
+        if (siblings2x2(p)) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, false, true>(p, st);
+    }
     return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false>(p, st);
 }
 
