@@ -1587,7 +1587,12 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part, bo
     case V_WGRAD_STEM: return "wgrad_stem_bf16";
     case V_STEM_BWD: return "stem_bwd_strip_bf16";
     case V_WGRAD_GEMM: return "wgrad_gemm_bf16";
-    case V_GEMM1X1: return "gemm1x1_bf16";
+    case V_GEMM1X1: {
+        int P, Q;
+        Gemm1x1Params gp;
+        return kernel && op != NGC_OP_BWD_DATA_DB && validate(desc, &P, &Q) == NGC_OK && gemm1x1_plan(desc, op, P, Q, &gp, nullptr) && resident1x1_takes(gp)
+                   ? "gemm1x1_bf16:resident" : "gemm1x1_bf16";
+    }
     case V_STAGED: {                                         // blocked copies in the workspace: the kernel that runs on them
         static thread_local char name[64];
         StagedPlan sp;

@@ -44,7 +44,7 @@ __device__ __forceinline__ void store16_result(void *dst, uint4 v, bool stream)
 // The NGC_* variables are read once per process, at the first use, into a table; env_switch(SW_X) returns the value of
 // NGC_X or nullptr.  ngc_reload_switches() (exported for the test suite) reads them again and bumps the epoch, which
 // also drops every cached plan.
-enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_FWD_FEW, SW_STREAM, SW_WGRAD_STREAM, SW_DRY_RUN, SW_COUNT };
+enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_FWD_FEW, SW_STREAM, SW_WGRAD_STREAM, SW_RESIDENT, SW_DRY_RUN, SW_COUNT };
 const char *env_switch(Switch s);
 uint32_t sw_epoch();
 // NGC_DRY_RUN=1: every launch is skipped after the host-side planning (host-path timing without a GPU)
@@ -162,6 +162,20 @@ __device__ __forceinline__ void wait_vmcnt(int n)
         NGC_VMCNT_CASE(31)
     default: __builtin_amdgcn_s_waitcnt(0x0F70); break;
     }
+#undef NGC_VMCNT_CASE
+}
+
+// up to 63; counts from 16 on are rounded down to a multiple of 4
+__device__ __forceinline__ void wait_vmcnt63(int n)
+{
+#define NGC_VMCNT_CASE(N) case N: __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14)); break;
+#define NGC_VMCNT_CASES(N) NGC_VMCNT_CASE(N) NGC_VMCNT_CASE(N + 1) NGC_VMCNT_CASE(N + 2) NGC_VMCNT_CASE(N + 3)
+    switch (n < 16 ? n : n < 60 ? n & ~3 : 60) {
+        NGC_VMCNT_CASES(0) NGC_VMCNT_CASES(4) NGC_VMCNT_CASES(8) NGC_VMCNT_CASES(12) NGC_VMCNT_CASE(16) NGC_VMCNT_CASE(20)
+        NGC_VMCNT_CASE(24) NGC_VMCNT_CASE(28) NGC_VMCNT_CASE(32) NGC_VMCNT_CASE(36) NGC_VMCNT_CASE(40) NGC_VMCNT_CASE(44)
+        NGC_VMCNT_CASE(48) NGC_VMCNT_CASE(52) NGC_VMCNT_CASE(56) NGC_VMCNT_CASE(60)
+    }
+#undef NGC_VMCNT_CASES
 #undef NGC_VMCNT_CASE
 }
 
@@ -669,6 +683,10 @@ __device__ __forceinline__ void wg_barrier_nofence()
 
 // launchers (each returns launch_result() after the launch)
 hipError_t launch_gemm1x1(const Gemm1x1Params &p, hipStream_t st);
+bool gemm1x1_wide_tiles(const Gemm1x1Params &p);      // 128-channel tiles (else 64)
+bool gemm1x1_siblings(const Gemm1x1Params &p);        // strided backprop-data that stores zero siblings in whole lines
+bool resident1x1_takes(const Gemm1x1Params &p);       // conv_resident1x1.hip; launch_gemm1x1 asks it first
+hipError_t launch_resident1x1(const Gemm1x1Params &p, hipStream_t st);
 hipError_t launch_zero_fill(void *dst, size_t bytes, hipStream_t st);
 hipError_t launch_igemm(const IgemmParams &p, int bn, uint32_t max_m, hipStream_t st);
 hipError_t launch_igemm3(const IgemmParams &p, int bn, uint32_t max_m, hipStream_t st);    // rank-3 spatial

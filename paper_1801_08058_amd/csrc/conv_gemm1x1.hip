@@ -423,7 +423,7 @@ static hipError_t launch_gemm1x1_l(const Gemm1x1Params &p, hipStream_t st)
 }
 
 // Strided backprop-data with 2 x 2 pixels per position, of results that take 32-bit offsets
-static bool siblings2x2(const Gemm1x1Params &p) { return p.zero_sib && p.os_h == 2 && p.os_w == 2 && p.out_bytes != 0; }
+bool gemm1x1_siblings(const Gemm1x1Params &p) { return p.zero_sib && p.os_h == 2 && p.os_w == 2 && p.out_bytes != 0; }
 
 // the NCHW modes exist for the dispatcher's own tile choices (FA = 2)
 template <int WM, int WN, int NS, int KB, int NL, int FA = 2>
@@ -435,7 +435,7 @@ static hipError_t launch_gemm1x1_t(const Gemm1x1Params &p, hipStream_t st)
     if constexpr (dispatcher_tile) {
         if (p.dbp) {
             if (p.in_nchw || p.out_nchw) return hipErrorInvalidValue;
-            if (siblings2x2(p)) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, true, true>(p, st);
+            if (gemm1x1_siblings(p)) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, true, true>(p, st);
             return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, true>(p, st);
         }
         if (p.in_nchw && p.out_nchw) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, true, true>(p, st);
@@ -444,7 +444,7 @@ static hipError_t launch_gemm1x1_t(const Gemm1x1Params &p, hipStream_t st)
     }
     if (p.in_nchw || p.out_nchw || p.dbp) return hipErrorInvalidValue;
     if constexpr (dispatcher_tile || FA == 4) {
-        if (siblings2x2(p)) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, false, true>(p, st);
+        if (gemm1x1_siblings(p)) return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false, false, true>(p, st);
     }
     return launch_gemm1x1_l<WM, WN, NS, KB, NL, FA, false, false>(p, st);
 }
@@ -456,7 +456,7 @@ static hipError_t launch_gemm1x1_t(const Gemm1x1Params &p, hipStream_t st)
 // 64-channel stages (1), a ring of 4 (2), the 128x128 tile with a ring of 3 (3) / 4 (4), or the
 // 256x128 tile whatever the size (5), or the 256x256 tile with 64x128 wave tiles (6; needs Cout % 256 == 0).
 // 128-channel tiles when they waste no more of a partial last tile than 64-channel tiles would (Cout % 16 == 0)
-static bool wide_tiles(const Gemm1x1Params &p)
+bool gemm1x1_wide_tiles(const Gemm1x1Params &p)
 {
     const int c128 = (p.Cout + 127) / 128, c64 = (p.Cout + 63) / 64;
     return p.Cout > 64 && c128 * 128 <= c64 * 64;
@@ -468,7 +468,7 @@ static int special_mode_variant(const Gemm1x1Params &p)
     const char *ev = env_switch(SW_G1_VARIANT);
     if (ev && atoi(ev) == 3) return 3;
     if (ev && atoi(ev) == 5) return 0;
-    if (!wide_tiles(p)) return 3;                      // same rules as the plain launches
+    if (!gemm1x1_wide_tiles(p)) return 3;                      // same rules as the plain launches
     const int c128 = (p.Cout + 127) / 128;
     const unsigned tiles = ((p.M + 255) / 256) * (unsigned)c128;
     return ((tiles < 2 * 256 && c128 >= 3) || p.Cin <= 64) ? 3 : 0;
@@ -479,16 +479,17 @@ static int special_mode_variant(const Gemm1x1Params &p)
 int gemm1x1_dbp_tile_m(const Gemm1x1Params &p)
 {
     const int variant = special_mode_variant(p);
-    if (wide_tiles(p)) return variant == 3 ? 128 : 256;
+    if (gemm1x1_wide_tiles(p)) return variant == 3 ? 128 : 256;
     return variant == 3 ? 256 : 512;
 }
 
 hipError_t launch_gemm1x1(const Gemm1x1Params &p, hipStream_t st)
 {
     const char *ev = env_switch(SW_G1_VARIANT);
+    if (resident1x1_takes(p)) return launch_resident1x1(p, st);
     int variant = ev ? atoi(ev) : 0;
     const int c128 = (p.Cout + 127) / 128;
-    const bool wide = wide_tiles(p);
+    const bool wide = gemm1x1_wide_tiles(p);
     if (p.in_nchw || p.out_nchw || p.dbp) {
         variant = special_mode_variant(p);
         if (wide) return variant == 3 ? launch_gemm1x1_t<2, 2, 3, 2, 1>(p, st) : launch_gemm1x1_t<4, 2, 3, 2, 2>(p, st);

@@ -26,7 +26,7 @@ CASES = [
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))
-@pytest.mark.parametrize("tile", [None, "0", "3", "5", "6"])
+@pytest.mark.parametrize("tile", [None, "0", "3", "5", "6"])      # None: the default kernel, which small nodes share with test_gpu_resident.py
 def test_zero_siblings(case, tile, monkeypatch):
     monkeypatch.setenv("NGC_FWD_FEW", "0")
     if tile:

@@ -136,3 +136,13 @@ LIMITS = [
 def test_large_nodes_off_the_blocked_kernels_keep_the_gather_gemm():
     for a, stride, dtype, layout, op, gather, stream in LIMITS:
         assert ng.ngc_conv_kernel(node(*a, stride=stride, dtype=dtype, xl=layout), op) == ("direct:gather" if gather < stream else "direct:stream"), a
+
+
+@pytest.mark.parametrize("c, k, h, n, op, taken", [
+    (416, 192, 27, 8, ng.NGC_OP_FWD, True), (416, 128, 27, 8, ng.NGC_OP_FWD, False), (208, 192, 27, 8, ng.NGC_OP_FWD, False),
+    (256, 512, 56, 64, ng.NGC_OP_FWD, True), (256, 512, 56, 24, ng.NGC_OP_FWD, False), (528, 192, 27, 8, ng.NGC_OP_FWD, False),
+    (256, 512, 56, 4, ng.NGC_OP_BWD_DATA, True), (256, 512, 56, 64, ng.NGC_OP_BWD_DATA, False), (64, 144, 56, 8, ng.NGC_OP_BWD_DATA, False),
+])
+def test_resident_filters_choice(c, k, h, n, op, taken):
+    d = ng.make_desc(n, c, h, h, k, 1, 1, (2, 2), w_layout=ng.NGC_BLOCKED_FWD if op == ng.NGC_OP_FWD else ng.NGC_BLOCKED_BWD)
+    assert ng.ngc_conv_kernel(d, op).endswith(":resident") == taken
