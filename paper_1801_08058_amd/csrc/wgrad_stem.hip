@@ -16,6 +16,10 @@
 // 32-position steps (a wave-level split of the reduction, summed through LDS in a fixed tree);
 // one workgroup per strip of dy rows; partials in register order to the workspace, summed in
 // index order by wgrad_stem_reduce (deterministic, no atomics).
+//
+// What bounds it (64 x 3 x 224 x 224, 64 channels, cold, with the second launch): the loads alone take 33 us, the products
+// alone 32 us, of either 12 us start, the tree and the partial sums; together 40.3 us (43.7 before the bookkeeping of a stage
+// was worked out ahead of the loop, 41.3 before the x operands were requested two fragments ahead).
 #include "common.h"
 
 namespace ngc {
@@ -159,9 +163,9 @@ __global__ __launch_bounds__(512) void wgrad_stem_bf16(const WgradStemParams p)
             for (int v = 0; v < 4; ++v) acc[kb][f][v] = 0.f;
 
     const int lane_col = (L & 3) * 8;
-    const int nfr = cg ? WST_NF - 1 : WST_NF;               // the 12th fragment does not exist
 
-    // ---- RING: stage s lives in buffer s % 3; raw input rows of stage s in staging area s & 1 behind the ring
+    // ---- RING: stage s lives in buffer s % 3; raw input rows of stage s in staging area s & 1 behind the ring.  Where a
+    // thread's pieces lie is worked out once: the instructions of a stage that are no operand reads or MFMAs were half of them.
     const ngc_u32x4 rw_dy = make_rsrc_words(p.dy, p.dy_bytes);
     const ngc_u32x4 rw_x = make_rsrc_words(p.x, p.x_bytes);
     unsigned char *raw0 = smem + 3 * stage_bytes;
@@ -170,80 +174,97 @@ __global__ __launch_bounds__(512) void wgrad_stem_bf16(const WgradStemParams p)
     int nxw = (xchunks - wave * 64 + 511) / 512;            // and its loads of input-row pieces
     nxw = nxw < 0 ? 0 : nxw > WST_XCH ? WST_XCH : nxw;
     const int lpw = nxw + ndy;
-    auto issue_stage = [&](int s) {                         // lpw loads, always
-        const int h0 = 2 * (p0 + s * p.SR) - p.pbh;
-        unsigned char *raw = raw0 + (s & 1) * raw_bytes;
+    const int stage_h = 2 * p.SR;                           // input rows between stages
+    int xh[WST_XCH], xoff[WST_XCH], xdst[WST_XCH];          // image row and byte offset in stage 0, byte of the even plane
+    const int dy_pln = __builtin_amdgcn_readfirstlane(wave / steps_full), dy_blk = wave - dy_pln * steps_full;      // this wave's first dy block
+    const unsigned dy_soff0 = (unsigned)((((img * KB + kt * 4 + dy_pln) * PQ) + p0 * p.Q + dy_blk * 32) * 32);
+    if constexpr (RING) {
 #pragma unroll
         for (int u = 0; u < WST_XCH; ++u) {
             const int i = tid + 512 * u;
-            const int ch = i % cpr;
-            const int rr = i / cpr;
-            const int c = rr / rows_in;
-            const int h = h0 + (rr - c * rows_in);
-            const bool ok = i < xchunks && (unsigned)h < (unsigned)p.H;
-            const unsigned off = ok ? (unsigned)(((((img * p.C + c) * p.H + h) * p.W) + ch * 8) * 2) : WST_OOB;
+            const int ch = i % cpr, rr = i / cpr, c = rr / rows_in;
+            xh[u] = i < xchunks ? 2 * p0 - p.pbh + (rr - c * rows_in) : -(1 << 30);      // no piece: outside in every stage
+            xoff[u] = (int)((((img * p.C + c) * p.H + xh[u]) * p.W + ch * 8) * 2u);
+            xdst[u] = rr * RPX + 8 + ch * 8;
+        }
+        // the zeros in front of and behind the rows of all three buffers: no piece covers them
+        for (int i = tid; i < 3 * 4 * p.C * rows_in; i += 512) {
+            const int row = i >> 2, buf = row / (p.C * rows_in), r = row - buf * (p.C * rows_in);
+            *reinterpret_cast<uint2 *>(smem + buf * stage_bytes + 4 * p.dyplane + r * RPX + (i & 1 ? PL : 0) + (i & 2 ? 8 + p.W : 0)) = make_uint2(0, 0);
+        }
+    }
+    auto issue_stage = [&](int s, int buf) {                // lpw loads, always
+        unsigned char *raw = raw0 + (s & 1) * raw_bytes;
+        const int dh = s * stage_h, dx = dh * p.W * 2;
+#pragma unroll
+        for (int u = 0; u < WST_XCH; ++u) {
+            const unsigned off = (unsigned)(xh[u] + dh) < (unsigned)p.H ? (unsigned)(xoff[u] + dx) : WST_OOB;
             if (wave * 64 + 512 * u < xchunks)              // wave-uniform; the staging area ends at a multiple of 64 pieces
                 dma_load_lds16(rw_x, raw + (wave * 64 + 512 * u) * 16, off, 0);
         }
-        unsigned char *base = smem + (s % 3) * stage_bytes;
+        // a dy block: 32 positions, 1 KB both in memory and in LDS
         const int r0 = s * p.SR;
-        int rows = rows_strip - r0;
-        if (rows > p.SR) rows = p.SR;
-        const int nvalid = rows * p.Q;
-        for (int it = wave; it < 4 * steps_full; it += 8) {
-            const int pln = it / steps_full, blk = it - pln * steps_full;
-            const unsigned dy_base = (unsigned)((((img * KB + kt * 4 + pln) * PQ) + (p0 + r0) * p.Q) * 32);
-            const int pos = blk * 32 + (lane >> 1);
-            const unsigned off = (pos < nvalid) ? dy_base + (unsigned)(pos * 32 + (lane & 1) * 16) : WST_OOB;
-            // the quotient comes out of the vector unit: hand the (wave-uniform) destination over as a scalar
-            dma_load_lds16(rw_dy, base + __builtin_amdgcn_readfirstlane(pln * p.dyplane + blk * 1024), off, 0);
-        }
-    };
-    auto split_x = [&](int s) {                             // own pieces of stage s: staging area -> parity planes
-        const unsigned char *raw = raw0 + (s & 1) * raw_bytes;
-        unsigned char *xs = smem + (s % 3) * stage_bytes + 4 * p.dyplane;
-#pragma unroll
-        for (int u = 0; u < WST_XCH; ++u) {
-            const int i = tid + 512 * u;
-            if (i < xchunks) {
-                const int ch = i % cpr;
-                const int rr = i / cpr;
-                const uint4 v = *reinterpret_cast<const uint4 *>(raw + i * 16);
-                unsigned char *row = xs + rr * RPX;
-                const uint2 ev = make_uint2((v.x & 0xFFFFu) | (v.y << 16), (v.z & 0xFFFFu) | (v.w << 16));
-                const uint2 od = make_uint2((v.x >> 16) | (v.y & 0xFFFF0000u), (v.z >> 16) | (v.w & 0xFFFF0000u));
-                *reinterpret_cast<uint2 *>(row + 8 + ch * 8) = ev;
-                *reinterpret_cast<uint2 *>(row + PL + 8 + ch * 8) = od;
-                if (ch == 0) {
-                    *reinterpret_cast<uint2 *>(row) = make_uint2(0, 0);
-                    *reinterpret_cast<uint2 *>(row + PL) = make_uint2(0, 0);
-                }
-                if (ch == cpr - 1) {
-                    *reinterpret_cast<uint2 *>(row + 8 + p.W) = make_uint2(0, 0);
-                    *reinterpret_cast<uint2 *>(row + PL + 8 + p.W) = make_uint2(0, 0);
-                }
+        const int nvalid = (rows_strip - r0 < p.SR ? rows_strip - r0 : p.SR) * p.Q;
+        unsigned soff = dy_soff0 + (unsigned)(r0 * p.Q * 32);
+        unsigned char *dst = smem + buf * stage_bytes + dy_pln * p.dyplane + dy_blk * 1024;
+        int blk = dy_blk;
+        for (int it = 0; it < ndy; ++it) {
+            // the range check leaves out the scalar offset: blocks that end past the strip take a per-lane one or none
+            unsigned voff = (unsigned)lane * 16;
+            if (blk * 32 + 32 > nvalid && blk * 32 + (lane >> 1) >= nvalid) voff = WST_OOB;
+            dma_load_lds16(rw_dy, dst, voff, blk * 32 < nvalid ? soff : 0u);
+            blk += 8;
+            dst += 8192;
+            soff += 8192;
+            while (blk >= steps_full) {
+                blk -= steps_full;
+                dst += p.dyplane - steps_full * 1024;
+                soff += (unsigned)(PQ * 32 - steps_full * 1024);
             }
         }
     };
+    auto split_x = [&](int s, int buf) {                    // own pieces of stage s: staging area -> parity planes
+        const unsigned char *raw = raw0 + (s & 1) * raw_bytes + tid * 16;
+        unsigned char *xs = smem + buf * stage_bytes + 4 * p.dyplane;
+#pragma unroll
+        for (int u = 0; u < WST_XCH; ++u) {
+            if (tid + 512 * u < xchunks) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(raw + 512 * 16 * u);
+                unsigned char *row = xs + xdst[u];
+                *reinterpret_cast<uint2 *>(row) = make_uint2(__builtin_amdgcn_perm(v.y, v.x, 0x05040100), __builtin_amdgcn_perm(v.w, v.z, 0x05040100));
+                *reinterpret_cast<uint2 *>(row + PL) = make_uint2(__builtin_amdgcn_perm(v.y, v.x, 0x07060302), __builtin_amdgcn_perm(v.w, v.z, 0x07060302));
+            }
+        }
+    };
+    auto wait_loads = [&](int n) {                          // wait_vmcnt of up to 11, fewer branches
+        if (n >= 8) __builtin_amdgcn_s_waitcnt(0x0F78);
+        else if (n == 7) __builtin_amdgcn_s_waitcnt(0x0F77);
+        else if (n == 6) __builtin_amdgcn_s_waitcnt(0x0F76);
+        else if (n == 5) __builtin_amdgcn_s_waitcnt(0x0F75);
+        else if (n >= 3) __builtin_amdgcn_s_waitcnt(0x0F73);
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+    };
 
     if constexpr (RING) {
-        issue_stage(0);
-        if (nstages > 1) issue_stage(1);
-        wait_vmcnt(nstages > 1 ? lpw : 0);                  // stage 0 has landed (this wave's part)
-        split_x(0);
+        issue_stage(0, 0);
+        if (nstages > 1) issue_stage(1, 1);
+        wait_loads(nstages > 1 ? lpw : 0);                  // stage 0 has landed (this wave's part)
+        split_x(0, 0);
     } else {
         issue_dy(0, 0);
         load_x(0);
         store_x(0);
     }
+    int buf = 0;                                            // s % 3
     for (int s = 0; s < nstages; ++s) {
         const bool more = s + 1 < nstages;
+        const int buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf == 0 ? 2 : buf - 1;
         if constexpr (RING) {
             // every wave has split its input pieces of stage s and seen its dy loads of stage s land; the barrier
             // makes that true for the workgroup and frees the buffer of stage s - 1 for the loads of stage s + 2
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             wg_barrier_nofence();
-            if (s + 2 < nstages) issue_stage(s + 2);
+            if (s + 2 < nstages) issue_stage(s + 2, buf2);
         } else {
             __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0): dy of stage s has landed (this wave's part)
             __syncthreads();
@@ -257,7 +278,7 @@ __global__ __launch_bounds__(512) void wgrad_stem_bf16(const WgradStemParams p)
         const int nsteps = (rows * p.Q) >> 5;               // rows*Q is a multiple of 8; partial steps handled by zero dy
         const int nsteps_up = (rows * p.Q + 31) >> 5;
         (void)nsteps;
-        const unsigned char *dys = smem + (RING ? s % 3 : s & 1) * stage_bytes;
+        const unsigned char *dys = smem + (RING ? buf : s & 1) * stage_bytes;
         const unsigned char *xs = dys + 4 * p.dyplane;
         for (int j = (wh - (s * steps_full) % 4 + 4) % 4; j < nsteps_up; j += 4) {
             // this lane group's 8 positions: m8 .. m8+7, all in dy row pr
@@ -267,30 +288,41 @@ __global__ __launch_bounds__(512) void wgrad_stem_bf16(const WgradStemParams p)
             const uint32_t pr = fd_div((uint32_t)m8, p.div_q);
             const uint32_t qa = (uint32_t)m8 - pr * p.div_q.d;
             const int pospart = (int)(2 * pr) * RPX + (int)qa * 2;
+            // x operands are requested two fragments ahead of the one being multiplied
+            uint32_t w[3][5];
+            const unsigned char *xp = xs + pospart;
+            auto request = [&](int f) {
+                const uint32_t *src = reinterpret_cast<const uint32_t *>(xp + colconst[f]);
+#pragma unroll
+                for (int i = 0; i < 5; ++i) w[f % 3][i] = src[i];
+            };
             bf16x8 a[4];
+            request(0);
+            request(1);
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) a[kb] = tr_frag_s(dys + kb * p.dyplane + dyo0, dys + kb * p.dyplane + dyo0 + 128);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int f = 0; f < WST_NF; ++f) {
-                if (f < nfr) {
-                    const uint32_t *src = reinterpret_cast<const uint32_t *>(xs + colconst[f] + pospart);
-                    const uint32_t w0 = src[0], w1 = src[1], w2 = src[2], w3 = src[3], w4 = src[4];
+                if (f + 2 < WST_NF) request(f + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                if (f < WST_NF - 1 || cg == 0) {
                     union { uint32_t d[4]; bf16x8 v; } u;
-                    u.d[0] = __builtin_amdgcn_alignbit(w1, w0, colsh[f]);
-                    u.d[1] = __builtin_amdgcn_alignbit(w2, w1, colsh[f]);
-                    u.d[2] = __builtin_amdgcn_alignbit(w3, w2, colsh[f]);
-                    u.d[3] = __builtin_amdgcn_alignbit(w4, w3, colsh[f]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) u.d[i] = __builtin_amdgcn_alignbit(w[f % 3][i + 1], w[f % 3][i], colsh[f]);
 #pragma unroll
                     for (int kb = 0; kb < 4; ++kb)
                         acc[kb][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kb], u.v, acc[kb][f], 0, 0, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         if constexpr (RING) {
             if (more) {
-                wait_vmcnt(s + 2 < nstages ? lpw : 0);              // stage s + 1 has landed (this wave's part)
-                split_x(s + 1);
+                wait_loads(s + 2 < nstages ? lpw : 0);              // stage s + 1 has landed (this wave's part)
+                split_x(s + 1, buf1);
             }
+            buf = buf1;
         } else {
             if (more) store_x((s + 1) & 1);
         }
