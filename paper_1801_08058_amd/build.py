@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libngconv.so")
 CALL = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))     # named for the interpreter it is built for
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "layout.hip", "conv_direct.hip", "conv_gather.hip", "conv_stream.hip", "wgrad_stream.hip", "conv_few.hip", "conv_igemm.hip", "conv_strip.hip", "conv_rows.hip", "conv_strip3.hip", "conv_stem.hip", "wgrad.hip", "wgrad_strip.hip", "wgrad_stem.hip", "wgrad_gemm.hip", "wgrad_taps.hip", "conv_gemm1x1.hip", "conv_resident1x1.hip", "bias_grad.hip", "softmax.hip", "conv3d_direct.hip", "api3d.hip", "static_scratch.hip", "switches.hip", "bwd1x1_fused.hip"]
+SOURCES = ["api.hip", "layout.hip", "conv_direct.hip", "conv_gather.hip", "conv_stream.hip", "wgrad_stream.hip", "conv_few.hip", "conv_waves.hip", "conv_igemm.hip", "conv_strip.hip", "conv_rows.hip", "conv_strip3.hip", "conv_stem.hip", "wgrad.hip", "wgrad_strip.hip", "wgrad_stem.hip", "wgrad_gemm.hip", "wgrad_taps.hip", "conv_gemm1x1.hip", "conv_resident1x1.hip", "bias_grad.hip", "softmax.hip", "conv3d_direct.hip", "api3d.hip", "static_scratch.hip", "switches.hip", "bwd1x1_fused.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
          # the first 16 words of scalar kernel arguments arrive in registers: without a round trip for them the second launch of a

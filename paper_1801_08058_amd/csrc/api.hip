@@ -116,7 +116,7 @@ ngc_conv_desc with_batch(const ngc_conv_desc *d, int n)
 
 enum Variant { V_INVALID, V_UNSUPPORTED, V_DIRECT, V_IGEMM_128, V_IGEMM_64, V_WGRAD_64, V_STRIP, V_WGRAD_STRIP, V_STEM_FWD, V_WGRAD_STEM, V_STEM_BWD, V_WGRAD_GEMM, V_GEMM1X1, V_ROWS, V_STAGED,
                // the kernels that take some of the nodes of the variant they are named after
-               V_DIRECT_GATHER, V_STRIP_FEW, V_GEMM1X1_FEW, V_WGRAD_STRIP_TAPS, V_WGRAD_GEMM_TAPS };
+               V_DIRECT_GATHER, V_STRIP_FEW, V_GEMM1X1_FEW, V_WGRAD_STRIP_TAPS, V_WGRAD_GEMM_TAPS, V_STRIP_WAVES };
 
 constexpr int NUM_CUS = 256;                      // MI355X
 constexpr size_t LDS_LIMIT = 160 * 1024;
@@ -1255,6 +1255,22 @@ double staged_fwd_bwd_us(const ngc_conv_desc *d, int op, Variant v, int P, int Q
     return few_strip_us(wgs, stages, taps, nf);
 }
 
+// plan of a node of V_STRIP_WAVES
+bool waves_plan(const ngc_conv_desc *d, int op, int P, int Q, ConvWavesParams *out)
+{
+    static thread_local PlanCache<CachedPlan<ConvWavesParams>> cache;
+    const PlanKey key = plan_key(d, op);
+    auto *e = cache.find(key);
+    if (!e) {
+        CachedPlan<ConvWavesParams> v;
+        memset(&v, 0, sizeof(v));
+        v.ok = conv_waves_plan(d, op, P, Q, FEW_CHOSEN, &v.v);
+        e = &cache.put(key, v);
+    }
+    if (e->ok) *out = e->v;
+    return e->ok;
+}
+
 // The one place that decides which kernel runs: workspace sizes, launches and reported names follow it.
 // part: the node is a group of images of a larger one or runs on the blocked copies of another
 Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
@@ -1267,6 +1283,8 @@ Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
     if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) &&
         conv_few_plan(d, op, P, Q, staged_fwd_bwd_us(d, op, v, P, Q), nullptr))
         return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
+    if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && v == V_STRIP && conv_waves_plan(d, op, P, Q, staged_fwd_bwd_us(d, op, v, P, Q), nullptr))
+        return V_STRIP_WAVES;
     if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, part)) return V_WGRAD_GEMM_TAPS;
     if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, part)) return V_WGRAD_STRIP_TAPS;
     return v;
@@ -1322,7 +1340,7 @@ bool db_fusable(const ngc_conv_desc *d, Variant v)
         return validate(d, &P, &Q) == NGC_OK && !strip_col_tiles(d, NGC_OP_BWD_DATA, P, Q);
     }
     if (v == V_GEMM1X1) return d->x_layout == NGC_NCHW16C && d->y_layout == NGC_NCHW16C;
-    return v == V_STRIP_FEW || v == V_GEMM1X1_FEW;
+    return v == V_STRIP_FEW || v == V_GEMM1X1_FEW || v == V_STRIP_WAVES;
 }
 
 // rows of partial channel sums the fused launches write
@@ -1350,6 +1368,10 @@ int db_fused_rows(const ngc_conv_desc *d, Variant v, int P, int Q)
         ConvFewParams fp;
         if (!conv_few_plan(d, NGC_OP_BWD_DATA, P, Q, FEW_CHOSEN, &fp)) return 0;
         rows = conv_few_dbp_rows(fp);
+    } else if (v == V_STRIP_WAVES) {
+        ConvWavesParams wp;
+        if (!waves_plan(d, NGC_OP_BWD_DATA, P, Q, &wp)) return 0;
+        rows = conv_waves_dbp_rows(wp);
     }
     return rows;
 }
@@ -1374,9 +1396,9 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         return base + round256((size_t)bias_grad_parts(t, d->h, d->w) * ((d->c + 15) / 16 * 16) * sizeof(float));
     }
     if (op == NGC_OP_BIAS_GRAD) return round256((size_t)bias_grad_parts(*d, P, Q) * ((d->k + 15) / 16 * 16) * sizeof(float));
-    if (op == NGC_OP_FWD && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW))
+    if (op == NGC_OP_FWD && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW || v == V_STRIP_WAVES))
         return d->w_layout == NGC_KCRS ? round256(filter_elems(d, NGC_BLOCKED_FWD) * 2) : 0;
-    if (op == NGC_OP_BWD_DATA && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW))
+    if (op == NGC_OP_BWD_DATA && (v == V_IGEMM_128 || v == V_IGEMM_64 || v == V_STRIP || v == V_ROWS || v == V_GEMM1X1 || v == V_STRIP_FEW || v == V_GEMM1X1_FEW || v == V_STRIP_WAVES))
         return d->w_layout == NGC_KCRS ? round256(filter_elems(d, NGC_BLOCKED_BWD) * 2) : 0;
     if (op == NGC_OP_BWD_DATA && v == V_STEM_BWD) {
         StemBwdPlan pl;
@@ -1573,6 +1595,7 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part, bo
         return kernel && validate(desc, &P, &Q) == NGC_OK && gather_streams(*desc, op == NGC_OP_BWD_DATA_DB ? NGC_OP_BWD_DATA : op, P, Q) ? "direct:stream" : "direct:gather";
     }
     // as a variant backprop-data has the family alone (callers compare the name), as the rank-3 ops do
+    case V_STRIP_WAVES: return kernel ? "strip_bf16:waves" : "strip_bf16";
     case V_STRIP_FEW: return kernel || op == NGC_OP_FWD ? "strip_bf16:few" : "strip_bf16";
     case V_GEMM1X1_FEW: return kernel || op == NGC_OP_FWD ? "gemm1x1_bf16:few" : "gemm1x1_bf16";
     case V_WGRAD_STRIP_TAPS: return "wgrad_strip_bf16:taps";
@@ -1706,6 +1729,16 @@ int ngc_conv_fwd(const ngc_conv_desc *desc, const void *x, const void *w, const 
         fp.relu = (desc->epilogue & NGC_EPI_RELU) ? 1 : 0;
         return launch_status(launch_conv_few(fp, st));
     }
+    if (v == V_STRIP_WAVES) {
+        ConvWavesParams wp;
+        if (!waves_plan(desc, NGC_OP_FWD, P, Q, &wp)) return NGC_UNSUPPORTED;
+        wp.in = static_cast<const uint16_t *>(x);
+        wp.wt = static_cast<const uint16_t *>(wt);
+        wp.out = static_cast<uint16_t *>(y);
+        wp.bias = (desc->epilogue & NGC_EPI_BIAS) ? bias : nullptr;
+        wp.relu = (desc->epilogue & NGC_EPI_RELU) ? 1 : 0;
+        return launch_status(launch_conv_waves(wp, st));
+    }
     if (v == V_STRIP) {
         StripParams sp;
         int nf;
@@ -1830,6 +1863,20 @@ int bwd_data_core(const ngc_conv_desc *desc, const void *dy, const void *w, cons
             fuse->rows = conv_few_dbp_rows(fp);
         }
         return launch_status(launch_conv_few(fp, st));
+    }
+    if (v == V_STRIP_WAVES) {
+        ConvWavesParams wp;
+        if (!waves_plan(desc, NGC_OP_BWD_DATA, P, Q, &wp)) return NGC_UNSUPPORTED;
+        wp.in = static_cast<const uint16_t *>(dy);
+        wp.wt = static_cast<const uint16_t *>(wt);
+        wp.out = static_cast<uint16_t *>(dx);
+        wp.mask = static_cast<const uint16_t *>(mask);
+        if (fuse) {
+            wp.dbp = fuse->partial;
+            wp.dbp_ld = fuse->ld;
+            fuse->rows = conv_waves_dbp_rows(wp);
+        }
+        return launch_status(launch_conv_waves(wp, st));
     }
     if (v == V_STRIP) {
         if (strip_zero_fill(desc)) {

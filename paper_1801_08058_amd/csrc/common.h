@@ -44,7 +44,7 @@ __device__ __forceinline__ void store16_result(void *dst, uint4 v, bool stream)
 // The NGC_* variables are read once per process, at the first use, into a table; env_switch(SW_X) returns the value of
 // NGC_X or nullptr.  ngc_reload_switches() (exported for the test suite) reads them again and bumps the epoch, which
 // also drops every cached plan.
-enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_FWD_FEW, SW_STREAM, SW_WGRAD_STREAM, SW_RESIDENT, SW_DRY_RUN, SW_COUNT };
+enum Switch { SW_CONV3D_RANK2, SW_CONV3D_STRIP, SW_DB_FUSE, SW_G1_NCHW, SW_G1_VARIANT, SW_GEMM1X1, SW_STEM_BH, SW_STEM_TP, SW_STRIP_BW, SW_STRIP_MERGE, SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_STRIDED, SW_STRIP_XCD, SW_WGG3_PARTS, SW_WGG_SLOTS, SW_WGG_SP, SW_WGG_TILE, SW_WGG_XCD, SW_WGRAD_G1, SW_WGRAD_GEMM, SW_WGRAD_LATE, SW_WGRAD_NCQ, SW_WGRAD_RING, SW_WGRAD_STRIP, SW_WSTEM_POS, SW_WSTEM_RING, SW_ROWS, SW_ROWS_LATE, SW_STAGED, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_WGRAD_NT, SW_STRIP_CPS, SW_GATHER_TILE, SW_GATHER_WGRAD, SW_WGRAD_TAPS, SW_FWD_FEW, SW_STREAM, SW_WGRAD_STREAM, SW_RESIDENT, SW_WAVES, SW_DRY_RUN, SW_COUNT };
 const char *env_switch(Switch s);
 uint32_t sw_epoch();
 // NGC_DRY_RUN=1: every launch is skipped after the host-side planning (host-path timing without a GPU)
@@ -562,6 +562,34 @@ hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st);
 // what the caller is asked for: whole 256 bytes, never none (a call without a workspace is refused) and, for partials of
 // exactly the static array's size, not more than that
 inline size_t wgrad_taps_workspace(const WgradTapsPlan &pl) { return pl.ws ? (pl.ws + 255) / 256 * 256 : 256; }
+
+// ---- forward and stride-1 backprop-data whose waves split the reduction (conv_waves.hip) ----
+struct ConvWavesParams {
+    const uint16_t *in;
+    const uint16_t *wt;
+    uint16_t *out;
+    const float *bias;         // may be null
+    const uint16_t *mask;      // may be null; else same shape / layout as out: out = (mask > 0) ? out : 0
+    float *dbp;                // may be null; else [groups * strips, rounded up to even][dbp_ld] fp32: channel sums of what was stored
+    int32_t dbp_ld;
+    int32_t N, Cin, Hin, Win, Cout, Hout, Wout;
+    int32_t TN, TP;            // images and output rows per position tile, of which a workgroup has two (TN > 1: whole images)
+    int32_t groups, strips;    // ceil(N/TN), ceil(Hout/TP)
+    int32_t PR, PC;            // patch rows of an image, patch columns
+    int32_t h0, w0;            // image row of patch row 0 relative to output row p0 * sh; image column of patch column 0
+    int32_t row_base;          // host: first patch row relative to the halo above an image
+    int32_t npix, npatch;      // positions, patch pixels of a tile
+    int32_t tiles, per_xcd;    // workgroups; of an XCD
+    int32_t sh, sw, relu, ntaps, S, bwd;
+    int32_t tap0, tap_dr, tap_ds;                        // LDS offset of tap (r, s): tap0 + r tap_dr + s tap_ds
+    int32_t rcp_pc, rcp_pr, rcp_q, rcp_tp, rcp_s;        // 65536 / PC + 1, ...
+    uint32_t in_bytes, wt_bytes, out_bytes;
+    FastDiv div_nk, div_strips, div_taps;
+};
+// staged_us: what the strip kernel is expected to take
+bool conv_waves_plan(const ngc_conv_desc *d, int op, int P, int Q, double staged_us, ConvWavesParams *q);
+int conv_waves_dbp_rows(const ConvWavesParams &p);
+hipError_t launch_conv_waves(const ConvWavesParams &p, hipStream_t st);
 
 // ---- forward and backprop-data of nodes with few output tiles (conv_few.hip) ----
 // One axis of a class of outputs.  Output i of the class lies at i * os + (residue) and meets the taps t0 + j * tstep, j < cnt, at the

@@ -146,3 +146,11 @@ def test_large_nodes_off_the_blocked_kernels_keep_the_gather_gemm():
 def test_resident_filters_choice(c, k, h, n, op, taken):
     d = ng.make_desc(n, c, h, h, k, 1, 1, (2, 2), w_layout=ng.NGC_BLOCKED_FWD if op == ng.NGC_OP_FWD else ng.NGC_BLOCKED_BWD)
     assert ng.ngc_conv_kernel(d, op).endswith(":resident") == taken
+
+
+def test_waves_that_split_the_reduction_take_long_reductions_on_small_images():
+    """Nodes that were timed with both kernels, on either side of the choice."""
+    waves = [(128, 512, 7, 7, 512, 3), (32, 512, 14, 14, 512, 3), (77, 256, 15, 9, 416, 5)]
+    strip = [(64, 64, 56, 56, 64, 3), (64, 128, 28, 28, 128, 3), (61, 112, 32, 16, 304, 3)]
+    for a in waves + strip:
+        assert ng.ngc_conv_kernel(node(*a, dtype="bf16", xl=BLK), FWD) == "strip_bf16" + (":waves" if a in waves else ""), a
