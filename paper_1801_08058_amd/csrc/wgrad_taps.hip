@@ -87,6 +87,97 @@ __device__ __forceinline__ void wait_loads(int n)
 #undef NGC_WT_CASE
 }
 
+// The end of a workgroup: the accumulators of its NH = 8 / ncq step streams become its partial, or with one part dw.  LDS is free.
+template <int NT, int NKB>
+__device__ __forceinline__ void wgrad_taps_finish(const WgradTapsParams &p, f32x4 (&acc)[NKB][NT], unsigned char *smem, const int part,
+                                                  const int tile, const int tiles, const int kb0, const int cb0, const int nk, const int nc,
+                                                  const int td, const int tap0, const int ntap)
+{
+    constexpr int NW = 8;
+    const int lane = threadIdx.x & 63, L = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ncq = p.ncq, lcq = ncq >> 1, NH = NW >> lcq, cq = wave & (ncq - 1), wh = wave >> lcq;
+    // ---- the sum of the NH step streams.  While all copies (and, with one part, dw on its way out) do not fit the LDS
+    // together, the upper half of the streams publishes and the lower half adds.
+    constexpr int UNITS = NKB * NT;                        // 1 KB pieces (16 k x 16 c of a tap) of a wave
+    f32x4 *red = reinterpret_cast<f32x4 *>(smem) + lane;
+    int nh = NH;
+    while (nh > 1 && (nh + 1) * ncq * UNITS > WT_RED_KB) {
+        nh >>= 1;
+        if (wh >= nh && wh < 2 * nh) {
+            f32x4 *d = red + ((wh - nh) * ncq + cq) * (UNITS * 64);
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) d[(kb * NT + t) * 64] = acc[kb][t];
+        }
+        __syncthreads();
+        if (wh < nh) {
+            const f32x4 *src = red + (wh * ncq + cq) * (UNITS * 64);
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[kb][t] += src[(kb * NT + t) * 64];
+        }
+        __syncthreads();
+    }
+    // dw of one part leaves through LDS so that the stores are contiguous ([k][c][tap] as in memory): accumulator element
+    // v of unit (kb, t) is k = 16 kb + 4 grp + v, c = 16 cq + L; the row pitch spreads the four groups over the banks
+    const int pitch = 16 * ncq * NT + 4;
+    float *tl = reinterpret_cast<float *>(smem) + (nh > 1 ? nh * ncq * UNITS * 256 : 0);
+    f32x4 *out = reinterpret_cast<f32x4 *>(p.partial) + ((size_t)part * tiles + tile) * ncq * (UNITS * 64) + lane;
+    if (nh == 1) {
+        if (wh == 0) {
+            if (p.nparts > 1) {
+                out += cq * (UNITS * 64);
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) out[(kb * NT + t) * 64] = acc[kb][t];
+            } else {
+                float *d = tl + (4 * grp) * pitch + (16 * cq + L) * NT;
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) d[(kb * 16 + v) * pitch + t] = acc[kb][t][v];
+            }
+        }
+    } else {
+        // the remaining copies fit: every wave adds a share of the units over all of them, in stream order
+        if (wh < nh) {
+            f32x4 *d = red + (wh * ncq + cq) * (UNITS * 64);
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) d[(kb * NT + t) * 64] = acc[kb][t];
+        }
+        __syncthreads();
+        for (int u = wave; u < ncq * UNITS; u += NW) {
+            f32x4 r = red[u * 64];
+            for (int h = 1; h < nh; ++h) r += red[(h * ncq * UNITS + u) * 64];
+            if (p.nparts > 1) {
+                out[u * 64] = r;
+            } else {
+                const int q = (int)(((float)u + 0.5f) * (1.0f / UNITS)), w = u - q * UNITS, kb = w / NT, t = w - kb * NT;
+                float *d = tl + (kb * 16 + 4 * grp) * pitch + (16 * q + L) * NT + t;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) d[v * pitch] = r[v];
+            }
+        }
+    }
+    if (p.nparts > 1) return;
+    __syncthreads();
+    const int taps = p.T * p.RS, C = p.CB * 16, rowlen = 16 * nc * NT;
+    float *dst = p.dw + ((size_t)kb0 * 16 * C + cb0 * 16) * taps + td * p.RS + tap0;
+    for (int k = wave; k < 16 * nk; k += NW)
+        for (int j = lane; j < rowlen; j += 64) {
+            const int c = j / NT, t = j - c * NT;
+            if (t < ntap) dst[((size_t)k * C + c) * taps + t] = tl[k * pitch + j];
+        }
+}
+
 // A launch starts with a cold instruction cache (every 64-byte line of code a round trip to the L2 or beyond), so code
 // that runs once is kept short: one copy of the stage loads and of the MFMA steps, geometry that does not depend on the
 // workgroup in the arguments.  The first version, 1600 instructions before its first load, took 9.9 us for a layer of
@@ -394,85 +485,176 @@ __global__ __launch_bounds__(512) void wgrad_taps_bf16(const WgradTapsParams p)
     }
     __syncthreads();                                       // all stage buffers are free
 
-    // ---- the sum of the NH step streams.  While all copies (and, with one part, dw on its way out) do not fit the LDS
-    // together, the upper half of the streams publishes and the lower half adds.
-    constexpr int UNITS = NKB * NT;                        // 1 KB pieces (16 k x 16 c of a tap) of a wave
-    f32x4 *red = reinterpret_cast<f32x4 *>(smem) + lane;
-    int nh = NH;
-    while (nh > 1 && (nh + 1) * ncq * UNITS > WT_RED_KB) {
-        nh >>= 1;
-        if (wh >= nh && wh < 2 * nh) {
-            f32x4 *d = red + ((wh - nh) * ncq + cq) * (UNITS * 64);
-#pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) d[(kb * NT + t) * 64] = acc[kb][t];
-        }
-        __syncthreads();
-        if (wh < nh) {
-            const f32x4 *src = red + (wh * ncq + cq) * (UNITS * 64);
-#pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[kb][t] += src[(kb * NT + t) * 64];
-        }
-        __syncthreads();
+    wgrad_taps_finish<NT, NKB>(p, acc, smem, part, tile, tiles, kb0, cb0, nk, nc, td, tap0, ntap);
+}
+
+// The same for 3x3-class windows (9 taps, any stride and dilation) with one 16-channel group of c per workgroup, rank 2: every wave
+// takes stages of its own, SR rows of at most 32 positions - one step - and their patch, through a ring of buffers of its own.  With
+// ncq = 1 no wave ever reads what another loaded, so the common stages of the kernel above only make the waves wait for each other,
+// 8 steps and a barrier at a time.  Here there is none: while the operands of a stage, already in registers, are multiplied, those of
+// the next one are read from LDS and two (NXB = 2) or one more are under way.  Loads past the last stage deliver zeros to buffers that
+// nobody reads, so that the wait is always for the same number of loads.
+// 512 -> 512 at 7x7, 128 images: 54.6 us with common stages, 42.8 here.  Bound by the LDS: 26 transposing reads of 512 bytes and 6 KB
+// of loads for 36 MFMAs.
+template <int NXB>
+__global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams p)
+{
+    constexpr int NT = 9, NKB = 4, NW = 8, RING = NXB == 2 ? 3 : 2, STAGE = (NKB + NXB) * 1024;
+    extern __shared__ __align__(16) unsigned char smem[];
+    preload_kernargs(p);
+    const int lane = threadIdx.x & 63, L = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    const int tiles = p.ktiles * p.ctiles;
+    int part = 0, tile = blockIdx.x;
+    if (p.xcd) {
+        const int j = blockIdx.x >> 3, pl = uniform_div(j, tiles);
+        tile = j - pl * tiles;
+        part = pl * 8 + (blockIdx.x & 7);
+        if (part >= p.nparts) return;                      // uniform per workgroup
+    } else if (p.nparts > 1) {
+        tile = uniform_div(blockIdx.x, p.nparts);
+        part = blockIdx.x - tile * p.nparts;
     }
-    // dw of one part leaves through LDS so that the stores are contiguous ([k][c][tap] as in memory): accumulator element
-    // v of unit (kb, t) is k = 16 kb + 4 grp + v, c = 16 cq + L; the row pitch spreads the four groups over the banks
-    const int pitch = 16 * ncq * NT + 4;
-    float *tl = reinterpret_cast<float *>(smem) + (nh > 1 ? nh * ncq * UNITS * 256 : 0);
-    f32x4 *out = reinterpret_cast<f32x4 *>(p.partial) + ((size_t)part * tiles + tile) * ncq * (UNITS * 64) + lane;
-    if (nh == 1) {
-        if (wh == 0) {
-            if (p.nparts > 1) {
-                out += cq * (UNITS * 64);
+    const int kt = uniform_div(tile, p.ctiles), cb0 = tile - kt * p.ctiles, kb0 = kt * NKB;
+
+    const int PQ = p.P * p.Q, HW = p.H * p.W, nrb = p.nrb;
+    const unsigned dy_pl = (unsigned)(PQ * 32), x_pl = (unsigned)(HW * 32);              // 16-channel planes
+    const unsigned dy_img = (unsigned)p.KB * dy_pl, x_img = (unsigned)p.CB * x_pl;
+    const int st_begin = part * p.tq + (part < p.trem ? part : p.trem);
+    const int st_end = st_begin + p.tq + (part < p.trem ? 1 : 0);
+    const ngc_u32x4 rs_dy = make_rsrc_words(p.dy, (unsigned)p.N * dy_img);
+    const ngc_u32x4 rs_x = make_rsrc_words(p.x, (unsigned)p.N * x_img);
+    unsigned char *const mine = smem + wave * (RING * STAGE);
+
+    // ---- loads: 32 positions of each of the four dy planes, NXB blocks of 32 patch pixels
+    const int lane2 = lane >> 1;
+    const int min_dh = -p.pbh, min_dw = -p.pbw, npatch = p.PRS * p.PC;
+    const float inv_pc = __builtin_amdgcn_rcpf((float)p.PC);
+    int x_row[NXB];
+    unsigned x_voff[NXB];
+#pragma unroll
+    for (int j = 0; j < NXB; ++j) {
+        const int px = j * 32 + lane2, pr = small_div(px, inv_pc), pc = px - (int)__umul24(pr, p.PC);
+        const bool ok = (px < npatch) & ((unsigned)(min_dw + pc) < (unsigned)p.W);
+        x_voff[j] = (unsigned)(((int)__umul24(pr, p.W) + pc) * 32 + (lane & 1) * 16);
+        x_row[j] = ok ? pr : 0x40000000;
+    }
+    int st = st_begin + wave, img = uniform_div(st, nrb), rb = st - img * nrb;           // the stage loaded next
+    const int img_step = uniform_div(NW, nrb), rb_step = NW - img_step * nrb;
+    int ibuf = 0;
+    auto issue = [&]() {
+        const int row0 = rb * p.SR;
+        int nvalid = (p.P - row0 < p.SR ? p.P - row0 : p.SR) * p.Q;
+        const bool live = st < st_end;
+        nvalid = live ? nvalid : 0;
+        const int h0 = row0 * p.sh + min_dh;
+        unsigned char *dst = mine + ibuf * STAGE;
+        const unsigned dy_org = (unsigned)img * dy_img + (unsigned)kb0 * dy_pl + (unsigned)(row0 * p.Q * 32);
+        const unsigned x_org = (unsigned)img * x_img + (unsigned)cb0 * x_pl + (unsigned)((h0 * p.W + min_dw) * 32);
+        const unsigned off = lane2 < nvalid ? dy_org + (unsigned)(lane * 16) : WT_OOB;
+        unsigned soff = 0;
+#pragma unroll
+        for (int i = 0; i < NKB; ++i, soff += dy_pl) dma_load_lds16(rs_dy, dst + i * 1024, off, soff);
+        const unsigned rlim = live ? (unsigned)p.H : 0u;
+#pragma unroll
+        for (int j = 0; j < NXB; ++j)
+            dma_load_lds16(rs_x, dst + (NKB + j) * 1024, (unsigned)(x_row[j] + h0) < rlim ? x_org + x_voff[j] : WT_OOB, 0);
+        st += NW;
+        img += img_step;
+        rb += rb_step;
+        if (rb >= nrb) {
+            rb -= nrb;
+            ++img;
+        }
+        ibuf = ibuf + 1 == RING ? 0 : ibuf + 1;
+    };
+#pragma unroll 1
+    for (int s = 0; s < RING; ++s) issue();
+
+    // ---- operand addresses: positions 4 grp + L / 4 and 16 further on; dy is zero past the last one, x stays inside the patch
+    int xo[2];
+    const int lane_pos = grp * 4 + (L >> 2), lane_col = (L & 3) * 8, stage_pos = p.SR * p.Q;
+    {
+        const float inv_q = __builtin_amdgcn_rcpf((float)p.Q);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int m = lane_pos + 16 * e, pos = m < stage_pos ? m : stage_pos - 1;
+            const int row = small_div(pos, inv_q), col = pos - (int)__umul24(row, p.Q);
+            xo[e] = (int)(__umul24(row, p.sh * p.PC) + __umul24(col, p.sw)) * 32 + NKB * 1024 + lane_col;
+        }
+    }
+    int tap_off[NT];
+    {
+        int r = 0, c = 0;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            tap_off[t] = (r * p.dil_h * p.PC + c * p.dil_w) * 32;
+            const bool wrap = ++c == p.S;
+            c = wrap ? 0 : c;
+            r += wrap ? 1 : 0;
+        }
+    }
+    f32x4 acc[NKB][NT];
+#pragma unroll
+    for (int a = 0; a < NKB; ++a)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[a][t][v] = 0.f;
+
+    int ms = st_begin + wave, mrb = ms - uniform_div(ms, nrb) * nrb, mbuf = 0;           // the stage whose operands are read next
+    auto load_a = [&](const unsigned char *base, bf16x8 (&a)[NKB]) {
+        const unsigned char *q = base + lane_pos * 32 + lane_col;
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) a[kb] = wt_frag(q + kb * 1024, q + kb * 1024 + 512);
+    };
+    auto load_b = [&](const unsigned char *base, int t) { return wt_frag(base + xo[0] + tap_off[t], base + xo[1] + tap_off[t]); };
+    // positions past the last one: dy is zero there, x is not and has to be where it is infinite or NaN
+    auto next_stage = [&](bf16x8 (&b)[NT]) {
+        const int rows = p.P - mrb * p.SR < p.SR ? p.P - mrb * p.SR : p.SR;
+        if (rows * p.Q < 32) keep_first(b, rows * p.Q - grp * 4);
+        ms += NW;
+        mrb += rb_step;
+        mrb = mrb >= nrb ? mrb - nrb : mrb;
+        mbuf = mbuf + 1 == RING ? 0 : mbuf + 1;
+    };
+    bf16x8 acur[NKB], b[NT];
+    __builtin_amdgcn_s_waitcnt(0x0F70 | ((RING - 1) * (NKB + NXB) & 15));                // all but the loads of the other stages
+    asm volatile("" ::: "memory");
+    if (ms < st_end) {
+        load_a(mine, acur);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) b[t] = load_b(mine, t);
+        next_stage(b);
+#pragma unroll 1
+        for (;;) {
+            const bool more = ms < st_end;
+            bf16x8 anext[NKB];
+            // the operands in registers were the last reads of their buffer
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue();
+            __builtin_amdgcn_s_waitcnt(0x0F70 | ((RING - 1) * (NKB + NXB) & 15));
+            asm volatile("" ::: "memory");
+            const unsigned char *base = mine + mbuf * STAGE;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) out[(kb * NT + t) * 64] = acc[kb][t];
-            } else {
-                float *d = tl + (4 * grp) * pitch + (16 * cq + L) * NT;
-#pragma unroll
-                for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) d[(kb * 16 + v) * pitch + t] = acc[kb][t][v];
+                    acc[kb][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(acur[kb], b[t], acc[kb][t], 0, 0, 0);
+                b[t] = load_b(base, t);
+                if (t == 2) load_a(base, anext);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        }
-    } else {
-        // the remaining copies fit: every wave adds a share of the units over all of them, in stream order
-        if (wh < nh) {
-            f32x4 *d = red + (wh * ncq + cq) * (UNITS * 64);
+            if (!more) break;                                            // what was read is a stage of zeros
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) d[(kb * NT + t) * 64] = acc[kb][t];
-        }
-        __syncthreads();
-        for (int u = wave; u < ncq * UNITS; u += NW) {
-            f32x4 r = red[u * 64];
-            for (int h = 1; h < nh; ++h) r += red[(h * ncq * UNITS + u) * 64];
-            if (p.nparts > 1) {
-                out[u * 64] = r;
-            } else {
-                const int q = (int)(((float)u + 0.5f) * (1.0f / UNITS)), w = u - q * UNITS, kb = w / NT, t = w - kb * NT;
-                float *d = tl + (kb * 16 + 4 * grp) * pitch + (16 * q + L) * NT + t;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) d[v * pitch] = r[v];
-            }
+            for (int kb = 0; kb < NKB; ++kb) acur[kb] = anext[kb];
+            next_stage(b);
         }
     }
-    if (p.nparts > 1) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                     // the loads of zeros are still on their way to the LDS
     __syncthreads();
-    const int taps = p.T * p.RS, C = p.CB * 16, rowlen = 16 * nc * NT;
-    float *dst = p.dw + ((size_t)kb0 * 16 * C + cb0 * 16) * taps + td * p.RS + tap0;
-    for (int k = wave; k < 16 * nk; k += NW)
-        for (int j = lane; j < rowlen; j += 64) {
-            const int c = j / NT, t = j - c * NT;
-            if (t < ntap) dst[((size_t)k * C + c) * taps + t] = tl[k * pitch + j];
-        }
+    wgrad_taps_finish<NT, NKB>(p, acc, smem, part, tile, tiles, kb0, cb0, NKB, 1, 0, 0, NT);
 }
 
 // dw[k][c][tap] = sum over parts (index order).  256 threads = 256 / SL outputs (float4: four k) x SL interleaved part
@@ -561,6 +743,58 @@ static bool wgrad_taps_xcd(long tiles, long parts) { return tiles > 1 && (parts 
 static long wgrad_taps_rounds(long tiles, long parts, bool r3)
 {
     return r3 && wgrad_taps_xcd(tiles, parts) ? ((parts + 7) / 8 * tiles + 31) / 32 : (tiles * parts + 255) / 256;
+}
+
+// Turns a finished plan into one of wgrad_taps_own_bf16 where that is expected to take less time: 64 k, 16 c, 9 taps a workgroup, as
+// many parts as one round of workgroups has room for or fewer.  Expected time, us: start and sum of the streams per round, the
+// stages of a wave, partials, dw, operands read; fitted to 219 launches of 110 drawn nodes, nine tenths of them within 8 %.  Those
+// nodes (0.3 GFLOP and more, images up to 32 x 32) take 2731 us without this kernel, 2526
+// with this choice, 2508 with the best split of either; 60 nodes that it was not fitted to 1566, 1455 and 1426.
+static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force)
+{
+    WgradTapsParams &q = out->p;
+    if (q.KB % 4 || q.Q > 32 || env_switch(SW_WGRAD_OWN)) return;         // the switch (any value): common stages, tests / benchmarks only
+    int sr = 32 / q.Q < q.P ? 32 / q.Q : q.P;
+    const int nb = (q.P + sr - 1) / sr;
+    sr = (q.P + nb - 1) / nb;
+    const long prs = (long)(sr - 1) * q.sh + rspan + 1, nstages = (long)q.N * nb, tiles = (long)(q.KB / 4) * q.CB;
+    const int nxb = prs * pc <= 64 ? 2 : (int)((prs * pc + 31) / 32);
+    if (nxb > 4 || nstages >= (1 << 23) || tiles >= (1 << 20)) return;
+    const double dw_mb = 36864e-6 * tiles;
+    const long most = tiles < 256 ? 256 / tiles : 1;
+    double best = 0.0;
+    long parts = 0;
+    for (long p = 1; p <= most && p <= nstages; ++p) {
+        if (force > 0 ? p != force % 1000 && force % 1000 : p > 1 && p * dw_mb * 1e6 > (double)NGC_STATIC_SCRATCH_BYTES) continue;
+        const long per = (nstages + p - 1) / p, rounds = (tiles * p + 255) / 256;
+        const double us = rounds * (10.7 + 0.78 * ((per + 7) / 8)) + (p > 1 ? 1.1 + 0.33 * p * dw_mb : 0.0) + 0.08 * dw_mb +
+                          0.0042 * tiles * p / 256.0 * per * (4 + nxb);
+        if (parts == 0 || us < best) {
+            best = us;
+            parts = p;
+        }
+    }
+    const bool same_tile = q.ncq == 1 && out->nkb == 4;
+    if (parts == 0 || (force > 0 ? !same_tile : best >= (same_tile ? 1.0 : 0.95) * out->us)) return;
+    q.SR = (int16_t)sr;
+    q.G = 1;
+    q.PRS = (int16_t)prs;
+    q.nrb = (int16_t)nb;
+    q.nib = q.N;
+    q.ncq = 1;
+    q.ktiles = (int16_t)(q.KB / 4);
+    q.ctiles = q.CB;
+    q.nparts = (int16_t)parts;
+    q.xcd = wgrad_taps_xcd(tiles, parts);
+    q.tq = (int32_t)(nstages / parts);
+    q.trem = (int16_t)(nstages % parts);
+    out->own = nxb;
+    out->nkb = 4;
+    // the rings; the sum: four waves' copies, then two and dw on its way out
+    const size_t ring = (size_t)8 * (nxb == 2 ? 3 : 2) * (4 + nxb) * 1024, sum = 4 * 36 * 1024;
+    out->lds = ring > sum ? ring : sum;
+    out->ws = parts > 1 ? (size_t)parts * tiles * 36864 : 0;
+    out->us = best;
 }
 
 bool wgrad_taps_plan(WgradTapsPlan *out)
@@ -715,6 +949,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     out->lds = stages > red ? stages : red;
     if (out->lds > 160 * 1024) return false;
     out->ws = b_parts > 1 ? (size_t)b_parts * tiles * b_ncq * b_nkb * nt * 1024 : 0;
+    out->own = 0;
     out->cycles = q.r3 ? 0.0 : best;
     double fixed;
     const double stage = wgrad_stage_cost(b_nkb, b_ncq, nt, (int)bd, (int)bx, b_ring, &fixed);
@@ -725,6 +960,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     // the GEMM has to be expected 8 % faster (1 x 80 -> 48, 8 x 22 x 52 /2, expected 12.3 / 13.4, takes 12.3 / 12.5; 40 nodes that change
     // kernels without this margin take 0.76 to 1.07 of the GEMM's time).
     if (q.r3) out->us = by_cycles_us < 1.09 * out->us ? by_cycles_us : 1.09 * out->us;
+    else if (nt == 9 && q.RS == 9) wgrad_taps_own_plan(out, rspan, (int)pc, fv);
     return true;
 }
 
@@ -751,6 +987,19 @@ static hipError_t launch_wgrad_taps_t(const WgradTapsPlan &pl, hipStream_t st)
     return launch_result();
 }
 
+template <int NXB>
+static hipError_t launch_wgrad_taps_own(const WgradTapsPlan &pl, hipStream_t st)
+{
+    static LdsLimitOnce lds_limit;                         // per template instantiation
+    const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&wgrad_taps_own_bf16<NXB>));
+    if (e != hipSuccess) return e;
+    const WgradTapsParams &p = pl.p;
+    const unsigned tiles = (unsigned)(p.ktiles * p.ctiles);
+    const dim3 grid(p.xcd ? 8u * ((p.nparts + 7) / 8) * tiles : (unsigned)p.nparts * tiles);
+    NGC_LAUNCH((wgrad_taps_own_bf16<NXB>), grid, dim3(512), pl.lds, st, p);
+    return launch_result();
+}
+
 template <int NT>
 static hipError_t launch_wgrad_taps_n(const WgradTapsPlan &pl, hipStream_t st)
 {
@@ -766,7 +1015,10 @@ static hipError_t launch_wgrad_taps_n(const WgradTapsPlan &pl, hipStream_t st)
 hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st)
 {
     hipError_t e = hipErrorInvalidValue;
-    switch (pl.nt) {
+    switch (pl.own ? 10 + pl.own : pl.nt) {
+    case 12: e = launch_wgrad_taps_own<2>(pl, st); break;
+    case 13: e = launch_wgrad_taps_own<3>(pl, st); break;
+    case 14: e = launch_wgrad_taps_own<4>(pl, st); break;
     case 1: e = launch_wgrad_taps_n<1>(pl, st); break;     // 3x1x1: three groups of one tap
     case 2: e = launch_wgrad_taps_n<2>(pl, st); break;
     case 3: e = launch_wgrad_taps_n<3>(pl, st); break;
