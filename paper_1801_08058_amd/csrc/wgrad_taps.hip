@@ -488,15 +488,23 @@ __global__ __launch_bounds__(512) void wgrad_taps_bf16(const WgradTapsParams p)
     wgrad_taps_finish<NT, NKB>(p, acc, smem, part, tile, tiles, kb0, cb0, nk, nc, td, tap0, ntap);
 }
 
+// Bytes from a pixel to the end of what its taps reach (9 taps, one of the rows of a tap group)
+__host__ __device__ inline int wgrad_own_zeros(const WgradTapsParams &p)
+{
+    return (((p.RS / p.S - 1) * p.dil_h * p.PC + (p.S - 1) * p.dil_w) * 32 + 32 + 15) & ~15;
+}
+
 // The same for 3x3-class windows (9 taps, any stride and dilation) with one 16-channel group of c per workgroup, rank 2: every wave
 // takes stages of its own, SR rows of at most 32 positions - one step - and their patch, through a ring of buffers of its own.  With
 // ncq = 1 no wave ever reads what another loaded, so the common stages of the kernel above only make the waves wait for each other,
 // 8 steps and a barrier at a time.  Here there is none: while the operands of a stage, already in registers, are multiplied, those of
 // the next one are read from LDS and two (NXB = 2) or one more are under way.  Loads past the last stage deliver zeros to buffers that
 // nobody reads, so that the wait is always for the same number of loads.
-// 512 -> 512 at 7x7, 128 images: 54.6 us with common stages, 42.8 here.  Bound by the LDS: 26 transposing reads of 512 bytes and 6 KB
+// 512 -> 512 at 7x7, 128 images: 54.6 us with common stages, 41.7 here (42.8 with
+// masks on the operands in place of zeros to read and an address addition per tap).  Bound by the LDS: 26 transposing reads of 512 bytes and 6 KB
 // of loads for 36 MFMAs.
-template <int NXB>
+// U3: three rows of three taps a pixel apart - the taps of a row are constants in the LDS reads.
+template <int NXB, bool U3>
 __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams p)
 {
     constexpr int NT = 9, NKB = 4, NW = 8, RING = NXB == 2 ? 3 : 2, STAGE = (NKB + NXB) * 1024;
@@ -572,16 +580,21 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
 #pragma unroll 1
     for (int s = 0; s < RING; ++s) issue();
 
-    // ---- operand addresses: positions 4 grp + L / 4 and 16 further on; dy is zero past the last one, x stays inside the patch
-    int xo[2];
-    const int lane_pos = grp * 4 + (L >> 2), lane_col = (L & 3) * 8, stage_pos = p.SR * p.Q;
+    // ---- operand addresses: positions 4 grp + L / 4 and 16 further on.  Positions past the last one, where dy is zero but x would be
+    // what some pixel holds, infinities and NaN included, read zeros behind the rings, as far as the taps reach.
+    const int zeros = NW * RING * STAGE, zero_bytes = wgrad_own_zeros(p);
+    for (int i = threadIdx.x * 4; i < zero_bytes; i += 2048) *reinterpret_cast<int *>(smem + zeros + i) = 0;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wg_barrier_nofence();
+    int xo[2], pos_of[2];
+    const int lane_pos = grp * 4 + (L >> 2), lane_col = (L & 3) * 8;
     {
         const float inv_q = __builtin_amdgcn_rcpf((float)p.Q);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const int m = lane_pos + 16 * e, pos = m < stage_pos ? m : stage_pos - 1;
-            const int row = small_div(pos, inv_q), col = pos - (int)__umul24(row, p.Q);
-            xo[e] = (int)(__umul24(row, p.sh * p.PC) + __umul24(col, p.sw)) * 32 + NKB * 1024 + lane_col;
+            pos_of[e] = lane_pos + 16 * e;
+            const int row = small_div(pos_of[e], inv_q), col = pos_of[e] - (int)__umul24(row, p.Q);
+            xo[e] = (int)(__umul24(row, p.sh * p.PC) + __umul24(col, p.sw)) * 32 + NKB * 1024 + lane_col + wave * (RING * STAGE);
         }
     }
     int tap_off[NT];
@@ -609,11 +622,17 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) a[kb] = wt_frag(q + kb * 1024, q + kb * 1024 + 512);
     };
-    auto load_b = [&](const unsigned char *base, int t) { return wt_frag(base + xo[0] + tap_off[t], base + xo[1] + tap_off[t]); };
-    // positions past the last one: dy is zero there, x is not and has to be where it is infinite or NaN
-    auto next_stage = [&](bf16x8 (&b)[NT]) {
-        const int rows = p.P - mrb * p.SR < p.SR ? p.P - mrb * p.SR : p.SR;
-        if (rows * p.Q < 32) keep_first(b, rows * p.Q - grp * 4);
+    auto x_at = [&](int (&at)[2]) {
+        const int nvalid = (p.P - mrb * p.SR < p.SR ? p.P - mrb * p.SR : p.SR) * p.Q;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) at[e] = pos_of[e] < nvalid ? xo[e] + mbuf * STAGE : zeros + lane_col;
+    };
+    auto load_b = [&](const int (&at)[2], int t) {
+        const int off = U3 ? (t / 3) * p.dil_h * p.PC * 32 : tap_off[t];
+        const unsigned char *q0 = smem + (at[0] + off), *q1 = smem + (at[1] + off);
+        return wt_frag(q0 + (U3 ? t % 3 * 32 : 0), q1 + (U3 ? t % 3 * 32 : 0));
+    };
+    auto next_stage = [&]() {
         ms += NW;
         mrb += rb_step;
         mrb = mrb >= nrb ? mrb - nrb : mrb;
@@ -623,10 +642,12 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
     __builtin_amdgcn_s_waitcnt(0x0F70 | ((RING - 1) * (NKB + NXB) & 15));                // all but the loads of the other stages
     asm volatile("" ::: "memory");
     if (ms < st_end) {
+        int at[2];
         load_a(mine, acur);
+        x_at(at);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) b[t] = load_b(mine, t);
-        next_stage(b);
+        for (int t = 0; t < NT; ++t) b[t] = load_b(at, t);
+        next_stage();
 #pragma unroll 1
         for (;;) {
             const bool more = ms < st_end;
@@ -636,20 +657,20 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
             issue();
             __builtin_amdgcn_s_waitcnt(0x0F70 | ((RING - 1) * (NKB + NXB) & 15));
             asm volatile("" ::: "memory");
-            const unsigned char *base = mine + mbuf * STAGE;
+            x_at(at);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb)
                     acc[kb][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(acur[kb], b[t], acc[kb][t], 0, 0, 0);
-                b[t] = load_b(base, t);
-                if (t == 2) load_a(base, anext);
+                b[t] = load_b(at, t);
+                if (t == 2) load_a(mine + mbuf * STAGE, anext);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (!more) break;                                            // what was read is a stage of zeros
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) acur[kb] = anext[kb];
-            next_stage(b);
+            next_stage();
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                     // the loads of zeros are still on their way to the LDS
@@ -759,7 +780,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force
     sr = (q.P + nb - 1) / nb;
     const long prs = (long)(sr - 1) * q.sh + rspan + 1, nstages = (long)q.N * nb, tiles = (long)(q.KB / 4) * q.CB;
     const int nxb = prs * pc <= 64 ? 2 : (int)((prs * pc + 31) / 32);
-    if (nxb > 4 || nstages >= (1 << 23) || tiles >= (1 << 20)) return;
+    if (nxb > 4 || nstages >= (1 << 23) || tiles >= (1 << 20)) return;     // a patch holds what the taps of a position reach: the zeros fit
     const double dw_mb = 36864e-6 * tiles;
     const long most = tiles < 256 ? 256 / tiles : 1;
     double best = 0.0;
@@ -791,7 +812,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force
     out->own = nxb;
     out->nkb = 4;
     // the rings; the sum: four waves' copies, then two and dw on its way out
-    const size_t ring = (size_t)8 * (nxb == 2 ? 3 : 2) * (4 + nxb) * 1024, sum = 4 * 36 * 1024;
+    const size_t ring = (size_t)8 * (nxb == 2 ? 3 : 2) * (4 + nxb) * 1024 + wgrad_own_zeros(q), sum = 4 * 36 * 1024;
     out->lds = ring > sum ? ring : sum;
     out->ws = parts > 1 ? (size_t)parts * tiles * 36864 : 0;
     out->us = best;
@@ -987,16 +1008,16 @@ static hipError_t launch_wgrad_taps_t(const WgradTapsPlan &pl, hipStream_t st)
     return launch_result();
 }
 
-template <int NXB>
+template <int NXB, bool U3>
 static hipError_t launch_wgrad_taps_own(const WgradTapsPlan &pl, hipStream_t st)
 {
     static LdsLimitOnce lds_limit;                         // per template instantiation
-    const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&wgrad_taps_own_bf16<NXB>));
+    const hipError_t e = lds_limit.raise(reinterpret_cast<const void *>(&wgrad_taps_own_bf16<NXB, U3>));
     if (e != hipSuccess) return e;
     const WgradTapsParams &p = pl.p;
     const unsigned tiles = (unsigned)(p.ktiles * p.ctiles);
     const dim3 grid(p.xcd ? 8u * ((p.nparts + 7) / 8) * tiles : (unsigned)p.nparts * tiles);
-    NGC_LAUNCH((wgrad_taps_own_bf16<NXB>), grid, dim3(512), pl.lds, st, p);
+    NGC_LAUNCH((wgrad_taps_own_bf16<NXB, U3>), grid, dim3(512), pl.lds, st, p);
     return launch_result();
 }
 
@@ -1016,9 +1037,9 @@ hipError_t launch_wgrad_taps(const WgradTapsPlan &pl, hipStream_t st)
 {
     hipError_t e = hipErrorInvalidValue;
     switch (pl.own ? 10 + pl.own : pl.nt) {
-    case 12: e = launch_wgrad_taps_own<2>(pl, st); break;
-    case 13: e = launch_wgrad_taps_own<3>(pl, st); break;
-    case 14: e = launch_wgrad_taps_own<4>(pl, st); break;
+    case 12: e = pl.p.S == 3 && pl.p.dil_w == 1 ? launch_wgrad_taps_own<2, true>(pl, st) : launch_wgrad_taps_own<2, false>(pl, st); break;
+    case 13: e = pl.p.S == 3 && pl.p.dil_w == 1 ? launch_wgrad_taps_own<3, true>(pl, st) : launch_wgrad_taps_own<3, false>(pl, st); break;
+    case 14: e = pl.p.S == 3 && pl.p.dil_w == 1 ? launch_wgrad_taps_own<4, true>(pl, st) : launch_wgrad_taps_own<4, false>(pl, st); break;
     case 1: e = launch_wgrad_taps_n<1>(pl, st); break;     // 3x1x1: three groups of one tap
     case 2: e = launch_wgrad_taps_n<2>(pl, st); break;
     case 3: e = launch_wgrad_taps_n<3>(pl, st); break;
