@@ -525,6 +525,7 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
         part = blockIdx.x - tile * p.nparts;
     }
     const int kt = uniform_div(tile, p.ctiles), cb0 = tile - kt * p.ctiles, kb0 = kt * NKB;
+    const int nk = p.KB - kb0 < NKB ? p.KB - kb0 : NKB;    // planes of the tile that exist; zeros for the others
 
     const int PQ = p.P * p.Q, HW = p.H * p.W, nrb = p.nrb;
     const unsigned dy_pl = (unsigned)(PQ * 32), x_pl = (unsigned)(HW * 32);              // 16-channel planes
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
         const unsigned off = lane2 < nvalid ? dy_org + (unsigned)(lane * 16) : WT_OOB;
         unsigned soff = 0;
 #pragma unroll
-        for (int i = 0; i < NKB; ++i, soff += dy_pl) dma_load_lds16(rs_dy, dst + i * 1024, off, soff);
+        for (int i = 0; i < NKB; ++i, soff += dy_pl) dma_load_lds16(rs_dy, dst + i * 1024, i < nk ? off : WT_OOB, i < nk ? soff : 0u);
         const unsigned rlim = live ? (unsigned)p.H : 0u;
 #pragma unroll
         for (int j = 0; j < NXB; ++j)
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(512) void wgrad_taps_own_bf16(const WgradTapsParams
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                     // the loads of zeros are still on their way to the LDS
     __syncthreads();
-    wgrad_taps_finish<NT, NKB>(p, acc, smem, part, tile, tiles, kb0, cb0, NKB, 1, 0, 0, NT);
+    wgrad_taps_finish<NT, NKB>(p, acc, smem, part, tile, tiles, kb0, cb0, nk, 1, 0, 0, NT);
 }
 
 // dw[k][c][tap] = sum over parts (index order).  256 threads = 256 / SL outputs (float4: four k) x SL interleaved part
@@ -770,15 +771,16 @@ static long wgrad_taps_rounds(long tiles, long parts, bool r3)
 // many parts as one round of workgroups has room for or fewer.  Expected time, us: start and sum of the streams per round, the
 // stages of a wave, partials, dw, operands read; fitted to 219 launches of 110 drawn nodes, nine tenths of them within 8 %.  Those
 // nodes (0.3 GFLOP and more, images up to 32 x 32) take 2731 us without this kernel, 2526
-// with this choice, 2508 with the best split of either; 60 nodes that it was not fitted to 1566, 1455 and 1426.
+// with this choice, 2508 with the best split of either; 60 nodes that it was not fitted to 1566, 1455 and 1426,
+// 110 with any multiple of 16 k 2209, 2057 and 2030, none of them slower by more than 3 %.
 static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force)
 {
     WgradTapsParams &q = out->p;
-    if (q.KB % 4 || q.Q > 32 || env_switch(SW_WGRAD_OWN)) return;         // the switch (any value): common stages, tests / benchmarks only
+    if (q.Q > 32 || env_switch(SW_WGRAD_OWN)) return;         // the switch (any value): common stages, tests / benchmarks only
     int sr = 32 / q.Q < q.P ? 32 / q.Q : q.P;
     const int nb = (q.P + sr - 1) / sr;
     sr = (q.P + nb - 1) / nb;
-    const long prs = (long)(sr - 1) * q.sh + rspan + 1, nstages = (long)q.N * nb, tiles = (long)(q.KB / 4) * q.CB;
+    const long prs = (long)(sr - 1) * q.sh + rspan + 1, nstages = (long)q.N * nb, tiles = (long)((q.KB + 3) / 4) * q.CB;
     const int nxb = prs * pc <= 64 ? 2 : (int)((prs * pc + 31) / 32);
     if (nxb > 4 || nstages >= (1 << 23) || tiles >= (1 << 20)) return;     // a patch holds what the taps of a position reach: the zeros fit
     const double dw_mb = 36864e-6 * tiles;
@@ -803,7 +805,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force
     q.nrb = (int16_t)nb;
     q.nib = q.N;
     q.ncq = 1;
-    q.ktiles = (int16_t)(q.KB / 4);
+    q.ktiles = (int16_t)((q.KB + 3) / 4);
     q.ctiles = q.CB;
     q.nparts = (int16_t)parts;
     q.xcd = wgrad_taps_xcd(tiles, parts);

@@ -25,6 +25,8 @@ CASES = [
     (Attrs(3, 16, 9, 9, 64, 3, 3, 1, 1, 2, 2, 2, 2, 2, 2), (1, 2)),              # dilation
     (Attrs(4, 16, 6, 6, 64, 3, 3, 1, 1, 1, 1, 0, 0, 0, 0), (1,)),                # no padding: 16 positions, whole images
     (Attrs(2, 16, 3, 21, 64, 1, 9, 1, 1, 1, 1, 0, 4, 0, 4), (1, 2)),             # nine taps in a row
+    (Attrs(6, 32, 7, 7, 80, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 3)),              # a tile of k with one 16-channel block
+    (Attrs(3, 16, 10, 12, 112, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 2, 16)),       # ... with three
     (Attrs(40, 32, 7, 7, 192, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 5)),            # the rings go round
 ]
 
