@@ -116,7 +116,12 @@ ngc_conv_desc with_batch(const ngc_conv_desc *d, int n)
 
 enum Variant { V_INVALID, V_UNSUPPORTED, V_DIRECT, V_IGEMM_128, V_IGEMM_64, V_WGRAD_64, V_STRIP, V_WGRAD_STRIP, V_STEM_FWD, V_WGRAD_STEM, V_STEM_BWD, V_WGRAD_GEMM, V_GEMM1X1, V_ROWS, V_STAGED,
                // the kernels that take some of the nodes of the variant they are named after
-               V_DIRECT_GATHER, V_STRIP_FEW, V_GEMM1X1_FEW, V_WGRAD_STRIP_TAPS, V_WGRAD_GEMM_TAPS, V_STRIP_WAVES };
+               V_DIRECT_GATHER, V_STRIP_FEW, V_GEMM1X1_FEW, V_WGRAD_STRIP_TAPS, V_WGRAD_GEMM_TAPS, V_STRIP_WAVES,
+               // ... as a part of another node: partials no larger than with common stages
+               V_WGRAD_STRIP_TAPS_PART, V_WGRAD_GEMM_TAPS_PART };
+
+bool wgrad_taps_part(Variant v) { return v == V_WGRAD_STRIP_TAPS_PART || v == V_WGRAD_GEMM_TAPS_PART; }
+bool wgrad_taps_variant(Variant v) { return v == V_WGRAD_STRIP_TAPS || v == V_WGRAD_GEMM_TAPS || wgrad_taps_part(v); }
 
 constexpr int NUM_CUS = 256;                      // MI355X
 constexpr size_t LDS_LIMIT = 160 * 1024;
@@ -1035,10 +1040,13 @@ bool wgrad_gemm_plan(const ngc_conv_desc *d, int P, int Q, WgradGemmParams *wp)
 }
 
 // several taps per pass (blocked nodes of more than one tap); nullptr: the per-tap GEMM.  Valid until the next plan.
-const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q)
+// part: the node is a group of images of a larger one or runs on the blocked copies of another.  Its partials then share the caller's
+// workspace with more, so they stay as small as the plan with common stages has them: what fitted the static array of
+// ngc_conv_bwd_filters_noalloc fits it still.
+const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q, bool part)
 {
     static thread_local PlanCache<CachedPlan<WgradTapsPlan>> cache;
-    const PlanKey key = plan_key(d);
+    const PlanKey key = plan_key(d, part);
     auto *e = cache.find(key);
     if (!e) {
         CachedPlan<WgradTapsPlan> v;
@@ -1054,7 +1062,7 @@ const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q)
             q.dil_h = (int16_t)d->dil_h; q.dil_w = (int16_t)d->dil_w;
             q.pbh = (int16_t)d->pad_below_h; q.pbw = (int16_t)d->pad_below_w;
             q.RS = (int8_t)(d->r * d->s); q.S = (int8_t)d->s;
-            v.ok = wgrad_taps_plan(&v.v);
+            v.ok = wgrad_taps_plan(&v.v, part);
         }
         e = &cache.put(key, v);
     }
@@ -1070,7 +1078,7 @@ const WgradTapsPlan *wgrad_taps_plan_of(const ngc_conv_desc *d, int P, int Q)
 // there too, and nodes on blocked copies, which do).
 const WgradTapsPlan *wgrad_taps_for_gemm(const ngc_conv_desc *d, int P, int Q, bool part)
 {
-    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q);
+    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q, part);
     WgradGemmParams q;
     if (!tp || env_switch(SW_WGRAD_TAPS) || !wgrad_gemm_plan(d, P, Q, &q)) return tp;     // the switch forces a split
     const size_t partials = (size_t)q.nparts * d->r * d->s * q.ktiles * q.ctiles * q.wk * q.wc * 64 * 64 * sizeof(float);
@@ -1089,7 +1097,7 @@ const WgradTapsPlan *wgrad_taps_for_strip(const ngc_conv_desc *d, int P, int Q, 
 {
     if (env_switch(SW_WGRAD_NCQ) || env_switch(SW_WGRAD_RING) || env_switch(SW_WGRAD_LATE) || env_switch(SW_WGRAD_G1) || env_switch(SW_WGRAD_NT))
         return nullptr;                                   // a switch that shapes the strip kernel asks for it
-    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q);
+    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q, part);
     WgradStripParams q;
     if (!tp || !wgrad_strip_plan(d, P, Q, &q, nullptr)) return nullptr;
     double fixed;
@@ -1285,8 +1293,8 @@ Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
         return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
     if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && v == V_STRIP && conv_waves_plan(d, op, P, Q, staged_fwd_bwd_us(d, op, v, P, Q), nullptr))
         return V_STRIP_WAVES;
-    if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, part)) return V_WGRAD_GEMM_TAPS;
-    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, part)) return V_WGRAD_STRIP_TAPS;
+    if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, part)) return part ? V_WGRAD_GEMM_TAPS_PART : V_WGRAD_GEMM_TAPS;
+    if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, part)) return part ? V_WGRAD_STRIP_TAPS_PART : V_WGRAD_STRIP_TAPS;
     return v;
 }
 
@@ -1411,7 +1419,7 @@ size_t workspace_bytes_uncached(const ngc_conv_desc *d, int op, Variant v, int P
         wgrad_stem_plan(d, P, Q, &wp, nullptr);
         return round256((size_t)d->n * wp.strips * (d->k / 64) * 2 * 4 * 6 * 64 * 16);
     }
-    if (op == NGC_OP_BWD_FILTERS && (v == V_WGRAD_GEMM_TAPS || v == V_WGRAD_STRIP_TAPS)) return wgrad_taps_workspace(*wgrad_taps_plan_of(d, P, Q));
+    if (op == NGC_OP_BWD_FILTERS && wgrad_taps_variant(v)) return wgrad_taps_workspace(*wgrad_taps_plan_of(d, P, Q, wgrad_taps_part(v)));
     if (op == NGC_OP_BWD_FILTERS && v == V_WGRAD_GEMM) {
         WgradGemmParams wp;
         wgrad_gemm_plan(d, P, Q, &wp);
@@ -1598,7 +1606,9 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part, bo
     case V_STRIP_WAVES: return kernel ? "strip_bf16:waves" : "strip_bf16";
     case V_STRIP_FEW: return kernel || op == NGC_OP_FWD ? "strip_bf16:few" : "strip_bf16";
     case V_GEMM1X1_FEW: return kernel || op == NGC_OP_FWD ? "gemm1x1_bf16:few" : "gemm1x1_bf16";
+    case V_WGRAD_STRIP_TAPS_PART:
     case V_WGRAD_STRIP_TAPS: return "wgrad_strip_bf16:taps";
+    case V_WGRAD_GEMM_TAPS_PART:
     case V_WGRAD_GEMM_TAPS: return "wgrad_gemm_bf16:taps";
     case V_IGEMM_128: return "igemm_bf16_128x128";
     case V_IGEMM_64: return "igemm_bf16_256x64";
@@ -2227,8 +2237,8 @@ static int bwd_filters(const ngc_conv_desc *desc, const void *x, const void *dy,
 
     const size_t need = workspace_bytes(desc, NGC_OP_BWD_FILTERS, v, P, Q);
     if (!ws || ws_bytes < need) return NGC_WORKSPACE_TOO_SMALL;
-    if (v == V_WGRAD_GEMM_TAPS || v == V_WGRAD_STRIP_TAPS) {
-        WgradTapsPlan pl = *wgrad_taps_plan_of(desc, P, Q);
+    if (wgrad_taps_variant(v)) {
+        WgradTapsPlan pl = *wgrad_taps_plan_of(desc, P, Q, wgrad_taps_part(v));
         pl.p.x = static_cast<const uint16_t *>(x);
         pl.p.dy = static_cast<const uint16_t *>(dy);
         pl.p.partial = static_cast<float *>(ws);

@@ -552,8 +552,9 @@ struct WgradTapsPlan {
     size_t lds, ws;            // bytes of LDS, of the partials (0: one part, dw written directly)
     double us, cycles;         // expected time; rank 2: the cycle count the split was chosen by
 };
-// fills in the split of out->p, whose shape fields are set; false: not for this kernel
-bool wgrad_taps_plan(WgradTapsPlan *out);
+// fills in the split of out->p, whose shape fields are set; false: not for this kernel.  within: stages of a wave's own only where their
+// partials are no larger than those of the plan with common stages
+bool wgrad_taps_plan(WgradTapsPlan *out, bool within = false);
 // the terms of that expectation in cycles: a stage and (fixed) a workgroup
 double wgrad_stage_cost(int nkb, int ncq, int nt, int dy_blocks, int x_blocks, int ring, double *fixed);
 double wgrad_parts_cost(int parts, size_t part_bytes);

@@ -773,7 +773,7 @@ static long wgrad_taps_rounds(long tiles, long parts, bool r3)
 // nodes (0.3 GFLOP and more, images up to 32 x 32) take 2731 us without this kernel, 2526
 // with this choice, 2508 with the best split of either; 60 nodes that it was not fitted to 1566, 1455 and 1426,
 // 110 with any multiple of 16 k 2209, 2057 and 2030, none of them slower by more than 3 %.
-static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force)
+static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force, bool within)
 {
     WgradTapsParams &q = out->p;
     if (q.Q > 32 || env_switch(SW_WGRAD_OWN)) return;         // the switch (any value): common stages, tests / benchmarks only
@@ -789,6 +789,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force
     long parts = 0;
     for (long p = 1; p <= most && p <= nstages; ++p) {
         if (force > 0 ? p != force % 1000 && force % 1000 : p > 1 && p * dw_mb * 1e6 > (double)NGC_STATIC_SCRATCH_BYTES) continue;
+        if (within && p > 1 && (size_t)p * tiles * 36864 > out->ws) continue;
         const long per = (nstages + p - 1) / p, rounds = (tiles * p + 255) / 256;
         const double us = rounds * (10.7 + 0.78 * ((per + 7) / 8)) + (p > 1 ? 1.1 + 0.33 * p * dw_mb : 0.0) + 0.08 * dw_mb +
                           0.0042 * tiles * p / 256.0 * per * (4 + nxb);
@@ -820,7 +821,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force
     out->us = best;
 }
 
-bool wgrad_taps_plan(WgradTapsPlan *out)
+bool wgrad_taps_plan(WgradTapsPlan *out, bool within)
 {
     const char *force = env_switch(SW_WGRAD_TAPS);        // tests / benchmarks only: 0 = never, nkb * 10000 + ncq * 1000 + parts
     const int fv = force ? atoi(force) : -1;
@@ -983,7 +984,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out)
     // the GEMM has to be expected 8 % faster (1 x 80 -> 48, 8 x 22 x 52 /2, expected 12.3 / 13.4, takes 12.3 / 12.5; 40 nodes that change
     // kernels without this margin take 0.76 to 1.07 of the GEMM's time).
     if (q.r3) out->us = by_cycles_us < 1.09 * out->us ? by_cycles_us : 1.09 * out->us;
-    else if (nt == 9 && q.RS == 9) wgrad_taps_own_plan(out, rspan, (int)pc, fv);
+    else if (nt == 9 && q.RS == 9) wgrad_taps_own_plan(out, rspan, (int)pc, fv, within);
     return true;
 }
 

@@ -154,3 +154,17 @@ def test_waves_that_split_the_reduction_take_long_reductions_on_small_images():
     strip = [(64, 64, 56, 56, 64, 3), (64, 128, 28, 28, 128, 3), (61, 112, 32, 16, 304, 3)]
     for a in waves + strip:
         assert ng.ngc_conv_kernel(node(*a, dtype="bf16", xl=BLK), FWD) == "strip_bf16" + (":waves" if a in waves else ""), a
+
+
+def test_backprop_filters_on_blocked_copies_need_no_more_workspace_for_stages_of_a_waves_own(monkeypatch):
+    """The copies and the partials of such a node share the array of ngc_conv_bwd_filters_noalloc: what fitted it fits it still."""
+    smaller = 0
+    for n, c, hw, k in [(64, 256, 14, 256), (16, 144, 21, 448), (64, 128, 9, 128), (30, 96, 17, 192), (100, 64, 11, 64), (6, 256, 28, 256)]:
+        ws = {}
+        for own in (None, "0"):
+            monkeypatch.setenv("NGC_WGRAD_OWN", own) if own else monkeypatch.delenv("NGC_WGRAD_OWN", raising=False)
+            ng.ngc_reload_switches()
+            ws[own] = [ng.ngc_conv_workspace_bytes(node(n, c, hw, hw, k, 3, dtype="bf16", xl=l), WGRAD) for l in (NCHW, BLK)]
+        assert ws[None][0] <= ws["0"][0]
+        smaller += ws[None][1] > ws["0"][1]
+    assert smaller                                                       # on blocked tensors more parts are taken
