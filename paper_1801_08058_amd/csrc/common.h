@@ -17,8 +17,9 @@
 // Cache policy of the stores of result tensors (buffer-store aux bits / non-temporal flag).  A result is written once
 // and not read again by the kernel that writes it; where a kernel's stores cover whole cache lines (every pixel of the
 // tensor, i.e. output pixel stride 1) they are marked as streaming, so they leave the L2 as they are written instead of
-// when the kernel ends (headline 3x3 layer: forward 18.9 -> 17.4 us).  Strided backprop-data writes every other pixel
-// per launch or per store instruction and keeps ordinary stores (streaming partial lines doubles its time).
+// when the kernel ends (headline 3x3 layer: forward 18.9 -> 17.4 us).  Strided backprop-data that writes every other pixel
+// per launch or per store instruction keeps ordinary stores (streaming partial lines doubles its time); where it writes whole
+// lines see SibLanes.
 // The buffer stores also carry the system-scope bit (aux 16: written through; another 2-4 % on the strip and stem
 // kernels).  NGC_ST_AUX = 0: ordinary stores everywhere.
 #ifndef NGC_ST_AUX
@@ -225,8 +226,16 @@ __device__ __forceinline__ uint4 lane_pair_exchange(uint32_t q0, uint32_t q1, ui
 // A lane that stores its 16 bytes (8 channels of a pixel) and zeros to the three others leaves every line to four instructions
 // that cover a quarter of it.  Instead a wave passes the 32 positions of a 16-channel block through 1 KB of LDS, and a store
 // covers 1 KB of a row: pixels (2i, 2j) and (2i, 2j + 1) of 16 positions, zeros included, then the zeros of the row below.
-// Whole lines, so they can be streaming stores.  Stride 2, four partial stores / here, us: 256 <- 512 channels at 56x56, 64 images
-// 38.6 / 32.1, 16 images 20.2 / 12.5; 128 <- 256, 64 images 21.4 / 14.9; 512 <- 256 at 28x28 17.7 / 14.2.
+// The stores are whole lines.  Large results stream; small ones (SIB_KEEP_BYTES) are written through without the streaming bit, which
+// takes them past the memory-side cache, where the next backward call finds them.  Four partial stores / streaming / written through, us,
+// backprop-data and -filters of the strided layer, and with those of the 1x1 layer below, which read dx, behind them:
+//   256 <- 512 channels, 56x56,   4 images (6.4 MB)  29.1 / 23.0 / 23.0 and  47.0 /  38.7 /  38.2
+//   512 <- 1024,         28x28,  32 images (26 MB)   49.4 / 46.0 / 46.2 and  79.3 /  79.9 /  76.4
+//   1024 <- 2048,        14x14,  64 images (26 MB)   72.0 / 69.0 / 70.1 and 111.0 / 117.1 / 108.6
+//   512 <- 1024,         28x28,  64 images (51 MB)   72.4 / 66.9 / 68.4 and 108.1 / 107.9 / 106.1 (with forward in front 88.5 / 90.9)
+//   256 <- 512,          56x56,  64 images (103 MB)  79.5 / 78.6 / 74.7 and 139.3 / 135.5 / 134.7 (102.7 / 106.3)
+//   256 <- 512,          56x56, 128 images (206 MB) 157.9 / 143.2 / 150.0 and 261.9 / 240.7 / 255.2
+constexpr size_t SIB_KEEP_BYTES = (size_t)32 << 20;
 struct SibLanes {
     unsigned even[2], odd[2];          // byte offset of this lane's 16 bytes in block 0: rows 2i and 2i + 1 of position 16 u + lane / 4
     __device__ __forceinline__ void place(int u, int lane, bool live, unsigned pixel, int oh, int ow, int Hout, int Wout)
@@ -235,8 +244,9 @@ struct SibLanes {
         even[u] = live && (!right || ow + 1 < Wout) ? pixel + (unsigned)(lane & 3) * 16 : 0x80000000u;
         odd[u] = even[u] != 0x80000000u && oh + 1 < Hout ? even[u] + (unsigned)Wout * 32u : 0x80000000u;
     }
-    // o: channels 8 (lane / 32) + 0 .. 7 of position lane % 32; block: byte offset of the channel block
-    __device__ __forceinline__ void store(unsigned char *lds, int lane, uint4 o, __amdgpu_buffer_rsrc_t rs, bool live, unsigned block)
+    // o: channels 8 (lane / 32) + 0 .. 7 of position lane % 32; block: byte offset of the channel block; stream (wave-uniform): past the
+    // memory-side cache
+    __device__ __forceinline__ void store(unsigned char *lds, int lane, uint4 o, __amdgpu_buffer_rsrc_t rs, bool live, unsigned block, bool stream)
     {
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         const u32x4 zero = {0, 0, 0, 0}, ov = {o.x, o.y, o.z, o.w};
@@ -247,8 +257,14 @@ struct SibLanes {
         for (int u = 0; u < 2; ++u) {
             u32x4 v = *reinterpret_cast<const u32x4 *>(lds + (16 * u + (lane >> 2)) * 32 + (lane & 1) * 16);
             if (lane & 2) v = zero;
-            __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(live && even[u] != 0x80000000u ? even[u] + block : 0x80000000u), 0, NGC_ST_AUX);
-            __builtin_amdgcn_raw_buffer_store_b128(zero, rs, (int)(live && odd[u] != 0x80000000u ? odd[u] + block : 0x80000000u), 0, NGC_ST_AUX);
+            const int at = (int)(live && even[u] != 0x80000000u ? even[u] + block : 0x80000000u), below = (int)(live && odd[u] != 0x80000000u ? odd[u] + block : 0x80000000u);
+            if (stream) {
+                __builtin_amdgcn_raw_buffer_store_b128(v, rs, at, 0, NGC_ST_AUX);
+                __builtin_amdgcn_raw_buffer_store_b128(zero, rs, below, 0, NGC_ST_AUX);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b128(v, rs, at, 0, NGC_ST_AUX & 16);
+                __builtin_amdgcn_raw_buffer_store_b128(zero, rs, below, 0, NGC_ST_AUX & 16);
+            }
         }
         asm volatile("" ::: "memory");
     }

@@ -365,7 +365,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NL)) void conv_gemm1x1_bf16(const G
                         }
                     }
                 }
-                if constexpr (SIB) sib.store(mine, lane, o, rs_out, (co_base >> 4) + h < CBout, (unsigned)(((co_base >> 4) + h) * HWout) * 32u);
+                if constexpr (SIB) sib.store(mine, lane, o, rs_out, (co_base >> 4) + h < CBout, (unsigned)(((co_base >> 4) + h) * HWout) * 32u, p.out_bytes > SIB_KEEP_BYTES);
             }
         }
     }

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
                     const unsigned block = (unsigned)(cb * HWout) * 32u;
                     const bool live = cb < CBout;                        // wave-uniform
                     if constexpr (SIB) {
-                        sib.store(mine, lane, o, rs_out, live, block);
+                        sib.store(mine, lane, o, rs_out, live, block, false);      // small results (resident1x1_takes)
                     } else {
                         const ngc_u32x4 ov = {o.x, o.y, o.z, o.w};
                         __builtin_amdgcn_raw_buffer_store_b128(ov, rs_out, (int)(live && off0 != R1_OOB ? off0 + block : R1_OOB), 0, NGC_ST_AUX);
