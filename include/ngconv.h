@@ -235,8 +235,9 @@ const char *ngc_conv_variant(const ngc_conv_desc *desc, int op);
 /* The same name with the kernel that runs behind the colon for every op: also "strip_bf16:few" and "gemm1x1_bf16:few" for
  * backprop-data, and "direct:stream" for the nodes of "direct:gather" whose operands go straight to registers
  * (backprop-filters: with the workspace that ngc_conv_workspace_bytes asks for), and "gemm1x1_bf16:resident" for the 1x1
- * nodes whose filters stay in registers (backprop-data: without the compounds, which run the GEMM), and "strip_bf16:waves" for
- * multi-tap nodes whose waves split the reduction.  Host only. */
+ * nodes whose filters stay in registers (backprop-data: without the compounds, which run the GEMM), "strip_bf16:waves" for
+ * multi-tap nodes whose waves split the reduction, and "wgrad_gemm_bf16:taps_own" and "wgrad_strip_bf16:taps_own" for the
+ * backprop-filters nodes of ":taps" whose waves take stages of their own.  Host only. */
 const char *ngc_conv_kernel(const ngc_conv_desc *desc, int op);
 
 /* ---- Convolution over three spatial axes (N, C, D, H, W) --------------------------------------

@@ -1569,6 +1569,15 @@ static size_t workspace_of(const ngc_conv_desc *desc, int op, bool part)
 
 size_t ngc_conv_workspace_bytes(const ngc_conv_desc *desc, int op) { return workspace_of(desc, op, false); }
 
+// a node of several taps per pass whose waves have stages of their own
+static bool wgrad_taps_own(const ngc_conv_desc *d, bool part)
+{
+    int P, Q;
+    if (validate(d, &P, &Q) != NGC_OK) return false;
+    const WgradTapsPlan *tp = wgrad_taps_plan_of(d, P, Q, part);
+    return tp && tp->own;
+}
+
 // kernel: the kernel behind the colon wherever one takes some of a variant's nodes (ngc_conv_kernel)
 static const char *variant_name(const ngc_conv_desc *desc, int op, bool part, bool kernel)
 {
@@ -1607,9 +1616,9 @@ static const char *variant_name(const ngc_conv_desc *desc, int op, bool part, bo
     case V_STRIP_FEW: return kernel || op == NGC_OP_FWD ? "strip_bf16:few" : "strip_bf16";
     case V_GEMM1X1_FEW: return kernel || op == NGC_OP_FWD ? "gemm1x1_bf16:few" : "gemm1x1_bf16";
     case V_WGRAD_STRIP_TAPS_PART:
-    case V_WGRAD_STRIP_TAPS: return "wgrad_strip_bf16:taps";
+    case V_WGRAD_STRIP_TAPS: return kernel && wgrad_taps_own(desc, part) ? "wgrad_strip_bf16:taps_own" : "wgrad_strip_bf16:taps";
     case V_WGRAD_GEMM_TAPS_PART:
-    case V_WGRAD_GEMM_TAPS: return "wgrad_gemm_bf16:taps";
+    case V_WGRAD_GEMM_TAPS: return kernel && wgrad_taps_own(desc, part) ? "wgrad_gemm_bf16:taps_own" : "wgrad_gemm_bf16:taps";
     case V_IGEMM_128: return "igemm_bf16_128x128";
     case V_IGEMM_64: return "igemm_bf16_256x64";
     case V_WGRAD_64: return "wgrad_bf16_64x64";

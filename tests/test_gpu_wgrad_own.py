@@ -26,7 +26,7 @@ CASES = [
     (Attrs(4, 16, 6, 6, 64, 3, 3, 1, 1, 1, 1, 0, 0, 0, 0), (1,)),                # no padding: 16 positions, whole images
     (Attrs(2, 16, 3, 21, 64, 1, 9, 1, 1, 1, 1, 0, 4, 0, 4), (1, 2)),             # nine taps in a row
     (Attrs(6, 32, 7, 7, 80, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 3)),              # a tile of k with one 16-channel block
-    (Attrs(3, 16, 10, 12, 112, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 2, 16)),       # ... with three
+    (Attrs(3, 16, 10, 12, 112, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 2, 15)),       # ... with three; a stage a part
     (Attrs(40, 32, 7, 7, 192, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1), (1, 5)),            # the rings go round
 ]
 
@@ -41,6 +41,7 @@ def test_own_stages(case, parts, monkeypatch):
     run = Run(a, "bf16", BLK, BLK, True)
     dw = run.bwd_filters(x, dy)
     assert ng.ngc_conv_variant(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16:taps"
+    assert ng.ngc_conv_kernel(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16:taps_own"
     assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
 
 
@@ -54,8 +55,10 @@ def test_own_stages_special_values(monkeypatch):
     monkeypatch.setenv("NGC_WGRAD_TAPS", "41001")
     run = Run(a, "bf16", BLK, BLK, True)
     own = run.bwd_filters(x, dy)
+    assert ng.ngc_conv_kernel(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16:taps_own"
     monkeypatch.setenv("NGC_WGRAD_OWN", "0")
     common = run.bwd_filters(x, dy)
+    assert ng.ngc_conv_kernel(run.last_desc, ng.NGC_OP_BWD_FILTERS) == "wgrad_gemm_bf16:taps"
     assert np.isnan(common).any() and np.isfinite(common).any()
     assert np.array_equal(np.isnan(own), np.isnan(common)) and np.array_equal(np.isinf(own), np.isinf(common))
 
