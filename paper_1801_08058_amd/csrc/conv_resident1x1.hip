@@ -7,7 +7,7 @@
 // anew, and where several channel tiles share an activation tile their rings hold the same lines, so few of the bytes in flight
 // are new ones.  Here a workgroup (8 waves, one a compute unit) holds the filters of all output channels as MFMA operands, at most
 // 128 registers a wave, and takes an equal share of the positions: the activations come through LDS once, a ring of 64 KB that
-// runs on over the tiles, the results leave straight from the registers.  A wave multiplies 32 FC channels by 32 PF positions;
+// runs on over the tiles, the results leave straight from the registers.  A wave multiplies 32 FC channels by 32 positions;
 // WN waves lie side by side over the channels, 8 / WN over the positions.  Products are added in the order of the GEMM: the
 // results are the same bits.
 //
@@ -32,10 +32,9 @@ struct Resident1x1Params {
 template <int KS, int WN>
 struct ResidentTile {
     static constexpr int FC = KS == 32 ? 1 : 2;                          // 32-channel fragments of a wave
-    static constexpr int PF = WN == 8 && KS == 4 ? 2 : 1;                // 32-position groups of a wave
-    static constexpr int WM = 8 / WN, NPG = WM * PF, T = 32 * NPG;       // positions of a tile
+    static constexpr int WM = 8 / WN, T = 32 * WM;                       // waves over the positions, positions of a tile
     static constexpr int LPW = (WN == 1 ? 2 : 1) * (KS == 32 && WN <= 2 ? 2 : 1);                          // loads per wave and slice
-    static constexpr int KSL = LPW * 8 / NPG, NSL = KS / KSL;            // 16-channel steps of a slice, slices of a tile
+    static constexpr int KSL = LPW * 8 / WM, NSL = KS / KSL;             // 16-channel steps of a slice, slices of a tile
     static constexpr int SLICE = LPW * 8192, NS = 65536 / SLICE + 1;     // ring buffers
     static constexpr size_t LDS = (size_t)NS * SLICE + 32 * FC * WN * 4, LDS_SIB = LDS + 8 * 1024;      // ring, bias; a block of results per wave
     static_assert(KS % KSL == 0, "slices of a tile");
@@ -46,7 +45,7 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
 {
     preload_kernargs(rp);
     typedef ResidentTile<KS, WN> G;
-    constexpr int FC = G::FC, PF = G::PF, WM = G::WM, NPG = G::NPG, T = G::T, LPW = G::LPW, KSL = G::KSL, NSL = G::NSL, SLICE = G::SLICE, NS = G::NS;
+    constexpr int FC = G::FC, WM = G::WM, T = G::T, LPW = G::LPW, KSL = G::KSL, NSL = G::NSL, SLICE = G::SLICE, NS = G::NS;
     const Gemm1x1Params &p = rp.g;
     extern __shared__ __align__(16) unsigned char smem[];
     float *bias_lds = reinterpret_cast<float *>(smem + NS * SLICE);
@@ -67,14 +66,13 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
     const __amdgpu_buffer_rsrc_t rs_wt = __builtin_amdgcn_make_buffer_rsrc((void *)p.wt, 0, (int)p.wt_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_out = __builtin_amdgcn_make_buffer_rsrc((void *)p.out, 0, (int)p.out_bytes, 0x00020000);
 
-    // ---- loads: piece q = wave + 8 i of a slice is position group q % NPG, 16-channel step q / NPG of it; lanes 0 .. 31 bring
+    // ---- loads: piece q = wave + 8 i of a slice is position group q % WM, 16-channel step q / WM of it; lanes 0 .. 31 bring
     // the first 8 channels of the 32 positions, lanes 32 .. 63 the others, so the wave that multiplies reads them in lane order
-    const int pg = wave % NPG;
     int itile = 0, islice = 0, ibuf = 0;
     unsigned voff = R1_OOB;
     auto issue = [&]() {
         if (islice == 0) {
-            const uint32_t m = first + (uint32_t)(itile * T + pg * 32 + l32);
+            const uint32_t m = first + (uint32_t)(itile * T + wm * 32 + l32);
             const uint32_t mm = m < end ? m : first;
             const uint32_t n = fd_div(mm, p.div_pq);
             const uint32_t rem = mm - n * p.div_pq.d;
@@ -87,7 +85,7 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const int q = wave + 8 * i;
-            const int cb = islice * KSL + q / NPG;
+            const int cb = islice * KSL + q / WM;
             const bool live = cb < CBin;                                 // wave-uniform
             dma_load_lds16(rw_in, smem + ibuf * SLICE + q * 1024, live ? voff : R1_OOB, live ? (unsigned)(cb * HWin * 32) : 0u);
         }
@@ -114,13 +112,13 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 
     const bool relu_b = p.relu != 0;
-    constexpr int ST = 2 * FC * PF * (SIB ? 4 : 1);                      // stores per wave and tile
+    constexpr int ST = 2 * FC * (SIB ? 4 : 1);                           // stores per wave and tile
     unsigned char *const mine = smem + NS * SLICE + 32 * FC * WN * 4 + wave * 1024;
 
     int g = 0, buf = 0;
     int since = 0, osl = 0;            // tiles stored since the loads of slice g were issued; slice of the iteration that issued them
     for (int t = 0; t < ntiles; ++t) {
-        f32x16 acc[FC][PF];
+        f32x16 acc[FC];
 #pragma unroll
         for (int f = 0; f < FC; ++f)
 #pragma unroll
@@ -128,10 +126,7 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
                 // bias_lds is written before the first barrier: the first tile takes it behind that one
                 if (t == 0 && f == 0 && j == 0) wg_barrier_nofence();
                 const float4 b4 = *reinterpret_cast<const float4 *>(bias_lds + co0 + 32 * f + 8 * j + 4 * lg);
-#pragma unroll
-                for (int b = 0; b < PF; ++b) {
-                    acc[f][b][4 * j] = b4.x; acc[f][b][4 * j + 1] = b4.y; acc[f][b][4 * j + 2] = b4.z; acc[f][b][4 * j + 3] = b4.w;
-                }
+                acc[f][4 * j] = b4.x; acc[f][4 * j + 1] = b4.y; acc[f][4 * j + 2] = b4.z; acc[f][4 * j + 3] = b4.w;
             }
 #pragma unroll
         for (int sl = 0; sl < NSL; ++sl) {
@@ -143,16 +138,13 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             wg_barrier_nofence();                                        // slice g complete; the buffer of slice g - 1 is free
             if (g + NS - 1 < total) issue();
-            const unsigned char *xs = smem + buf * SLICE + (wm * PF) * 1024 + lane * 16;
+            const unsigned char *xs = smem + buf * SLICE + wm * 1024 + lane * 16;
             buf = buf + 1 == NS ? 0 : buf + 1;
 #pragma unroll
             for (int kk = 0; kk < KSL; ++kk) {
+                const bf16x8 xb = *reinterpret_cast<const bf16x8 *>(xs + kk * WM * 1024);
 #pragma unroll
-                for (int b = 0; b < PF; ++b) {
-                    const bf16x8 xb = *reinterpret_cast<const bf16x8 *>(xs + (kk * NPG + b) * 1024);
-#pragma unroll
-                    for (int f = 0; f < FC; ++f) acc[f][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[f][sl * KSL + kk], xb, acc[f][b], 0, 0, 0);
-                }
+                for (int f = 0; f < FC; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[f][sl * KSL + kk], xb, acc[f], 0, 0, 0);
             }
             // the next slice's loads were issued in iteration g + 2 - NS (or before the first)
             if (sl == nsl - 1) ++since;
@@ -168,53 +160,50 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
             }
         }
         // ---- ReLU (bias is in the accumulators), one RNE rounding, lane-pair exchange, 16-byte stores
+        const uint32_t m0 = first + (uint32_t)(t * T + wm * 32);
+        // byte offset of the 16-channel block 0 of a position's output pixel
+        auto pixel = [&](uint32_t m) {
+            const uint32_t mm = m < end ? m : first;
+            const uint32_t n = fd_div(mm, p.div_pq);
+            const uint32_t rem = mm - n * p.div_pq.d;
+            const uint32_t i = fd_div(rem, p.div_q);
+            const uint32_t j = rem - i * p.div_q.d;
+            const int oh = (int)i * p.os_h + p.oa_h, ow = (int)j * p.os_w + p.oa_w;
+            struct { unsigned off; int oh, ow; } r = {(unsigned)((int)n * CBout * HWout + oh * p.Wout + ow) * 32u, oh, ow};
+            return r;
+        };
+        unsigned off0 = R1_OOB;
+        SibLanes sib;
+        if constexpr (!SIB) {
+            if (m0 + l32 < end) off0 = pixel(m0 + l32).off + lg * 16;
+        } else {
 #pragma unroll
-        for (int b = 0; b < PF; ++b) {
-            const uint32_t m0 = first + (uint32_t)(t * T + (wm * PF + b) * 32);
-            // byte offset of the 16-channel block 0 of a position's output pixel
-            auto pixel = [&](uint32_t m) {
-                const uint32_t mm = m < end ? m : first;
-                const uint32_t n = fd_div(mm, p.div_pq);
-                const uint32_t rem = mm - n * p.div_pq.d;
-                const uint32_t i = fd_div(rem, p.div_q);
-                const uint32_t j = rem - i * p.div_q.d;
-                const int oh = (int)i * p.os_h + p.oa_h, ow = (int)j * p.os_w + p.oa_w;
-                struct { unsigned off; int oh, ow; } r = {(unsigned)((int)n * CBout * HWout + oh * p.Wout + ow) * 32u, oh, ow};
-                return r;
-            };
-            unsigned off0 = R1_OOB;
-            SibLanes sib;
-            if constexpr (!SIB) {
-                if (m0 + l32 < end) off0 = pixel(m0 + l32).off + lg * 16;
-            } else {
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t m = m0 + 16 * u + (lane >> 2);
+                const auto px = pixel(m);
+                sib.place(u, lane, m < end, px.off, px.oh, px.ow, p.Hout, p.Wout);
+            }
+        }
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const uint32_t m = m0 + 16 * u + (lane >> 2);
-                    const auto px = pixel(m);
-                    sib.place(u, lane, m < end, px.off, px.oh, px.ow, p.Hout, p.Wout);
+        for (int f = 0; f < FC; ++f)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x16 &v = acc[f];
+                const uint32_t q0 = relu_bf16x2(pack_bf16x2_hw(v[8 * h], v[8 * h + 1]), relu_b);
+                const uint32_t q1 = relu_bf16x2(pack_bf16x2_hw(v[8 * h + 2], v[8 * h + 3]), relu_b);
+                const uint32_t q2 = relu_bf16x2(pack_bf16x2_hw(v[8 * h + 4], v[8 * h + 5]), relu_b);
+                const uint32_t q3 = relu_bf16x2(pack_bf16x2_hw(v[8 * h + 6], v[8 * h + 7]), relu_b);
+                const uint4 o = lane_pair_exchange(q0, q1, q2, q3);
+                const int cb = (co0 >> 4) + 2 * f + h;
+                const unsigned block = (unsigned)(cb * HWout) * 32u;
+                const bool live = cb < CBout;                            // wave-uniform
+                if constexpr (SIB) {
+                    sib.store(mine, lane, o, rs_out, live, block, false);      // small results (resident1x1_takes)
+                } else {
+                    const ngc_u32x4 ov = {o.x, o.y, o.z, o.w};
+                    __builtin_amdgcn_raw_buffer_store_b128(ov, rs_out, (int)(live && off0 != R1_OOB ? off0 + block : R1_OOB), 0, NGC_ST_AUX);
                 }
             }
-#pragma unroll
-            for (int f = 0; f < FC; ++f)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x16 &v = acc[f][b];
-                    const uint32_t q0 = relu_bf16x2(pack_bf16x2_hw(v[8 * h], v[8 * h + 1]), relu_b);
-                    const uint32_t q1 = relu_bf16x2(pack_bf16x2_hw(v[8 * h + 2], v[8 * h + 3]), relu_b);
-                    const uint32_t q2 = relu_bf16x2(pack_bf16x2_hw(v[8 * h + 4], v[8 * h + 5]), relu_b);
-                    const uint32_t q3 = relu_bf16x2(pack_bf16x2_hw(v[8 * h + 6], v[8 * h + 7]), relu_b);
-                    const uint4 o = lane_pair_exchange(q0, q1, q2, q3);
-                    const int cb = (co0 >> 4) + 2 * f + h;
-                    const unsigned block = (unsigned)(cb * HWout) * 32u;
-                    const bool live = cb < CBout;                        // wave-uniform
-                    if constexpr (SIB) {
-                        sib.store(mine, lane, o, rs_out, live, block, false);      // small results (resident1x1_takes)
-                    } else {
-                        const ngc_u32x4 ov = {o.x, o.y, o.z, o.w};
-                        __builtin_amdgcn_raw_buffer_store_b128(ov, rs_out, (int)(live && off0 != R1_OOB ? off0 + block : R1_OOB), 0, NGC_ST_AUX);
-                    }
-                }
-        }
     }
 }
 
@@ -234,14 +223,18 @@ static hipError_t launch_resident(const Gemm1x1Params &p, hipStream_t st)
     return launch_result();
 }
 
-// Nodes it is expected to run faster than the GEMM, from 1150 launches at stride 2 and 250 at stride 1 (where it is level or
-// slower).  GEMM / here, us.  Backprop-data: up to 2 million results of lattice positions (4 x 56x56, 256 <- 512 11.4 / 6.9, 3570 positions
-// 256 <- 464 13.5 / 8.4; above, the GEMM's tiles fill the chip: 30 x 55x55, 128 <- 304 11.9 / 12.4), except 64 channels or fewer from more than
-// 128 (64 <- 144, 5916 positions 6.4 / 7.1): 0.87 of the time over 413 nodes, 1.2 at worst.  Forward: reductions of more than 208
-// channels whose output channels leave the GEMM 64-channel tiles, so that one of 256 positions is all a workgroup has (416 -> 192,
-// 1456 positions 10.6 / 6.1; 400 -> 32, 10506 15.2 / 8.2; 256 -> 64, 13986 10.8 / 8.2; with 128-channel tiles 240 -> 128, 5040 5.6 / 7.4), and
-// large nodes whose activations the GEMM reads for several channel tiles (368 -> 256, 30400 18.9 / 15.0; 96 -> 432, 26754 11.7 / 8.9 is
-// left out with 48 -> 160, 71214 10.5 / 8.3: 32 -> 128, 56661 6.7 / 7.3): 46 of 447 nodes, 0.69 of their time, 1.1 at worst.
+// Nodes it is expected to run faster than the GEMM.  GEMM / here, us, operands from memory; m: positions.  Backprop-data (stride 2 x 2; 366
+// drawn nodes, a graph of calls): up to 1.6 million results of lattice positions (256 <- 512, m 3136 13.3 / 7.6; 80 <- 400, m 12240
+// 14.0 / 9.0; above, the GEMM's tiles fill the chip: 192 <- 288, m 10143 10.2 / 11.2), of channels whose filters pay for being fetched by
+// every workgroup: more than 64 from more than 64 (48 <- 112, m 32490 7.5 / 8.3; 32 <- 208, m 45849 9.6 / 15.1), up to 256 (352 <- 48, m 5236
+// 5.4 / 6.3; 368 <- 176, m 4805 7.1 / 8.0), 512 only from 65 to 128 (0.76 to 0.91 of the time).  What is taken has 0.83 of the GEMM's
+// time, 1.05 at worst.  Forward, columns strided (rows alone, 496 -> 144, m 18496 11.2 / 13.8: the GEMM reads whole lines there):
+// reductions of more than 208 channels whose output channels leave the GEMM 64-channel tiles, so that one of 256 positions is all a
+// workgroup has (416 -> 192, m 1456 10.6 / 6.1; 400 -> 32, m 10506 15.2 / 8.2; 256 -> 64, m 13986 10.8 / 8.2; with 128-channel tiles
+// 240 -> 128, m 5040 5.6 / 7.4), and large nodes whose activations the GEMM reads for several channel tiles (368 -> 256, m 30400
+// 18.9 / 15.0; 96 -> 432, m 26754 11.7 / 8.9 is left out with 48 -> 160, m 71214 10.5 / 8.3: 32 -> 128, m 56661 6.7 / 7.3): 0.69 of the
+// time of the 72 of 834 drawn nodes that are taken, strides up to 4, 1.03 at worst.  500 nodes of either direction that are taken and were
+// not part of that: 0.77 of the time, one above 1.05 (160 <- 320, m 8712 8.5 / 9.4).
 bool resident1x1_takes(const Gemm1x1Params &p)
 {
     const char *force = env_switch(SW_RESIDENT);                         // tests only: 0 = never, 1 = all it can
@@ -251,9 +244,10 @@ bool resident1x1_takes(const Gemm1x1Params &p)
     const bool sib = gemm1x1_siblings(p);
     if (p.os_h * p.os_w > 1 && !sib) return false;
     if (!(p.Cin <= 256 ? p.Cout <= 512 : p.Cin <= 512 && p.Cout <= 256)) return false;
+    if (sib && (p.Cin <= 64 ? p.Cout > 256 : p.Cout <= 64 || (p.Cin > 128 && p.Cout > 256))) return false;
     if (force) return true;
-    if (sib) return (uint64_t)p.M * p.Cout < 2000000 && !(p.Cin > 128 && p.Cout <= 64);
-    if (p.is_h == 1 && p.is_w == 1) return false;
+    if (sib) return (uint64_t)p.M * p.Cout < 1600000;
+    if (p.is_w == 1) return false;
     return (p.Cin > 208 && !gemm1x1_wide_tiles(p)) || (p.Cin >= 176 && p.Cout > 128 && p.M >= 24000);
 }
 
@@ -264,17 +258,13 @@ hipError_t launch_resident1x1(const Gemm1x1Params &p, hipStream_t st)
         if (p.Cin <= 64) {
             if (p.Cout <= 64) return launch_resident<4, 1, true>(p, st);
             if (p.Cout <= 128) return launch_resident<4, 2, true>(p, st);
-            return p.Cout <= 256 ? launch_resident<4, 4, true>(p, st) : launch_resident<4, 8, true>(p, st);
+            return launch_resident<4, 4, true>(p, st);
         }
         if (p.Cin <= 128) {
-            if (p.Cout <= 64) return launch_resident<8, 1, true>(p, st);
             if (p.Cout <= 128) return launch_resident<8, 2, true>(p, st);
             return p.Cout <= 256 ? launch_resident<8, 4, true>(p, st) : launch_resident<8, 8, true>(p, st);
         }
-        if (p.Cin <= 256) {
-            if (p.Cout <= 128) return launch_resident<16, 2, true>(p, st);
-            return p.Cout <= 256 ? launch_resident<16, 4, true>(p, st) : launch_resident<16, 8, true>(p, st);
-        }
+        if (p.Cin <= 256) return p.Cout <= 128 ? launch_resident<16, 2, true>(p, st) : launch_resident<16, 4, true>(p, st);
         return p.Cout <= 128 ? launch_resident<32, 4, true>(p, st) : launch_resident<32, 8, true>(p, st);
     }
     if (p.Cin <= 256) {

@@ -148,6 +148,17 @@ def test_resident_filters_choice(c, k, h, n, op, taken):
     assert ng.ngc_conv_kernel(d, op).endswith(":resident") == taken
 
 
+def test_resident_filters_leave_nodes_to_the_gemm_that_it_runs_faster():
+    """1x1 nodes that were timed with both kernels, a tenth or more apart: strides, channels of x and y, positions."""
+    fwd = [((2, 1), 496, 144, 18496, False), ((2, 1), 400, 160, 19778, False), ((1, 2), 496, 144, 18496, True)]
+    bwd = [((2, 2), 352, 48, 5236, False), ((2, 2), 480, 16, 3072, False), ((2, 2), 368, 176, 4805, False), ((2, 2), 192, 288, 10143, False),
+           ((2, 2), 64, 80, 27848, False), ((2, 2), 80, 400, 12240, True), ((2, 2), 208, 240, 7290, True), ((2, 2), 256, 48, 3600, True)]
+    for op, wl, nodes in ((FWD, ng.NGC_BLOCKED_FWD, fwd), (BWD, ng.NGC_BLOCKED_BWD, bwd)):
+        for stride, c, k, m, taken in nodes:
+            d = ng.make_desc(1, c, stride[0], stride[1] * m, k, 1, 1, stride, w_layout=wl)
+            assert ng.ngc_conv_kernel(d, op) == "gemm1x1_bf16" + (":resident" if taken else ""), (stride, c, k, m)
+
+
 def test_waves_that_split_the_reduction_take_long_reductions_on_small_images():
     """Nodes that were timed with both kernels, on either side of the choice."""
     waves = [(128, 512, 7, 7, 512, 3), (32, 512, 14, 14, 512, 3), (77, 256, 15, 9, 416, 5)]
