@@ -1263,6 +1263,27 @@ double staged_fwd_bwd_us(const ngc_conv_desc *d, int op, Variant v, int P, int Q
     return few_strip_us(wgs, stages, taps, nf);
 }
 
+// What the strip kernel is expected to take on a node of one class of taps, us, operands from memory, against conv_waves_plan's own
+// expectation: stages of 16 input channels in rounds of workgroups, of as many to a compute unit as its LDS holds where that is more than
+// one, and the bytes: what the workgroups of a strip's channel tiles read, what is written.  Fitted to 1341 launches of drawn nodes, nine
+// tenths within 10 % (one workgroup to a compute unit), 14 % (several), 24 % (strided forward).  0: column tiles, no estimate.
+double strip_node_us(const ngc_conv_desc *d, int op, int P, int Q)
+{
+    StripParams sp;
+    int nf;
+    size_t lds;
+    bool empty;
+    if (!strip_plan_class(d, op, 0, 0, P, Q, &sp, &nf, &lds, &empty) || empty || sp.ncolt > 1) return 0.0;
+    const int nk = (sp.Cout + 63) / 64, together = lds * 4 <= LDS_LIMIT ? 4 : lds * 3 <= LDS_LIMIT ? 3 : lds * 2 <= LDS_LIMIT ? 2 : 1;
+    const long wgs = (long)sp.groups * sp.strips * nk, rounds = (wgs + NUM_CUS - 1) / NUM_CUS, full = (wgs + NUM_CUS * together - 1) / (NUM_CUS * together);
+    const double stages = sp.Cin / 16, taps = sp.ntaps, share = wgs > NUM_CUS ? (double)wgs / NUM_CUS : 1.0;
+    const double in_mb = 2e-6 * sp.N * sp.Cin * sp.Hin * sp.Win, out_mb = 2e-6 * sp.N * sp.Cout * (op == NGC_OP_FWD ? P * Q : d->h * d->w);
+    if (d->stride_h > 1 || d->stride_w > 1)
+        return 3.42 + stages * (share * (0.161 + taps * (0.0211 + 0.0172 * nf)) + rounds * taps * nf * 0.0199) + 0.0624 * nk * in_mb + 0.1875 * out_mb;
+    if (together == 1) return 1.43 + rounds * (1.74 + stages * (0.334 + taps * (0.0365 + 0.0228 * nf))) + 0.101 * nk * in_mb + 0.2215 * out_mb;
+    return 3.02 + stages * (rounds * (0.0055 + 0.0314 * taps * nf) + full * (0.1075 + 0.0296 * taps)) + 0.0869 * nk * in_mb + 0.2935 * out_mb;
+}
+
 // plan of a node of V_STRIP_WAVES
 bool waves_plan(const ngc_conv_desc *d, int op, int P, int Q, ConvWavesParams *out)
 {
@@ -1291,7 +1312,7 @@ Variant pick_uncached(const ngc_conv_desc *d, int op, bool part)
     if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && (v == V_STRIP || v == V_GEMM1X1) && blocked_bf16(d) &&
         conv_few_plan(d, op, P, Q, staged_fwd_bwd_us(d, op, v, P, Q), nullptr))
         return v == V_STRIP ? V_STRIP_FEW : V_GEMM1X1_FEW;
-    if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && v == V_STRIP && conv_waves_plan(d, op, P, Q, staged_fwd_bwd_us(d, op, v, P, Q), nullptr))
+    if ((op == NGC_OP_FWD || op == NGC_OP_BWD_DATA) && v == V_STRIP && conv_waves_plan(d, op, P, Q, strip_node_us(d, op, P, Q), nullptr))
         return V_STRIP_WAVES;
     if (v == V_WGRAD_GEMM && wgrad_taps_for_gemm(d, P, Q, part)) return part ? V_WGRAD_GEMM_TAPS_PART : V_WGRAD_GEMM_TAPS;
     if (v == V_WGRAD_STRIP && wgrad_taps_for_strip(d, P, Q, part)) return part ? V_WGRAD_STRIP_TAPS_PART : V_WGRAD_STRIP_TAPS;

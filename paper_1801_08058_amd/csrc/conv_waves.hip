@@ -454,12 +454,15 @@ bool conv_waves_plan(const ngc_conv_desc *d, int op, int P, int Q, double staged
         // A switch that shapes the strip kernel, or rules out another one in its favour, asks for it
         for (Switch sw : {SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_BW, SW_STRIP_XCD, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_STRIP_CPS, SW_STRIP_STRIDED, SW_ROWS, SW_FWD_FEW})
             if (env_switch(sw)) return false;
-        // Expected time, us: a start and, per round of workgroups, start, sum and stores and the steps of a wave.  Fitted to 215
-        // launches of nodes of 0.5 GFLOP or more, nine tenths within 6 %.  The strip kernel gains with the size of its strips and of a
-        // launch, this one with the length of the reduction: 25 of the 215 are taken, 0.63 to 1.0 of the strip kernel's time but for
-        // three (57 x 208 -> 416 at 10x27 backwards 45.2 / 54.0), all of them 5212 us against 5294 without and 5189 the better of each.
-        const double rounds = (q.tiles + 255) / 256;
-        if (staged_us == 0.0 || 1.2 + rounds * (4.83 + 0.572 * ((steps + 3) / 4)) >= 0.97 * staged_us) return false;
+        // Expected time, us, operands from memory: a start and, per round of workgroups, start, sum and stores and the steps of a wave;
+        // the bytes: patches loaded, tensors read and written.  Fitted to 1341 launches of drawn nodes (32 MFLOP to 150 GFLOP, both
+        // operands up to 400 MB), nine tenths within 9 %.  The strip kernel gains with the size of its strips and of a launch, this one
+        // with the length of the reduction: 418 of the 1341 are taken, 0.82 of the strip kernel's time, 3 above 1.05 (the worst 85 x 928
+        // -> 464 at 60x10, 1x3, backwards 190.6 / 224.1).  168 of the rest would gain, 7 % of their time; the others lose up to all of it.
+        // 600 taken launches that were not part of the fit, a third with mask and channel sums: 0.81 of the time, 9 above 1.05.
+        const double rounds = (q.tiles + 255) / 256, patch_mb = 4e-6 * q.tiles * q.npatch * Cin;
+        const double us = 1.6 + rounds * (4.09 + 0.522 * ((steps + 3) / 4)) + 0.0696 * patch_mb + 0.0855e-6 * in_bytes + 0.187e-6 * out_bytes;
+        if (us >= 0.93 * staged_us) return false;            // no estimate (0): never
     }
     const int L = lo_w < 0 ? -lo_w : 0, T = lo_h < 0 ? -lo_h : 0;
     // LDS offset of tap (r, s): tap0 + r tap_dr + s tap_ds
