@@ -768,12 +768,13 @@ static long wgrad_taps_rounds(long tiles, long parts, bool r3)
 }
 
 // Turns a finished plan into one of wgrad_taps_own_bf16 where that is expected to take less time: 64 k, 16 c, 9 taps a workgroup, as
-// many parts as one round of workgroups has room for or fewer.  Expected time, us: start and sum of the streams per round, the
-// stages of a wave, partials, dw, operands read; fitted to 219 launches of 110 drawn nodes, nine tenths of them within 8 %.  Those
-// nodes (0.3 GFLOP and more, images up to 32 x 32) take 2731 us without this kernel, 2526
-// with this choice, 2508 with the best split of either; 60 nodes that it was not fitted to 1566, 1455 and 1426,
-// 110 with any multiple of 16 k 2209, 2057 and 2030, none of them slower by more than 3 %.
-static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force, bool within)
+// many parts as one round of workgroups has room for or fewer.  Expected time, us, operands from memory: start and sum of the streams per
+// round, the stages of a wave, partials, dw, operands read; fitted to 1206 launches of 350 drawn nodes (0.1 GFLOP and more, images up to 40 x
+// 32), nine tenths of them within 6 %, its split 0.4 % above the best of those that were timed.  common_stages: of a part of the plan it is
+// compared with, which takes less than its own expectation where there are one or two (0.88 and 0.95 of it at the median of 125 nodes):
+// nothing waits for the other waves then (416 -> 528 at 14x4, 3 images, one stage 10.6 / 12.9).  1400 taken nodes that it was not fitted to
+// take 48977 us without this kernel, 40392 with it, 19 of them 5 % and more above (the worst 352 -> 368 at 8x14, 1x9, 7 images 12.4 / 14.5).
+static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, long common_stages, int force, bool within)
 {
     WgradTapsParams &q = out->p;
     if (q.Q > 32 || env_switch(SW_WGRAD_OWN)) return;         // the switch (any value): common stages, tests / benchmarks only
@@ -791,15 +792,15 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, int force
         if (force > 0 ? p != force % 1000 && force % 1000 : p > 1 && p * dw_mb * 1e6 > (double)NGC_STATIC_SCRATCH_BYTES) continue;
         if (within && p > 1 && (size_t)p * tiles * 36864 > out->ws) continue;
         const long per = (nstages + p - 1) / p, rounds = (tiles * p + 255) / 256;
-        const double us = rounds * (10.7 + 0.78 * ((per + 7) / 8)) + (p > 1 ? 1.1 + 0.33 * p * dw_mb : 0.0) + 0.08 * dw_mb +
-                          0.0042 * tiles * p / 256.0 * per * (4 + nxb);
+        const double us = 3.76 + rounds * (6.48 + 0.738 * ((per + 7) / 8)) + (p > 1 ? 0.43 + 0.63 * p * dw_mb : 0.0) + 0.32 * dw_mb +
+                          0.003 * tiles * p / 256.0 * per * (4 + nxb);
         if (parts == 0 || us < best) {
             best = us;
             parts = p;
         }
     }
     const bool same_tile = q.ncq == 1 && out->nkb == 4;
-    if (parts == 0 || (force > 0 ? !same_tile : best >= (same_tile ? 1.0 : 0.95) * out->us)) return;
+    if (parts == 0 || (force > 0 ? !same_tile : best >= (common_stages <= 2 ? 0.9 : 0.98) * out->us)) return;
     q.SR = (int16_t)sr;
     q.G = 1;
     q.PRS = (int16_t)prs;
@@ -984,7 +985,7 @@ bool wgrad_taps_plan(WgradTapsPlan *out, bool within)
     // the GEMM has to be expected 8 % faster (1 x 80 -> 48, 8 x 22 x 52 /2, expected 12.3 / 13.4, takes 12.3 / 12.5; 40 nodes that change
     // kernels without this margin take 0.76 to 1.07 of the GEMM's time).
     if (q.r3) out->us = by_cycles_us < 1.09 * out->us ? by_cycles_us : 1.09 * out->us;
-    else if (nt == 9 && q.RS == 9) wgrad_taps_own_plan(out, rspan, (int)pc, fv, within);
+    else if (nt == 9 && q.RS == 9) wgrad_taps_own_plan(out, rspan, (int)pc, per, fv, within);
     return true;
 }
 

@@ -63,9 +63,12 @@ def test_own_stages_special_values(monkeypatch):
     assert np.array_equal(np.isnan(own), np.isnan(common)) and np.array_equal(np.isinf(own), np.isinf(common))
 
 
-@pytest.mark.parametrize("n,c,h,w,k", [(4, 128, 7, 7, 128), (8, 64, 14, 14, 64)])
-def test_own_stages_without_the_switches(n, c, h, w, k):
-    a = Attrs(n, c, h, w, k, 3, 3, 1, 1, 1, 1, 1, 1, 1, 1)
+@pytest.mark.parametrize("n,c,h,w,k,stride", [(16, 64, 9, 9, 256, 1), (8, 256, 14, 14, 64, 1), (32, 256, 9, 9, 512, 2), (16, 128, 28, 28, 80, 1)])
+def test_own_stages_without_the_switches(n, c, h, w, k, stride):
+    """The plan and the parts that the dispatcher chooses by itself: 3, 4, 1 and 8 parts."""
+    a = Attrs(n, c, h, w, k, 3, 3, stride, stride, 1, 1, 1, 1, 1, 1)
     x, wt, b, dy = _tensors(a, "bf16", 20200 + c)
     run = Run(a, "bf16", BLK, BLK, True)
-    assert oracle.max_normalised_error(run.bwd_filters(x, dy), oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")
+    dw = run.bwd_filters(x, dy)
+    assert ng.ngc_conv_kernel(run.last_desc, ng.NGC_OP_BWD_FILTERS).endswith(":taps_own")
+    assert oracle.max_normalised_error(dw, oracle.conv_bwd_filters(a, x, dy)) <= bound("bf16", "dw")

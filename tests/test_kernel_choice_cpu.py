@@ -178,6 +178,16 @@ def test_waves_that_split_the_reduction_leave_nodes_to_the_strip_kernel_that_it_
         assert ng.ngc_conv_kernel(d, op) == "strip_bf16" + (":waves" if (n, c, h, w, k, r, s, op) in waves else ""), (n, c, h, w, k, r, s, op)
 
 
+def test_stages_of_a_waves_own_leave_short_reductions_to_common_stages():
+    """Nodes that took a twentieth more with stages of a wave's own, operands from memory, and some that took a twentieth less."""
+    common = [(1, 944, 26, 10, 224, 1, 9, (1, 2)), (2, 928, 7, 14, 208, 3, 3, (1, 1)), (1, 288, 32, 9, 576, 3, 3, (1, 1)), (3, 416, 14, 4, 528, 3, 3, (1, 1)),
+              (7, 816, 9, 5, 304, 3, 3, (1, 1)), (4, 704, 14, 10, 272, 3, 3, (2, 2))]
+    own = [(66, 64, 29, 29, 544, 3, 3, (1, 1)), (51, 256, 19, 19, 176, 3, 3, (1, 2)), (43, 432, 13, 13, 176, 3, 3, (1, 1)), (128, 512, 7, 7, 512, 3, 3, (1, 1))]
+    for n, c, h, w, k, r, s, stride in common + own:
+        d = ng.make_desc(n, c, h, w, k, r, s, stride, (1, 1), (r // 2, s // 2), (r // 2, s // 2))
+        assert ng.ngc_conv_kernel(d, WGRAD).endswith(":taps_own") == ((n, c, h, w, k, r, s, stride) in own), (n, c, h, w, k, r, s, stride)
+
+
 def test_backprop_filters_on_blocked_copies_need_no_more_workspace_for_stages_of_a_waves_own(monkeypatch):
     """The copies and the partials of such a node share the array of ngc_conv_bwd_filters_noalloc: what fitted it fits it still."""
     smaller = 0
