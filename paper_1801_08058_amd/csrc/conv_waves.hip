@@ -116,7 +116,7 @@ __global__ __launch_bounds__(512) void conv_waves_bf16(const ConvWavesParams p)
         woff[a] = none ? WV_OOB : (unsigned)(k * 32 + (g & 1) * 16 + (g >> 1) * p.Cout * 32);
     }
     const int tap_r = small_div(lane, p.rcp_s), tap_s = lane - __umul24(tap_r, p.S);      // lane l holds tap l
-    const int toffv = p.tap0 + tap_r * p.tap_dr + tap_s * p.tap_ds, slabv = lane * CB * p.Cout * 32;
+    const int toffv = p.tap0 + tap_r * p.tap_dr + tap_s * p.tap_ds, slabv = (int)((unsigned)lane * (unsigned)(CB * p.Cout * 32));      // past the last tap: any value
     const int w_chunk = 2 * p.Cout * 32;
     int w_soff = c_first * w_chunk, wt = t_first, wc = c_first, wleft = n_steps;       // the step whose filters are requested next
     auto load_w = [&](int i) {

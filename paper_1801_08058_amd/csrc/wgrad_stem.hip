@@ -184,7 +184,7 @@ __global__ __launch_bounds__(512) void wgrad_stem_bf16(const WgradStemParams p)
             const int i = tid + 512 * u;
             const int ch = i % cpr, rr = i / cpr, c = rr / rows_in;
             xh[u] = i < xchunks ? 2 * p0 - p.pbh + (rr - c * rows_in) : -(1 << 30);      // no piece: outside in every stage
-            xoff[u] = (int)((((img * p.C + c) * p.H + xh[u]) * p.W + ch * 8) * 2u);
+            xoff[u] = (int)(((unsigned)((img * p.C + c) * p.H + xh[u]) * (unsigned)p.W + (unsigned)ch * 8u) * 2u);      // no piece: any value
             xdst[u] = rr * RPX + 8 + ch * 8;
         }
         // the zeros in front of and behind the rows of all three buffers: no piece covers them
