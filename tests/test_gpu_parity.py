@@ -52,10 +52,11 @@ def _check_backward_compounds(run, a, x_in, w, dy, ref_dx, tol):
 
 @pytest.fixture(params=["base", "default"])
 def route(request, monkeypatch):
-    """base: the kernels that take some of a variant's nodes (few output tiles, several taps per pass, gather GEMM: the names
-    with a suffix) are off, so that small shapes reach the kernel a test is about; default: the dispatcher's choice."""
+    """base: the kernels that take some of a variant's nodes (few output tiles, several taps per pass, gather GEMM, filters in
+    registers, waves that split the reduction: the names with a suffix) are off, so that small shapes reach the kernel a test is
+    about; default: the dispatcher's choice."""
     if request.param == "base":
-        for switch in ("NGC_FWD_FEW", "NGC_WGRAD_TAPS", "NGC_GATHER_TILE"):
+        for switch in ("NGC_FWD_FEW", "NGC_WGRAD_TAPS", "NGC_GATHER_TILE", "NGC_RESIDENT", "NGC_WAVES"):
             monkeypatch.setenv(switch, "0")
     return request.param
 
@@ -63,6 +64,7 @@ def route(request, monkeypatch):
 def _runs(desc, op, expect, route="default"):
     name = ng.ngc_conv_variant(desc, op)
     assert name.startswith(expect) and (route != "base" or ":" not in name), name
+    assert route != "base" or ng.ngc_conv_kernel(desc, op) == name
 
 
 def _check_all(a: Attrs, dtype: str, xl: int, yl: int, pre: bool, seed: int, expect_variant=None, route="default"):
