@@ -15,8 +15,9 @@ OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "layout.hip", "conv_direct.hip", "conv_gather.hip", "conv_stream.hip", "wgrad_stream.hip", "conv_few.hip", "conv_waves.hip", "conv_igemm.hip", "conv_strip.hip", "conv_rows.hip", "conv_strip3.hip", "conv_stem.hip", "wgrad.hip", "wgrad_strip.hip", "wgrad_stem.hip", "wgrad_gemm.hip", "wgrad_taps.hip", "conv_gemm1x1.hip", "conv_resident1x1.hip", "bias_grad.hip", "softmax.hip", "conv3d_direct.hip", "api3d.hip", "static_scratch.hip", "switches.hip", "bwd1x1_fused.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
-         # the first 16 words of scalar kernel arguments arrive in registers: without a round trip for them the second launch of a
-         # split reduction ends 0.3 us earlier (the three calls of the headline layer 61.0 -> 59.2 us, of a small fp32 layer 17.4 -> 17.1)
+         # the first 16 words of scalar kernel arguments arrive in registers: no round trip for them at the start of a kernel.  Without /
+         # with, us: the three calls of the headline layer 65.2 / 64.4, of an odd-channel layer 32.6 / 32.3, softmax of 32768 x 1000 and its
+         # backprop 58.1 / 57.4, an fp32 layer 88.0 / 87.7; nothing slower
          "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Rpass-analysis=kernel-resource-usage"]
 

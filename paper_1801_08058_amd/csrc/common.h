@@ -245,7 +245,7 @@ struct SibLanes {
         odd[u] = even[u] != 0x80000000u && oh + 1 < Hout ? even[u] + (unsigned)Wout * 32u : 0x80000000u;
     }
     // o: channels 8 (lane / 32) + 0 .. 7 of position lane % 32; block: byte offset of the channel block; stream (wave-uniform): past the
-    // memory-side cache
+    // memory-side cache.  Four store instructions whatever live is (conv_resident1x1.hip counts them)
     __device__ __forceinline__ void store(unsigned char *lds, int lane, uint4 o, __amdgpu_buffer_rsrc_t rs, bool live, unsigned block, bool stream)
     {
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));

@@ -112,7 +112,9 @@ __global__ __launch_bounds__(512) void conv1x1_resident(const Resident1x1Params 
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 
     const bool relu_b = p.relu != 0;
-    constexpr int ST = 2 * FC * (SIB ? 4 : 1);                           // stores per wave and tile
+    // Stores per wave and tile, for the waits below.  A store out of range counts: its offset is out of range, there is no branch around
+    // it, and as the size of the result is not known at compile time no path can do without the instruction.
+    constexpr int ST = 2 * FC * (SIB ? 4 : 1);
     unsigned char *const mine = smem + NS * SLICE + 32 * FC * WN * 4 + wave * 1024;
 
     int g = 0, buf = 0;

@@ -13,10 +13,11 @@
 // Zeros around the images are shared: the columns between two rows serve as the right halo of one and the left halo of the other, and
 // so do the rows between two images of a tile.  Two 7x7 images then take 137 pixels instead of 162.
 //
-// What bounds it: the issue of one wave (4 waves of 13 position groups, one a SIMD, took 33.9 us where these take 31.3: a matrix
-// instruction leaves a lone wave every 27 cycles, two waves every 17), the LDS, and some 5 us of start, sum and stores per round of
-// workgroups.  Strip kernel / here, us: 512 -> 512 at 7x7, 128 images 41.8 / 31.1; 512 -> 512 at 14x14, 32 images 36.9 / 29.4;
-// 256 -> 256 at 14x14, 64 images 21.0 / 18.0; 464 -> 368 at 14x9, 2x2 stride 2, 75 images 27.9 / 17.7.
+// What bounds it: the issue of a wave (4 waves of 13 position groups, one a SIMD, took 33.9 us where these take 31.3), the LDS, and some
+// 4 us of start, sum and stores per round of workgroups: of the cycles that the compute units are busy the matrix pipes work 0.54, the LDS
+// 0.59, 0.18 of it bank conflicts (512 -> 512 at 7x7).  Strip kernel / here, us, the same operands again and again: 512 -> 512 at 7x7,
+// 128 images 41.8 / 31.1; 512 -> 512 at 14x14, 32 images 36.9 / 29.4; 256 -> 256 at 14x14, 64 images 21.0 / 18.0; 464 -> 368 at 14x9, 2x2
+// stride 2, 75 images 27.9 / 17.7.
 #include "common.h"
 
 #include <math.h>

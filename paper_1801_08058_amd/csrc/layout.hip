@@ -273,11 +273,13 @@ hipError_t launch_layout_convert(int elem_bytes, int n, int c, int h, int w, con
         uint16_t *d = static_cast<uint16_t *>(dst);
         const int v = (HW % 8 == 0) ? 8 : (HW % 4 == 0) ? 4 : (HW % 2 == 0) ? 2 : 1;
         if (src_layout == NGC_NCHW) {
-            // Ordinary stores leave the copy in the memory-side cache (256 MB) for the kernel that reads it, streaming ones save
-            // the conversion a tenth.  Streaming / ordinary, us, conversion alone and with a read of the copy behind it: 26 MB
-            // 10.1 / 11.8 and 28.5 / 27.9, 103 MB 34.7 / 36.9 and 68.1 / 64.4, 257 MB 83.7 / 86.0 and 149.5 / 149.0, 411 MB
-            // 134.6 / 140.0 and 234.1 / 239.2.  256 channels at 56x56, 64 images, with the three calls of a 1x1 layer of 64
-            // channels behind it 118.9 / 110.9.
+            // Ordinary stores leave the copy in the memory-side cache (256 MB) for the kernel that reads it.  Streaming / ordinary,
+            // us, a graph of conversions of tensors in memory, alone, with a forward 1x1 convolution to 64 channels behind each, and
+            // with all three calls of that layer:
+            //   0.1 MB  2.3 /  2.3,   6.3 /   6.0,   17.5 /  17.2        26 MB  12.7 / 11.4,   21.7 /  18.4,   44.7 /  41.6
+            //   0.8 MB  2.8 /  2.7,   7.4 /   6.7,   19.4 /  18.5       103 MB  42.3 / 36.5,   69.8 /  59.8,  123.7 / 114.3
+            //   6.4 MB  4.1 /  4.5,  11.0 /   9.7,   27.1 /  25.9       206 MB  81.1 / 71.3,  126.6 / 120.5,  225.9 / 214.9
+            // Copies that do not stay there: a conversion and a read 257 MB 149.5 / 149.0, 411 MB 234.1 / 239.2.
             const int stream = (size_t)n * CB * HW * 32 > ((size_t)240 << 20);
             if (v == 8) NGC_LAUNCH(nchw_to_blocked16_b16<8>, grid, block, 0, st, s, d, c, HW, stream);
             else if (v == 4) NGC_LAUNCH(nchw_to_blocked16_b16<4>, grid, block, 0, st, s, d, c, HW, stream);
