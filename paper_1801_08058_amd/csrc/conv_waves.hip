@@ -456,7 +456,7 @@ bool conv_waves_plan(const ngc_conv_desc *d, int op, int P, int Q, double staged
         for (Switch sw : {SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_BW, SW_STRIP_XCD, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_STRIP_CPS, SW_STRIP_STRIDED, SW_ROWS, SW_FWD_FEW})
             if (env_switch(sw)) return false;
         // Expected time, us, operands from memory: a start and, per round of workgroups, start, sum and stores and the steps of a wave;
-        // the bytes: patches loaded, tensors read and written.  Fitted to 1341 launches of drawn nodes (32 MFLOP to 150 GFLOP, both
+        // the bytes: patches loaded, tensors read and written.  Fitted to 1341 launches of drawn nodes (39 MFLOP to 144 GFLOP, both
         // operands up to 400 MB), nine tenths within 9 %.  The strip kernel gains with the size of its strips and of a launch, this one
         // with the length of the reduction: 418 of the 1341 are taken, 0.82 of the strip kernel's time, 3 above 1.05 (the worst 85 x 928
         // -> 464 at 60x10, 1x3, backwards 190.6 / 224.1).  168 of the rest would gain, 7 % of their time; the others lose up to all of it.
