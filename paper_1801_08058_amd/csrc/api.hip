@@ -1263,10 +1263,11 @@ double staged_fwd_bwd_us(const ngc_conv_desc *d, int op, Variant v, int P, int Q
     return few_strip_us(wgs, stages, taps, nf);
 }
 
-// What the strip kernel is expected to take on a node of one class of taps, us, operands from memory, against conv_waves_plan's own
-// expectation: stages of 16 input channels in rounds of workgroups, of as many to a compute unit as its LDS holds where that is more than
-// one, and the bytes: what the workgroups of a strip's channel tiles read, what is written.  Fitted to 1341 launches of drawn nodes, nine
-// tenths within 10 % (one workgroup to a compute unit), 14 % (several), 24 % (strided forward).  0: column tiles, no estimate.
+// What the strip kernel is expected to take on a node of one class of taps, us, against conv_waves_plan's own expectation: stages of 16
+// input channels in rounds of workgroups, of as many to a compute unit as its LDS holds where that is more than one, and the bytes: what the
+// workgroups of a strip's channel tiles read, what is written.  Fitted to the mean of operands from memory and from the caches over 22090
+// drawn launches where neither kernel takes twice the other's time, nine tenths within 6 % and 14 % above, 13 % and 33 % (several to a compute
+// unit) below and above.  0: column tiles, no estimate.
 double strip_node_us(const ngc_conv_desc *d, int op, int P, int Q)
 {
     StripParams sp;
@@ -1278,10 +1279,9 @@ double strip_node_us(const ngc_conv_desc *d, int op, int P, int Q)
     const long wgs = (long)sp.groups * sp.strips * nk, rounds = (wgs + NUM_CUS - 1) / NUM_CUS, full = (wgs + NUM_CUS * together - 1) / (NUM_CUS * together);
     const double stages = sp.Cin / 16, taps = sp.ntaps, share = wgs > NUM_CUS ? (double)wgs / NUM_CUS : 1.0;
     const double in_mb = 2e-6 * sp.N * sp.Cin * sp.Hin * sp.Win, out_mb = 2e-6 * sp.N * sp.Cout * (op == NGC_OP_FWD ? P * Q : d->h * d->w);
-    if (d->stride_h > 1 || d->stride_w > 1)
-        return 3.42 + stages * (share * (0.161 + taps * (0.0211 + 0.0172 * nf)) + rounds * taps * nf * 0.0199) + 0.0624 * nk * in_mb + 0.1875 * out_mb;
-    if (together == 1) return 1.43 + rounds * (1.74 + stages * (0.334 + taps * (0.0365 + 0.0228 * nf))) + 0.101 * nk * in_mb + 0.2215 * out_mb;
-    return 3.02 + stages * (rounds * (0.0055 + 0.0314 * taps * nf) + full * (0.1075 + 0.0296 * taps)) + 0.0869 * nk * in_mb + 0.2935 * out_mb;
+    if (d->stride_h > 1 || d->stride_w > 1) return 4.45 + stages * (share * (0.237 + taps * 0.0116) + rounds * taps * nf * 0.0399) + 0.0501 * nk * in_mb + 0.0294 * out_mb;
+    if (together == 1) return 2.61 + rounds * (2.5 + stages * (0.415 + taps * (0.0338 + 0.0223 * nf))) + 0.084 * nk * in_mb + 0.117 * out_mb;
+    return 4.98 + stages * (rounds * taps * nf * 0.0351 + full * (0.104 + 0.0204 * taps)) + 0.0802 * nk * in_mb + 0.1066 * out_mb;
 }
 
 // plan of a node of V_STRIP_WAVES

@@ -15,6 +15,7 @@
 // the start (filters, first tile) on small ones.  Two workgroups a compute unit measured 31 us there.
 #include "common.h"
 
+#include <math.h>
 #include <stdlib.h>
 
 namespace ngc {
@@ -225,18 +226,32 @@ static hipError_t launch_resident(const Gemm1x1Params &p, hipStream_t st)
     return launch_result();
 }
 
-// Nodes it is expected to run faster than the GEMM.  GEMM / here, us, operands from memory; m: positions.  Backprop-data (stride 2 x 2; 366
-// drawn nodes, a graph of calls): up to 1.6 million results of lattice positions (256 <- 512, m 3136 13.3 / 7.6; 80 <- 400, m 12240
-// 14.0 / 9.0; above, the GEMM's tiles fill the chip: 192 <- 288, m 10143 10.2 / 11.2), of channels whose filters pay for being fetched by
-// every workgroup: more than 64 from more than 64 (48 <- 112, m 32490 7.5 / 8.3; 32 <- 208, m 45849 9.6 / 15.1), up to 256 (352 <- 48, m 5236
-// 5.4 / 6.3; 368 <- 176, m 4805 7.1 / 8.0), 512 only from 65 to 128 (0.76 to 0.91 of the time).  What is taken has 0.83 of the GEMM's
-// time, 1.05 at worst.  Forward, columns strided (rows alone, 496 -> 144, m 18496 11.2 / 13.8: the GEMM reads whole lines there):
-// reductions of more than 208 channels whose output channels leave the GEMM 64-channel tiles, so that one of 256 positions is all a
-// workgroup has (416 -> 192, m 1456 10.6 / 6.1; 400 -> 32, m 10506 15.2 / 8.2; 256 -> 64, m 13986 10.8 / 8.2; with 128-channel tiles
-// 240 -> 128, m 5040 5.6 / 7.4), and large nodes whose activations the GEMM reads for several channel tiles (368 -> 256, m 30400
-// 18.9 / 15.0; 96 -> 432, m 26754 11.7 / 8.9 is left out with 48 -> 160, m 71214 10.5 / 8.3: 32 -> 128, m 56661 6.7 / 7.3): 0.69 of the
-// time of the 72 of 834 drawn nodes that are taken, strides up to 4, 1.03 at worst.  500 nodes of either direction that are taken and were
-// not part of that: 0.77 of the time, one above 1.05 (160 <- 320, m 8712 8.5 / 9.4).
+// Forward with strided columns (rows alone, 496 -> 144 channels, 18496 positions, GEMM / here 11.2 / 13.8: the GEMM reads whole lines there),
+// expected times of both, us: here a start, tiles of a workgroup, slices of a tile, bytes, the filters that every workgroup fetches; the GEMM
+// rounds of tiles, 32-channel steps, bytes, the activations once per channel tile.  Fitted to the mean of operands from memory and from the
+// caches over 26499 drawn nodes, strides up to 3, nine tenths within 8 % and 13 %.  2057 nodes are taken, where 5 % less is
+// expected: 30398 -> 24863 us, 28 above 1.05 of the GEMM's time; of 10697 others 823, 12642 -> 10338, 17 above, 1.22 at worst.
+static bool resident1x1_faster(const Gemm1x1Params &p)
+{
+    const bool deep = p.Cin > 256, wide = gemm1x1_wide_tiles(p);
+    const int wn = deep ? (p.Cout <= 32 ? 1 : p.Cout <= 64 ? 2 : 8) : p.Cout <= 64 ? 1 : p.Cout <= 256 ? 4 : 8;       // as launch_resident1x1
+    const int loads = (wn == 1 ? 2 : 1) * (deep && wn <= 2 ? 2 : 1), slices = (p.Cin / 16 + loads * wn - 1) / (loads * wn);
+    const double chunk = ceil(ceil(p.M / 256.0) / 8) * 8, tiles = ceil(chunk / (256 / wn)), wgs = ceil(p.M / chunk);
+    const double in_mb = 2e-6 * p.Cin * (p.M / p.div_q.d) * p.Win, out_mb = 2e-6 * p.Cout * p.M, filters_mb = 2e-6 * p.Cin * p.Cout;
+    const double here = 4.76 + tiles * (0.462 + 0.329 * slices) + 0.0983 * in_mb + 0.095 * out_mb + filters_mb * (2.92 + 0.0067 * wgs);
+    const double across = ceil(p.Cout / (wide ? 128.0 : 64.0)), gt = ceil(p.M / (wide ? 128.0 : 256.0)) * across, steps = (p.Cin + 31) / 32;
+    const double rounds = ceil(gt / 256), share = gt > 256 ? gt / 256 : 1.0;
+    const double gemm = wide ? 3.54 + rounds * (0.845 + 0.02 * steps) + share * steps * 0.22 + in_mb * (0.0831 + 0.0294 * across)
+                             : 3.75 + rounds * (0.428 + 0.1013 * steps) + share * steps * 0.271 + in_mb * (0.0954 + 0.0288 * across) + 0.038 * out_mb;
+    return here < 0.95 * gemm;
+}
+
+// Nodes it is expected to run faster than the GEMM.  GEMM / here, us, operands from memory; m: positions.  Backprop-data (stride 2 x 2): up to
+// 2 million results of lattice positions (256 <- 512, m 3136 13.3 / 7.6; 80 <- 400, m 12240 14.0 / 9.0; above, the GEMM's tiles fill the chip:
+// 128 <- 112, m 32129 11.2 / 12.2), of channels whose filters pay for being fetched by every workgroup: more than 64 from more than 64 (48 <- 112,
+// m 32490 7.5 / 8.3; 32 <- 208, m 45849 9.6 / 15.1), up to 256 (352 <- 48, m 5236 5.4 / 6.3; 368 <- 176, m 4805 7.1 / 8.0), 512 only from 65 to
+// 128.  Of 11893 drawn nodes with an instance 10083 are taken, the mean of operands from memory and from the caches 66148 -> 56358 us, 48 above
+// 1.05 of the GEMM's time, 1.16 at worst.
 bool resident1x1_takes(const Gemm1x1Params &p)
 {
     const char *force = env_switch(SW_RESIDENT);                         // tests only: 0 = never, 1 = all it can
@@ -248,9 +263,8 @@ bool resident1x1_takes(const Gemm1x1Params &p)
     if (!(p.Cin <= 256 ? p.Cout <= 512 : p.Cin <= 512 && p.Cout <= 256)) return false;
     if (sib && (p.Cin <= 64 ? p.Cout > 256 : p.Cout <= 64 || (p.Cin > 128 && p.Cout > 256))) return false;
     if (force) return true;
-    if (sib) return (uint64_t)p.M * p.Cout < 1600000;
-    if (p.is_w == 1) return false;
-    return (p.Cin > 208 && !gemm1x1_wide_tiles(p)) || (p.Cin >= 176 && p.Cout > 128 && p.M >= 24000);
+    if (sib) return (uint64_t)p.M * p.Cout < 2000000;
+    return p.is_w > 1 && resident1x1_faster(p);
 }
 
 // The smallest instance that holds the filters; forward has those its rule reaches, the others run the next larger one

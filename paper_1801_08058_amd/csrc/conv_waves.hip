@@ -455,15 +455,14 @@ bool conv_waves_plan(const ngc_conv_desc *d, int op, int P, int Q, double staged
         // A switch that shapes the strip kernel, or rules out another one in its favour, asks for it
         for (Switch sw : {SW_STRIP_NF, SW_STRIP_ROWS, SW_STRIP_BW, SW_STRIP_XCD, SW_STRIP_TAIL, SW_STRIP_SPLIT, SW_STRIP_CPS, SW_STRIP_STRIDED, SW_ROWS, SW_FWD_FEW})
             if (env_switch(sw)) return false;
-        // Expected time, us, operands from memory: a start and, per round of workgroups, start, sum and stores and the steps of a wave;
-        // the bytes: patches loaded, tensors read and written.  Fitted to 1341 launches of drawn nodes (39 MFLOP to 144 GFLOP, both
-        // operands up to 400 MB), nine tenths within 9 %.  The strip kernel gains with the size of its strips and of a launch, this one
-        // with the length of the reduction: 418 of the 1341 are taken, 0.82 of the strip kernel's time, 3 above 1.05 (the worst 85 x 928
-        // -> 464 at 60x10, 1x3, backwards 190.6 / 224.1).  168 of the rest would gain, 7 % of their time; the others lose up to all of it.
-        // 600 taken launches that were not part of the fit, a third with mask and channel sums: 0.81 of the time, 9 above 1.05.
+        // Expected time, us: a start and, per round of workgroups, start, sum and stores and the steps of a wave; the bytes: patches
+        // loaded, tensors read and written.  Fitted as strip_node_us, nine tenths within 8 % below and 16 % above.  The strip kernel gains
+        // with the size of its strips and of a launch, this one with the length of the reduction: 3351 of 31617 drawn
+        // launches are taken, 120622 -> 102889 us, 51 above 1.05 of the strip kernel's time; of 10569 others 1170, 41996 -> 35491, 14 above,
+        // 1.15 at worst.
         const double rounds = (q.tiles + 255) / 256, patch_mb = 4e-6 * q.tiles * q.npatch * Cin;
-        const double us = 1.6 + rounds * (4.09 + 0.522 * ((steps + 3) / 4)) + 0.0696 * patch_mb + 0.0855e-6 * in_bytes + 0.187e-6 * out_bytes;
-        if (us >= 0.93 * staged_us) return false;            // no estimate (0): never
+        const double us = 2.99 + rounds * (4.2 + 0.538 * ((steps + 3) / 4)) + 0.051 * patch_mb + 0.0494e-6 * in_bytes + 0.0295e-6 * out_bytes;
+        if (us >= 0.97 * staged_us) return false;            // no estimate (0): never
     }
     const int L = lo_w < 0 ? -lo_w : 0, T = lo_h < 0 ? -lo_h : 0;
     // LDS offset of tap (r, s): tap0 + r tap_dr + s tap_ds
