@@ -760,11 +760,12 @@ static double wgrad_taps_us(long rounds, long per, double stage, double fixed, s
 // whether the tiles of a part are kept on one XCD
 static bool wgrad_taps_xcd(long tiles, long parts) { return tiles > 1 && (parts % 8 == 0 || parts >= 64); }
 
-// Rounds of workgroups, one to a compute unit.  Rank 3 counts the fullest XCD where they are ordered by XCD: 84 parts of 3 tiles are 33
-// for its 32 compute units (3 x 32 -> 32, 21 x 17 x 43 25.1 us, 42 parts of 6 tiles 19.0).
-static long wgrad_taps_rounds(long tiles, long parts, bool r3)
+// Rounds of workgroups, one to a compute unit.  by_xcd (rank 3 and stages of a wave's own): of the fullest XCD where they are ordered by XCD: 84
+// parts of 3 tiles are 33 for its 32 compute units (3 x 32 -> 32, 21 x 17 x 43 25.1 us, 42 parts of 6 tiles 19.0; 112 x 48 -> 64 at 105x22, own
+// stages, 84 parts 50.7, 78 parts 32.4).
+static long wgrad_taps_rounds(long tiles, long parts, bool by_xcd)
 {
-    return r3 && wgrad_taps_xcd(tiles, parts) ? ((parts + 7) / 8 * tiles + 31) / 32 : (tiles * parts + 255) / 256;
+    return by_xcd && wgrad_taps_xcd(tiles, parts) ? ((parts + 7) / 8 * tiles + 31) / 32 : (tiles * parts + 255) / 256;
 }
 
 // Turns a finished plan into one of wgrad_taps_own_bf16 where that is expected to take less time: 64 k, 16 c, 9 taps a workgroup, as
@@ -772,8 +773,8 @@ static long wgrad_taps_rounds(long tiles, long parts, bool r3)
 // round, the stages of a wave, partials, dw, operands read; fitted to 1206 launches of 350 drawn nodes (0.1 GFLOP and more, images up to 40 x
 // 32), nine tenths of them within 6 %, its split 0.4 % above the best of those that were timed.  common_stages: of a part of the plan it is
 // compared with, which takes less than its own expectation where there are one or two (0.88 and 0.95 of it at the median of 125 nodes):
-// nothing waits for the other waves then (416 -> 528 at 14x4, 3 images, one stage 10.6 / 12.9).  1400 taken nodes that it was not fitted to
-// take 48977 us without this kernel, 40392 with it, 19 of them 5 % and more above (the worst 352 -> 368 at 8x14, 1x9, 7 images 12.4 / 14.5).
+// nothing waits for the other waves then (416 -> 528 at 14x4, 3 images, one stage 10.6 / 12.9).  Of 8139 other drawn nodes 2980 are taken, the
+// mean of operands from memory and from the caches 105108 -> 88186 us (the best of each 87534), 15 above 1.05 (2 x 16 -> 256 at 45x14 11.3 / 13.1).
 static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, long common_stages, int force, bool within)
 {
     WgradTapsParams &q = out->p;
@@ -791,7 +792,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, long comm
     for (long p = 1; p <= most && p <= nstages; ++p) {
         if (force > 0 ? p != force % 1000 && force % 1000 : p > 1 && p * dw_mb * 1e6 > (double)NGC_STATIC_SCRATCH_BYTES) continue;
         if (within && p > 1 && (size_t)p * tiles * 36864 > out->ws) continue;
-        const long per = (nstages + p - 1) / p, rounds = (tiles * p + 255) / 256;
+        const long per = (nstages + p - 1) / p, rounds = wgrad_taps_rounds(tiles, p, true);      // of the fullest XCD
         const double us = 3.76 + rounds * (6.48 + 0.738 * ((per + 7) / 8)) + (p > 1 ? 0.43 + 0.63 * p * dw_mb : 0.0) + 0.32 * dw_mb +
                           0.003 * tiles * p / 256.0 * per * (4 + nxb);
         if (parts == 0 || us < best) {
@@ -800,7 +801,7 @@ static void wgrad_taps_own_plan(WgradTapsPlan *out, int rspan, int pc, long comm
         }
     }
     const bool same_tile = q.ncq == 1 && out->nkb == 4;
-    if (parts == 0 || (force > 0 ? !same_tile : best >= (common_stages <= 2 ? 0.9 : 0.98) * out->us)) return;
+    if (parts == 0 || (force > 0 ? !same_tile : best >= (common_stages <= 2 ? 0.9 : 1.0) * out->us)) return;
     q.SR = (int16_t)sr;
     q.G = 1;
     q.PRS = (int16_t)prs;

@@ -188,6 +188,16 @@ def test_stages_of_a_waves_own_leave_short_reductions_to_common_stages():
         assert ng.ngc_conv_kernel(d, WGRAD).endswith(":taps_own") == ((n, c, h, w, k, r, s, stride) in own), (n, c, h, w, k, r, s, stride)
 
 
+@pytest.mark.parametrize("n,c,h,w,k", [(112, 48, 105, 22, 64), (75, 16, 80, 19, 176), (117, 16, 79, 11, 160), (109, 16, 103, 30, 144)])
+def test_parts_of_stages_of_a_waves_own_fill_every_xcd_once(n, c, h, w, k):
+    """Parts in multiples of 8 or 64 and more are dealt to the 8 XCDs, whose 32 compute units hold so many (part, tile) pairs at a time."""
+    d = ng.make_desc(n, c, h, w, k, 3, 3, (1, 1), (1, 1), (1, 1), (1, 1))
+    tiles = (k + 63) // 64 * (c // 16)
+    parts = ng.ngc_conv_workspace_bytes(d, WGRAD) // (tiles * 36864)
+    assert ng.ngc_conv_kernel(d, WGRAD).endswith(":taps_own") and parts >= 64
+    assert (parts + 7) // 8 * tiles <= 32
+
+
 def test_backprop_filters_on_blocked_copies_need_no_more_workspace_for_stages_of_a_waves_own(monkeypatch):
     """The copies and the partials of such a node share the array of ngc_conv_bwd_filters_noalloc: what fitted it fits it still."""
     smaller = 0
